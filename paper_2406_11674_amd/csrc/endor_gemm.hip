@@ -5,43 +5,33 @@
 // at once, computed on the sparse form as Section 7 ("Efficient Compute Unit") suggests.
 //
 // Shape of the computation.  v_mfma_f32_16x16x32_f16 multiplies a 16 x 32 block of W (its A
-// operand: lane l holds the 8 consecutive columns 8*(l/16) .. +7 of row l%16) with a 32 x 16
-// block of X^T (B operand: lane l holds the same 8 columns of right-hand side l%16) into a
-// 16 x 16 fp32 tile.  So one wave owns 16 rows of W and walks them 256 columns at a time
-// (4096 elements per round, 8 matrix instructions); the 16 bytes an expander lane produces
-// per step are exactly one lane's A operand, and the expansion is shared by all nb
-// right-hand sides.
+// operand: lane l holds 8 columns of row l%16) with a 32 x 16 block of X^T (B operand: lane l
+// holds the same 8 columns of right-hand side l%16) into a 16 x 16 fp32 tile.  A wave owns 16
+// rows of W and walks them 256 columns (a round) at a time: 4096 elements, 64 bitmap words, 8
+// matrix instructions.  Which 32 columns an instruction takes is free as long as both operands
+// agree, so lane l simply owns the bitmap word l/16 of row l%16 and its step t is byte t of that
+// word: the lane's place in its row's values is a register that grows by popcounts, and the
+// expanded bytes need no exchange between lanes.
 //
-// A round, for the lane that is (row r = l/4, word j = l%4) while loading and
-// (row l%16, column block l/16) while multiplying:
-//   1. the lane's 64 bitmap bits of the segment (loaded a round ahead); popcount; prefix over
-//      the row's four words (DPP quad broadcasts).  Each row has its own cursor into `values`
-//      (its 1 bits so far), so the 16 rows are 16 independent streams.
-//   2. per bitmap byte, one table entry in LDS: (values of the row's segment before the byte)
-//      << 8 | the byte.
-//   3. eight steps: read the entry of (row, byte), read the byte's window of values (16 bytes
-//      from the row's cursor plus the entry's count) straight from memory, move the values to
-//      the positions of the 1 bits with v_perm_b32 (selectors from a table indexed by the
-//      byte), and issue the matrix instruction against the 16-byte fragment of X.
-// Values are not staged: the windows of a row's neighbouring bytes overlap and the vector
-// cache serves the overlap.  The expansion runs in the loading role's lane order, where the
-// four lanes of a quad read neighbouring windows of one row, and the expanded 16 bytes are
-// handed to the multiplying lane with ds_bpermute.  (An earlier form staged every row's slice
-// in LDS and gathered the values one by one: 126 / 138 us for 1 / 16 right-hand sides on
-// 28672 x 8192, bound by LDS; this one takes 91 / 101 us, bound by the rate at which the
-// vector cache accepts line accesses.)  A round's eight window loads per lane go out back to
-// back behind one wave-uniform bounds test; the rounds at the very ends of `values` take a
-// rolled loop with guarded element-wise loads instead.
-// X: the four waves of a workgroup work on neighbouring row groups and the same column
-// range; the round's 256 columns of all right-hand sides are brought to LDS once per
-// workgroup (global_load_lds_dwordx4, double buffered, one barrier per round) and every wave
-// reads its B operands from there.
+// A round:
+//   1. the lane's bitmap word (loaded two rounds ahead) is counted, the row's four words are
+//      summed with lane swaps, and the row's slice of `values` (consecutive) is asked for, 16
+//      bytes per lane, neighbouring lanes taking neighbouring units of one row;
+//   2. a round later the slices go to LDS, row by row;
+//   3. eight steps: per bitmap nibble the window of four values it may consume (three dwords
+//      from the dword below), shifted into place and moved to the positions of the 1 bits with
+//      v_perm_b32, whose selectors come from a 16-entry table; then the matrix instruction.
+// X goes to LDS once per workgroup and round (four row groups share it), in the order in which
+// the steps read it, double buffered.
 //
-// Work is split over rows (16 per wave) and, to have enough waves, over column ranges
-// (ksplit ranges per row group); the starting cursor of a row at a column range comes from
-// the tile offset table (rank of an arbitrary position = chunk start + tile offset +
-// popcount of the tile's words below it).  Partial sums of the column ranges go to a scratch
-// buffer and are added in a fixed order by a second kernel, so results are reproducible.
+// Measured on 28672 x 8192, half kept, 16 right-hand sides: 80 us (the form before, which read
+// every byte's 20-byte window from memory through the vector cache and handed the expanded bytes
+// on with ds_bpermute: 112 us; with 3 right-hand sides on 4099 x 5005, three in ten kept: 18
+// against 25 us).  What bounds it: LDS serves 65 clocks of every step's 95 (64 lanes at random
+// addresses cost 7 clocks per dword, six dwords per byte), the vector ALUs are busy 44 % of the
+// time, memory alone would take 45 us.  Measured alternatives: the windows as three aligned
+// 8-byte reads and selects (48 clocks of LDS, 25 % more vector instructions) 84 us; two rounds of
+// values in flight 84; three workgroups per compute unit 85; units of 64 aligned bytes 84.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -53,38 +43,277 @@
 namespace {
 
 using endor_device::chunk_base;
+using endor_device::global_ptr;
 using endor_device::load_to_lds16;
-using endor_device::window_finish;
-using endor_device::window_guarded;
-using endor_device::window_issue;
-using endor_device::WindowLoad;
-using endor_device::windows_inside;
-using endor_device::place_window;
-using endor_device::window_tables_init;
-using endor_device::WindowTables;
 using endor_device::u32x4;
 using endor_device::wait_loads_to_lds;
 using endor_device::wave_sum;
-using endor_layout::chunks_of;
 using endor_layout::chunk_total_bytes;
 using endor_layout::dims_ok;
 using endor_layout::kChunkStride;
-using endor_layout::kTileElems;
-using endor_layout::kTilesPerChunk;
 using endor_layout::kTileWords;
+using endor_layout::kTilesPerChunk;
 using endor_layout::workspace_bytes_n;
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRows = 16;               // rows of W per wave: the M of the matrix instruction
-constexpr int kSegCols = 256;           // columns per round
+constexpr int kSegCols = 256;           // columns per round: a 64-bit bitmap word per lane
 constexpr int kSteps = kSegCols / 32;   // matrix instructions per round
-constexpr int kInfoStride = 36;         // dwords per row of the entry table (32 used; 36 spreads the LDS banks)
-constexpr int kMaxSplit = 16;           // column ranges per row group at most
+constexpr int kAccs = 4;                // accumulators taken in turn
 constexpr int kGemmWaves = 4;           // waves (row groups) per workgroup; they share the tile of X
-constexpr int kXPitch = 2 * kSegCols + 16;  // bytes between right-hand sides in the LDS tile of X: 132 dwords, so the
-                                            // 16-byte reads of eight lanes (eight right-hand sides) cover all 32 banks
+constexpr int kBlockRows = kRows * kGemmWaves;
+constexpr int kXStep = 64 * 16;         // bytes of the tile of X one matrix instruction reads: 16 per lane, in lane order
+
+// Where the 8 columns 64*mq + 8*t of right-hand side n sit in the tile of X.  A step's 64 fragments
+// fill kXStep bytes, so reading them is free of bank conflicts; the exclusive-or spreads the 32
+// fragments of one right-hand side, which are stored together, over the banks.
+__device__ __forceinline__ uint32_t x_slot(uint32_t n, uint32_t mq, uint32_t t) {
+    return kXStep * t + 256 * mq + 16 * (n ^ t ^ (8 * (mq & 1)));
+}
+
+// Selectors of the value placement: entry n, for a nibble n of the bitmap, holds the two v_perm_b32
+// selectors that move the nibble's consecutive values (a window of four halves in two dwords) to
+// the positions of its 1 bits.  A selector byte of 0x0c yields zero, so 0 bits need no mask.
+// 16 entries of 8 bytes: every lookup of a wave is free of bank conflicts.
+struct alignas(16) NibbleTable {
+    uint64_t sel[16];
+};
+
+__device__ __forceinline__ void nibble_table_init(NibbleTable &T, uint32_t t) {
+    if (t < 16) {
+        uint32_t s[2] = {0x0c0c0c0cu, 0x0c0c0c0cu};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if ((t >> e) & 1) {
+                const uint32_t k = __popc(t & ((1u << e) - 1));  // half of the window this element takes: 0..3
+                s[e >> 1] ^= ((((2 * k + 1) << 8) | (2 * k)) ^ 0x0c0cu) << (16 * (e & 1));
+            }
+        }
+        T.sel[t] = uint64_t(s[0]) | (uint64_t(s[1]) << 32);
+    }
+}
+
+// LDS operations of one wave execute in issue order; the fences only pin the compiler.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Sum over a row's four lanes (lane l and those 16, 32, 48 lanes away), and the sum over the ones
+// before this lane.
+__device__ __forceinline__ uint32_t row_sum(uint32_t x, uint32_t mq, uint32_t *before) {
+    const auto s16 = __builtin_amdgcn_permlane16_swap(x, x, false, false);   // the pair's even lane; its odd lane
+    const uint32_t pair = s16[0] + s16[1];
+    const auto s32 = __builtin_amdgcn_permlane32_swap(pair, pair, false, false);  // lanes 0..31's pair; lanes 32..63's
+    *before = ((mq & 1) ? s16[0] : 0) + ((mq & 2) ? s32[0] : 0);
+    return s32[0] + s32[1];
+}
+
+__device__ const u32x4 g_dummy = {0u, 0u, 0u, 0u};  // read where there is nothing to read
+
+// How many 16-byte units of a row's slice are asked for a round ahead, and how: kRowsPer rows per
+// load instruction (neighbouring lanes take a row's neighbouring units, so an instruction covers
+// whole cache lines and no line is asked for twice).  kTail: one more load brings unit kUnits of
+// every row.  A row with more units gets the rest when its round is staged.
+template <int kClass>
+struct Fetch;
+template <>
+struct Fetch<0> {  // 97 values per row and round
+    enum { kUnits = 13, kRowsPer = 4, kTail = 0 };
+};
+template <>
+struct Fetch<1> {  // 161 values
+    enum { kUnits = 21, kRowsPer = 3, kTail = 0 };
+};
+template <>
+struct Fetch<2> {  // all 256
+    enum { kUnits = 32, kRowsPer = 2, kTail = 1 };
+};
+
+constexpr int kPitch = 560;  // bytes between the staged slices of two rows: 256 values and 14 bytes of slack make 33 units;
+                             // 140 dwords put the 16 rows on 16 different groups of LDS banks
+constexpr int kStageBytes = kRows * kPitch;  // a window's pieces reach at most 526 + 24 bytes into a slice
+
+// What a lane needs to know of a round besides its values.
+struct Round {
+    uint64_t word;   // this lane's 64 bits
+    uint32_t at;     // byte offset of the word's first value in the staging area
+    uint32_t off;    // byte offset of the row's first value from the row's first value of the whole part
+    uint32_t units;  // the row's units
+    uint32_t whole;  // those that lie inside `values` as a whole (they come first)
+    // wave-uniform
+    uint32_t late;  // the first unit that was not asked for ahead; kNoneLate if no row has one
+    bool ragged;    // some row has a unit that reaches over the end of `values`
+};
+
+constexpr uint32_t kNoneLate = 64;
+
+// One wave's 16 rows of W, walked 256 columns (a round) at a time.
+//
+// Lane = (row mr = lane%16, word mq = lane/16), which is the operand layout of the matrix
+// instruction with the columns of a round renumbered: step t multiplies byte t of every lane's
+// bitmap word, i.e. columns 64*mq + 8*t .. +7, and X is read in the same order.  A lane thus works
+// through its own 64-bit word, its position inside the row's slice held in a register.
+template <int kClass>
+struct RowStreams {
+    using F = Fetch<kClass>;
+    static constexpr int kLoads = (kRows + F::kRowsPer - 1) / F::kRowsPer;
+    struct Pieces {
+        u32x4 d[kLoads + F::kTail];
+    };
+
+    uint32_t mr, mq;
+    uint32_t fu, frow;  // fetching: this lane's unit, and its row inside a load's kRowsPer
+    uintptr_t vbeg, vend;
+    uintptr_t row_first;  // the range's first value of row mr
+    uintptr_t wave_base;  // the unit that holds the range's first value of the wave's first row (wave-uniform)
+    uint32_t delta;       // row_first - wave_base
+    uint32_t lo, hi;      // offsets from wave_base between which units may be read
+    bool far;             // wave-uniform: the rows lie too far apart for 32-bit offsets
+    uint32_t off;         // bytes of the row's values before the next round
+
+    __device__ __forceinline__ void init(uint32_t lane) {
+        mr = lane & 15;
+        mq = lane >> 4;
+        const uint32_t l = lane < F::kRowsPer * F::kUnits ? lane : F::kRowsPer * F::kUnits - 1;
+        frow = l / F::kUnits;
+        fu = l % F::kUnits;
+    }
+
+    // Start a range of columns.  (A range is at most a few thousand rounds long, so offsets inside a
+    // row fit 32 bits whatever the matrix.)
+    __device__ __forceinline__ void begin(uintptr_t vbeg_, uintptr_t vend_, uintptr_t first) {
+        vbeg = vbeg_;
+        vend = vend_;
+        row_first = first;
+        const uintptr_t b = first & ~uintptr_t(15);
+        wave_base = (uintptr_t(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)))) << 32) |
+                    static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)));
+        constexpr uintptr_t kSpan = uintptr_t(1) << 28;
+        far = __builtin_amdgcn_ballot_w64(first - wave_base >= kSpan) != 0;
+        delta = static_cast<uint32_t>(first - wave_base);
+        lo = wave_base >= vbeg ? 0u : static_cast<uint32_t>(vbeg - wave_base);  // a table that lies may put the base anywhere
+        hi = vend <= wave_base ? 0u : vend - wave_base < 2 * kSpan ? static_cast<uint32_t>(vend - wave_base) : uint32_t(2 * kSpan);
+        if (wave_base < vbeg && vbeg - wave_base > 15) hi = 0;
+        off = 0;
+    }
+
+    __device__ __forceinline__ uint32_t load_row(int i) const {
+        const uint32_t row = i * F::kRowsPer + frow;
+        return (i + 1) * F::kRowsPer <= kRows || row < kRows ? row : kRows - 1;
+    }
+
+    // Start a round: its bitmap word is here, its values are asked for.  There is no branch around
+    // the loads (the compiler would wait for them where it ends): a lane without a unit of its own
+    // reads the row's last one again, and a round that cannot be read this way reads a dummy.
+    __device__ __forceinline__ void fetch(uint64_t w, Round &R, Pieces &P) {
+        R.word = w;
+        uint32_t before;
+        const uint32_t cnt = row_sum(__popcll(w), mq, &before);
+        const uint32_t start = delta + off;
+        const uint32_t shift = start & 15u;
+        R.at = mr * kPitch + shift + 2 * before;
+        R.off = off;
+        off += 2 * cnt;
+        R.units = cnt ? (shift + 2 * cnt + 15) >> 4 : 0u;
+        const uint32_t first = start & ~15u;
+        const uint32_t room = hi > first ? (hi - first) >> 4 : 0u;  // whole units from here to the end of `values`
+        R.whole = R.units < room ? R.units : room;
+        R.ragged = __builtin_amdgcn_ballot_w64(R.whole < R.units) != 0;
+        R.late = F::kTail != 0 || __builtin_amdgcn_ballot_w64(R.whole > F::kUnits) == 0 ? kNoneLate : uint32_t(F::kUnits);
+        // a unit before the beginning of `values` (the array is not 16-byte aligned, the very first
+        // row), rows too far apart, next to no values: nothing is asked for ahead
+        const bool here = __builtin_amdgcn_ballot_w64(first < lo) == 0 && hi >= 16 && !far;
+        if (!here) {
+            R.whole = 0;
+            R.ragged = true;
+            R.late = kNoneLate;
+        }
+        const uintptr_t base = here ? wave_base : reinterpret_cast<uintptr_t>(&g_dummy);
+        const uint32_t info = here && R.whole ? (first << 2) | (R.whole - 1) : 0u;  // first unit << 6 | last one to read
+        auto load = [&](uint32_t row_info, uint32_t unit) -> u32x4 {
+            const uint32_t l = row_info & 63u;
+            return *global_ptr<u32x4>(base + (((row_info >> 6) + (unit < l ? unit : l)) << 4));
+        };
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i)
+            P.d[i] = load(static_cast<uint32_t>(
+                              __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * load_row(i)), static_cast<int>(info))), fu);
+        if (F::kTail) P.d[kLoads] = load(info, F::kUnits);
+    }
+
+    // The round's values into LDS.
+    __device__ __forceinline__ void stage(uint8_t *lds, const Round &R, const Pieces &P) const {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) *reinterpret_cast<u32x4 *>(lds + load_row(i) * kPitch + 16 * fu) = P.d[i];
+        if (F::kTail) *reinterpret_cast<u32x4 *>(lds + mr * kPitch + 16 * F::kUnits) = P.d[kLoads];
+        if (R.late == kNoneLate && !R.ragged) return;  // wave-uniform
+        const uintptr_t first = (row_first + R.off) & ~uintptr_t(15);
+        for (uint32_t u = R.late + mq; u < R.whole; u += 4)
+            *reinterpret_cast<u32x4 *>(lds + mr * kPitch + 16 * u) = *global_ptr<u32x4>(first + 16 * u);
+        // the units over an end of `values` (usually one): element by element, zero outside
+        for (uint32_t u = R.whole + mq; u < R.units; u += 4) {
+            uint32_t h[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {  // unconditional loads from a safe address, sorted out afterwards
+                const uintptr_t p = first + 16 * u + 2 * j;
+                const bool in = p >= vbeg && p + 2 <= vend;
+                const uint32_t v = *global_ptr<uint16_t>(in ? p : reinterpret_cast<uintptr_t>(&g_dummy));
+                h[j] = in ? v : 0u;
+            }
+            u32x4 d;
+            d.x = h[0] | (h[1] << 16);
+            d.y = h[2] | (h[3] << 16);
+            d.z = h[4] | (h[5] << 16);
+            d.w = h[6] | (h[7] << 16);
+            *reinterpret_cast<u32x4 *>(lds + mr * kPitch + 16 * u) = d;
+        }
+    }
+};
+
+struct alignas(4) Dwords3 {
+    uint32_t a, b, c;
+};
+
+// Byte t of the lane's word expanded to the 16 bytes of an A operand.  `at`: byte offset in `lds`
+// of the byte's first value; moved on to the next byte's.
+__device__ __forceinline__ u32x4 expand_byte(const NibbleTable &T, const uint8_t *lds, uint64_t word, int t, uint32_t &at) {
+    const uint32_t half = static_cast<uint32_t>(t < 4 ? word : word >> 32);
+    const int sh = 8 * (t & 3);
+    const uint32_t n0 = (sh == 0 ? half << 3 : half >> ((sh - 3) & 31)) & 0x78u;  // low nibble * 8
+    const uint32_t n1 = (half >> (sh + 1)) & 0x78u;                               // high nibble * 8
+    const uint32_t at1 = at + 2 * __popc(n0);
+    const Dwords3 v0 = *reinterpret_cast<const Dwords3 *>(lds + (at & ~3u));
+    const Dwords3 v1 = *reinterpret_cast<const Dwords3 *>(lds + (at1 & ~3u));
+    const uint64_t s0 = *reinterpret_cast<const uint64_t *>(reinterpret_cast<const uint8_t *>(T.sel) + n0);
+    const uint64_t s1 = *reinterpret_cast<const uint64_t *>(reinterpret_cast<const uint8_t *>(T.sel) + n1);
+    const uint32_t x0 = __builtin_amdgcn_alignbyte(v0.b, v0.a, at), x1 = __builtin_amdgcn_alignbyte(v0.c, v0.b, at);
+    const uint32_t y0 = __builtin_amdgcn_alignbyte(v1.b, v1.a, at1), y1 = __builtin_amdgcn_alignbyte(v1.c, v1.b, at1);
+    u32x4 d;
+    d.x = __builtin_amdgcn_perm(x0, x0, static_cast<uint32_t>(s0));
+    d.y = __builtin_amdgcn_perm(x1, x0, static_cast<uint32_t>(s0 >> 32));
+    d.z = __builtin_amdgcn_perm(y0, y0, static_cast<uint32_t>(s1));
+    d.w = __builtin_amdgcn_perm(y1, y0, static_cast<uint32_t>(s1 >> 32));
+    at = at1 + 2 * __popc(n1);
+    return d;
+}
+
+// A round's eight matrix instructions.  kAccs accumulators in turn: shorter chains of sums, and
+// neighbouring instructions are independent.
+__device__ __forceinline__ void multiply_round(const NibbleTable &T, const uint8_t *lds, const uint8_t *xt, uint32_t x_lane,
+                                               const Round &R, f32x4 (&acc)[kAccs]) {
+    uint32_t at = R.at;
+#pragma unroll
+    for (int t = 0; t < kSteps; ++t) {
+        const u32x4 a = expand_byte(T, lds, R.word, t, at);
+        const u32x4 b = *reinterpret_cast<const u32x4 *>(xt + kXStep * t + (x_lane ^ (16 * t)));
+        acc[t % kAccs] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b),
+                                                                acc[t % kAccs], 0, 0, 0);
+    }
+}
 
 struct GemmParams {
     const uint64_t *bitmap;
@@ -92,282 +321,274 @@ struct GemmParams {
     const uint32_t *chunk_total;
     const uint32_t *tile_off;
     const uint16_t *x;  // nb right-hand sides of cols fp16 values, ldx elements apart
-    float *out;         // ksplit == 1: y (nb x rows); else the scratch: ksplit x nb x rows partial sums
+    float *y;           // nb x rows
+    float *partial;     // sums of the row blocks that several workgroups share: slot x nb x kBlockRows
     int64_t rows, cols, nnz, ldx;
     int32_t nb;
-    uint32_t ksplit;
-    uint32_t segs_per_split;  // rounds per column range
-    uint32_t x_fast;          // every fragment of X is a 16-byte aligned, in-range load
+    uint32_t segs;    // rounds per row block (the last one may lie past the last column)
+    uint32_t per_wg;  // rounds per workgroup
+    uint32_t rounds;  // in all
 };
 
 struct alignas(16) GemmScratch {
-    WindowTables tables;  // selectors of the value placement, per byte pattern
-    // per wave and (row, bitmap byte): values of the row's segment before it << 8 | byte
-    uint32_t info[kGemmWaves][kRows][kInfoStride];
-    // the segment's 256 columns of the 16 right-hand sides, for this round and the next
-    alignas(16) uint8_t xt[2][ENDOR_GEMM_MAX_BATCH][kXPitch];
+    NibbleTable table;
+    // the segment's 256 columns of the 16 right-hand sides in the order the steps read them, for
+    // this round and the next
+    alignas(16) uint8_t xt[2][kSteps * kXStep];
+    alignas(16) uint8_t stage[kGemmWaves][kStageBytes];  // per wave: the round's values, row by row
 };
 
-// value of lane `k` of each group of four lanes, in all four
-template <int k>
-__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
-    return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), k * 0x55, 0xf, 0xf, false));
-}
-
-// 64 bits of the bitmap starting at bit position e, of which the first nbits (0..64) count
-__device__ __forceinline__ uint64_t bits_at(const uint64_t *bitmap, int64_t nwords, int64_t e, int64_t nbits) {
-    if (nbits <= 0) return 0;
-    const int64_t w0 = e >> 6;
-    const uint32_t bs = static_cast<uint32_t>(e & 63);
-    uint64_t word = (w0 < nwords ? bitmap[w0] : 0) >> bs;
-    if (bs != 0) word |= (w0 + 1 < nwords ? bitmap[w0 + 1] : 0) << (64 - bs);
-    if (nbits < 64) word &= (uint64_t(1) << nbits) - 1;
-    return word;
-}
-
-__global__ __launch_bounds__(64 * kGemmWaves) void endor_gemm_f16_kernel(GemmParams G) {
+// A workgroup takes per_wg consecutive rounds of the whole product, counted row block by row block
+// (64 rows, a group of 16 per wave) and inside a block from left to right: every workgroup has the
+// same amount of work whatever the shape, and a row block is shared by few of them.  A block that
+// lies inside one workgroup's share is written to y, the parts of the others go to the slot
+// (workgroup + block) of the scratch.
+//
+// kAligned: rows of W start on 64-bit bitmap words (cols a multiple of 64: every model shape) and
+// X moves in whole aligned 16-byte pieces.  The general form funnels a lane's bitmap bits out of
+// two words and loads X element by element.  kXUnits: 16-byte pieces of X per thread and round,
+// 1 for up to eight right-hand sides, else 2.
+template <int kClass, bool kAligned, int kXUnits>
+__global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(GemmParams G) {
     __shared__ GemmScratch S;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // a workgroup: kGemmWaves neighbouring groups of 16 rows, one column range.  A group past
-    // the last row still runs (with no valid row): its wave takes part in loading X.
-    const uint32_t group = (blockIdx.x / G.ksplit) * kGemmWaves + wave;
-    const uint32_t split = blockIdx.x % G.ksplit;
-    const int64_t row0 = int64_t(group) * kRows;
     const int64_t n = G.rows * G.cols;
     const int64_t nwords = (n + 63) >> 6;
-    const int64_t total_segs = (G.cols + kSegCols - 1) / kSegCols;
-    const int64_t seg_begin = int64_t(split) * G.segs_per_split;
-    int64_t seg_end = seg_begin + G.segs_per_split;
-    if (seg_end > total_segs) seg_end = total_segs;
-    const int64_t c_begin = seg_begin * kSegCols;
-
-    window_tables_init(S.tables, threadIdx.x);  // visible after the first round's barrier
-    uint32_t(*info)[kInfoStride] = S.info[wave];
-
-    // ---- loading role: row lr = lane/4, word lj = lane%4 of a segment
-    const uint32_t lr = lane >> 2, lj = lane & 3;
-    const int64_t my_row = row0 + lr;
-    const bool row_ok = my_row < G.rows;
     const uintptr_t vbeg = reinterpret_cast<uintptr_t>(G.values);
     const uintptr_t vend = vbeg + 2 * static_cast<uintptr_t>(G.nnz);
+    nibble_table_init(S.table, threadIdx.x);  // visible after the first round's barrier
+    RowStreams<kClass> V;
+    V.init(lane);
+    const uint32_t mr = V.mr, mq = V.mq;
+    const uint32_t x_lane = x_slot(mr, mq, 0);
 
-    // Cursor of every row at the first column of the range: the number of 1 bits before flat
-    // position e_r = row*cols + c_begin is (start of its chunk) + (tile offset) + (1 bits of
-    // the tile's words below e_r).  Lane r < 16 looks up the first two terms of row r, the
-    // whole wave counts the third for each row in turn; all loads go out before the first
-    // result is needed, so the 16 lookups cost one trip to memory, not sixteen.
-    uintptr_t cursor = vbeg;
-    if (c_begin < G.cols && row0 < G.rows) {  // wave-uniform
-        const int64_t e_first = row0 * G.cols + c_begin;
-        const uint32_t c_first = static_cast<uint32_t>(e_first >> 20);  // chunk = 2^20 positions
-        int64_t last_row = row0 + kRows - 1;
-        if (last_row >= G.rows) last_row = G.rows - 1;
-        const uint32_t span = static_cast<uint32_t>((last_row * G.cols + c_begin) >> 20) - c_first;  // chunks after the first
-        // totals of the chunks the 16 rows start in, scanned: lane k holds sum of chunks c_first .. c_first+k
-        uint32_t incl = 0;
-        uint64_t wide = 0;  // the same for rows so wide that the 16 starts span more than 64 chunks
-        if (span <= 64) {
-            const uint32_t ct = lane < span ? G.chunk_total[c_first + lane] : 0u;
-            incl = endor_device::wave_inclusive_scan(ct);  // < 2^26
-        }
-        const uint64_t cb0 = chunk_base(G.chunk_total, c_first, lane);
-        // per-row part, lane r for row r
-        uint64_t head = 0;  // chunk start + tile offset of row `lane`
-        {
-            const int64_t row = row0 + (lane & 15);
-            const int64_t e = (row < G.rows ? row : last_row) * G.cols + c_begin;
-            const uint32_t c = static_cast<uint32_t>(e >> 20);
-            const uint32_t k = c - c_first;  // <= span
-            uint32_t before_chunk = static_cast<uint32_t>(
-                __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * (k ? k - 1 : 0)), static_cast<int>(incl)));
-            if (k == 0) before_chunk = 0;
-            if (span > 64) {
-                for (uint32_t j = c_first; j < c; ++j) wide += G.chunk_total[j];
-                before_chunk = 0;
+    uint32_t r = blockIdx.x * G.per_wg;
+    const uint32_t r_end = G.rounds - r < G.per_wg ? G.rounds : r + G.per_wg;
+    while (r < r_end) {
+        const uint32_t block = r / G.segs, seg_begin = r % G.segs;
+        const uint32_t left_in_block = G.segs - seg_begin;
+        const uint32_t count = r_end - r < left_in_block ? r_end - r : left_in_block;  // rounds of this part
+        r += count;
+        // a group past the last row still runs (with no valid row): its wave takes part in loading X
+        const int64_t row0 = int64_t(block) * kBlockRows + wave * kRows;
+        const int64_t c_begin = int64_t(seg_begin) * kSegCols;
+        // columns of the part, counted from c_begin
+        const uint32_t width = G.cols - c_begin <= 0 ? 0u : G.cols - c_begin < int64_t(count) * kSegCols ? static_cast<uint32_t>(G.cols - c_begin)
+                                                                            : count * kSegCols;
+
+        // This lane's 64 bitmap bits of a round: row mr, columns 64*mq .. of the round.  In two halves:
+        // the loads alone (unconditional, from a position that exists), and what they mean, once they
+        // are needed.
+        const bool row_ok = row0 + mr < G.rows;
+        const int64_t word_bit = (row_ok ? row0 + mr : 0) * G.cols + c_begin + 64 * mq;  // round 0's first bit
+        const uint64_t *my_words = G.bitmap + (word_bit >> 6);
+        struct WordLoad {
+            uint64_t lo, hi;
+        };
+        auto word_there = [&](uint32_t k) { return row_ok && k * kSegCols + 64 * mq < width; };
+        auto load_word = [&](uint32_t k) -> WordLoad {
+            const bool there = word_there(k);
+            const uint64_t *p = there ? my_words + k * (kSegCols / 64) : G.bitmap;
+            WordLoad L;
+            L.lo = *p;
+            L.hi = 0;
+            if (!kAligned) L.hi = p[there && (word_bit >> 6) + k * (kSegCols / 64) + 1 < nwords ? 1 : 0];
+            return L;
+        };
+        auto take_word = [&](uint32_t k, WordLoad L) -> uint64_t {
+            uint64_t w = L.lo;
+            if (!kAligned) {
+                const uint32_t bs = static_cast<uint32_t>(word_bit & 63);
+                w = (w >> bs) | ((L.hi << 1) << (63 - bs));  // hi << (64 - bs), and nothing when bs is 0
+                const uint32_t have = width - (k * kSegCols + 64 * mq);
+                if (have < 64) w &= (uint64_t(1) << have) - 1;
             }
-            const uint32_t tl = static_cast<uint32_t>((e >> 12) % kTilesPerChunk);
-            head = cb0 + wide + before_chunk + G.tile_off[size_t(c) * kChunkStride + tl];
-        }
-        // the tile's words below e_r, for each row
-        uint64_t words[kRows];
+            return word_there(k) ? w : 0;
+        };
+        WordLoad w0 = load_word(0), w1 = load_word(1), w2 = load_word(2);
+
+        // The round's 256 columns of X go to LDS once per workgroup, 32 pieces of 16 bytes per
+        // right-hand side: thread t carries pieces t and 256 + t through registers (loaded while the
+        // round before is multiplied, stored before the round's barrier).  Columns past the part's
+        // end count as zero.
+        struct XPieces {
+            u32x4 d[kXUnits];
+            uint16_t h[kXUnits][8];
+        };
+        const uint16_t *x_row[kXUnits];
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const int64_t row = row0 + r < G.rows ? row0 + r : last_row;
-            const int64_t e = row * G.cols + c_begin;
-            const int64_t w = (e >> 12) * kTileWords + lane, we = e >> 6;
-            uint64_t word = 0;
-            if (w <= we) word = G.bitmap[w];  // w <= we < number of words
-            if (w == we) word &= (uint64_t(1) << (e & 63)) - 1;
-            words[r] = word;
+        for (int i = 0; i < kXUnits; ++i) {
+            const int b = static_cast<int>(i * 2 * kGemmWaves + (threadIdx.x >> 5));
+            x_row[i] = G.x + int64_t(b < G.nb ? b : G.nb - 1) * G.ldx + c_begin;
         }
-        uint32_t below = 0;  // lane r: 1 bits of row r's tile below e_r
+        const uint32_t x_col = 8 * (threadIdx.x & 31);
+        auto x_fetch = [&](uint32_t k, XPieces &X) {
+            const uint32_t c = k * kSegCols + x_col;
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const uint32_t sum = wave_sum(__popcll(words[r]));
-            if (lane == static_cast<uint32_t>(r)) below = sum;
-        }
-        const uint64_t rank = head + below;  // lane r < 16: row r
-        const uint32_t lo = static_cast<uint32_t>(
-            __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * lr), static_cast<int>(static_cast<uint32_t>(rank))));
-        const uint32_t hi = static_cast<uint32_t>(
-            __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * lr), static_cast<int>(static_cast<uint32_t>(rank >> 32))));
-        cursor = vbeg + 2 * ((uint64_t(hi) << 32) | lo);
-    }
-
-    // ---- multiplying role: row mr = lane%16 (A) / right-hand side mr (B), column block mq = lane/16
-    const uint32_t mr = lane & 15, mq = lane >> 4;
-    const bool x_ok = static_cast<int32_t>(mr) < G.nb;
-
-    // Shapes whose rows start on 64-bit word boundaries (cols a multiple of 64: every model
-    // shape) read a lane's bitmap word with one aligned load; others funnel it out of two.
-    const bool word_rows = (G.cols & 63) == 0;  // wave-uniform
-    const uint64_t *my_words = G.bitmap + ((row_ok ? my_row : 0) * G.cols >> 6) + lj;
-
-    // this lane's 64 bitmap bits of a segment (loading role)
-    auto load_word = [&](int64_t seg) -> uint64_t {
-        const int64_t col = seg * kSegCols + 64 * lj;
-        if (word_rows) return (row_ok && col < G.cols) ? my_words[(seg * kSegCols) >> 6] : 0;
-        return row_ok ? bits_at(G.bitmap, nwords, my_row * G.cols + col, G.cols - col) : 0;
-    };
-
-    // Expansion happens in the loading role (a quad of lanes = four neighbouring bytes of one
-    // row, whose windows share cache lines; with the multiplying role's lane order every lane
-    // of a load would touch a line of its own, and the vector cache's access rate was the
-    // bound: 1400 accesses per round against 400).  The expanded 16 bytes then move to the lane
-    // that multiplies them: lane 16*j + r takes those of lane 4*r + j.
-    const int from_lane = static_cast<int>(4 * (4 * mr + mq));  // byte index for ds_bpermute
-
-    // The segment's 256 columns of X go to LDS once per workgroup: wave w brings the right-hand
-    // sides 4w .. 4w+3 (those below nb), 512 bytes each, with the first 32 lanes.
-    auto load_x_tile = [&](int64_t seg, uint32_t buf) {
-        const int64_t c0 = seg * kSegCols;
-        const bool whole = G.x_fast && c0 + kSegCols <= G.cols;  // aligned 16-byte pieces, all in range
+            for (int i = 0; i < kXUnits; ++i) {
+                if (kAligned) {
+                    X.d[i] = *reinterpret_cast<const u32x4 *>(x_row[i] + (c < width ? c : 0));
+                } else {
 #pragma unroll
-        for (int i = 0; i < ENDOR_GEMM_MAX_BATCH / kGemmWaves; ++i) {
-            const int b = static_cast<int>(wave) * (ENDOR_GEMM_MAX_BATCH / kGemmWaves) + i;
-            if (b < G.nb && lane < 32) {
-                const uint16_t *src = G.x + int64_t(b) * G.ldx + c0;
-                u32x4 *dst = reinterpret_cast<u32x4 *>(S.xt[buf][b]);
-                if (whole) {
-                    load_to_lds16<false>(reinterpret_cast<const u32x4 *>(src) + lane, dst);
+                    for (int j = 0; j < 8; ++j) X.h[i][j] = x_row[i][c + j < width ? c + j : 0];
+                }
+            }
+        };
+        auto x_store = [&](uint32_t k, uint32_t buf, const XPieces &X) {
+            const uint32_t c = k * kSegCols + x_col;
+#pragma unroll
+            for (int i = 0; i < kXUnits; ++i) {
+                u32x4 f;
+                if (kAligned) {
+                    f = X.d[i];
+                    if (c >= width) f = u32x4{0u, 0u, 0u, 0u};
                 } else {
                     uint32_t h[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) h[j] = (c0 + 8 * lane + j < G.cols) ? uint32_t(src[8 * lane + j]) : 0u;
-                    u32x4 f;
+                    for (int j = 0; j < 8; ++j) h[j] = c + j < width ? uint32_t(X.h[i][j]) : 0u;
                     f.x = h[0] | (h[1] << 16);
                     f.y = h[2] | (h[3] << 16);
                     f.z = h[4] | (h[5] << 16);
                     f.w = h[6] | (h[7] << 16);
-                    dst[lane] = f;
                 }
+                const uint32_t b = i * 2 * kGemmWaves + (threadIdx.x >> 5), u = threadIdx.x & 31;
+                *reinterpret_cast<u32x4 *>(S.xt[buf] + x_slot(b, u >> 3, u & 7)) = f;
             }
-        }
-    };
-
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (seg_begin < seg_end) load_x_tile(seg_begin, 0);
-    uint64_t word = seg_begin < seg_end ? load_word(seg_begin) : 0;
-    for (int64_t seg = seg_begin; seg < seg_end; ++seg) {
-        const uint32_t buf = static_cast<uint32_t>(seg - seg_begin) & 1u;
-        // this wave's part of the round's tile of X has landed; after the barrier the whole tile
-        // has, and every wave is through the previous round (whose tile the next load overwrites)
-        wait_loads_to_lds();
-        __syncthreads();
-        if (seg + 1 < seg_end) load_x_tile(seg + 1, buf ^ 1u);
-        // ---- entries of the lane's 8 bitmap bytes
-        const uint32_t pc = __popcll(word);
-        const uint32_t p0 = quad_bcast<0>(pc), p1 = quad_bcast<1>(pc), p2 = quad_bcast<2>(pc), p3 = quad_bcast<3>(pc);
-        const uint32_t cnt = p0 + p1 + p2 + p3;  // values of the row's segment: <= 256
-        {
-            uint32_t at = (lj > 0 ? p0 : 0) + (lj > 1 ? p1 : 0) + (lj > 2 ? p2 : 0);
-            uint32_t e8[8];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const uint32_t byte = static_cast<uint32_t>(word >> (8 * b)) & 0xffu;
-                e8[b] = (at << 8) | byte;
-                at += __popc(byte);
-            }
-            u32x4 lo, hi;
-            lo.x = e8[0];
-            lo.y = e8[1];
-            lo.z = e8[2];
-            lo.w = e8[3];
-            hi.x = e8[4];
-            hi.y = e8[5];
-            hi.z = e8[6];
-            hi.w = e8[7];
-            u32x4 *ip = reinterpret_cast<u32x4 *>(&info[lr][lj * 8]);
-            ip[0] = lo;
-            ip[1] = hi;
-        }
-        // LDS operations of one wave execute in issue order; the fences only pin the compiler
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-        // ---- loads: the next segment's bitmap word, this segment's windows
-        const uint64_t next_word = seg + 1 < seg_end ? load_word(seg + 1) : 0;
-        const uint8_t *xt = &S.xt[buf][mr][16 * mq];  // right-hand side mr, column block mq of step 0
-        // one step's expanded 16 bytes of row lr go to the lane that multiplies them
-        auto step = [&](int t, u32x4 e) {
-            u32x4 a;
-            a.x = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(from_lane, static_cast<int>(e.x)));
-            a.y = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(from_lane, static_cast<int>(e.y)));
-            a.z = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(from_lane, static_cast<int>(e.z)));
-            a.w = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(from_lane, static_cast<int>(e.w)));
-            const u32x4 xb = *reinterpret_cast<const u32x4 *>(xt + 64 * t);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, xb), acc, 0,
-                                                         0, 0);
         };
-        // every window of this round starts in [cursor, cursor + 2 cnt] of its row; all rows' windows
-        // lie inside `values` except in the rounds at the very ends of the array
-        const bool row_inside = windows_inside(cursor, cursor + 2 * uintptr_t(cnt), vbeg, vend);
-        if (__builtin_amdgcn_ballot_w64(!row_inside) == 0) {  // wave-uniform
-            uint32_t entry[kSteps];
-            WindowLoad win[kSteps];
+        XPieces X;
+        x_fetch(0, X);
+
+        // Cursor of every row at the first column of the range: the number of 1 bits before flat
+        // position e_r = row*cols + c_begin is (start of its chunk) + (tile offset) + (1 bits of
+        // the tile's words below e_r).  Lane r < 16 looks up the first two terms of row r, the
+        // whole wave counts the third for each row in turn; all loads go out before the first
+        // result is needed, so the 16 lookups cost one trip to memory, not sixteen.
+        uintptr_t cursor = vbeg;
+        if (c_begin < G.cols && row0 < G.rows) {  // wave-uniform
+            const int64_t e_first = row0 * G.cols + c_begin;
+            const uint32_t c_first = static_cast<uint32_t>(e_first >> 20);  // chunk = 2^20 positions
+            int64_t last_row = row0 + kRows - 1;
+            if (last_row >= G.rows) last_row = G.rows - 1;
+            const uint32_t span = static_cast<uint32_t>((last_row * G.cols + c_begin) >> 20) - c_first;  // chunks after the first
+            // totals of the chunks the 16 rows start in, scanned: lane k holds sum of chunks c_first .. c_first+k
+            uint32_t incl = 0;
+            uint64_t wide = 0;  // the same for rows so wide that the 16 starts span more than 64 chunks
+            if (span <= 64) {
+                const uint32_t ct = lane < span ? G.chunk_total[c_first + lane] : 0u;
+                incl = endor_device::wave_inclusive_scan(ct);  // < 2^26
+            }
+            const uint64_t cb0 = chunk_base(G.chunk_total, c_first, lane);
+            // per-row part, lane r for row r
+            uint64_t head = 0;  // chunk start + tile offset of row `lane`
+            {
+                const int64_t row = row0 + (lane & 15);
+                const int64_t e = (row < G.rows ? row : last_row) * G.cols + c_begin;
+                const uint32_t c = static_cast<uint32_t>(e >> 20);
+                const uint32_t k = c - c_first;  // <= span
+                uint32_t before_chunk = static_cast<uint32_t>(
+                    __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * (k ? k - 1 : 0)), static_cast<int>(incl)));
+                if (k == 0) before_chunk = 0;
+                if (span > 64) {
+                    for (uint32_t j = c_first; j < c; ++j) wide += G.chunk_total[j];
+                    before_chunk = 0;
+                }
+                const uint32_t tl = static_cast<uint32_t>((e >> 12) % kTilesPerChunk);
+                head = cb0 + wide + before_chunk + G.tile_off[size_t(c) * kChunkStride + tl];
+            }
+            // the tile's words below e_r, for each row
+            uint64_t words[kRows];
+    #pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const int64_t row = row0 + r < G.rows ? row0 + r : last_row;
+                const int64_t e = row * G.cols + c_begin;
+                const int64_t w = (e >> 12) * kTileWords + lane, we = e >> 6;
+                uint64_t word = 0;
+                if (w <= we) word = G.bitmap[w];  // w <= we < number of words
+                if (w == we) word &= (uint64_t(1) << (e & 63)) - 1;
+                words[r] = word;
+            }
+            uint32_t below = 0;  // lane r: 1 bits of row r's tile below e_r
+    #pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const uint32_t sum = wave_sum(__popcll(words[r]));
+                if (lane == static_cast<uint32_t>(r)) below = sum;
+            }
+            const uint64_t rank = head + below;  // lane r < 16: row r
+            const uint32_t lo = static_cast<uint32_t>(
+                __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * mr), static_cast<int>(static_cast<uint32_t>(rank))));
+            const uint32_t hi = static_cast<uint32_t>(
+                __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * mr), static_cast<int>(static_cast<uint32_t>(rank >> 32))));
+            cursor = vbeg + 2 * ((uint64_t(hi) << 32) | lo);
+        }
+
+        V.begin(vbeg, vend, cursor);
+
+        // A round's values are in flight while the one before is multiplied, its bitmap words one
+        // round longer.  The loop body handles two rounds: no register is copied from one buffer to
+        // the other (a copy would wait for the load).
+        f32x4 acc[kAccs] = {};
+        typename RowStreams<kClass>::Pieces P;
+        Round R;
+        V.fetch(take_word(0, w0), R, P);
+        auto round = [&](uint32_t k, int buf, WordLoad &wk) {
+            // the round's values and tile of X have arrived; after the barrier the whole tile is in
+            // LDS, and every wave is through the round before (whose tile is stored over next)
+            x_store(k, buf, X);
+            V.stage(S.stage[wave], R, P);
+            __syncthreads();
+            const Round now = R;
+            x_fetch(k + 1, X);
+            const uint64_t w = take_word(k + 1, wk);
+            wk = load_word(k + 3);
+            V.fetch(w, R, P);
+            multiply_round(S.table, S.stage[wave], S.xt[buf], x_lane, now, acc);
+            wave_lds_sync();  // the next round's LDS writes must stay behind this round's LDS reads
+        };
+        // always whole pairs: a round past the part's end has no bits and a tile of X of zeros
+        for (uint32_t k = 0; k < count; k += 2) {
+            round(k, 0, w1);
+            round(k + 1, 1, w2);
+        }
+        __syncthreads();  // every wave is through with the tiles of X before the next part's are stored
+
+        // ---- lane l holds rows 4*(l/16) .. +3 of right-hand side l%16
+        f32x4 sum = acc[0];
 #pragma unroll
-            for (int t = 0; t < kSteps; ++t) entry[t] = info[lr][t * 4 + lj];
+        for (int k = 1; k < kAccs; ++k) sum += acc[k];
+        if (static_cast<int32_t>(mr) < G.nb) {
+            if (count == G.segs) {
+                float *dst = G.y + int64_t(mr) * G.rows + row0 + 4 * mq;
 #pragma unroll
-            for (int t = 0; t < kSteps; ++t) win[t] = window_issue(cursor + 2 * uintptr_t(entry[t] >> 8));
-#pragma unroll
-            for (int t = 0; t < kSteps; ++t)
-                step(t, place_window(S.tables, entry[t] & 0xffu,
-                                     window_finish(win[t], cursor + 2 * uintptr_t(entry[t] >> 8))));
-        } else {
-#pragma unroll 1
-            for (int t = 0; t < kSteps; ++t) {
-                const uint32_t entry = info[lr][t * 4 + lj];
-                step(t, place_window(S.tables, entry & 0xffu,
-                                     window_guarded(cursor + 2 * uintptr_t(entry >> 8), vbeg, vend)));
+                for (int i = 0; i < 4; ++i)
+                    if (row0 + 4 * mq + i < G.rows) dst[i] = sum[i];
+            } else {
+                const size_t slot = size_t(blockIdx.x) + block;
+                *reinterpret_cast<f32x4 *>(G.partial + (slot * G.nb + mr) * kBlockRows + wave * kRows + 4 * mq) = sum;
             }
         }
-        // the next round's LDS writes must stay behind this round's LDS reads
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        cursor += 2 * uintptr_t(cnt);
-        word = next_word;
-    }
-
-    // ---- lane l holds rows 4*(l/16) .. +3 of right-hand side l%16
-    if (x_ok) {
-        float *dst = G.out + (size_t(split) * G.nb + mr) * G.rows + row0 + 4 * mq;
-        const float a4[4] = {acc[0], acc[1], acc[2], acc[3]};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (row0 + 4 * mq + i < G.rows) dst[i] = a4[i];
     }
 }
 
-// y[b][i] = sum over the column ranges, in ascending order
+// y[b][i] = the parts of row i's block, added in ascending order.  One workgroup per row block.
 __global__ __launch_bounds__(256) void endor_gemm_reduce_kernel(const float *__restrict__ partial, float *__restrict__ y,
-                                                                int64_t count, uint32_t ksplit) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= count) return;
-    float s = partial[i];
-    for (uint32_t k = 1; k < ksplit; ++k) s += partial[size_t(k) * count + i];
-    y[i] = s;
+                                                                int64_t rows, int32_t nb, uint32_t segs, uint32_t per_wg) {
+    const uint32_t block = blockIdx.x;
+    const uint32_t first = uint32_t(uint64_t(block) * segs / per_wg), last = uint32_t((uint64_t(block + 1) * segs - 1) / per_wg);
+    if (first == last) return;  // one workgroup's block: written already
+    for (uint32_t i = threadIdx.x; i < uint32_t(nb) * kBlockRows; i += 256) {
+        const int64_t row = int64_t(block) * kBlockRows + i % kBlockRows;
+        const float *src = partial + size_t(first + block) * nb * kBlockRows + i;
+        const size_t step = size_t(nb) * kBlockRows;
+        float s = src[0];
+        uint32_t k = first + 1;
+        for (; k + 3 <= last; k += 4, src += 4 * step) {
+            const float a = src[step], b = src[2 * step], c = src[3 * step], d = src[4 * step];
+            s = (((s + a) + b) + c) + d;
+        }
+        for (; k <= last; ++k, src += step) s += src[step];
+        if (row < rows) y[(i / kBlockRows) * rows + row] = s;
+    }
 }
 
 __global__ __launch_bounds__(256) void endor_gemm_zero_kernel(float *__restrict__ y, int64_t count) {
@@ -375,38 +596,69 @@ __global__ __launch_bounds__(256) void endor_gemm_zero_kernel(float *__restrict_
     if (i < count) y[i] = 0.0f;
 }
 
-// Column ranges per row group.  The chip holds kResident workgroups at a time (four per compute
-// unit: 104 registers give four waves per SIMD, and a workgroup puts one wave on each), so the
-// launch runs in ceil(workgroups / kResident) waves of workgroups, each as long as one
-// workgroup: its rounds plus a start-up worth about two.  Pick the split that minimises the
-// product (measured on 28672 x 8192: 4 ranges 98 us, 6 ranges, which spill into a third wave,
-// 111 us; on 8192 x 28672: 8 ranges, exactly one wave of workgroups, 84 us, 10 ranges 94 us),
-// the smaller one on a tie.
-constexpr int64_t kResident = 256 * 4;
-uint32_t choose_split(int64_t rows, int64_t cols) {
-    const int64_t groups = (rows + kRows - 1) / kRows;
-    const int64_t wgs = (groups + kGemmWaves - 1) / kGemmWaves;
-    const int64_t segs = (cols + kSegCols - 1) / kSegCols;
-    int64_t best = 1, best_cost = -1;
-    for (int64_t k = 1; k <= kMaxSplit && k <= segs; ++k) {
-        const int64_t per = (segs + k - 1) / k;
-        if ((k - 1) * per >= segs) continue;  // the last range would be empty
-        const int64_t cost = ((wgs * k + kResident - 1) / kResident) * (per + 2);
-        if (best_cost < 0 || cost < best_cost) {
-            best = k;
-            best_cost = cost;
-        }
+// How the product's rounds are shared out: every workgroup gets the same number of consecutive
+// rounds, so many that kResident workgroups (two per compute unit: 52 KB of LDS and up to 256
+// registers each) do all of them at once, and so many that a row block has at most kMaxParts parts.
+// Whole blocks, which need no second kernel, where that costs a workgroup no more than kWholeSlack
+// rounds (the kernel takes about as long as two rounds).  Small products, kSmall rounds or fewer per
+// workgroup, run as workgroups of two rounds (they are taken in pairs).  These, and those that fit
+// the chip at once, never reach into a second block: starting on a block takes as long as several
+// rounds (2053 x 1031: 13.8 us, 19.7 us with workgroups that cross from block to block).
+constexpr int64_t kResident = 256 * 2;
+constexpr int64_t kMaxParts = 16;
+constexpr int64_t kWholeSlack = 2;
+constexpr int64_t kSmall = 4;
+
+struct Plan {
+    uint32_t blocks, segs, per_wg, rounds, wgs;
+    bool split;  // some row block is shared
+};
+
+Plan make_plan(int64_t rows, int64_t cols) {
+    Plan p;
+    const int64_t blocks = (rows + kBlockRows - 1) / kBlockRows;
+    int64_t segs = (cols + kSegCols - 1) / kSegCols;
+    int64_t per = (blocks * segs + kResident - 1) / kResident;  // blocks * segs is below 2^27: rows*cols < 2^34
+    per = (per + 1) & ~int64_t(1);
+    if (per <= kSmall) per = 2;
+    const int64_t least = (segs + kMaxParts - 1) / kMaxParts;
+    if (per < least) per = least;
+    const int64_t parts = (segs + per - 1) / per;
+    if (per <= kSmall || blocks * parts <= kResident) segs = parts * per;  // rounds past the last column have no bits
+    const int64_t rounds = blocks * segs;
+    const int64_t whole = (per + segs - 1) / segs * segs;
+    if (whole - per <= kWholeSlack) per = whole;
+    p.blocks = static_cast<uint32_t>(blocks);
+    p.segs = static_cast<uint32_t>(segs);
+    p.per_wg = static_cast<uint32_t>(per);
+    p.rounds = static_cast<uint32_t>(rounds);
+    p.wgs = static_cast<uint32_t>((rounds + per - 1) / per);
+    p.split = per % segs != 0;
+    return p;
+}
+
+template <int kClass>
+void launch_gemm(const GemmParams &G, bool aligned, dim3 grid, dim3 block, hipStream_t s) {
+    if (G.nb <= 8) {
+        if (aligned)
+            hipLaunchKernelGGL((endor_gemm_f16_kernel<kClass, true, 1>), grid, block, 0, s, G);
+        else
+            hipLaunchKernelGGL((endor_gemm_f16_kernel<kClass, false, 1>), grid, block, 0, s, G);
+    } else {
+        if (aligned)
+            hipLaunchKernelGGL((endor_gemm_f16_kernel<kClass, true, 2>), grid, block, 0, s, G);
+        else
+            hipLaunchKernelGGL((endor_gemm_f16_kernel<kClass, false, 2>), grid, block, 0, s, G);
     }
-    return static_cast<uint32_t>(best);
 }
 
 }  // namespace
 
 extern "C" size_t endor_gemm_scratch_bytes(int64_t rows, int64_t cols, int nb) {
     if (!dims_ok(rows, cols) || nb < 1 || nb > ENDOR_GEMM_MAX_BATCH || rows == 0 || cols == 0) return 0;
-    const uint32_t ksplit = choose_split(rows, cols);
-    if (ksplit == 1) return 0;
-    return (static_cast<size_t>(ksplit) * nb * rows * sizeof(float) + 255) & ~size_t(255);
+    const Plan p = make_plan(rows, cols);
+    if (!p.split) return 0;
+    return ((size_t(p.wgs) + p.blocks) * nb * kBlockRows * sizeof(float) + 255) & ~size_t(255);
 }
 
 extern "C" endor_status endor_gemm_f16(int64_t rows, int64_t cols, const uint8_t *d_bitmap, const uint16_t *d_values,
@@ -433,9 +685,9 @@ extern "C" endor_status endor_gemm_f16(int64_t rows, int64_t cols, const uint8_t
     const int64_t n = rows * cols;
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 255)) return ENDOR_ERR_INVALID_ARG;
     if (workspace_bytes < workspace_bytes_n(n)) return ENDOR_ERR_BUFFER_TOO_SMALL;
-    const uint32_t ksplit = choose_split(rows, cols);
+    const Plan p = make_plan(rows, cols);
     const size_t need = endor_gemm_scratch_bytes(rows, cols, nb);
-    if (ksplit > 1) {
+    if (p.split) {
         if (!d_scratch || (reinterpret_cast<uintptr_t>(d_scratch) & 255)) return ENDOR_ERR_INVALID_ARG;
         if (scratch_bytes < need) return ENDOR_ERR_BUFFER_TOO_SMALL;
     }
@@ -445,23 +697,29 @@ extern "C" endor_status endor_gemm_f16(int64_t rows, int64_t cols, const uint8_t
     G.chunk_total = static_cast<const uint32_t *>(d_workspace);
     G.tile_off = reinterpret_cast<const uint32_t *>(static_cast<const char *>(d_workspace) + chunk_total_bytes(n));
     G.x = d_x;
-    G.out = ksplit == 1 ? d_y : static_cast<float *>(d_scratch);
+    G.y = d_y;
+    G.partial = static_cast<float *>(d_scratch);
     G.rows = rows;
     G.cols = cols;
     G.nnz = nnz;
     G.ldx = ldx;
     G.nb = nb;
-    G.ksplit = ksplit;
-    const int64_t segs = (cols + kSegCols - 1) / kSegCols;
-    G.segs_per_split = static_cast<uint32_t>((segs + ksplit - 1) / ksplit);
-    G.x_fast = ((reinterpret_cast<uintptr_t>(d_x) & 15) == 0 && (ldx * 2) % 16 == 0) ? 1u : 0u;
-    const int64_t groups = (rows + kRows - 1) / kRows;
-    const int64_t blocks = (groups + kGemmWaves - 1) / kGemmWaves * ksplit;
-    hipLaunchKernelGGL(endor_gemm_f16_kernel, dim3(static_cast<unsigned>(blocks)), dim3(64 * kGemmWaves), 0, s, G);
+    G.segs = p.segs;
+    G.per_wg = p.per_wg;
+    G.rounds = p.rounds;
+    const bool aligned = cols % 64 == 0 && (reinterpret_cast<uintptr_t>(d_x) & 15) == 0 && ldx % 8 == 0;
+    const dim3 grid(p.wgs), block(64 * kGemmWaves);
+    // How many units of a row are asked for ahead, by the average density: 3.5 standard deviations
+    // of a row's count in a round (16 sqrt(p (1 - p)) values) above its mean still fit.
+    if (nnz <= n / 50 * 13)
+        launch_gemm<0>(G, aligned, grid, block, s);
+    else if (nnz <= n / 50 * 26)
+        launch_gemm<1>(G, aligned, grid, block, s);
+    else
+        launch_gemm<2>(G, aligned, grid, block, s);
     if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
-    if (ksplit > 1) {
-        hipLaunchKernelGGL(endor_gemm_reduce_kernel, dim3(static_cast<unsigned>((count + 255) / 256)), dim3(256), 0, s,
-                           static_cast<const float *>(d_scratch), d_y, count, ksplit);
+    if (p.split) {
+        hipLaunchKernelGGL(endor_gemm_reduce_kernel, dim3(p.blocks), dim3(256), 0, s, G.partial, d_y, rows, nb, p.segs, p.per_wg);
         if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
     }
     return ENDOR_OK;

@@ -769,6 +769,32 @@ def test_gemm_is_exact_on_integer_valued_inputs(shape):
     assert np.array_equal(got, orc.gemm_f16(rows, cols, c.bitmap, c.values, X16))
 
 
+@pytest.mark.parametrize("keep", [0.1, 0.4, 0.8], ids=["sparse", "half", "dense"])
+@pytest.mark.parametrize("shape", [(63, 255), (65, 257), (129, 513), (200, 5000), (70, 8449), (1100, 768)], ids=str)
+@pytest.mark.parametrize("nb", [8, 9])
+def test_gemm_rounds_parts_and_overfull_rows_are_exact(shape, keep, nb):
+    """The edges of the product's partition (16-row groups, 64-row blocks, 256-column rounds, row
+    blocks cut into several workgroups' parts) on every density class of the value prefetch, with
+    rows that hold more values than it asks for ahead, an empty row, and `values` off its 16-byte
+    boundary at both ends.  Small integers: every sum is exact in fp32, so the result must be equal."""
+    rows, cols = shape
+    _say(f"gemm edges shape={shape} keep={keep} nb={nb}")
+    g = np.random.default_rng(rows * 7 + cols + nb)
+    p = np.full(rows, keep)
+    p[3::17] = 1.0
+    p[7] = 0.0
+    wi = (g.integers(1, 9, (rows, cols)) * (g.random((rows, cols)) < p[:, None])).astype(np.float16)
+    X16 = g.integers(-8, 9, (nb, cols)).astype(np.float16)
+    c = endor.compress(wi)
+    buf = torch.full((c.nnz + 16,), 0x7E00, dtype=torch.int16, device="cuda")          # NaN patterns around
+    buf[5:5 + c.nnz] = torch.from_numpy(c.values.view(np.int16)).cuda()
+    m = endor.DeviceMatrix(rows, cols, torch.from_numpy(c.bitmap).cuda(), buf[5:5 + c.nnz], c.nnz)
+    ws, _ = endor.build_offsets(m)
+    Y = endor.gemm_f16(m, ws, torch.from_numpy(X16.view(np.int16)).cuda().view(torch.float16))
+    torch.cuda.synchronize()
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.gemm_f16(rows, cols, c.bitmap, c.values, X16))
+
+
 def test_gemm_subnormal_inputs_count_in_full():
     rows, cols = 20, 700
     g = np.random.default_rng(5)
