@@ -398,11 +398,12 @@ def compress_device(dense, values=None, row_offsets: bool = False, stream=None):
         values = torch.empty(rows * cols, dtype=torch.int16 if eb == 2 else torch.uint8, device=dev)
     ws = _new_workspace(workspace_bytes(rows, cols), dev)
     ro = torch.empty(rows + 1, dtype=torch.int64, device=dev) if row_offsets else None
-    nnz = torch.zeros(1, dtype=torch.int64, device=dev)
+    nnz = torch.empty(1, dtype=torch.int64, pin_memory=True)  # the kernels write it across the host link
     fn = lib().endor_compress_device if eb == 2 else lib().endor_compress_device_u8
     _check(fn(rows, cols, _dptr(dense), _dptr(bitmap), _dptr(values), values.numel(), _dptr(ws), ws.numel(),
               _dptr(ro), _dptr(nnz), _stream_handle(stream)), "endor_compress_device")
-    n = int(nnz.item())
+    (torch.cuda.current_stream() if stream is None else stream).synchronize()
+    n = int(nnz)
     if n > values.numel():
         raise EndorError(2, f"endor_compress_device: {n} non-zeros, capacity {values.numel()}")
     return DeviceMatrix(rows, cols, bitmap, values[:n], n), ws, ro

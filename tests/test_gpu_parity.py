@@ -583,6 +583,18 @@ def test_compress_device_u8_matches_oracle(shape):
     _check_device_compress(synth.pruned_int8(shape[0], shape[1], 0.5, seed=sum(shape)))
 
 
+@pytest.mark.parametrize("shape", [(9000, 1), (5000, 3), (700, 64), (3, 9000), (257, 4096), (1, 8192)], ids=str)
+@pytest.mark.parametrize("wide", [True, False], ids=["fp16", "u8"])
+def test_compress_device_row_offsets_written_while_packing(shape, wide):
+    """Row starts per tile from none to 4096, at tile starts, word starts and inside words."""
+    g = np.random.default_rng(shape[0] + shape[1])
+    w = g.integers(1, 200, shape).astype(np.uint16 if wide else np.uint8)
+    w[g.random(shape) < 0.5] = 0
+    _, v, ro = orc.compress(w)
+    m, _, dro = endor.compress_device(torch.from_numpy(w.view(np.int16) if wide else w).cuda(), row_offsets=True)
+    assert m.nnz == v.size and np.array_equal(dro.cpu().numpy(), ro)
+
+
 def test_compress_device_counting_pass_and_capacity():
     w = synth.pruned_fp16(100, 4099, 0.5, seed=3)
     nnz_true = int(np.count_nonzero(w))
