@@ -156,7 +156,8 @@ __device__ __forceinline__ u32x4 place_window(const WindowTables &T, uint32_t bi
 // The 16 bytes (8 values of 16 bits) at byte address p, which is 2-byte aligned only.  Read as
 // the 20 bytes from the dword boundary below p and shifted into place: a load whose address
 // is not a multiple of 4 costs the cache nearly twice the accesses (measured).  Normal cached
-// loads: the windows overlap.
+// loads: the windows overlap.  The first 16 of the 20 bytes are loaded, the last 4 come from
+// another lane's window (window_fifth).
 //
 // In two halves, so that a caller issues the loads of all its windows before it uses the
 // first; the caller guarantees that the 20 bytes lie inside the array.  (With the load under a
@@ -166,31 +167,32 @@ __device__ __forceinline__ u32x4 place_window(const WindowTables &T, uint32_t bi
 // through window_guarded in a loop of their own.)
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 
-struct WindowLoad {
-    u32x4 d;      // the four dwords from the dword boundary at or below p
-    uint32_t d4;  // the fifth: the last value of a shifted window
-};
-
 // true when every window that starts in [first, last] can be read with window_issue
 __device__ __forceinline__ bool windows_inside(uintptr_t first, uintptr_t last, uintptr_t vbeg, uintptr_t vend) {
     return (first & ~uintptr_t(3)) >= vbeg && last + 20 <= vend;
 }
 
-__device__ __forceinline__ WindowLoad window_issue(uintptr_t p) {
-    const uintptr_t a = p & ~uintptr_t(3);
-    WindowLoad L;
-    L.d = *global_ptr<u32x4_a4>(a);
-    L.d4 = *global_ptr<uint32_t>(a + 16);
-    return L;
+// `base`: wave-uniform, on a dword boundary; `off`: the window's byte offset from it.
+__device__ __forceinline__ u32x4 window_issue(uintptr_t base, uint32_t off) {
+    return *global_ptr<u32x4_a4>(base + (off & ~3u));
 }
 
-__device__ __forceinline__ u32x4 window_finish(const WindowLoad &L, uintptr_t p) {
-    const uint32_t sh = static_cast<uint32_t>(p) & 3u;  // 0 or 2
+// The fifth dword, which holds the last value of a shifted window, matters to a byte with all 8 bits
+// set only, and then it is the first dword of the next byte's window.  So where lane l + 1 holds
+// the next byte's window, it comes from there (`after`: the one after lane 63's) and not from memory:
+// a vector load costs its 16 address clocks however little it brings.
+__device__ __forceinline__ uint32_t window_fifth(u32x4 d, uint32_t after) {
+    return static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(static_cast<int>(after), static_cast<int>(d.x), 0x130, 0xf, 0xf, false));  // wave_shl:1
+}
+
+__device__ __forceinline__ u32x4 window_finish(u32x4 d, uint32_t fifth, uint32_t off) {
+    const uint32_t sh = off & 3u;  // 0 or 2
     u32x4 w;
-    w.x = __builtin_amdgcn_alignbyte(L.d.y, L.d.x, sh);
-    w.y = __builtin_amdgcn_alignbyte(L.d.z, L.d.y, sh);
-    w.z = __builtin_amdgcn_alignbyte(L.d.w, L.d.z, sh);
-    w.w = __builtin_amdgcn_alignbyte(L.d4, L.d.w, sh);
+    w.x = __builtin_amdgcn_alignbyte(d.y, d.x, sh);
+    w.y = __builtin_amdgcn_alignbyte(d.z, d.y, sh);
+    w.z = __builtin_amdgcn_alignbyte(d.w, d.z, sh);
+    w.w = __builtin_amdgcn_alignbyte(fifth, d.w, sh);
     return w;
 }
 

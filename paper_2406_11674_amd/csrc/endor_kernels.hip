@@ -60,7 +60,7 @@ using endor_device::load_to_lds16;
 using endor_device::window_finish;
 using endor_device::window_guarded;
 using endor_device::window_issue;
-using endor_device::WindowLoad;
+using endor_device::window_fifth;
 using endor_device::windows_inside;
 using endor_device::place_window;
 using endor_device::window_tables_init;
@@ -776,7 +776,7 @@ struct GemvParams {
 // y[i] = sum_j W[i][j] * x[j] straight from the compressed form: the dense row is never
 // written.  One wave per row walks the row's 4096-column segments.  Per segment: popcount and
 // scan the lane's bitmap word, leave one entry per bitmap byte in LDS ((values of the segment
-// before the byte) << 8 | the byte); then a lane takes the bytes lane, 64 + lane, ... in turn,
+// before the byte) << 9 | the byte); then a lane takes the bytes lane, 64 + lane, ... in turn,
 // reads each byte's window of values straight from memory, places the values by the byte's
 // bit pattern and feeds the fp16 pairs to multiply-adds against the matching 8 entries of x.
 // Elements whose bit is 0 enter as +0.0, as they would from the dense matrix.  The next
@@ -786,7 +786,11 @@ struct GemvParams {
 // with x shared through LDS as below 64-67 us; a wave taking four rows in turn 143 us: a wave's
 // segments run one after the other, so what counts is the number of independent waves.  Counters
 // of the 72 us form: the vector cache handles some 530 line accesses per segment, 128 of them
-// for x, where 200 would do if no two lanes shared a line.)
+// for x, where 200 would do if no two lanes shared a line.)  Since then: loads issued back to back,
+// the fifth dword of a window from the neighbouring lane instead of from memory, and the windows
+// addressed by 32-bit offsets from a scalar base: 8192 x 28672 with inputs not in any cache 67 ->
+// 60 us, 4.4 TB/s; the vector ALUs are busy two thirds of the time, and a wave waits for its
+// windows.  More waves per unit by a register cap (80 or 64 instead of 96): 4 and 25 % slower.
 constexpr int kGemvSeg = 4096;  // columns a wave expands at a time
 
 // kFastX: x is 16-byte aligned and cols a multiple of 8, so x moves in whole aligned 16-byte
@@ -815,7 +819,10 @@ __global__ __launch_bounds__(64 * kGemvWaves) void endor_gemv_f16_kernel(GemvPar
     const int64_t row_bit = (row_ok ? i : 0) * G.cols;
     const uintptr_t vbeg = reinterpret_cast<uintptr_t>(G.values);
     const uintptr_t vend = vbeg + 2 * static_cast<uintptr_t>(G.nnz);
-    uint64_t next_value = row_ok ? static_cast<uint64_t>(G.row_offsets[i]) : 0;
+    // wave-uniform, and the compiler has to know: the window loads then take it from scalar registers
+    const uint64_t row_first = row_ok ? static_cast<uint64_t>(G.row_offsets[i]) : 0;
+    uint64_t next_value = (uint64_t(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(row_first >> 32)))) << 32) |
+                          static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(row_first)));
     GemvSink sink;
     sink.acc = 0.0f;
 
@@ -866,13 +873,16 @@ __global__ __launch_bounds__(64 * kGemvWaves) void endor_gemv_f16_kernel(GemvPar
         const uint32_t pc = __popcll(word);
         const uint32_t incl = wave_inclusive_scan(pc);
         const uint32_t cnt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+        const uintptr_t vseg = vbeg + 2 * next_value;  // the segment's first value
+        const uintptr_t vbase = vseg & ~uintptr_t(3);
         {
-            uint32_t at = incl - pc;  // values of the segment before this lane's word
+            // values of the segment before this lane's word, from the dword boundary below its first value
+            uint32_t at = incl - pc + (static_cast<uint32_t>(vseg) >> 1 & 1u);
             uint32_t e8[8];
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
                 const uint32_t byte = static_cast<uint32_t>(word >> (8 * b)) & 0xffu;
-                e8[b] = (at << 8) | byte;
+                e8[b] = (at << 9) | byte;
                 at += __popc(byte);
             }
             u32x4 lo, hi;
@@ -888,24 +898,28 @@ __global__ __launch_bounds__(64 * kGemvWaves) void endor_gemv_f16_kernel(GemvPar
             reinterpret_cast<u32x4 *>(entry)[2 * lane + 1] = hi;
         }
         wave_lds_sync();
-        const uintptr_t vseg = vbeg + 2 * next_value;
         if (windows_inside(vseg, vseg + 2 * uintptr_t(cnt), vbeg, vend)) {  // wave-uniform
             uint32_t e[kGemvSeg / 512];
-            WindowLoad win[kGemvSeg / 512];
+            u32x4 win[kGemvSeg / 512];
 #pragma unroll
             for (int k = 0; k < kGemvSeg / 512; ++k) e[k] = entry[k * 64 + lane];
 #pragma unroll
-            for (int k = 0; k < kGemvSeg / 512; ++k) win[k] = window_issue(vseg + 2 * uintptr_t(e[k] >> 8));
+            for (int k = 0; k < kGemvSeg / 512; ++k) win[k] = window_issue(vbase, e[k] >> 8);
+            // the first dword after the segment's last window, for lane 63's last byte
+            const uint32_t end = *global_ptr<uint32_t>((vseg + 2 * uintptr_t(cnt)) & ~uintptr_t(3));
 #pragma unroll
             for (int k = 0; k < kGemvSeg / 512; ++k) {
-                const u32x4 w = window_finish(win[k], vseg + 2 * uintptr_t(e[k] >> 8));
+                const uint32_t after = k + 1 < kGemvSeg / 512
+                                           ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(win[(k + 1) % (kGemvSeg / 512)].x)))
+                                           : end;
+                const u32x4 w = window_finish(win[k], window_fifth(win[k], after), e[k] >> 8);
                 sink(place_window(s_tables, e[k] & 0xffu, w), s_x[buf][k * 64 + lane]);
             }
         } else {  // a segment at the very beginning or end of `values`
 #pragma unroll 1
             for (int k = 0; k < kGemvSeg / 512; ++k) {
                 const uint32_t e = entry[k * 64 + lane];
-                const u32x4 w = window_guarded(vseg + 2 * uintptr_t(e >> 8), vbeg, vend);
+                const u32x4 w = window_guarded(vbase + (e >> 8), vbeg, vend);
                 sink(place_window(s_tables, e & 0xffu, w), s_x[buf][k * 64 + lane]);
             }
         }

@@ -693,6 +693,26 @@ def test_gemv_unaligned_x_and_device_row_offsets():
     assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - ref) <= _gemv_tolerance(w, x16, cols))
 
 
+@pytest.mark.parametrize("keep", [1.0, 0.97, 0.5])
+@pytest.mark.parametrize("voff", [0, 1, 2, 3])
+def test_gemv_full_bytes_take_their_last_value_from_the_next_window(keep, voff):
+    """A bitmap byte with all bits set whose values start in the middle of a dword needs a fifth
+    dword, which another lane's window (for lane 63: another step's, for the last byte of a segment:
+    a load of its own) provides.  Every alignment of the row starts, two and a bit segments per row;
+    small integers, so the result must be exact."""
+    rows, cols = 11, 2 * 4096 + 513
+    g = np.random.default_rng(voff + int(100 * keep))
+    wi = (g.integers(1, 9, (rows, cols)) * (g.random((rows, cols)) < keep)).astype(np.float16)
+    x16 = g.integers(-8, 9, cols).astype(np.float16)
+    c = endor.compress(wi)
+    buf = torch.full((c.nnz + 16,), 0x7E00, dtype=torch.int16, device="cuda")          # NaN patterns around
+    buf[voff:voff + c.nnz] = torch.from_numpy(c.values.view(np.int16)).cuda()
+    m = endor.DeviceMatrix(rows, cols, torch.from_numpy(c.bitmap).cuda(), buf[voff:voff + c.nnz], c.nnz)
+    y = endor.gemv_f16(m, torch.from_numpy(c.row_offsets).cuda(), torch.from_numpy(x16.view(np.int16)).cuda().view(torch.float16))
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy().astype(np.float64), orc.gemv_f16(rows, cols, c.bitmap, c.values, x16))
+
+
 def test_gemv_nonfinite_x_like_the_dense_product():
     rows, cols = 4, 100
     w = synth.pruned_fp16(rows, cols, 0.5, seed=9)
