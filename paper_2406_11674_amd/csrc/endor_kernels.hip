@@ -495,6 +495,78 @@ __global__ __launch_bounds__(64) void endor_expand_kernel(BatchParams P) {
     expand_tile<E>(s_scratch, lane, word, vbeg + E * (base + o0), cnt, vbeg, vend, sink);
 }
 
+// Both kernels in one for a small matrix: a workgroup of kSmallWaves waves (one tile each) counts the
+// bitmap before its tiles itself, all of it, instead of reading a table another kernel has to build
+// first, and writes its part of the table on the way.  Two dependent launches were most of the time
+// of a small call; the bitmap is read n/2^16 times on average, from the second-level cache.
+constexpr int kSmallWaves = 4;
+
+template <int E, bool kAlignedOut>
+__global__ __launch_bounds__(64 * kSmallWaves) void endor_decompress_small_kernel(MatParams M) {
+    __shared__ WaveScratch<E> s_scratch[kSmallWaves];
+    __shared__ uint32_t s_before[2][kSmallWaves];  // 1 bits before the workgroup's chunk, and from there to its first tile
+    __shared__ uint32_t s_cnt[kSmallWaves];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t tile0 = blockIdx.x * kSmallWaves;  // a chunk's tiles are a multiple of a workgroup's
+    const uint32_t tile = tile0 + wave;
+    const uint32_t c = tile0 / kTilesPerChunk;
+    const int64_t full_words = M.n >> 6;
+    const uint32_t tail_bits = static_cast<uint32_t>(M.n & 63);
+    const uint32_t ntiles = static_cast<uint32_t>((M.n + kTileElems - 1) / kTileElems);
+    const uint64_t word = load_word_guarded(M.bitmap, int64_t(tile) * kTileWords + lane, full_words, tail_bits);
+
+    // the words before the workgroup's tiles (all of them complete), eight per thread and pass
+    uint32_t before[2] = {0, 0};
+    const uint32_t nwords = tile0 * kTileWords, chunk_word = c * kTilesPerChunk * kTileWords;
+    for (uint32_t w0 = 0; w0 < nwords; w0 += 8 * 64 * kSmallWaves) {
+        uint64_t x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t w = w0 + k * 64 * kSmallWaves + threadIdx.x;
+            x[k] = M.bitmap[w < nwords ? w : nwords - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t w = w0 + k * 64 * kSmallWaves + threadIdx.x;
+            const uint32_t pc = w < nwords ? __popcll(x[k]) : 0;
+            before[0] += w < chunk_word ? pc : 0u;
+            before[1] += w < chunk_word ? 0u : pc;
+        }
+    }
+    const uint32_t b0 = wave_sum(before[0]), b1 = wave_sum(before[1]), cnt = wave_sum(__popcll(word));
+    if (lane == 0) {
+        s_before[0][wave] = b0;
+        s_before[1][wave] = b1;
+        s_cnt[wave] = cnt;
+    }
+    __syncthreads();
+    uint32_t base = 0, off = 0, total = 0;  // before the chunk; from there to this tile; and to the end of the workgroup's tiles
+#pragma unroll
+    for (uint32_t v = 0; v < kSmallWaves; ++v) {
+        base += s_before[0][v];
+        off += s_before[1][v] + (v < wave ? s_cnt[v] : 0u);
+        total += s_before[1][v] + s_cnt[v];
+    }
+    uint32_t *to = M.tile_off + size_t(c) * kChunkStride;
+    const uint32_t tl = tile % kTilesPerChunk;
+    if (lane == 0) to[tl] = off;
+    // the chunk's last workgroup with a tile completes its table: tiles past the end count as empty
+    if (tile0 + kSmallWaves >= ntiles || tl + kSmallWaves - wave == kTilesPerChunk) {
+        for (uint32_t t = (tile0 % kTilesPerChunk) + kSmallWaves + threadIdx.x; t <= kTilesPerChunk; t += 64 * kSmallWaves) to[t] = total;
+        if (threadIdx.x == 0) M.chunk_total[c] = total;
+    }
+    if (tile >= ntiles) return;
+    const uintptr_t vbeg = reinterpret_cast<uintptr_t>(M.values);
+    const uintptr_t vend = vbeg + E * static_cast<uintptr_t>(M.nnz);
+    const int64_t e0 = int64_t(tile) * kTileElems;
+    const int64_t left = M.n - e0;
+    StoreSink<E, kAlignedOut, false> sink;
+    sink.out = reinterpret_cast<uint8_t *>(M.dense) + e0 * E;
+    sink.nvalid = left < kTileElems ? static_cast<uint32_t>(left) : uint32_t(kTileElems);
+    expand_tile<E>(s_scratch[wave], lane, word, vbeg + E * (uint64_t(base) + off), cnt, vbeg, vend, sink);
+}
+
 // This lane's 64 bits of a segment of `nbits` (<= 4096) bits that starts at an arbitrary
 // bit position e of the bitmap: bits e + 64*lane .. +63, funnelled out of two neighbouring
 // words, with everything past the segment (or past the bitmap) cleared.
@@ -1284,6 +1356,32 @@ void launch_expand(const Group &g, hipStream_t s) {
         hipLaunchKernelGGL((endor_expand_kernel<E, true, kTileElems, false>), grid, dim3(64), 0, s, g.P);
 }
 
+// Largest matrix (in elements) that the one-kernel form takes: two chunks.  Measured back to back,
+// half kept, fp16: 1024 x 1024 7.7 us against 10.0 with two kernels, 1024 x 2048 8.7 against 11.2,
+// 2048 x 2048 12.7 against 11.0 (every workgroup counts all of the bitmap before its tiles).
+constexpr int64_t kSmallElems = int64_t(1) << 21;
+
+template <int E>
+void launch_small(const Group &g, hipStream_t s) {
+    const MatParams &M = g.P.m[0];
+    const dim3 grid(static_cast<unsigned>((M.n + kTileElems * kSmallWaves - 1) / (kTileElems * kSmallWaves)));
+    if (g.aligned_out)
+        hipLaunchKernelGGL((endor_decompress_small_kernel<E, true>), grid, dim3(64 * kSmallWaves), 0, s, M);
+    else
+        hipLaunchKernelGGL((endor_decompress_small_kernel<E, false>), grid, dim3(64 * kSmallWaves), 0, s, M);
+}
+
+// A bitmap that the kernels fetch from pinned host memory would cross the link once per workgroup of
+// the one-kernel form, so that form is for device memory only.
+bool in_device_memory(const void *p) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();  // not the launch's error
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice;
+}
+
 // The shared driver of every device entry point.  `mats` holds 16-bit typed pointers;
 // with elem_bytes == 1 they are really 8-bit (endor_matrix_u8 has the same layout).
 endor_status run_batch(const endor_matrix *mats, int count, void *d_workspace, size_t workspace_bytes,
@@ -1318,6 +1416,14 @@ endor_status run_batch(const endor_matrix *mats, int count, void *d_workspace, s
         const int nb = count - b < ENDOR_MAX_BATCH ? count - b : ENDOR_MAX_BATCH;
         fill_group(mats + b, nb, need, elem_bytes, ws, workspace_bytes, &off, &g);
         if (g.chunks == 0) continue;
+        if (build && expand && g.P.count == 1 && g.P.m[0].n <= kSmallElems && in_device_memory(g.P.m[0].bitmap)) {
+            if (elem_bytes == 2)
+                launch_small<2>(g, s);
+            else
+                launch_small<1>(g, s);
+            if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
+            continue;
+        }
         if (build) {
             hipLaunchKernelGGL(endor_tile_offsets_kernel, dim3(g.chunks), dim3(kCountBlock), 0, s, g.P);
             if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;

@@ -147,6 +147,31 @@ def test_row_offsets_tile_aligned_total():
     assert np.array_equal(ro.cpu().numpy(), orc.row_offsets(rows, cols, c.bitmap))
 
 
+@pytest.mark.parametrize("shape", [(1, 1), (1, 4096), (1, 16383), (1, 16385), (64, 16384), (1, (1 << 20) + 1), (3, 400001),
+                                   (2048, 1024), (2097, 1001)], ids=str)
+@pytest.mark.parametrize("wide", [True, False], ids=["fp16", "u8"])
+def test_small_decompress_writes_the_same_output_and_table(shape, wide):
+    """Matrices of up to two chunks are decompressed by one kernel that counts the bitmap itself, larger
+    ones by two: around a workgroup's four tiles, a chunk, and the limit, the output and every entry
+    of the table left in the workspace (used by the calls that reuse it) are those of the host."""
+    rows, cols = shape
+    c = (_random_compressed if wide else _random_compressed_u8)(rows, cols, 0.5, seed=cols)
+    m = endor.to_device(c)
+    ws = torch.full((endor.workspace_bytes(rows, cols),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = endor.decompress(m, workspace=ws)
+    torch.cuda.synchronize()
+    expect = orc.decompress(rows, cols, c.bitmap, c.values)
+    assert np.array_equal(out.cpu().numpy().view(expect.dtype), expect)
+    chunks = -(-(-(-rows * cols // 4096)) // 256)
+    host, dev = endor.build_offsets_host(c), ws.cpu().numpy()
+    first = -(-4 * chunks // 256) * 256
+    assert np.array_equal(dev[:4 * chunks], host[:4 * chunks])
+    assert np.array_equal(dev[first:first + 4 * 257 * chunks], host[first:first + 4 * 257 * chunks])
+    again = endor.decompress_with_offsets(m, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(again.cpu().numpy().view(expect.dtype), expect)
+
+
 def test_empty_matrices():
     for rows, cols in [(0, 5), (5, 0), (0, 0)]:
         c = endor.Compressed(rows, cols, np.zeros(0, np.uint8), np.zeros(0, np.uint16), None)
