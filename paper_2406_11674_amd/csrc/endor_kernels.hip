@@ -672,6 +672,7 @@ struct ColsParams {
     const int64_t *row_offsets;  // rows + 1
     const int64_t *sel;          // nsel column indices
     int64_t rows, cols, nnz, nsel;
+    uint32_t stage_units;        // 16-byte units of `values` the staging area holds (kStaged)
 };
 
 // 64 bits of row-aligned "virtual word" k of a row that starts at bit row_bit: bits
@@ -695,13 +696,14 @@ __device__ __forceinline__ uint64_t row_word(const uint64_t *bitmap, int64_t nwo
 // column index, two LDS reads and a handful of 32-bit operations for
 //     rank = row_offsets[i] + before[piece] + popcount(bits of the piece below the column),
 // and one 2-byte load of values[rank] (or a zero).  Queries are taken four at a time so that
-// their loads are in flight together.  (Measured alternative that lost: streaming the row's
-// whole value slice into LDS first and gathering from there - the 30-50 KB of LDS per row
-// leave three workgroups per compute unit and the kernel becomes latency-bound: 110-150 us
-// against 80 us for a tenth of the columns of 8192 x 28672.)
-template <int E>
+// their loads are in flight together.
+//
+// kStaged: the row's whole value slice goes straight to LDS (no registers) while the bitmap is
+// worked on, and the queries read it there; the host says when that pays.
+template <int E, bool kStaged>
 __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C) {
-    extern __shared__ uint32_t s_dyn[];  // [np] 32-bit pieces of the row's bitmap | [np] 1 bits of the row before each
+    // [np] 32-bit pieces of the row's bitmap | [np] 1 bits of the row before each | staged values
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
     __shared__ uint32_t s_wave[2][kWaves];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
@@ -711,6 +713,28 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     const uint32_t nvw = static_cast<uint32_t>((C.cols + 63) >> 6);
     uint32_t *s_piece = s_dyn;
     uint32_t *s_before = s_dyn + 2 * nvw;
+
+    // The row's values, on their way to LDS while the bitmap is worked on: 16-byte units from the
+    // boundary at or below the first one.  A row that does not fit, or whose units reach over an end of
+    // the array, is gathered from memory.
+    const int64_t row_first = C.row_offsets[i];
+    const uintptr_t vaddr = reinterpret_cast<uintptr_t>(C.values) + E * static_cast<uintptr_t>(row_first);
+    const uint8_t *stage = reinterpret_cast<const uint8_t *>(s_dyn + 4 * nvw);
+    uint32_t staged = 0;  // of the row's values, those in LDS
+    if (kStaged) {
+        const int64_t row_next = C.row_offsets[i + 1];
+        const uintptr_t vbeg = reinterpret_cast<uintptr_t>(C.values), vend = vbeg + E * static_cast<uintptr_t>(C.nnz);
+        const uintptr_t a16 = vaddr & ~uintptr_t(15);
+        const uint64_t count = row_first >= 0 && row_next > row_first && row_next <= C.nnz ? static_cast<uint64_t>(row_next - row_first) : 0;
+        const uint64_t units = ((vaddr - a16) + E * count + 15) >> 4;
+        if (count != 0 && units <= C.stage_units && a16 >= vbeg && a16 + 16 * units <= vend) {  // workgroup-uniform
+            staged = static_cast<uint32_t>(count);
+            u32x4 *to = reinterpret_cast<u32x4 *>(s_dyn + 4 * nvw);
+            for (uint32_t u0 = 64 * wave; u0 < units; u0 += kBlock)
+                if (u0 + lane < units) load_to_lds16(reinterpret_cast<const u32x4 *>(a16) + u0 + lane, to + u0);
+        }
+        stage += vaddr - a16;
+    }
 
     // first round of column indices: in flight during the bitmap work
     constexpr int kQ = 4;  // queries per thread and round
@@ -747,9 +771,9 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
             s_before[2 * k + 1] = excl + __popc(lo);
         }
     }
+    if (kStaged) wait_loads_to_lds();
     __syncthreads();
 
-    const int64_t row_first = C.row_offsets[i];
     // values from the row's first to the end of the array; none if the offset is not inside it
     const uint64_t room = (row_first >= 0 && row_first <= C.nnz) ? static_cast<uint64_t>(C.nnz - row_first) : 0;
     const uint8_t *row_values = static_cast<const uint8_t *>(C.values) + E * row_first;
@@ -773,6 +797,12 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
             const uint32_t b = cc & 31;
             const uint32_t r = s_before[cc >> 5] + __popc(piece & ((1u << b) - 1));  // rank inside the row
             hit[u] = live[u] && ((piece >> b) & 1) != 0 && r < room;
+            if (kStaged && staged) {  // workgroup-uniform
+                const uint32_t at = r < staged ? r : 0u;  // a table that is not this bitmap's stays inside the area
+                v[u] = (E == 2) ? uint32_t(reinterpret_cast<const uint16_t *>(stage)[at]) : uint32_t(stage[at]);
+                hit[u] = hit[u] && r < staged;
+                continue;
+            }
             // The load itself is unconditional (a query without a value reads the first selected
             // index instead and drops it): with the load under the test, the compiler waits for
             // memory after every query and every store, one at a time.
@@ -1846,6 +1876,7 @@ extern "C" endor_status endor_gemv_f16(int64_t rows, int64_t cols, const uint8_t
 
 namespace {
 
+constexpr size_t kMaxColsLds = 40 * 1024, kMinColsStage = 6 * 1024;
 constexpr int64_t kMaxGatherCols = int64_t(1) << 18;  // the row's bitmap and its prefixes live in LDS (16 bytes per 64 columns)
 
 endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t *d_bitmap, const void *d_values,
@@ -1875,10 +1906,27 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     const size_t lds = static_cast<size_t>((cols + 63) / 64) * 4 * sizeof(uint32_t);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid(static_cast<unsigned>(rows));
-    if (elem_bytes == 2)
-        hipLaunchKernelGGL((endor_gather_cols_kernel<2>), grid, dim3(kBlock), lds, s, C);
-    else
-        hipLaunchKernelGGL((endor_gather_cols_kernel<1>), grid, dim3(kBlock), lds, s, C);
+    // room for an eighth more values than a row has on average
+    const size_t stage = (static_cast<size_t>(nnz / rows) * 9 / 8 * elem_bytes + 256 + 15) & ~size_t(15);
+    // Staging pays when most 64-byte lines of a row's values are wanted anyway (a sixteenth of the
+    // columns; the gather then costs a cache access per value, staging one per 64 bytes), the row is
+    // long enough for that to matter and short enough for four workgroups per compute unit.  Measured,
+    // gather against staged: a tenth of 8192 x 28672 65 / 62 us, three tenths 135 / 112, 8-bit 51 / 41, one
+    // in five kept 53 / 39, four tenths of 28672 x 8192 186 / 121; but 8192 x 28672 with four in five kept
+    // (52 KB a row) 89 / 105, a fifth of 5003 x 3171 (4 KB) 11 / 13, a tenth of 30000 x 700 39 / 49.
+    const bool staged = nsel >= cols / 16 && stage >= kMinColsStage && lds + stage <= kMaxColsLds;
+    C.stage_units = static_cast<uint32_t>(stage / 16);
+    if (elem_bytes == 2) {
+        if (staged)
+            hipLaunchKernelGGL((endor_gather_cols_kernel<2, true>), grid, dim3(kBlock), lds + stage, s, C);
+        else
+            hipLaunchKernelGGL((endor_gather_cols_kernel<2, false>), grid, dim3(kBlock), lds, s, C);
+    } else {
+        if (staged)
+            hipLaunchKernelGGL((endor_gather_cols_kernel<1, true>), grid, dim3(kBlock), lds + stage, s, C);
+        else
+            hipLaunchKernelGGL((endor_gather_cols_kernel<1, false>), grid, dim3(kBlock), lds, s, C);
+    }
     if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
     return ENDOR_OK;
 }

@@ -1247,6 +1247,35 @@ def test_decompress_cols_matches_oracle(shape, wide):
     assert np.array_equal(out.cpu().numpy().view(expect.dtype), expect)
 
 
+@pytest.mark.parametrize("wide", [True, False], ids=["fp16", "u8"])
+@pytest.mark.parametrize("voff", [0, 1, 9])
+def test_decompress_cols_with_staged_rows(wide, voff):
+    """Long rows and many selected columns: the values of a row are staged in LDS, except those of a row
+    with far more than the average (gathered) and of a row whose 16-byte units reach over an end of the
+    array.  Selections on both sides of the rule, repeated and out-of-range columns."""
+    rows, cols = 9, 16384 if wide else 32768
+    g = np.random.default_rng(voff)
+    w = g.integers(1, 200, (rows, cols)).astype(np.uint16 if wide else np.uint8)
+    p = np.full(rows, 0.4)
+    p[2], p[5] = 1.0, 0.0
+    w[g.random((rows, cols)) >= p[:, None]] = 0
+    c = endor.compress(w)
+    dt = torch.int16 if wide else torch.uint8
+    buf = torch.full((c.nnz + 32,), 0x5A, dtype=dt, device="cuda")
+    buf[voff:voff + c.nnz] = torch.from_numpy(c.values.view(np.int16) if wide else c.values).cuda()
+    m = endor.DeviceMatrix(rows, cols, torch.from_numpy(c.bitmap).cuda(), buf[voff:voff + c.nnz], c.nnz)
+    ro = torch.from_numpy(c.row_offsets).cuda()
+    for nsel in (cols // 16 - 1, cols // 16, cols // 3):
+        sel = g.integers(0, cols, nsel).astype(np.int64)
+        sel[7] = -1
+        out = torch.full((rows, nsel), 0x33, dtype=dt, device="cuda")
+        endor.decompress_cols(m, ro, torch.from_numpy(sel).cuda(), out=out)
+        torch.cuda.synchronize()
+        expect = w[:, sel]
+        expect[:, 7] = 0x33
+        assert np.array_equal(out.cpu().numpy().view(w.dtype), expect)
+
+
 def test_decompress_cols_out_of_range_index_is_skipped():
     rows, cols = 12, 5000
     w = synth.pruned_fp16(rows, cols, 0.5, seed=79)
