@@ -1,7 +1,7 @@
 // Wave-level building blocks shared by the device code of the Endor library (gfx950, wave64):
 // prefix sums across the lanes of a wave with DPP row shifts and broadcasts, the lookup of
 // a chunk's absolute start from the per-chunk totals of the offset table, and the window
-// form of the expansion used by the fused products.
+// form of the expansion used by the matrix-vector product.
 #ifndef ENDOR_DEVICE_H_
 #define ENDOR_DEVICE_H_
 

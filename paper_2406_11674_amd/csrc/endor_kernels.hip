@@ -26,10 +26,10 @@
 // The same tile expander, fed differently, gives the row-subset kernel (Section 4.2's
 // selective load) and - run backwards, as a scatter - the pack step of the device-side
 // compressor (Algorithm 1).  The element width (2 bytes, or 1 for the 8-bit variant of
-// Section 4.2) is a template parameter throughout.  The products on the compressed form
-// (here the matrix-vector one; the small-batch one has a file of its own) expand in
-// registers instead: a bitmap byte's values are one 16-byte window of `values`, read
-// straight from memory and put in place with byte permutes.
+// Section 4.2) is a template parameter throughout.  The matrix-vector product on the
+// compressed form expands in registers instead: a bitmap byte's values are one 16-byte
+// window of `values`, read straight from memory and put in place with byte permutes (the
+// small-batch product has a file of its own).
 //
 // One rule shaped all of these kernels: a load under a per-lane test whose result is used
 // after the test is waited for on the spot, so several of them in a row are as many trips
