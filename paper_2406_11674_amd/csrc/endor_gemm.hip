@@ -231,6 +231,12 @@ struct RowStreams {
             R.whole = 0;
             R.ragged = true;
             R.late = kNoneLate;
+            if (far) {  // rows of ten million columns and more: whole units when the round is staged
+                const uintptr_t f = (row_first + R.off) & ~uintptr_t(15);
+                const uintptr_t units = f >= vbeg && vend > f ? (vend - f) >> 4 : 0;
+                R.whole = R.units < units ? R.units : static_cast<uint32_t>(units);
+                R.late = 0;
+            }
         }
         const uintptr_t base = here ? wave_base : reinterpret_cast<uintptr_t>(&g_dummy);
         const uint32_t info = here && R.whole ? (first << 2) | (R.whole - 1) : 0u;  // first unit << 6 | last one to read
