@@ -28,7 +28,7 @@
 // every byte's 20-byte window from memory through the vector cache and handed the expanded bytes
 // on with ds_bpermute: 112 us; with 3 right-hand sides on 4099 x 5005, three in ten kept: 18
 // against 25 us).  What bounds it: LDS serves 65 clocks of every step's 95 (64 lanes at random
-// addresses cost 7 clocks per dword, six dwords per byte), the vector ALUs are busy 44 % of the
+// addresses cost 7 clocks per dword, six dwords per byte), the vector ALUs are busy 42 % of the
 // time, memory alone would take 45 us.  Measured alternatives: the windows as three aligned
 // 8-byte reads and selects (48 clocks of LDS, 25 % more vector instructions) 84 us; two rounds of
 // values in flight 84; three workgroups per compute unit 85; units of 64 aligned bytes 84.

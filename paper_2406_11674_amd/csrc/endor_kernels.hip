@@ -891,7 +891,7 @@ struct GemvParams {
 // for x, where 200 would do if no two lanes shared a line.)  Since then: loads issued back to back,
 // the fifth dword of a window from the neighbouring lane instead of from memory, and the windows
 // addressed by 32-bit offsets from a scalar base: 8192 x 28672 with inputs not in any cache 67 ->
-// 60 us, 4.4 TB/s; the vector ALUs are busy two thirds of the time, and a wave waits for its
+// 60 us, 4.4 TB/s; the vector ALUs are busy 62 % of the time, and a wave waits for its
 // windows.  More waves per unit by a register cap (80 or 64 instead of 96): 4 and 25 % slower.
 constexpr int kGemvSeg = 4096;  // columns a wave expands at a time
 
@@ -1101,7 +1101,7 @@ struct CompressParams {
 };
 
 // Algorithm 1, step 1 on the device: the position bitmap, and each tile's count in its slot of the
-// offset table (the table then comes from a scan of the counts, 3 us, instead of a second pass over
+// offset table (the table then comes from a scan of the counts, 5 us, instead of a second pass over
 // the bitmap, 6.5 us on 28672 x 8192).  One wave per tile; the lane
 // bit groups of the 4096 elements are assembled into 64-bit words through LDS.
 template <int E, bool kAlignedIn>
