@@ -38,6 +38,7 @@
 
 #include "endor.h"
 #include "endor_device.h"
+#include "endor_gemm_units.h"
 #include "endor_layout.h"
 
 namespace {
@@ -48,6 +49,17 @@ using endor_device::load_to_lds16;
 using endor_device::u32x4;
 using endor_device::wait_loads_to_lds;
 using endor_device::wave_sum;
+using endor_gemm_units::Fetch;
+using endor_gemm_units::fetch_lane;
+using endor_gemm_units::fetch_row;
+using endor_gemm_units::kFetchLoads;
+using endor_gemm_units::kRows;
+using endor_gemm_units::kSpan;
+using endor_gemm_units::Limits;
+using endor_gemm_units::limits_of;
+using endor_gemm_units::Slice;
+using endor_gemm_units::slice_of;
+using endor_gemm_units::unit_offset;
 using endor_layout::chunk_total_bytes;
 using endor_layout::dims_ok;
 using endor_layout::kChunkStride;
@@ -58,7 +70,6 @@ using endor_layout::workspace_bytes_n;
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRows = 16;               // rows of W per wave: the M of the matrix instruction
 constexpr int kSegCols = 256;           // columns per round: a 64-bit bitmap word per lane
 constexpr int kSteps = kSegCols / 32;   // matrix instructions per round
 constexpr int kAccs = 4;                // accumulators taken in turn
@@ -114,25 +125,6 @@ __device__ __forceinline__ uint32_t row_sum(uint32_t x, uint32_t mq, uint32_t *b
 
 __device__ const u32x4 g_dummy = {0u, 0u, 0u, 0u};  // read where there is nothing to read
 
-// How many 16-byte units of a row's slice are asked for a round ahead, and how: kRowsPer rows per
-// load instruction (neighbouring lanes take a row's neighbouring units, so an instruction covers
-// whole cache lines and no line is asked for twice).  kTail: one more load brings unit kUnits of
-// every row.  A row with more units gets the rest when its round is staged.
-template <int kClass>
-struct Fetch;
-template <>
-struct Fetch<0> {  // 97 values per row and round
-    enum { kUnits = 13, kRowsPer = 4, kTail = 0 };
-};
-template <>
-struct Fetch<1> {  // 161 values
-    enum { kUnits = 21, kRowsPer = 3, kTail = 0 };
-};
-template <>
-struct Fetch<2> {  // all 256
-    enum { kUnits = 32, kRowsPer = 2, kTail = 1 };
-};
-
 constexpr int kPitch = 560;  // bytes between the staged slices of two rows: 256 values and 14 bytes of slack make 33 units;
                              // 140 dwords put the 16 rows on 16 different groups of LDS banks
 constexpr int kStageBytes = kRows * kPitch;  // a window's pieces reach at most 526 + 24 bytes into a slice
@@ -160,7 +152,7 @@ constexpr uint32_t kNoneLate = 64;
 template <int kClass>
 struct RowStreams {
     using F = Fetch<kClass>;
-    static constexpr int kLoads = (kRows + F::kRowsPer - 1) / F::kRowsPer;
+    static constexpr int kLoads = kFetchLoads<kClass>;
     struct Pieces {
         u32x4 d[kLoads + F::kTail];
     };
@@ -171,14 +163,14 @@ struct RowStreams {
     uintptr_t row_first;  // the range's first value of row mr
     uintptr_t wave_base;  // the unit that holds the range's first value of the wave's first row (wave-uniform)
     uint32_t delta;       // row_first - wave_base
-    uint32_t lo, hi;      // offsets from wave_base between which units may be read
+    Limits limits;        // what may be read around wave_base
     bool far;             // wave-uniform: the rows lie too far apart for 32-bit offsets
     uint32_t off;         // bytes of the row's values before the next round
 
     __device__ __forceinline__ void init(uint32_t lane) {
         mr = lane & 15;
         mq = lane >> 4;
-        const uint32_t l = lane < F::kRowsPer * F::kUnits ? lane : F::kRowsPer * F::kUnits - 1;
+        const uint32_t l = fetch_lane<kClass>(lane);
         frow = l / F::kUnits;
         fu = l % F::kUnits;
     }
@@ -192,19 +184,13 @@ struct RowStreams {
         const uintptr_t b = first & ~uintptr_t(15);
         wave_base = (uintptr_t(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)))) << 32) |
                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)));
-        constexpr uintptr_t kSpan = uintptr_t(1) << 28;
         far = __builtin_amdgcn_ballot_w64(first - wave_base >= kSpan) != 0;
         delta = static_cast<uint32_t>(first - wave_base);
-        lo = wave_base >= vbeg ? 0u : static_cast<uint32_t>(vbeg - wave_base);  // a table that lies may put the base anywhere
-        hi = vend <= wave_base ? 0u : vend - wave_base < 2 * kSpan ? static_cast<uint32_t>(vend - wave_base) : uint32_t(2 * kSpan);
-        if (wave_base < vbeg && vbeg - wave_base > 15) hi = 0;
+        limits = limits_of(vbeg, vend, wave_base);
         off = 0;
     }
 
-    __device__ __forceinline__ uint32_t load_row(int i) const {
-        const uint32_t row = i * F::kRowsPer + frow;
-        return (i + 1) * F::kRowsPer <= kRows || row < kRows ? row : kRows - 1;
-    }
+    __device__ __forceinline__ uint32_t load_row(int i) const { return fetch_row<kClass>(i, frow); }
 
     // Start a round: its bitmap word is here, its values are asked for.  There is no branch around
     // the loads (the compiler would wait for them where it ends): a lane without a unit of its own
@@ -214,19 +200,17 @@ struct RowStreams {
         uint32_t before;
         const uint32_t cnt = row_sum(__popcll(w), mq, &before);
         const uint32_t start = delta + off;
-        const uint32_t shift = start & 15u;
-        R.at = mr * kPitch + shift + 2 * before;
+        R.at = mr * kPitch + (start & 15u) + 2 * before;
         R.off = off;
         off += 2 * cnt;
-        R.units = cnt ? (shift + 2 * cnt + 15) >> 4 : 0u;
-        const uint32_t first = start & ~15u;
-        const uint32_t room = hi > first ? (hi - first) >> 4 : 0u;  // whole units from here to the end of `values`
-        R.whole = R.units < room ? R.units : room;
+        const Slice slice = slice_of(limits, start, cnt);
+        R.units = slice.units;
+        R.whole = slice.whole;
         R.ragged = __builtin_amdgcn_ballot_w64(R.whole < R.units) != 0;
         R.late = F::kTail != 0 || __builtin_amdgcn_ballot_w64(R.whole > F::kUnits) == 0 ? kNoneLate : uint32_t(F::kUnits);
         // a unit before the beginning of `values` (the array is not 16-byte aligned, the very first
         // row), rows too far apart, next to no values: nothing is asked for ahead
-        const bool here = __builtin_amdgcn_ballot_w64(first < lo) == 0 && hi >= 16 && !far;
+        const bool here = __builtin_amdgcn_ballot_w64((start & ~15u) < limits.lo) == 0 && limits.ready && !far;
         if (!here) {
             R.whole = 0;
             R.ragged = true;
@@ -239,10 +223,9 @@ struct RowStreams {
             }
         }
         const uintptr_t base = here ? wave_base : reinterpret_cast<uintptr_t>(&g_dummy);
-        const uint32_t info = here && R.whole ? (first << 2) | (R.whole - 1) : 0u;  // first unit << 6 | last one to read
+        const uint32_t info = here ? slice.info : 0u;
         auto load = [&](uint32_t row_info, uint32_t unit) -> u32x4 {
-            const uint32_t l = row_info & 63u;
-            return *global_ptr<u32x4>(base + (((row_info >> 6) + (unit < l ? unit : l)) << 4));
+            return *global_ptr<u32x4>(base + unit_offset(row_info, unit));
         };
 #pragma unroll
         for (int i = 0; i < kLoads; ++i)

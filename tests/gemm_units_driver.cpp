@@ -1,0 +1,123 @@
+// The address arithmetic of the small-batch product's value loads (endor_gemm_units.h), replayed on
+// the host for every load of every round of small products, the round asked for behind the last one
+// included: each must lie inside `values` (or be the dummy), and together they must bring
+// every unit that lies inside `values`.  Built and run by tests/test_gemm_units.py; not part of the
+// library.
+#include <cstdint>
+#include <cstdio>
+#include <vector>
+
+#include "endor_gemm_units.h"
+
+using namespace endor_gemm_units;
+
+static uint64_t state = 0x243F6A8885A308D3ull;
+static uint64_t rnd() {
+    state ^= state << 13;
+    state ^= state >> 7;
+    state ^= state << 17;
+    return state;
+}
+
+static long replayed = 0;
+
+// Rows row0 .. of one wave over rounds [k0, k1): cnt[row][round] values each, row_begin[row] of them before a row's first round.
+// Returns a complaint, or null.
+template <int kClass>
+static const char *wave(uint64_t vbeg, uint64_t vend, const std::vector<std::vector<uint32_t>> &cnt,
+                        const std::vector<uint64_t> &row_begin, int row0, int k0, int k1) {
+    using F = Fetch<kClass>;
+    const int rows = static_cast<int>(cnt.size());
+    uint64_t first[kRows];
+    for (int r = 0; r < kRows; ++r) {
+        const int row = row0 + r < rows ? row0 + r : rows - 1;
+        first[r] = vbeg + 2 * row_begin[row];
+        for (int k = 0; k < k0; ++k) first[r] += 2 * cnt[row][k];
+    }
+    const uint64_t base = first[0] & ~uint64_t(15);
+    const Limits L = limits_of(vbeg, vend, base);
+    uint32_t off[kRows] = {};
+    const int count = k1 - k0;
+    for (int k = 0; k <= ((count + 1) & ~1); ++k) {
+        Slice s[kRows];
+        bool here = L.ready;
+        for (int r = 0; r < kRows; ++r) {
+            const uint32_t c = row0 + r < rows && k < count ? cnt[row0 + r][k0 + k] : 0u;
+            const uint32_t start = static_cast<uint32_t>(first[r] - base) + off[r];
+            s[r] = slice_of(L, start, c);
+            if ((start & ~15u) < L.lo) here = false;
+            off[r] += 2 * c;
+        }
+        if (!here) continue;  // every load reads the dummy, every unit comes element by element
+        bool got[kRows][64] = {};
+        auto load = [&](int r, uint32_t unit) {
+            const uint64_t p = base + unit_offset(s[r].info, unit);
+            ++replayed;
+            const uint64_t slice = (first[r] + off[r] - 2 * (row0 + r < rows && k < count ? cnt[row0 + r][k0 + k] : 0u)) & ~uint64_t(15);
+            if (unit < s[r].whole && p != slice + 16 * unit) return "a unit was read from another place";
+            if (unit < 64) got[r][unit] = true;
+            return p >= vbeg && p + 16 <= vend ? nullptr : "a unit outside the values was read";
+        };
+        for (int i = 0; i < kFetchLoads<kClass>; ++i)
+            for (uint32_t lane = 0; lane < 64; ++lane) {
+                const uint32_t l = fetch_lane<kClass>(lane);
+                if (const char *bad = load(fetch_row<kClass>(i, l / F::kUnits), l % F::kUnits)) return bad;
+            }
+        for (int r = 0; r < kRows; ++r) {
+            if (F::kTail)
+                if (const char *bad = load(r, F::kUnits)) return bad;
+            for (uint32_t u = 0; u < s[r].whole; ++u)
+                if (!got[r][u] && (F::kTail || u < F::kUnits)) return "a unit was not asked for";
+            if (s[r].whole > s[r].units || s[r].units > 33) return "too many units";
+            const uint64_t end = base + unit_offset(s[r].info, 63) + 16;
+            if (s[r].whole && (end > vend || base + unit_offset(s[r].info, 0) < vbeg)) return "a late unit lies outside";
+        }
+    }
+    return nullptr;
+}
+
+int main() {
+    int cases = 0;
+    for (int rows : {1, 2, 16, 17, 40})
+        for (int rounds : {1, 2, 3, 9})
+            for (int shape = 0; shape < 7; ++shape)
+                for (uint32_t align = 0; align < 16; align += 2)
+                    for (int cut = 0; cut < 3; ++cut) {
+                        std::vector<std::vector<uint32_t>> cnt(rows, std::vector<uint32_t>(rounds));
+                        std::vector<uint64_t> begin(rows);
+                        uint64_t nnz = 0;
+                        for (int r = 0; r < rows; ++r) {
+                            begin[r] = nnz;
+                            for (int k = 0; k < rounds; ++k) {
+                                uint32_t c = static_cast<uint32_t>(rnd() % 257);      // 0: any density
+                                if (shape == 1) c = 256;                              // everything kept
+                                if (shape == 2) c = 0;                                // nothing
+                                if (shape == 3) c = r == 0 ? 0 : 120 + rnd() % 20;    // an empty first row
+                                if (shape == 4) c = r == 0 ? k % 2 : 90;              // a first row of single values
+                                if (shape == 5) c = rnd() % 3 ? 0 : rnd() % 40;       // sparse
+                                if (shape == 6) c = r % 3 ? 0 : 128;                  // empty rows
+                                cnt[r][k] = c;
+                                nnz += c;
+                            }
+                        }
+                        // cut: the array ends with the last value, in the middle (nnz too small), or at its 3rd value
+                        const uint64_t have = cut == 0 ? nnz : cut == 1 ? nnz / 2 : nnz < 3 ? nnz : 3;
+                        const uint64_t vbeg = 0x7f0000000000ull + align, vend = vbeg + 2 * have;
+                        for (int row0 = 0; row0 < rows; row0 += kRows)
+                            for (int k0 = 0; k0 < rounds; k0 += 4) {
+                                const int k1 = k0 + 4 < rounds ? k0 + 4 : rounds;
+                                const char *bad[3] = {wave<0>(vbeg, vend, cnt, begin, row0, k0, k1),
+                                                      wave<1>(vbeg, vend, cnt, begin, row0, k0, k1),
+                                                      wave<2>(vbeg, vend, cnt, begin, row0, k0, k1)};
+                                for (int c = 0; c < 3; ++c)
+                                    if (bad[c]) {
+                                        std::printf("rows %d rounds %d shape %d values at %u mod 16, cut %d, row %d, round %d, class %d: %s\n",
+                                                    rows, rounds, shape, align, cut, row0, k0, c, bad[c]);
+                                        return 1;
+                                    }
+                                ++cases;
+                            }
+                    }
+    std::printf("ok %d waves, %ld loads\n", cases, replayed);
+    return 0;
+}
