@@ -135,10 +135,10 @@ struct Round {
     uint32_t at;     // byte offset of the word's first value in the staging area
     uint32_t off;    // byte offset of the row's first value from the row's first value of the whole part
     uint32_t units;  // the row's units
-    uint32_t whole;  // those that lie inside `values` as a whole (they come first)
+    uint32_t whole;  // those that are read whole (they come first)
     // wave-uniform
     uint32_t late;  // the first unit that was not asked for ahead; kNoneLate if no row has one
-    bool ragged;    // some row has a unit that reaches over the end of `values`
+    bool ragged;    // some row has a unit that reaches over an end of `values`
 };
 
 constexpr uint32_t kNoneLate = 64;
@@ -165,6 +165,7 @@ struct RowStreams {
     uint32_t delta;       // row_first - wave_base
     Limits limits;        // what may be read around wave_base
     bool far;             // wave-uniform: the rows lie too far apart for 32-bit offsets
+    bool ahead;           // wave-uniform: units are asked for a round ahead (not far, and not next to no values)
     uint32_t off;         // bytes of the row's values before the next round
 
     __device__ __forceinline__ void init(uint32_t lane) {
@@ -187,6 +188,7 @@ struct RowStreams {
         far = __builtin_amdgcn_ballot_w64(first - wave_base >= kSpan) != 0;
         delta = static_cast<uint32_t>(first - wave_base);
         limits = limits_of(vbeg, vend, wave_base);
+        ahead = limits.ready && !far;
         off = 0;
     }
 
@@ -194,7 +196,7 @@ struct RowStreams {
 
     // Start a round: its bitmap word is here, its values are asked for.  There is no branch around
     // the loads (the compiler would wait for them where it ends): a lane without a unit of its own
-    // reads the row's last one again, and a round that cannot be read this way reads a dummy.
+    // reads the row's last one again, and a range that cannot be read this way reads a dummy.
     __device__ __forceinline__ void fetch(uint64_t w, Round &R, Pieces &P) {
         R.word = w;
         uint32_t before;
@@ -206,14 +208,11 @@ struct RowStreams {
         const Slice slice = slice_of(limits, start, cnt);
         R.units = slice.units;
         R.whole = slice.whole;
-        R.ragged = __builtin_amdgcn_ballot_w64(R.whole < R.units) != 0;
+        uint32_t info = slice.info;
         R.late = F::kTail != 0 || __builtin_amdgcn_ballot_w64(R.whole > F::kUnits) == 0 ? kNoneLate : uint32_t(F::kUnits);
-        // a unit before the beginning of `values` (the array is not 16-byte aligned, the very first
-        // row), rows too far apart, next to no values: nothing is asked for ahead
-        const bool here = __builtin_amdgcn_ballot_w64((start & ~15u) < limits.lo) == 0 && limits.ready && !far;
-        if (!here) {
+        if (!ahead) {  // nothing is asked for ahead
+            info = 0;
             R.whole = 0;
-            R.ragged = true;
             R.late = kNoneLate;
             if (far) {  // rows of ten million columns and more: whole units when the round is staged
                 const uintptr_t f = (row_first + R.off) & ~uintptr_t(15);
@@ -222,8 +221,8 @@ struct RowStreams {
                 R.late = 0;
             }
         }
-        const uintptr_t base = here ? wave_base : reinterpret_cast<uintptr_t>(&g_dummy);
-        const uint32_t info = here ? slice.info : 0u;
+        R.ragged = __builtin_amdgcn_ballot_w64(R.whole < R.units) != 0;
+        const uintptr_t base = ahead ? wave_base : reinterpret_cast<uintptr_t>(&g_dummy);
         auto load = [&](uint32_t row_info, uint32_t unit) -> u32x4 {
             return *global_ptr<u32x4>(base + unit_offset(row_info, unit));
         };

@@ -70,7 +70,8 @@ constexpr Limits limits_of(uint64_t vbeg, uint64_t vend, uint64_t base) {
 // A row's slice of a round: cnt values from offset `start`.
 struct Slice {
     uint32_t units;  // those that hold a value
-    uint32_t whole;  // those that lie inside `values` as a whole (they come first)
+    uint32_t whole;  // those that are read whole: from the first one up to the end of `values`; none in the round
+                     // in which the row begins before the array's first whole unit
     uint32_t info;   // first unit << 6 | the last one to read, counted from it
 };
 
@@ -78,7 +79,7 @@ constexpr Slice slice_of(const Limits &L, uint32_t start, uint32_t cnt) {
     Slice s{};
     const uint32_t shift = start & 15u, first = start & ~15u;
     s.units = cnt ? (shift + 2 * cnt + 15) >> 4 : 0u;
-    const uint32_t room = L.hi > first ? (L.hi - first) >> 4 : 0u;  // whole units from here to the end of `values`
+    const uint32_t room = first >= L.lo && L.hi > first ? (L.hi - first) >> 4 : 0u;  // whole units from here to the end of `values`
     s.whole = s.units < room ? s.units : room;
     s.info = s.whole ? (first << 2) | (s.whole - 1) : L.idle << 6;
     return s;

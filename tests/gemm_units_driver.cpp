@@ -40,15 +40,20 @@ static const char *wave(uint64_t vbeg, uint64_t vend, const std::vector<std::vec
     const int count = k1 - k0;
     for (int k = 0; k <= ((count + 1) & ~1); ++k) {
         Slice s[kRows];
-        bool here = L.ready;
         for (int r = 0; r < kRows; ++r) {
             const uint32_t c = row0 + r < rows && k < count ? cnt[row0 + r][k0 + k] : 0u;
             const uint32_t start = static_cast<uint32_t>(first[r] - base) + off[r];
             s[r] = slice_of(L, start, c);
-            if ((start & ~15u) < L.lo) here = false;
+            // a row goes element by element only where it does not begin in a unit that can be read whole,
+            // or reaches over the end: no other row's position matters
+            const uint64_t unit = base + (start & ~15u), inside = unit >= vbeg && unit < vend ? (vend - unit) >> 4 : 0;
+            if (L.ready && s[r].whole != (inside < s[r].units ? inside : s[r].units)) return "units that could be read whole are not";
             off[r] += 2 * c;
         }
-        if (!here) continue;  // every load reads the dummy, every unit comes element by element
+        if (!L.ready) {  // every load reads the dummy, every unit comes element by element
+            if (vend >= base + 48) return "an array of whole units is not read by units";
+            continue;
+        }
         bool got[kRows][64] = {};
         auto load = [&](int r, uint32_t unit) {
             const uint64_t p = base + unit_offset(s[r].info, unit);
