@@ -38,6 +38,7 @@
 
 #include "endor.h"
 #include "endor_device.h"
+#include "endor_gemm_plan.h"
 #include "endor_gemm_units.h"
 #include "endor_layout.h"
 
@@ -49,6 +50,11 @@ using endor_device::load_to_lds16;
 using endor_device::u32x4;
 using endor_device::wait_loads_to_lds;
 using endor_device::wave_sum;
+using endor_gemm_plan::kBlockRows;
+using endor_gemm_plan::kGemmWaves;
+using endor_gemm_plan::kSegCols;
+using endor_gemm_plan::make_plan;
+using endor_gemm_plan::Plan;
 using endor_gemm_units::Fetch;
 using endor_gemm_units::fetch_lane;
 using endor_gemm_units::fetch_row;
@@ -70,11 +76,8 @@ using endor_layout::workspace_bytes_n;
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kSegCols = 256;           // columns per round: a 64-bit bitmap word per lane
 constexpr int kSteps = kSegCols / 32;   // matrix instructions per round
 constexpr int kAccs = 4;                // accumulators taken in turn
-constexpr int kGemmWaves = 4;           // waves (row groups) per workgroup; they share the tile of X
-constexpr int kBlockRows = kRows * kGemmWaves;
 constexpr int kXStep = 64 * 16;         // bytes of the tile of X one matrix instruction reads: 16 per lane, in lane order
 
 // Where the 8 columns 64*mq + 8*t of right-hand side n sit in the tile of X.  A step's 64 fragments
@@ -526,16 +529,18 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
             V.stage(S.stage[wave], R, P);
             __syncthreads();
             const Round now = R;
-            x_fetch(k + 1, X);
-            const uint64_t w = take_word(k + 1, wk);
-            wk = load_word(k + 3);
-            V.fetch(w, R, P);
+            if (k + 1 < count) {  // not behind the last round: that was an eighth of a product of one-round blocks
+                x_fetch(k + 1, X);
+                const uint64_t w = take_word(k + 1, wk);
+                wk = load_word(k + 3);
+                V.fetch(w, R, P);
+            }
             multiply_round(S.table, S.stage[wave], S.xt[buf], x_lane, now, acc);
             wave_lds_sync();  // the next round's LDS writes must stay behind this round's LDS reads
         };
-        // always whole pairs: a round past the part's end has no bits and a tile of X of zeros
         for (uint32_t k = 0; k < count; k += 2) {
             round(k, 0, w1);
+            if (k + 1 >= count) break;
             round(k + 1, 1, w2);
         }
         __syncthreads();  // every wave is through with the tiles of X before the next part's are stored
@@ -582,47 +587,6 @@ __global__ __launch_bounds__(256) void endor_gemm_reduce_kernel(const float *__r
 __global__ __launch_bounds__(256) void endor_gemm_zero_kernel(float *__restrict__ y, int64_t count) {
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (i < count) y[i] = 0.0f;
-}
-
-// How the product's rounds are shared out: every workgroup gets the same number of consecutive
-// rounds, so many that kResident workgroups (two per compute unit: 52 KB of LDS and up to 256
-// registers each) do all of them at once, and so many that a row block has at most kMaxParts parts.
-// Whole blocks, which need no second kernel, where that costs a workgroup no more than kWholeSlack
-// rounds (the kernel takes about as long as two rounds).  Small products, kSmall rounds or fewer per
-// workgroup, run as workgroups of two rounds (they are taken in pairs).  These, and those that fit
-// the chip at once, never reach into a second block: starting on a block takes as long as several
-// rounds (2053 x 1031: 13.8 us, 19.7 us with workgroups that cross from block to block).
-constexpr int64_t kResident = 256 * 2;
-constexpr int64_t kMaxParts = 16;
-constexpr int64_t kWholeSlack = 2;
-constexpr int64_t kSmall = 4;
-
-struct Plan {
-    uint32_t blocks, segs, per_wg, rounds, wgs;
-    bool split;  // some row block is shared
-};
-
-Plan make_plan(int64_t rows, int64_t cols) {
-    Plan p;
-    const int64_t blocks = (rows + kBlockRows - 1) / kBlockRows;
-    int64_t segs = (cols + kSegCols - 1) / kSegCols;
-    int64_t per = (blocks * segs + kResident - 1) / kResident;  // blocks * segs is below 2^27: rows*cols < 2^34
-    per = (per + 1) & ~int64_t(1);
-    if (per <= kSmall) per = 2;
-    const int64_t least = (segs + kMaxParts - 1) / kMaxParts;
-    if (per < least) per = least;
-    const int64_t parts = (segs + per - 1) / per;
-    if (per <= kSmall || blocks * parts <= kResident) segs = parts * per;  // rounds past the last column have no bits
-    const int64_t rounds = blocks * segs;
-    const int64_t whole = (per + segs - 1) / segs * segs;
-    if (whole - per <= kWholeSlack) per = whole;
-    p.blocks = static_cast<uint32_t>(blocks);
-    p.segs = static_cast<uint32_t>(segs);
-    p.per_wg = static_cast<uint32_t>(per);
-    p.rounds = static_cast<uint32_t>(rounds);
-    p.wgs = static_cast<uint32_t>((rounds + per - 1) / per);
-    p.split = per % segs != 0;
-    return p;
 }
 
 template <int kClass>

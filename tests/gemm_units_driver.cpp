@@ -1,12 +1,12 @@
 // The address arithmetic of the small-batch product's value loads (endor_gemm_units.h), replayed on
-// the host for every load of every round of small products, the round asked for behind the last one
-// included: each must lie inside `values` (or be the dummy), and together they must bring
+// the host for every load of every round of small products: each must lie inside `values` (or be the dummy), and together they must bring
 // every unit that lies inside `values`.  Built and run by tests/test_gemm_units.py; not part of the
 // library.
 #include <cstdint>
 #include <cstdio>
 #include <vector>
 
+#include "endor_gemm_plan.h"
 #include "endor_gemm_units.h"
 
 using namespace endor_gemm_units;
@@ -38,10 +38,10 @@ static const char *wave(uint64_t vbeg, uint64_t vend, const std::vector<std::vec
     const Limits L = limits_of(vbeg, vend, base);
     uint32_t off[kRows] = {};
     const int count = k1 - k0;
-    for (int k = 0; k <= ((count + 1) & ~1); ++k) {
+    for (int k = 0; k < count; ++k) {
         Slice s[kRows];
         for (int r = 0; r < kRows; ++r) {
-            const uint32_t c = row0 + r < rows && k < count ? cnt[row0 + r][k0 + k] : 0u;
+            const uint32_t c = row0 + r < rows ? cnt[row0 + r][k0 + k] : 0u;
             const uint32_t start = static_cast<uint32_t>(first[r] - base) + off[r];
             s[r] = slice_of(L, start, c);
             // a row goes element by element only where it does not begin in a unit that can be read whole,
@@ -58,7 +58,7 @@ static const char *wave(uint64_t vbeg, uint64_t vend, const std::vector<std::vec
         auto load = [&](int r, uint32_t unit) {
             const uint64_t p = base + unit_offset(s[r].info, unit);
             ++replayed;
-            const uint64_t slice = (first[r] + off[r] - 2 * (row0 + r < rows && k < count ? cnt[row0 + r][k0 + k] : 0u)) & ~uint64_t(15);
+            const uint64_t slice = (first[r] + off[r] - 2 * (row0 + r < rows ? cnt[row0 + r][k0 + k] : 0u)) & ~uint64_t(15);
             if (unit < s[r].whole && p != slice + 16 * unit) return "a unit was read from another place";
             if (unit < 64) got[r][unit] = true;
             return p >= vbeg && p + 16 <= vend ? nullptr : "a unit outside the values was read";
@@ -81,7 +81,38 @@ static const char *wave(uint64_t vbeg, uint64_t vend, const std::vector<std::vec
     return nullptr;
 }
 
+// The partition of one shape: every round done once, the parts of a shared row block at most kMaxParts,
+// their slots of the scratch all different, and no workgroup that takes blocks of few rounds one after
+// the other while there are more blocks than workgroups on the chip.
+static const char *partition(int64_t rows, int64_t cols) {
+    using namespace endor_gemm_plan;
+    const Plan p = make_plan(rows, cols);
+    const int64_t need = (cols + kSegCols - 1) / kSegCols;
+    if (int64_t(p.blocks) != (rows + kBlockRows - 1) / kBlockRows || p.segs < need) return "rounds are missing";
+    if (int64_t(p.rounds) != int64_t(p.blocks) * p.segs || p.per_wg == 0) return "the rounds do not add up";
+    if (int64_t(p.wgs) != (int64_t(p.rounds) + p.per_wg - 1) / p.per_wg) return "the workgroups do not add up";
+    if ((int64_t(p.wgs) * 64 * kGemmWaves) >> 32) return "too many threads for a launch";
+    if (p.split != (p.per_wg % p.segs != 0)) return "a split that is not announced";
+    if (int64_t(p.blocks) > kResident && need <= kNarrow && p.per_wg != p.segs && p.blocks <= kMaxGrid) return "blocks of few rounds are chained";
+    if (p.segs > need + p.per_wg) return "rounds of nothing";
+    for (int64_t block : {int64_t(0), int64_t(p.blocks) / 2, int64_t(p.blocks) - 1}) {
+        const int64_t first = block * p.segs / p.per_wg, last = ((block + 1) * p.segs - 1) / p.per_wg;
+        if (last - first > kMaxParts) return "too many parts";
+        if (p.split && last + block >= int64_t(p.wgs) + p.blocks) return "a part without a slot";
+        if (block + 1 < int64_t(p.blocks) && ((block + 1) * p.segs) / p.per_wg + block + 1 <= last + block) return "a slot used twice";
+    }
+    return nullptr;
+}
+
 int main() {
+    for (int64_t rows : {int64_t(1), int64_t(64), int64_t(65), int64_t(2053), int64_t(28672), int64_t(32768), int64_t(32769), int64_t(36864), int64_t(131072), int64_t(524289), int64_t(2147483632)})
+        for (int64_t cols : {int64_t(1), int64_t(100), int64_t(256), int64_t(257), int64_t(768), int64_t(1031), int64_t(3072), int64_t(3073), int64_t(8192), int64_t(28672), int64_t(1) << 24, (int64_t(1) << 34) - 1}) {
+            if (cols > ((int64_t(1) << 34) - 1) / rows) continue;
+            if (const char *bad = partition(rows, cols)) {
+                std::printf("%ld x %ld: %s\n", (long)rows, (long)cols, bad);
+                return 1;
+            }
+        }
     int cases = 0;
     for (int rows : {1, 2, 16, 17, 40})
         for (int rounds : {1, 2, 3, 9})

@@ -852,6 +852,22 @@ def test_gemm_rounds_parts_and_overfull_rows_are_exact(shape, keep, nb):
     assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.gemm_f16(rows, cols, c.bitmap, c.values, X16))
 
 
+@pytest.mark.parametrize("shape", [(32769, 100), (33000, 256), (33000, 257), (32800, 768), (32770, 3100)], ids=str)
+def test_gemm_more_row_blocks_than_workgroups_on_the_chip(shape):
+    """Tall matrices: a workgroup per row block of one, two, three rounds (odd numbers leave the loop in
+    the middle), and blocks of 13 rounds, which workgroups share.  Small integers: the result is exact."""
+    rows, cols = shape
+    _say(f"gemm tall shape={shape}")
+    g = np.random.default_rng(cols)
+    wi = np.zeros((rows, cols), np.float16)
+    at = g.random((rows, cols), dtype=np.float32) < 0.4
+    wi[at] = g.integers(1, 9, int(at.sum()))
+    X16 = g.integers(-8, 9, (3, cols)).astype(np.float16)
+    c = endor.compress(wi)
+    got = _gpu_gemm(c, X16)
+    assert np.array_equal(got, orc.gemm_f16(rows, cols, c.bitmap, c.values, X16))
+
+
 def test_gemm_subnormal_inputs_count_in_full():
     rows, cols = 20, 700
     g = np.random.default_rng(5)
