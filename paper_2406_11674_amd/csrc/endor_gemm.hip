@@ -58,9 +58,9 @@ using endor_gemm_plan::Plan;
 using endor_gemm_units::Fetch;
 using endor_gemm_units::fetch_lane;
 using endor_gemm_units::fetch_row;
+using endor_gemm_units::is_far;
 using endor_gemm_units::kFetchLoads;
 using endor_gemm_units::kRows;
-using endor_gemm_units::kSpan;
 using endor_gemm_units::Limits;
 using endor_gemm_units::limits_of;
 using endor_gemm_units::Slice;
@@ -167,8 +167,8 @@ struct RowStreams {
     uintptr_t wave_base;  // the unit that holds the range's first value of the wave's first row (wave-uniform)
     uint32_t delta;       // row_first - wave_base
     Limits limits;        // what may be read around wave_base
-    bool far;             // wave-uniform: the rows lie too far apart for 32-bit offsets
-    bool ahead;           // wave-uniform: units are asked for a round ahead (not far, and not next to no values)
+    bool far;             // wave-uniform: some value may lie too far from wave_base for 32-bit offsets
+    bool ahead;           // wave-uniform, of a range that is not far: there is a unit to ask for ahead
     uint32_t off;         // bytes of the row's values before the next round
 
     __device__ __forceinline__ void init(uint32_t lane) {
@@ -179,19 +179,19 @@ struct RowStreams {
         fu = l % F::kUnits;
     }
 
-    // Start a range of columns.  (A range is at most a few thousand rounds long, so offsets inside a
-    // row fit 32 bits whatever the matrix.)
-    __device__ __forceinline__ void begin(uintptr_t vbeg_, uintptr_t vend_, uintptr_t first) {
+    // Start a range of `width` columns: at most 2^30 (a sixteenth of a matrix of one row), so an offset
+    // inside a row's range stays below 2^31 whatever the matrix.
+    __device__ __forceinline__ void begin(uintptr_t vbeg_, uintptr_t vend_, uintptr_t first, uint32_t width) {
         vbeg = vbeg_;
         vend = vend_;
         row_first = first;
         const uintptr_t b = first & ~uintptr_t(15);
         wave_base = (uintptr_t(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)))) << 32) |
                     static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)));
-        far = __builtin_amdgcn_ballot_w64(first - wave_base >= kSpan) != 0;
+        far = __builtin_amdgcn_ballot_w64(is_far(first, wave_base, width)) != 0;
         delta = static_cast<uint32_t>(first - wave_base);
         limits = limits_of(vbeg, vend, wave_base);
-        ahead = limits.ready && !far;
+        ahead = limits.ready;
         off = 0;
     }
 
@@ -208,32 +208,45 @@ struct RowStreams {
         R.at = mr * kPitch + (start & 15u) + 2 * before;
         R.off = off;
         off += 2 * cnt;
-        const Slice slice = slice_of(limits, start, cnt);
-        R.units = slice.units;
-        R.whole = slice.whole;
-        uint32_t info = slice.info;
-        R.late = F::kTail != 0 || __builtin_amdgcn_ballot_w64(R.whole > F::kUnits) == 0 ? kNoneLate : uint32_t(F::kUnits);
-        if (!ahead) {  // nothing is asked for ahead
-            info = 0;
-            R.whole = 0;
-            R.late = kNoneLate;
-            if (far) {  // rows of ten million columns and more: whole units when the round is staged
-                const uintptr_t f = (row_first + R.off) & ~uintptr_t(15);
-                const uintptr_t units = f >= vbeg && vend > f ? (vend - f) >> 4 : 0;
-                R.whole = R.units < units ? R.units : static_cast<uint32_t>(units);
-                R.late = 0;
-            }
+        if (far) {
+            fetch_far(cnt, R, P);
+        } else {
+            const Slice slice = slice_of(limits, start, cnt);
+            R.units = slice.units;
+            R.whole = ahead ? slice.whole : 0u;
+            const uint32_t info = ahead ? slice.info : 0u;
+            const uintptr_t base = ahead ? wave_base : reinterpret_cast<uintptr_t>(&g_dummy);
+            auto load = [&](uint32_t row_info, uint32_t unit) -> u32x4 {
+                return *global_ptr<u32x4>(base + unit_offset(row_info, unit));
+            };
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i)
+                P.d[i] = load(static_cast<uint32_t>(
+                                  __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * load_row(i)), static_cast<int>(info))), fu);
+            if (F::kTail) P.d[kLoads] = load(info, F::kUnits);
         }
         R.ragged = __builtin_amdgcn_ballot_w64(R.whole < R.units) != 0;
-        const uintptr_t base = ahead ? wave_base : reinterpret_cast<uintptr_t>(&g_dummy);
-        auto load = [&](uint32_t row_info, uint32_t unit) -> u32x4 {
-            return *global_ptr<u32x4>(base + unit_offset(row_info, unit));
+        R.late = F::kTail != 0 || __builtin_amdgcn_ballot_w64(R.whole > F::kUnits) == 0 ? kNoneLate : uint32_t(F::kUnits);
+    }
+
+    // The same with each row's whole address handed to the lanes that load for it.
+    __device__ __forceinline__ void fetch_far(uint32_t cnt, Round &R, Pieces &P) const {
+        uintptr_t first = (row_first + R.off) & ~uintptr_t(15);
+        const uintptr_t room = first >= vbeg && vend > first ? (vend - first) >> 4 : 0;
+        R.units = cnt ? ((static_cast<uint32_t>(row_first + R.off) & 15u) + 2 * cnt + 15) >> 4 : 0u;
+        R.whole = R.units < room ? R.units : static_cast<uint32_t>(room);
+        if (R.whole == 0) first = reinterpret_cast<uintptr_t>(&g_dummy);
+        const uint32_t last = R.whole ? R.whole - 1 : 0u;
+        auto of_row = [](uint32_t row, uint32_t x) {
+            return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(static_cast<int>(4 * row), static_cast<int>(x)));
         };
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i)
-            P.d[i] = load(static_cast<uint32_t>(
-                              __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * load_row(i)), static_cast<int>(info))), fu);
-        if (F::kTail) P.d[kLoads] = load(info, F::kUnits);
+        for (int i = 0; i < kLoads; ++i) {
+            const uint32_t row = load_row(i), l = of_row(row, last);
+            const uintptr_t p = (uintptr_t(of_row(row, static_cast<uint32_t>(first >> 32))) << 32) | of_row(row, static_cast<uint32_t>(first));
+            P.d[i] = *global_ptr<u32x4>(p + 16 * (fu < l ? fu : l));
+        }
+        if (F::kTail) P.d[kLoads] = *global_ptr<u32x4>(first + 16 * (F::kUnits < last ? F::kUnits : last));
     }
 
     // The round's values into LDS.
@@ -513,7 +526,7 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
             cursor = vbeg + 2 * ((uint64_t(hi) << 32) | lo);
         }
 
-        V.begin(vbeg, vend, cursor);
+        V.begin(vbeg, vend, cursor, width);
 
         // A round's values are in flight while the one before is multiplied, its bitmap words one
         // round longer.  The loop body handles two rounds: no register is copied from one buffer to

@@ -47,7 +47,14 @@ constexpr uint32_t fetch_row(int load, uint32_t row_of_load) {
                : kRows - 1;
 }
 
-constexpr uint64_t kSpan = uint64_t(1) << 28;  // bytes; rows that start further apart do not share a base
+constexpr uint64_t kSpan = uint64_t(1) << 28;  // bytes
+
+// A row whose values of a range of `width` columns may lie too far from the wave's base (the unit of its
+// first row's first value) for offsets of 32 bits: rows of more than some ten million columns, whose 16
+// starts are far apart, and ranges of more than 2^27 columns.  Others stay below base + 2 * kSpan.
+constexpr bool is_far(uint64_t first, uint64_t base, uint32_t width) {
+    return first - base >= kSpan || 2 * uint64_t(width) > kSpan;
+}
 
 // What may be read around `base`, a 16-byte boundary: the unit of the first value of the wave's first
 // row.  An array that is not 16-byte aligned begins inside that unit, which then is not read.
@@ -60,7 +67,7 @@ struct Limits {
 constexpr Limits limits_of(uint64_t vbeg, uint64_t vend, uint64_t base) {
     Limits L{};
     L.lo = base >= vbeg ? 0u : static_cast<uint32_t>(vbeg - base);  // a table that lies may put the base anywhere
-    L.hi = vend <= base ? 0u : vend - base < 2 * kSpan ? static_cast<uint32_t>(vend - base) : static_cast<uint32_t>(2 * kSpan);
+    L.hi = vend <= base ? 0u : vend - base < 3 * kSpan ? static_cast<uint32_t>(vend - base) : static_cast<uint32_t>(3 * kSpan);
     if (base < vbeg && vbeg - base > 15) L.hi = 0;
     L.idle = L.lo ? 1u : 0u;
     L.ready = L.hi >= 16 * (L.idle + 1);

@@ -104,7 +104,34 @@ static const char *partition(int64_t rows, int64_t cols) {
     return nullptr;
 }
 
+// Matrices larger than can be walked here: wherever a row of a range that is not far may stand, its units
+// are all read whole, and the offsets of any range fit 32 bits.
+static const char *extremes() {
+    using namespace endor_gemm_plan;
+    const uint64_t vbeg = 0x7f0000000000ull, vend = vbeg + (uint64_t(1) << 35);
+    const Limits L = limits_of(vbeg, vend, vbeg);
+    for (uint64_t delta : {uint64_t(0), uint64_t(14), kSpan - 2, kSpan, uint64_t(1) << 33})
+        for (uint64_t width : {uint64_t(256), kSpan / 4, kSpan / 2, kSpan / 2 + 1, kSpan, 2 * kSpan}) {
+            if (is_far(vbeg + delta, vbeg, static_cast<uint32_t>(width))) {
+                if (delta < kSpan && 2 * width <= kSpan) return "a short range counts as far";
+                continue;
+            }
+            for (uint64_t off : {uint64_t(0), width, 2 * width - 512}) {
+                const Slice s = slice_of(L, static_cast<uint32_t>(delta + off), 256);
+                if (s.whole != s.units) return "units of a long range are not read whole";
+                if (unit_offset(s.info, 0) != ((delta + off) & ~uint64_t(15))) return "a unit of a long range is read from another place";
+            }
+        }
+    const Plan p = make_plan(1, (int64_t(1) << 34) - 1);
+    if (2 * uint64_t(p.per_wg) * kSegCols >> 32) return "offsets inside a range do not fit";
+    return nullptr;
+}
+
 int main() {
+    if (const char *bad = extremes()) {
+        std::printf("%s\n", bad);
+        return 1;
+    }
     for (int64_t rows : {int64_t(1), int64_t(64), int64_t(65), int64_t(2053), int64_t(28672), int64_t(32768), int64_t(32769), int64_t(36864), int64_t(131072), int64_t(524289), int64_t(2147483632)})
         for (int64_t cols : {int64_t(1), int64_t(100), int64_t(256), int64_t(257), int64_t(768), int64_t(1031), int64_t(3072), int64_t(3073), int64_t(8192), int64_t(28672), int64_t(1) << 24, (int64_t(1) << 34) - 1}) {
             if (cols > ((int64_t(1) << 34) - 1) / rows) continue;

@@ -1216,6 +1216,34 @@ def test_more_than_2_pow_32_elements_sparse_random():
     assert np.array_equal(rsel.cpu().numpy().view(np.uint16), expect)
 
 
+@pytest.mark.parametrize("cols,keep", [(19_000_003, 0.48), (19_000_064, 0.48), (19_000_003, 0.9)])
+def test_gemm_rows_too_far_apart_for_32_bit_offsets(cols, keep):
+    """16 rows of 19 million columns span more than 2^28 bytes of values and 64 chunks of the offset table:
+    their units are fetched with whole addresses, and their starts looked up one by one.  A second group
+    of one row takes the ordinary way.  One row keeps everything (more units than are asked for ahead),
+    one has a long gap.  Values off a 16-byte boundary with NaN patterns around them; small integers, so
+    that every sum is exact in fp32 and in the reference's fp64."""
+    rows, nb, voff = 17, 3, 3
+    _say(f"gemm far rows cols={cols} keep={keep}")
+    gen = torch.Generator(device="cuda").manual_seed(cols)
+    w = torch.randint(1, 9, (rows, cols), device="cuda", generator=gen, dtype=torch.int16).to(torch.float16)
+    kept = torch.rand((rows, cols), device="cuda", generator=gen) < keep
+    kept[3] = True
+    kept[5, 1000:100_000] = False
+    w *= kept
+    X = torch.randint(-8, 9, (nb, cols), device="cuda", generator=gen, dtype=torch.int16).to(torch.float16)
+    c, ws, _ = endor.compress_device(w.view(torch.int16))
+    buf = torch.full((c.nnz + 16,), 0x7E00, dtype=torch.int16, device="cuda")
+    buf[voff:voff + c.nnz] = c.values
+    m = endor.DeviceMatrix(rows, cols, c.bitmap, buf[voff:voff + c.nnz], c.nnz)
+    Y = endor.gemm_f16(m, ws, X)
+    ref = torch.zeros((nb, rows), dtype=torch.float64, device="cuda")
+    for a in range(0, cols, 1 << 21):
+        ref += X[:, a:a + (1 << 21)].double() @ w[:, a:a + (1 << 21)].double().t()
+    torch.cuda.synchronize()
+    assert torch.equal(Y.double(), ref)
+
+
 def test_host_built_offset_table_serves_the_device():
     """The table built at compression time on the host, copied over, replaces the device pass."""
     rows, cols = 1031, 2053
