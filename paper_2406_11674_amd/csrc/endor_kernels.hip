@@ -722,7 +722,8 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     const uint8_t *stage = reinterpret_cast<const uint8_t *>(s_dyn + 4 * nvw);
     uint32_t staged = 0;  // of the row's values, those in LDS
     if (kStaged) {
-        const int64_t row_next = C.row_offsets[i + 1];
+        // how much is staged; a row that turns out to have more values is gathered after all
+        const int64_t row_next = i + 1 < C.rows ? C.row_offsets[i + 1] : C.nnz;
         const uintptr_t vbeg = reinterpret_cast<uintptr_t>(C.values), vend = vbeg + E * static_cast<uintptr_t>(C.nnz);
         const uintptr_t a16 = vaddr & ~uintptr_t(15);
         const uint64_t count = row_first >= 0 && row_next > row_first && row_next <= C.nnz ? static_cast<uint64_t>(row_next - row_first) : 0;
@@ -771,7 +772,10 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
             s_before[2 * k + 1] = excl + __popc(lo);
         }
     }
-    if (kStaged) wait_loads_to_lds();
+    if (kStaged) {
+        wait_loads_to_lds();
+        if (carry > staged) staged = 0;  // carry: the row's 1 bits; the next entry of row_offsets is not this row's end
+    }
     __syncthreads();
 
     // values from the row's first to the end of the array; none if the offset is not inside it
@@ -798,9 +802,9 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
             const uint32_t r = s_before[cc >> 5] + __popc(piece & ((1u << b) - 1));  // rank inside the row
             hit[u] = live[u] && ((piece >> b) & 1) != 0 && r < room;
             if (kStaged && staged) {  // workgroup-uniform
-                const uint32_t at = r < staged ? r : 0u;  // a table that is not this bitmap's stays inside the area
+                // r: less than the row's 1 bits if the bit is set, at most that if not
+                const uint32_t at = r < staged ? r : 0u;
                 v[u] = (E == 2) ? uint32_t(reinterpret_cast<const uint16_t *>(stage)[at]) : uint32_t(stage[at]);
-                hit[u] = hit[u] && r < staged;
                 continue;
             }
             // The load itself is unconditional (a query without a value reads the first selected

@@ -1320,6 +1320,38 @@ def test_decompress_cols_with_staged_rows(wide, voff):
         assert np.array_equal(out.cpu().numpy().view(w.dtype), expect)
 
 
+@pytest.mark.parametrize("wide", [True, False], ids=["fp16", "u8"])
+def test_decompress_cols_takes_only_row_starts_from_the_table(wide):
+    """A row's values are those from its own entry of row_offsets on: rows kept in another order than the
+    matrix's, rows that share values, and whatever stands behind the last row's entry give the same
+    result whether a row is staged or gathered."""
+    rows, cols = 8, 16384 if wide else 32768
+    g = np.random.default_rng(5)
+    w = g.integers(1, 200, (rows, cols)).astype(np.uint16 if wide else np.uint8)
+    w[g.random((rows, cols)) >= 0.4] = 0
+    w[3] = w[2]                                                                       # shares its values below
+    c = endor.compress(w)
+    dt = torch.int16 if wide else torch.uint8
+    order = [5, 0, 7, 2, 1, 6, 4]
+    parts, ro, at = [], np.zeros(rows + 1, np.int64), 0
+    for r in order:
+        ro[r] = at
+        parts.append(w[r][w[r] != 0])
+        at += parts[-1].size
+    ro[3] = ro[2]
+    values = np.concatenate(parts)
+    values = np.concatenate([values, np.zeros(c.nnz - values.size, values.dtype)])
+    m = endor.DeviceMatrix(rows, cols, torch.from_numpy(c.bitmap).cuda(),
+                           torch.from_numpy(values.view(np.int16) if wide else values).cuda(), c.nnz)
+    sel = np.sort(g.permutation(cols)[:cols // 4]).astype(np.int64)
+    for behind in (ro[rows - 1] + 1, ro[rows - 1] + 500, -3, c.nnz):
+        ro[rows] = behind
+        out = torch.full((rows, sel.size), 0x33, dtype=dt, device="cuda")
+        endor.decompress_cols(m, torch.from_numpy(ro).cuda(), torch.from_numpy(sel).cuda(), out=out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(w.dtype), w[:, sel])
+
+
 def test_decompress_cols_out_of_range_index_is_skipped():
     rows, cols = 12, 5000
     w = synth.pruned_fp16(rows, cols, 0.5, seed=79)
