@@ -1487,10 +1487,12 @@ endor_matrix one_matrix(int64_t rows, int64_t cols, const uint8_t *d_bitmap, con
 
 // Per-row offsets from a finished table.  A matrix without elements has no chunks and no tiles: all
 // entries are 0 then.
+int64_t row_offsets_blocks(int64_t rows) { return (rows + 1 + kWaves - 1) / kWaves; }
+bool row_offsets_ok(int64_t rows) { return row_offsets_blocks(rows) <= 0x7fffffff; }
+
 endor_status launch_row_offsets(const MatParams &M, int64_t rows, int64_t cols, int64_t *d_row_offsets, hipStream_t s) {
-    const int64_t entries = rows + 1;
-    if ((entries + kWaves - 1) / kWaves > 0x7fffffff) return ENDOR_ERR_UNSUPPORTED;
-    const unsigned blocks = static_cast<unsigned>((entries + kWaves - 1) / kWaves);
+    if (!row_offsets_ok(rows)) return ENDOR_ERR_UNSUPPORTED;
+    const unsigned blocks = static_cast<unsigned>(row_offsets_blocks(rows));
     hipLaunchKernelGGL(endor_row_offsets_kernel, dim3(blocks), dim3(kBlock), 0, s, M, rows, cols, d_row_offsets);
     return hipGetLastError() == hipSuccess ? ENDOR_OK : ENDOR_ERR_HIP;
 }
@@ -1782,8 +1784,9 @@ endor_status run_compress_device(int64_t rows, int64_t cols, const void *d_dense
         if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) & 255)) return ENDOR_ERR_INVALID_ARG;
         if (workspace_bytes < workspace_bytes_n(n)) return ENDOR_ERR_BUFFER_TOO_SMALL;
     }
-    // the table (and the row offsets) come from the ordinary offsets path, run on the
-    // bitmap the mask kernel writes
+    if (d_row_offsets && !row_offsets_ok(rows)) return ENDOR_ERR_UNSUPPORTED;
+    // mask kernel: the bitmap, and each tile's count in its slot of the table; scan kernel: the table;
+    // pack kernel: the values, the row offsets and the total
     CompressParams C{};
     C.dense = d_dense;
     C.bitmap = reinterpret_cast<uint64_t *>(d_bitmap);

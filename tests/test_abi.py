@@ -135,6 +135,10 @@ def test_widened_entry_points_reject_bad_arguments_without_launching():
     assert L.endor_compress_device(4, 64, fake, fake, fake, 256, fake, 16, None, fake, None) == 2
     assert L.endor_compress_device(4, 64, fake, fake, fake, -1, fake, ws, None, fake, None) == 1
     assert L.endor_compress_device(1 << 20, 1 << 20, fake, fake, fake, 256, fake, ws, None, fake, None) == 3
+    # row offsets of more rows than a launch of the row-offset kernel reaches
+    huge = 4 * 0x7fffffff
+    assert L.endor_compress_device(huge, 1, fake, fake, fake, 256, fake, 1 << 34, fake, fake, None) == 3
+    assert L.endor_compress_device_u8(huge, 1, fake, fake, fake, 256, fake, 1 << 34, fake, fake, None) == 3
     # host table builder
     assert L.endor_build_offsets_host(4, 64, None, fake, ws) == 1
     assert L.endor_build_offsets_host(-1, 64, fake, fake, ws) == 1
