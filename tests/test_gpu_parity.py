@@ -1075,9 +1075,60 @@ def test_decompress_straight_from_pinned_host_memory():
     assert np.array_equal(out.cpu().numpy().view(np.uint16), _expect(c))
 
 
+@pytest.mark.parametrize("wide", [True, False], ids=["fp16", "u8"])
+def test_small_decompress_straight_from_pinned_host_memory(wide):
+    """A matrix small enough for the one-kernel form, its bitmap in pinned host memory: the two-kernel form
+    runs instead, with the same output and table."""
+    rows, cols = 300, 1001
+    c = (_random_compressed if wide else _random_compressed_u8)(rows, cols, 0.5, seed=8)
+    blob = endor.pin(c)
+    nb = endor.bitmap_bytes(rows, cols)
+    vals = blob.keep[(nb + 255) // 256 * 256:]
+    m = endor.DeviceMatrix(rows, cols, blob.keep[:nb], vals.view(torch.int16) if wide else vals, c.nnz)
+    assert m.bitmap.is_pinned()
+    out = torch.full((rows, cols), 0x5A, dtype=torch.int16 if wide else torch.uint8, device="cuda")
+    ws = torch.full((endor.workspace_bytes(rows, cols),), 0xFF, dtype=torch.uint8, device="cuda")
+    endor.decompress(m, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    expect = orc.decompress(rows, cols, c.bitmap, c.values)
+    assert np.array_equal(out.cpu().numpy().view(expect.dtype), expect)
+    host, dev = endor.build_offsets_host(c), ws.cpu().numpy()
+    assert np.array_equal(dev[:4], host[:4]) and np.array_equal(dev[256:256 + 4 * 257], host[256:256 + 4 * 257])
+
+
 # ---------------------------------------------------------------------------
 # the device entry points only enqueue kernels: they can be captured into a HIP graph
 # ---------------------------------------------------------------------------
+def test_small_decompress_in_a_hip_graph_replays_correctly():
+    """The one-kernel form looks at the bitmap's kind of memory on the host; captured, it is one kernel
+    node, which reads what the buffers hold when it is replayed."""
+    rows, cols = 700, 1000
+    cs = [endor.compress(synth.pruned_fp16(rows, cols, 0.5, seed=40 + i)) for i in range(3)]
+    nnz = max(c.nnz for c in cs)
+    bitmap = torch.zeros(endor.bitmap_bytes(rows, cols), dtype=torch.uint8, device="cuda")
+    values = torch.zeros(nnz, dtype=torch.int16, device="cuda")
+    m = endor.DeviceMatrix(rows, cols, bitmap, values, nnz)
+    out = torch.empty((rows, cols), dtype=torch.int16, device="cuda")
+    ws = torch.empty(endor.workspace_bytes(rows, cols), dtype=torch.uint8, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    endor.decompress(m, out=out, workspace=ws, stream=side)                    # warm-up outside capture
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        endor.decompress(m, out=out, workspace=ws, stream=torch.cuda.current_stream())
+    for c in cs + cs[:1]:
+        bitmap.copy_(torch.from_numpy(c.bitmap))
+        values[:c.nnz].copy_(torch.from_numpy(c.values.view(np.int16)))
+        out.fill_(POISON)
+        ws.fill_(0xFF)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint16), _expect(c))
+
+
 def test_decompress_batch_in_a_hip_graph_replays_correctly():
     shapes = [(300, 4099), (64, 4096), (1031, 2053)]
     cs = [endor.compress(synth.pruned_fp16(r, c, 0.5, seed=60 + i)) for i, (r, c) in enumerate(shapes)]
