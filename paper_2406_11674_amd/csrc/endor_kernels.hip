@@ -45,6 +45,7 @@
 
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "endor.h"
 #include "endor_device.h"
@@ -672,7 +673,7 @@ struct ColsParams {
     const int64_t *row_offsets;  // rows + 1
     const int64_t *sel;          // nsel column indices
     int64_t rows, cols, nnz, nsel;
-    uint32_t stage_units;        // 16-byte units of `values` the staging area holds (kStaged)
+    uint32_t stage_units;        // 16-byte units the staging area holds, one of them spare (kStaged)
 };
 
 // 64 bits of row-aligned "virtual word" k of a row that starts at bit row_bit: bits
@@ -717,18 +718,23 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     // The row's values, on their way to LDS while the bitmap is worked on: 16-byte units from the
     // boundary at or below the first one.  A row that does not fit, or whose units reach over an end of
     // the array, is gathered from memory.
-    const int64_t row_first = C.row_offsets[i];
+    // Staged: the row's entry and the next one in one trip; for the last row, which has no next one, the one
+    // before (a single row is never staged).
+    const bool last_row = i + 1 == C.rows;
+    const int64_t *entry = C.row_offsets + (kStaged && last_row ? i - 1 : i);
+    const int64_t entry0 = entry[0], entry1 = kStaged ? entry[1] : 0;
+    const int64_t row_first = kStaged && last_row ? entry1 : entry0;
     const uintptr_t vaddr = reinterpret_cast<uintptr_t>(C.values) + E * static_cast<uintptr_t>(row_first);
     const uint8_t *stage = reinterpret_cast<const uint8_t *>(s_dyn + 4 * nvw);
     uint32_t staged = 0;  // of the row's values, those in LDS
     if (kStaged) {
         // how much is staged; a row that turns out to have more values is gathered after all
-        const int64_t row_next = i + 1 < C.rows ? C.row_offsets[i + 1] : C.nnz;
+        const int64_t row_next = last_row ? C.nnz : entry1;
         const uintptr_t vbeg = reinterpret_cast<uintptr_t>(C.values), vend = vbeg + E * static_cast<uintptr_t>(C.nnz);
         const uintptr_t a16 = vaddr & ~uintptr_t(15);
         const uint64_t count = row_first >= 0 && row_next > row_first && row_next <= C.nnz ? static_cast<uint64_t>(row_next - row_first) : 0;
         const uint64_t units = ((vaddr - a16) + E * count + 15) >> 4;
-        if (count != 0 && units <= C.stage_units && a16 >= vbeg && a16 + 16 * units <= vend) {  // workgroup-uniform
+        if (count != 0 && units < C.stage_units && a16 >= vbeg && a16 + 16 * units <= vend) {  // workgroup-uniform
             staged = static_cast<uint32_t>(count);
             u32x4 *to = reinterpret_cast<u32x4 *>(s_dyn + 4 * nvw);
             for (uint32_t u0 = 64 * wave; u0 < units; u0 += kBlock)
@@ -774,7 +780,8 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     }
     if (kStaged) {
         wait_loads_to_lds();
-        if (carry > staged) staged = 0;  // carry: the row's 1 bits; the next entry of row_offsets is not this row's end
+        // carry: the row's 1 bits.  More than are staged: the next entry of row_offsets is not this row's end.
+        if (static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(carry))) > staged) staged = 0;
     }
     __syncthreads();
 
@@ -783,50 +790,58 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     const uint8_t *row_values = static_cast<const uint8_t *>(C.values) + E * row_first;
     uint8_t *row_out = static_cast<uint8_t *>(C.out) + E * i * C.nsel;
     const uint64_t ucols = static_cast<uint64_t>(C.cols);
-    for (int64_t q0 = 0; q0 < C.nsel; q0 += kQ * kBlock) {
-        int64_t cn[kQ];
+    // The queries.  kFromLds: the row's values are staged.  (Two loops, not one with a test: the test cost the
+    // staged form 15 % and the gather up to 5 %.)
+    auto answer = [&](auto from_lds) {
+        constexpr bool kFromLds = decltype(from_lds)::value;
+        for (int64_t q0 = 0; q0 < C.nsel; q0 += kQ * kBlock) {
+            int64_t cn[kQ];
 #pragma unroll
-        for (int u = 0; u < kQ; ++u) {  // the next round's indices
-            const int64_t q = q0 + (kQ + u) * kBlock + threadIdx.x;
-            cn[u] = q < C.nsel ? C.sel[q] : -1;
-        }
-        uint32_t v[kQ];
-        bool live[kQ], hit[kQ];
-#pragma unroll
-        for (int u = 0; u < kQ; ++u) {
-            // an index outside the matrix (or past nsel) leaves its output column untouched
-            live[u] = static_cast<uint64_t>(c[u]) < ucols;
-            const uint32_t cc = live[u] ? static_cast<uint32_t>(c[u]) : 0u;
-            const uint32_t piece = s_piece[cc >> 5];
-            const uint32_t b = cc & 31;
-            const uint32_t r = s_before[cc >> 5] + __popc(piece & ((1u << b) - 1));  // rank inside the row
-            hit[u] = live[u] && ((piece >> b) & 1) != 0 && r < room;
-            if (kStaged && staged) {  // workgroup-uniform
-                // r: less than the row's 1 bits if the bit is set, at most that if not
-                const uint32_t at = r < staged ? r : 0u;
-                v[u] = (E == 2) ? uint32_t(reinterpret_cast<const uint16_t *>(stage)[at]) : uint32_t(stage[at]);
-                continue;
+            for (int u = 0; u < kQ; ++u) {  // the next round's indices
+                const int64_t q = q0 + (kQ + u) * kBlock + threadIdx.x;
+                cn[u] = q < C.nsel ? C.sel[q] : -1;
             }
-            // The load itself is unconditional (a query without a value reads the first selected
-            // index instead and drops it): with the load under the test, the compiler waits for
-            // memory after every query and every store, one at a time.
-            const uint8_t *at = hit[u] ? row_values + size_t(E) * r : reinterpret_cast<const uint8_t *>(C.sel);
-            v[u] = (E == 2) ? uint32_t(*reinterpret_cast<const uint16_t *>(at)) : uint32_t(*at);
-        }
+            uint32_t v[kQ];
+            bool live[kQ], hit[kQ];
 #pragma unroll
-        for (int u = 0; u < kQ; ++u) v[u] = hit[u] ? v[u] : 0u;
-#pragma unroll
-        for (int u = 0; u < kQ; ++u) {
-            const int64_t q = q0 + u * kBlock + threadIdx.x;
-            if (live[u]) {
-                if (E == 2)
-                    reinterpret_cast<uint16_t *>(row_out)[q] = static_cast<uint16_t>(v[u]);
-                else
-                    row_out[q] = static_cast<uint8_t>(v[u]);
+            for (int u = 0; u < kQ; ++u) {
+                // an index outside the matrix (or past nsel) leaves its output column untouched
+                live[u] = static_cast<uint64_t>(c[u]) < ucols;
+                const uint32_t cc = live[u] ? static_cast<uint32_t>(c[u]) : 0u;
+                const uint32_t piece = s_piece[cc >> 5];
+                const uint32_t b = cc & 31;
+                const uint32_t r = s_before[cc >> 5] + __popc(piece & ((1u << b) - 1));  // rank inside the row
+                hit[u] = live[u] && ((piece >> b) & 1) != 0 && r < room;
+                if (kFromLds) {
+                    // r is at most the row's 1 bits: one value past the staged ones, in the area's spare unit
+                    v[u] = (E == 2) ? uint32_t(reinterpret_cast<const uint16_t *>(stage)[r]) : uint32_t(stage[r]);
+                    continue;
+                }
+                // The load itself is unconditional (a query without a value reads the first selected
+                // index instead and drops it): with the load under the test, the compiler waits for
+                // memory after every query and every store, one at a time.
+                const uint8_t *at = hit[u] ? row_values + size_t(E) * r : reinterpret_cast<const uint8_t *>(C.sel);
+                v[u] = (E == 2) ? uint32_t(*reinterpret_cast<const uint16_t *>(at)) : uint32_t(*at);
             }
-            c[u] = cn[u];
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) v[u] = hit[u] ? v[u] : 0u;
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) {
+                const int64_t q = q0 + u * kBlock + threadIdx.x;
+                if (live[u]) {
+                    if (E == 2)
+                        reinterpret_cast<uint16_t *>(row_out)[q] = static_cast<uint16_t>(v[u]);
+                    else
+                        row_out[q] = static_cast<uint8_t>(v[u]);
+                }
+                c[u] = cn[u];
+            }
         }
-    }
+    };
+    if (kStaged && staged)  // workgroup-uniform
+        answer(std::true_type{});
+    else
+        answer(std::false_type{});
 }
 
 // ---------------------------------------------------------------- fused consumer: y = W x
@@ -1883,7 +1898,7 @@ extern "C" endor_status endor_gemv_f16(int64_t rows, int64_t cols, const uint8_t
 
 namespace {
 
-constexpr size_t kMaxColsLds = 40 * 1024, kMinColsStage = 6 * 1024;
+constexpr size_t kMaxColsLds = 40 * 1024, kMinColsStage = 6 * 1024, kLdsPerUnit = 160 * 1024;
 constexpr int64_t kMaxGatherCols = int64_t(1) << 18;  // the row's bitmap and its prefixes live in LDS (16 bytes per 64 columns)
 
 endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t *d_bitmap, const void *d_values,
@@ -1913,15 +1928,27 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     const size_t lds = static_cast<size_t>((cols + 63) / 64) * 4 * sizeof(uint32_t);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid(static_cast<unsigned>(rows));
-    // room for an eighth more values than a row has on average
+    // room for an eighth more values than a row has on average, and a spare unit
     const size_t stage = (static_cast<size_t>(nnz / rows) * 9 / 8 * elem_bytes + 256 + 15) & ~size_t(15);
     // Staging pays when most 64-byte lines of a row's values are wanted anyway (a sixteenth of the
     // columns; the gather then costs a cache access per value, staging one per 64 bytes), the row is
     // long enough for that to matter and short enough for four workgroups per compute unit.  Measured,
-    // gather against staged: a tenth of 8192 x 28672 65 / 62 us, three tenths 135 / 112, 8-bit 51 / 41, one
-    // in five kept 53 / 39, four tenths of 28672 x 8192 186 / 121; but 8192 x 28672 with four in five kept
+    // gather against staged: a tenth of 8192 x 28672 65 / 63 us, three tenths 135 / 114, 8-bit 50 / 41, one
+    // in five kept 52 / 39, three tenths of 36864 x 9216 198 / 138; but 8192 x 28672 with four in five kept
     // (52 KB a row) 89 / 105, a fifth of 5003 x 3171 (4 KB) 11 / 13, a tenth of 30000 x 700 39 / 49.
-    const bool staged = nsel >= cols / 16 && stage >= kMinColsStage && lds + stage <= kMaxColsLds;
+    const bool rows_fit = nsel >= cols / 16 && stage >= kMinColsStage && lds + stage <= kMaxColsLds;
+    // And there has to be a lot to read or to answer: otherwise a workgroup's wait for its row shows, while
+    // the gather finds values that the memory-side cache holds.  A tenth of 2048 x 16384 9 / 12 us, three
+    // tenths 17 / 19, half 25 / 25; 3000 x 36864, 8-bit (55 MB), a tenth 21 / 25, a fifth 43 / 35; 4096 x
+    // 28672, one in five kept (47 MB), 0.07 of the columns 17 / 19, 0.15 37 / 29; 0.07 of 7200 x 12000,
+    // 8-bit, 16 / 18; of 9216 x 9216, two in five kept (68 MB) 20 / 21, half kept (85 MB) 24 / 22.
+    const int64_t asked = rows * nsel;
+    const bool much = nnz * elem_bytes >= (int64_t(9) << 23) || asked >= 14000000 || (rows >= 28 * 256 && asked >= 8000000);
+    // Or all rows on the chip at once, none of them long: a fifth of 1024 x 16384, 8-bit, 9.5 / 8.3 us, half
+    // 17 / 13; fp16, four in five kept (26 KB a row), a fifth 9.7 / 11.2.
+    const bool at_once = rows <= 2048 && static_cast<size_t>(rows) * (lds + stage) <= 256 * kLdsPerUnit && nsel >= cols / 5 &&
+                         nnz * elem_bytes <= rows * 20480;
+    const bool staged = rows > 1 && rows_fit && (much || at_once);
     C.stage_units = static_cast<uint32_t>(stage / 16);
     if (elem_bytes == 2) {
         if (staged)

@@ -1394,9 +1394,10 @@ def test_decompress_cols_takes_only_row_starts_from_the_table(wide):
     values = np.concatenate([values, np.zeros(c.nnz - values.size, values.dtype)])
     m = endor.DeviceMatrix(rows, cols, torch.from_numpy(c.bitmap).cuda(),
                            torch.from_numpy(values.view(np.int16) if wide else values).cuda(), c.nnz)
-    sel = np.sort(g.permutation(cols)[:cols // 4]).astype(np.int64)
-    for behind in (ro[rows - 1] + 1, ro[rows - 1] + 500, -3, c.nnz):
+    for behind, nsel in ((ro[rows - 1] + 1, cols // 5), (ro[rows - 1] + 1, cols // 5 - 1), (ro[rows - 1] + 500, cols),
+                         (-3, cols // 4), (c.nnz, cols // 4)):                          # gathered below a fifth
         ro[rows] = behind
+        sel = np.sort(g.permutation(cols)[:nsel]).astype(np.int64)
         out = torch.full((rows, sel.size), 0x33, dtype=dt, device="cuda")
         endor.decompress_cols(m, torch.from_numpy(ro).cuda(), torch.from_numpy(sel).cuda(), out=out)
         torch.cuda.synchronize()
