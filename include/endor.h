@@ -149,7 +149,8 @@ endor_status endor_build_offsets_host(int64_t rows, int64_t cols, const uint8_t 
  * of the rows*cols output elements is written exactly once, with the next unread
  * value where the bit is 1 and the all-zero pattern where it is 0.  Builds the
  * offset table into d_workspace first (same work as endor_build_offsets without
- * row offsets), then expands.
+ * row offsets), then expands; a small matrix (up to 2^21 elements, bitmap in device
+ * memory) takes one kernel for both, which leaves the same table.
  */
 endor_status endor_decompress(int64_t rows, int64_t cols,
                               const uint8_t *d_bitmap, const uint16_t *d_values, int64_t nnz,
@@ -167,7 +168,7 @@ endor_status endor_decompress_with_offsets(int64_t rows, int64_t cols,
 /*
  * DEVICE.  Decompress `count` matrices (e.g. all linear weights of one decoder
  * layer) with one pair of launches per ENDOR_MAX_BATCH matrices instead of one
- * pair per matrix.  `mats` is a HOST array, read before the call returns.
+ * pair per matrix (a single small matrix: one launch).  `mats` is a HOST array, read before the call returns.
  * Matrix m uses the workspace slice that starts at the sum of
  * endor_workspace_bytes() of the matrices before it.
  */
@@ -189,7 +190,7 @@ endor_status endor_decompress_batch_with_offsets(const endor_matrix *mats, int c
  * ENDOR_STATIC_SCRATCH_BYTES bytes of device memory that is part of the library's code
  * object (each GPU the library runs on holds its own copy until the process ends), so the
  * call takes no workspace and performs no allocation of any kind; apart from resolving the
- * array's address on its first call on a device it only enqueues the same two kernels as
+ * array's address on its first call on a device it only enqueues the same kernels as
  * endor_decompress_batch.  Limit: the batch's endor_batch_workspace_bytes() must not exceed
  * ENDOR_STATIC_SCRATCH_BYTES (about 4 * 2^30 elements in total), else
  * ENDOR_ERR_BUFFER_TOO_SMALL and nothing is launched.  Every call on a GPU shares that GPU's
@@ -262,8 +263,9 @@ endor_status endor_decompress_rows_u8(int64_t rows, int64_t cols,
  * Section 4.1 "Compression"): d_dense (rows*cols elements, device) is turned into
  * d_bitmap (endor_bitmap_bytes, fully written, pad bits zero) and d_values (packed
  * non-zeros in row-major order).  The number of non-zeros is only known on the device:
- * it is written to *d_nnz_out (device int64, required), and no value is ever written at
- * or past values_capacity, so a caller that cannot bound nnz runs with capacity 0 first
+ * it is written to *d_nnz_out (int64, required: any address the device can write, for
+ * instance pinned host memory, which the host may read once the stream has completed the
+ * call), and no value is ever written at or past values_capacity, so a caller that cannot bound nnz runs with capacity 0 first
  * (bitmap, offsets and *d_nnz_out are still produced) or passes capacity rows*cols.
  * d_row_offsets (device, rows+1 entries) is optional.  Afterwards d_workspace holds the
  * tile offset table of the new bitmap, ready for the *_with_offsets entry points.

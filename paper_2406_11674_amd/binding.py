@@ -385,8 +385,8 @@ def decompress_cols(m: DeviceMatrix, row_offsets, sel, out=None, stream=None):
 def compress_device(dense, values=None, row_offsets: bool = False, stream=None):
     """endor_compress_device[_u8] on a 2-d device tensor of 2- or 1-byte elements.
     Returns (DeviceMatrix, workspace, row_offsets or None).  `values`: preallocated
-    buffer (its length is the capacity); default rows*cols elements.  Synchronises once
-    to read the number of non-zeros back."""
+    buffer (its length is the capacity); default rows*cols elements.  Waits for the stream
+    to read the number of non-zeros, which the kernels write to pinned host memory."""
     torch = _torch()
     rows, cols = dense.shape
     eb = dense.element_size()

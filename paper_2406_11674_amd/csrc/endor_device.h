@@ -88,7 +88,7 @@ __device__ __forceinline__ void wait_loads_to_lds() { __builtin_amdgcn_s_waitcnt
 
 // ---------------------------------------------------------------- expansion of 16-bit values, window form
 //
-// For the kernels that consume the expanded elements in registers (the products): the values
+// For the kernel that consumes the expanded elements in registers (the matrix-vector product): the values
 // a bitmap byte consumes are consecutive in `values`, at most 8 of them, so a lane reads that
 // window of 16 bytes straight from memory (neighbouring lanes' windows overlap, the cache
 // serves the overlap) and moves the values to their positions with v_perm_b32, whose

@@ -24,7 +24,7 @@
 // X goes to LDS once per workgroup and round (four row groups share it), in the order in which
 // the steps read it, double buffered.
 //
-// Measured on 28672 x 8192, half kept, 16 right-hand sides: 80 us (the form before, which read
+// Measured on 28672 x 8192, half kept, 16 right-hand sides: 78 us (the form before, which read
 // every byte's 20-byte window from memory through the vector cache and handed the expanded bytes
 // on with ds_bpermute: 112 us; with 3 right-hand sides on 4099 x 5005, three in ten kept: 18
 // against 25 us).  What bounds it: LDS serves 65 clocks of every step's 95 (64 lanes at random
@@ -46,9 +46,7 @@ namespace {
 
 using endor_device::chunk_base;
 using endor_device::global_ptr;
-using endor_device::load_to_lds16;
 using endor_device::u32x4;
-using endor_device::wait_loads_to_lds;
 using endor_device::wave_sum;
 using endor_gemm_plan::kBlockRows;
 using endor_gemm_plan::kGemmWaves;

@@ -14,7 +14,8 @@ constexpr int kGemmWaves = 4;  // waves (groups of 16 rows) per workgroup; they 
 constexpr int kBlockRows = endor_gemm_units::kRows * kGemmWaves;
 
 // Every workgroup gets the same number of consecutive rounds, counted row block by row block: so many
-// that kResident workgroups do all of them at once, and so many that a row block has at most kMaxParts
+// that kResident workgroups do all of them at once (two per compute unit; three fit most forms, 52 KB of
+// LDS and 125 to 183 registers each, but shared out for three 28672 x 8192 took 85 us, for two 80), and so many that a row block has at most kMaxParts
 // parts.  Whole blocks, which need no second kernel, where that costs a workgroup no more than
 // kWholeSlack rounds (the kernel takes about as long as two rounds).  Small products, kSmall rounds or
 // fewer per workgroup, run as workgroups of two rounds.  These, and those that fit the chip at once,

@@ -499,7 +499,8 @@ __global__ __launch_bounds__(64) void endor_expand_kernel(BatchParams P) {
 // Both kernels in one for a small matrix: a workgroup of kSmallWaves waves (one tile each) counts the
 // bitmap before its tiles itself, all of it, instead of reading a table another kernel has to build
 // first, and writes its part of the table on the way.  Two dependent launches were most of the time
-// of a small call; the bitmap is read n/2^16 times on average, from the second-level cache.
+// of a small call; the bitmap is read n/2^15 times in all (n/2^14 workgroups, half of it each on
+// average), from the second-level cache.
 constexpr int kSmallWaves = 4;
 
 template <int E, bool kAlignedOut>
