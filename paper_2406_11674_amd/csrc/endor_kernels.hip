@@ -782,6 +782,7 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     if (kStaged) {
         wait_loads_to_lds();
         // carry: the row's 1 bits.  More than are staged: the next entry of row_offsets is not this row's end.
+        // (Costs 0.5 of 63 us on a tenth of 8192 x 28672; to find it out query by query cost 1 us.)
         if (static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(carry))) > staged) staged = 0;
     }
     __syncthreads();
