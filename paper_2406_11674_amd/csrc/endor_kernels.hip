@@ -26,10 +26,8 @@
 // The same tile expander, fed differently, gives the row-subset kernel (Section 4.2's
 // selective load) and - run backwards, as a scatter - the pack step of the device-side
 // compressor (Algorithm 1).  The element width (2 bytes, or 1 for the 8-bit variant of
-// Section 4.2) is a template parameter throughout.  The matrix-vector product on the
-// compressed form expands in registers instead: a bitmap byte's values are one 16-byte
-// window of `values`, read straight from memory and put in place with byte permutes (the
-// small-batch product has a file of its own).
+// Section 4.2) is a template parameter throughout.  The products on the compressed form
+// have files of their own.
 //
 // One rule shaped all of these kernels: a load under a per-lane test whose result is used
 // after the test is waited for on the spot, so several of them in a row are as many trips
@@ -39,8 +37,7 @@
 //
 // The path is bound by memory traffic (2 bytes written, 1/8 + 2p bytes read per
 // element), so there is no matrix-core work here; all arithmetic on the format is
-// integer and the values are only ever moved, never interpreted (the product kernel
-// apart).
+// integer and the values are only ever moved, never interpreted.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -58,14 +55,6 @@ using endor_device::dpp_or_zero;
 using endor_device::global_ptr;
 using endor_device::global_ptr_mut;
 using endor_device::load_to_lds16;
-using endor_device::window_finish;
-using endor_device::window_guarded;
-using endor_device::window_issue;
-using endor_device::window_fifth;
-using endor_device::windows_inside;
-using endor_device::place_window;
-using endor_device::window_tables_init;
-using endor_device::WindowTables;
 using endor_device::row_inclusive_scan;
 using endor_device::u32x4;
 using endor_device::wave_inclusive_scan;
@@ -844,214 +833,6 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
         answer(std::true_type{});
     else
         answer(std::false_type{});
-}
-
-// ---------------------------------------------------------------- fused consumer: y = W x
-
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ float wave_sum_f32(float x) {
-    // same lane order as wave_inclusive_scan, so the result does not depend on timing
-#define ENDOR_DPP_ADD_F32(ctrl, rowmask)                                                                     \
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), ctrl, rowmask, \
-                                                               0xf, true))
-    ENDOR_DPP_ADD_F32(0x111, 0xf);
-    ENDOR_DPP_ADD_F32(0x112, 0xf);
-    ENDOR_DPP_ADD_F32(0x114, 0xf);
-    ENDOR_DPP_ADD_F32(0x118, 0xf);
-    ENDOR_DPP_ADD_F32(0x142, 0xa);
-    ENDOR_DPP_ADD_F32(0x143, 0xc);
-#undef ENDOR_DPP_ADD_F32
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
-}
-
-// Sink that multiplies the expanded fp16 elements with the matching 8 entries of x and
-// accumulates in fp32.  Each product of two fp16 numbers is exact in fp32 and each step is
-// one fused multiply-add with fp16 operands widened in the instruction (v_fma_mix_f32), so
-// fp16 subnormals count in full (the packed dot-product instructions flush them).
-struct GemvSink {
-    float acc;
-    __device__ __forceinline__ void pair(uint32_t w2, uint32_t x2) {
-#pragma clang fp contract(off)  // keep the two multiply-adds apart: fused into a dot product they would flush
-        const f16x2 w = __builtin_bit_cast(f16x2, w2);
-        const f16x2 x = __builtin_bit_cast(f16x2, x2);
-        acc = __builtin_fmaf(static_cast<float>(w.x), static_cast<float>(x.x), acc);
-        acc = __builtin_fmaf(static_cast<float>(w.y), static_cast<float>(x.y), acc);
-    }
-    // 8 expanded elements against the matching 8 entries of x
-    __device__ __forceinline__ void operator()(u32x4 d, u32x4 x) {
-        pair(d.x, x.x);
-        pair(d.y, x.y);
-        pair(d.z, x.z);
-        pair(d.w, x.w);
-    }
-};
-
-struct GemvParams {
-    const uint64_t *bitmap;
-    const uint16_t *values;
-    const int64_t *row_offsets;  // rows + 1
-    const uint16_t *x;           // cols fp16
-    float *y;                    // rows fp32
-    int64_t rows, cols, nnz;
-};
-
-// y[i] = sum_j W[i][j] * x[j] straight from the compressed form: the dense row is never
-// written.  One wave per row walks the row's 4096-column segments.  Per segment: popcount and
-// scan the lane's bitmap word, leave one entry per bitmap byte in LDS ((values of the segment
-// before the byte) << 9 | the byte); then a lane takes the bytes lane, 64 + lane, ... in turn,
-// reads each byte's window of values straight from memory, places the values by the byte's
-// bit pattern and feeds the fp16 pairs to multiply-adds against the matching 8 entries of x.
-// Elements whose bit is 0 enter as +0.0, as they would from the dense matrix.  The next
-// segment's bitmap word is loaded before the current one is worked on.
-// (Measured alternatives on 28672 x 8192, half kept: values staged in LDS and gathered element
-// by element 83 us, staged and read as windows 76 us, windows straight from memory 72 us, and
-// with x shared through LDS as below 64-67 us; a wave taking four rows in turn 143 us: a wave's
-// segments run one after the other, so what counts is the number of independent waves.  Counters
-// of the 72 us form: the vector cache handles some 530 line accesses per segment, 128 of them
-// for x, where 200 would do if no two lanes shared a line.)  Since then: loads issued back to back,
-// the fifth dword of a window from the neighbouring lane instead of from memory, and the windows
-// addressed by 32-bit offsets from a scalar base: 8192 x 28672 with inputs not in any cache 67 ->
-// 60 us, 4.4 TB/s; the vector ALUs are busy 62 % of the time, and a wave waits for its
-// windows.  More waves per unit by a register cap (80 or 64 instead of 96): 4 and 25 % slower.
-constexpr int kGemvSeg = 4096;  // columns a wave expands at a time
-
-// kFastX: x is 16-byte aligned and cols a multiple of 8, so x moves in whole aligned 16-byte
-// pieces (the general path builds each piece from 8 guarded loads).
-//
-// The kGemvWaves rows of a workgroup walk their segments in step, so the segment's 4096 entries
-// of x are brought to LDS once per workgroup (one 16-byte piece per thread, straight from
-// memory into LDS on the fast path, double buffered, one barrier per segment) instead of once
-// per row: x is the same 8 KB for every row, and fetching it per row cost a quarter of the
-// vector cache's accesses.
-constexpr int kGemvWaves = 8;
-constexpr int kGemvXRounds = (kGemvSeg / 8 + 64 * kGemvWaves - 1) / (64 * kGemvWaves);  // 16-byte pieces of x per thread and segment
-
-template <bool kFastX>
-__global__ __launch_bounds__(64 * kGemvWaves) void endor_gemv_f16_kernel(GemvParams G) {
-    __shared__ WindowTables s_tables;
-    __shared__ uint32_t s_entry[kGemvWaves][kGemvSeg / 8];
-    __shared__ u32x4 s_x[2][kGemvSeg / 8];
-    window_tables_init(s_tables, threadIdx.x);  // visible after the first segment's barrier
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t lane = threadIdx.x & 63;
-    const int64_t i = int64_t(blockIdx.x) * kGemvWaves + wave;
-    const bool row_ok = i < G.rows;  // a wave past the last row still helps loading x
-    uint32_t *entry = s_entry[wave];
-    const int64_t nwords = (G.rows * G.cols + 63) >> 6;
-    const int64_t row_bit = (row_ok ? i : 0) * G.cols;
-    const uintptr_t vbeg = reinterpret_cast<uintptr_t>(G.values);
-    const uintptr_t vend = vbeg + 2 * static_cast<uintptr_t>(G.nnz);
-    // wave-uniform, and the compiler has to know: the window loads then take it from scalar registers
-    const uint64_t row_first = row_ok ? static_cast<uint64_t>(G.row_offsets[i]) : 0;
-    uint64_t next_value = (uint64_t(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(row_first >> 32)))) << 32) |
-                          static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(row_first)));
-    GemvSink sink;
-    sink.acc = 0.0f;
-
-    // this thread's piece of the segment of x that starts at column c0
-    auto load_x = [&](int64_t c0, uint32_t buf) {
-#pragma unroll
-        for (int q = 0; q < kGemvXRounds; ++q) {
-            const uint32_t piece = q * 64 * kGemvWaves + threadIdx.x;
-            if (64 * kGemvWaves * kGemvXRounds > kGemvSeg / 8 && piece >= kGemvSeg / 8) break;  // more threads than pieces
-            const int64_t c = c0 + 8 * int64_t(piece);
-            if (kFastX) {
-                // past the row's end x reads as zero (the expanded elements there are zero, but
-                // zero times whatever LDS held could be NaN)
-                if (c < G.cols)
-                    load_to_lds16<false>(reinterpret_cast<const u32x4 *>(G.x + c), &s_x[buf][q * 64 * kGemvWaves + 64 * wave]);
-                else
-                    s_x[buf][piece] = u32x4{0u, 0u, 0u, 0u};
-            } else {
-                uint32_t h[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) h[j] = (c + j < G.cols) ? uint32_t(G.x[c + j]) : 0u;
-                u32x4 f;
-                f.x = h[0] | (h[1] << 16);
-                f.y = h[2] | (h[3] << 16);
-                f.z = h[4] | (h[5] << 16);
-                f.w = h[6] | (h[7] << 16);
-                s_x[buf][piece] = f;
-            }
-        }
-    };
-    auto row_word = [&](int64_t c0) -> uint64_t {  // no branch: a segment that does not exist has no bits
-        const int64_t left = G.cols - c0;
-        const uint32_t nbits = (!row_ok || left <= 0) ? 0u : left < kGemvSeg ? static_cast<uint32_t>(left) : uint32_t(kGemvSeg);
-        return segment_word(G.bitmap, nwords, row_bit + c0, nbits, lane);
-    };
-
-    if (G.cols > 0) load_x(0, 0);
-    uint64_t word = row_word(0);
-    uint32_t buf = 0;
-    for (int64_t c0 = 0; c0 < G.cols; c0 += kGemvSeg, buf ^= 1u) {
-        const int64_t left = G.cols - c0;
-        // this thread's piece of the segment's x has landed; after the barrier all of them have,
-        // and every wave is through the previous segment (whose x the next load overwrites)
-        wait_loads_to_lds();
-        __syncthreads();
-        if (left > kGemvSeg) load_x(c0 + kGemvSeg, buf ^ 1u);
-        const uint64_t next_word = row_word(c0 + kGemvSeg);
-        const uint32_t pc = __popcll(word);
-        const uint32_t incl = wave_inclusive_scan(pc);
-        const uint32_t cnt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
-        const uintptr_t vseg = vbeg + 2 * next_value;  // the segment's first value
-        const uintptr_t vbase = vseg & ~uintptr_t(3);
-        {
-            // values of the segment before this lane's word, from the dword boundary below its first value
-            uint32_t at = incl - pc + (static_cast<uint32_t>(vseg) >> 1 & 1u);
-            uint32_t e8[8];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const uint32_t byte = static_cast<uint32_t>(word >> (8 * b)) & 0xffu;
-                e8[b] = (at << 9) | byte;
-                at += __popc(byte);
-            }
-            u32x4 lo, hi;
-            lo.x = e8[0];
-            lo.y = e8[1];
-            lo.z = e8[2];
-            lo.w = e8[3];
-            hi.x = e8[4];
-            hi.y = e8[5];
-            hi.z = e8[6];
-            hi.w = e8[7];
-            reinterpret_cast<u32x4 *>(entry)[2 * lane] = lo;
-            reinterpret_cast<u32x4 *>(entry)[2 * lane + 1] = hi;
-        }
-        wave_lds_sync();
-        if (windows_inside(vseg, vseg + 2 * uintptr_t(cnt), vbeg, vend)) {  // wave-uniform
-            uint32_t e[kGemvSeg / 512];
-            u32x4 win[kGemvSeg / 512];
-#pragma unroll
-            for (int k = 0; k < kGemvSeg / 512; ++k) e[k] = entry[k * 64 + lane];
-#pragma unroll
-            for (int k = 0; k < kGemvSeg / 512; ++k) win[k] = window_issue(vbase, e[k] >> 8);
-            // the first dword after the segment's last window, for lane 63's last byte
-            const uint32_t end = *global_ptr<uint32_t>((vseg + 2 * uintptr_t(cnt)) & ~uintptr_t(3));
-#pragma unroll
-            for (int k = 0; k < kGemvSeg / 512; ++k) {
-                const uint32_t after = k + 1 < kGemvSeg / 512
-                                           ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(win[(k + 1) % (kGemvSeg / 512)].x)))
-                                           : end;
-                const u32x4 w = window_finish(win[k], window_fifth(win[k], after), e[k] >> 8);
-                sink(place_window(s_tables, e[k] & 0xffu, w), s_x[buf][k * 64 + lane]);
-            }
-        } else {  // a segment at the very beginning or end of `values`
-#pragma unroll 1
-            for (int k = 0; k < kGemvSeg / 512; ++k) {
-                const uint32_t e = entry[k * 64 + lane];
-                const u32x4 w = window_guarded(vbase + (e >> 8), vbeg, vend);
-                sink(place_window(s_tables, e & 0xffu, w), s_x[buf][k * 64 + lane]);
-            }
-        }
-        wave_lds_sync();  // the next segment's entries stay behind this segment's reads
-        next_value += cnt;
-        word = next_word;
-    }
-    const float total = wave_sum_f32(sink.acc);
-    if (lane == 0 && row_ok) G.y[i] = total;
 }
 
 // ---------------------------------------------------------------- device-side compression
@@ -1859,41 +1640,6 @@ extern "C" endor_status endor_compress_device_u8(int64_t rows, int64_t cols, con
                                                  int64_t *d_row_offsets, int64_t *d_nnz_out, void *stream) {
     return run_compress_device<1>(rows, cols, d_dense, d_bitmap, d_values, values_capacity, d_workspace,
                                   workspace_bytes, d_row_offsets, d_nnz_out, stream);
-}
-
-// ---------------------------------------------------------------- fused consumer
-
-extern "C" endor_status endor_gemv_f16(int64_t rows, int64_t cols, const uint8_t *d_bitmap,
-                                       const uint16_t *d_values, int64_t nnz, const int64_t *d_row_offsets,
-                                       const uint16_t *d_x, float *d_y, void *stream) {
-    if (rows < 0 || cols < 0 || nnz < 0) return ENDOR_ERR_INVALID_ARG;
-    if (!dims_ok(rows, cols)) return ENDOR_ERR_UNSUPPORTED;
-    if (rows == 0) return ENDOR_OK;
-    if (rows > 0x7fffffff) return ENDOR_ERR_UNSUPPORTED;
-    if (!d_y || (reinterpret_cast<uintptr_t>(d_y) & 3)) return ENDOR_ERR_INVALID_ARG;
-    if (!d_row_offsets || (reinterpret_cast<uintptr_t>(d_row_offsets) & 7)) return ENDOR_ERR_INVALID_ARG;
-    if (cols > 0) {
-        if (nnz > rows * cols) return ENDOR_ERR_INVALID_ARG;
-        if (!d_bitmap || (reinterpret_cast<uintptr_t>(d_bitmap) & 7)) return ENDOR_ERR_INVALID_ARG;
-        if (!d_x || (reinterpret_cast<uintptr_t>(d_x) & 1)) return ENDOR_ERR_INVALID_ARG;
-        if (nnz > 0 && (!d_values || (reinterpret_cast<uintptr_t>(d_values) & 1))) return ENDOR_ERR_INVALID_ARG;
-    }
-    GemvParams G;
-    G.bitmap = reinterpret_cast<const uint64_t *>(d_bitmap);
-    G.values = d_values;
-    G.row_offsets = d_row_offsets;
-    G.x = d_x;
-    G.y = d_y;
-    G.rows = rows;
-    G.cols = cols;
-    G.nnz = nnz;
-    const dim3 grid(static_cast<unsigned>((rows + kGemvWaves - 1) / kGemvWaves)), block(64 * kGemvWaves);
-    if ((reinterpret_cast<uintptr_t>(d_x) & 15) == 0 && cols % 8 == 0)
-        hipLaunchKernelGGL(endor_gemv_f16_kernel<true>, grid, block, 0, static_cast<hipStream_t>(stream), G);
-    else
-        hipLaunchKernelGGL(endor_gemv_f16_kernel<false>, grid, block, 0, static_cast<hipStream_t>(stream), G);
-    if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
-    return ENDOR_OK;
 }
 
 // ---------------------------------------------------------------- selected columns (Section 4.2)
