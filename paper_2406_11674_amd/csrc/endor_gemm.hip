@@ -40,6 +40,7 @@
 #include "endor_device.h"
 #include "endor_gemm_plan.h"
 #include "endor_gemm_units.h"
+#include "endor_gemv.h"
 #include "endor_layout.h"
 
 namespace {
@@ -595,11 +596,6 @@ __global__ __launch_bounds__(256) void endor_gemm_reduce_kernel(const float *__r
     }
 }
 
-__global__ __launch_bounds__(256) void endor_gemm_zero_kernel(float *__restrict__ y, int64_t count) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i < count) y[i] = 0.0f;
-}
-
 template <int kClass>
 void launch_gemm(const GemmParams &G, bool aligned, dim3 grid, dim3 block, hipStream_t s) {
     if (G.nb <= 8) {
@@ -636,9 +632,7 @@ extern "C" endor_status endor_gemm_f16(int64_t rows, int64_t cols, const uint8_t
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t count = int64_t(nb) * rows;
     if (cols == 0) {
-        // an empty sum: every output is +0.0 (a fill kernel, so that the call can be captured into a graph)
-        hipLaunchKernelGGL(endor_gemm_zero_kernel, dim3(static_cast<unsigned>((count + 255) / 256)), dim3(256), 0, s, d_y,
-                           count);
+        endor_gemv::zero(d_y, count, s);  // an empty sum: every output is +0.0
         return hipGetLastError() == hipSuccess ? ENDOR_OK : ENDOR_ERR_HIP;
     }
     if (nnz > rows * cols || ldx < cols) return ENDOR_ERR_INVALID_ARG;
@@ -653,6 +647,22 @@ extern "C" endor_status endor_gemm_f16(int64_t rows, int64_t cols, const uint8_t
     if (p.split) {
         if (!d_scratch || (reinterpret_cast<uintptr_t>(d_scratch) & 255)) return ENDOR_ERR_INVALID_ARG;
         if (scratch_bytes < need) return ENDOR_ERR_BUFFER_TOO_SMALL;
+    }
+    if (endor_gemv::takes(rows, cols, nb)) {  // a few right-hand sides: no scratch is used
+        endor_gemv::SmallProduct q;
+        q.bitmap = reinterpret_cast<const uint64_t *>(d_bitmap);
+        q.values = d_values;
+        q.chunk_total = static_cast<const uint32_t *>(d_workspace);
+        q.tile_off = reinterpret_cast<const uint32_t *>(static_cast<const char *>(d_workspace) + chunk_total_bytes(n));
+        q.x = d_x;
+        q.y = d_y;
+        q.rows = rows;
+        q.cols = cols;
+        q.nnz = nnz;
+        q.ldx = ldx;
+        q.nb = nb;
+        endor_gemv::small_product(q, s);
+        return hipGetLastError() == hipSuccess ? ENDOR_OK : ENDOR_ERR_HIP;
     }
     GemmParams G;
     G.bitmap = reinterpret_cast<const uint64_t *>(d_bitmap);
