@@ -189,10 +189,12 @@ def _torch():
 
 
 def _stream_handle(stream) -> int:
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # The current stream's handle alone: building the Stream object that torch.cuda.current_stream()
+    # returns takes 2.9 us, this 0.3, of the 7.4 us that enqueueing a small call took (now 4.8).
     torch = _torch()
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return int(stream.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dptr(t) -> int:
