@@ -274,10 +274,10 @@ __device__ __forceinline__ uint32_t half_mask(uint32_t b) {
 // element with a bounds check.  kBurst holds the steps' results back and releases all of
 // them after the last step: measured 11 % faster when almost everything is stores (one
 // element in ten kept), 6 % slower at three in ten, so the host picks it by density.
-template <int E, bool kAlignedOut, bool kBurst>
+template <int E, bool kAlignedOut, bool kBurst, uint32_t kElems = kTileElems>
 struct StoreSink {
-    uint8_t *out;     // byte address of the tile's first output element
-    uint32_t nvalid;  // elements of the tile that exist (<= 4096)
+    uint8_t *out;     // byte address of the tile's first output element (of kElems)
+    uint32_t nvalid;  // elements of the tile that exist
     u32x4 held[kBurst ? Shape<E>::kSteps : 1];
     // how far a loop over the steps must be unrolled for `held` to stay in registers
     static constexpr int kStepUnroll = kBurst ? Shape<E>::kSteps : 1;
@@ -285,7 +285,7 @@ struct StoreSink {
         __builtin_nontemporal_store(d, reinterpret_cast<u32x4 *>(out + size_t(le) * E));
     }
     __device__ __forceinline__ void operator()(int k, uint32_t le, u32x4 d) {
-        if (kAlignedOut && nvalid == kTileElems) {
+        if (kAlignedOut && nvalid == kElems) {
             if (kBurst) {
                 held[k] = d;
                 if (k == Shape<E>::kSteps - 1) {
@@ -485,77 +485,115 @@ __global__ __launch_bounds__(64) void endor_expand_kernel(BatchParams P) {
     expand_tile<E>(s_scratch, lane, word, vbeg + E * (base + o0), cnt, vbeg, vend, sink);
 }
 
-// Both kernels in one for a small matrix: a workgroup of kSmallWaves waves (one tile each) counts the
-// bitmap before its tiles itself, all of it, instead of reading a table another kernel has to build
-// first, and writes its part of the table on the way.  Two dependent launches were most of the time
-// of a small call; the bitmap is read n/2^15 times in all (n/2^14 workgroups, half of it each on
-// average), from the second-level cache.
-constexpr int kSmallWaves = 4;
+// Both kernels in one for a small matrix: a workgroup of kSmallTiles tiles counts the bitmap before them
+// itself, all of it, instead of reading a table another kernel has to build first, and writes its part of
+// the table on the way.  Two dependent launches were most of the time of a small call.  What bounds it is
+// a chain: the launch, the bitmap (read n/2^15 times in all, from the second-level cache), the values, the
+// stores.  So the counting is one trip to memory where a thread has no more than kBatch pieces of it, and four
+// waves share a tile, a quarter each, which shortens what follows.
+constexpr int kSmallTiles = 4;
+constexpr int kParts = 4;  // waves per tile
+constexpr int kSmallWaves = kSmallTiles * kParts;
+constexpr int kPartWords = kTileWords / kParts, kPartElems = kTileElems / kParts;
+static_assert(kSmallWaves == 16 && kPartWords == 16, "a value per wave, and a word, in each of 16 lanes");
+
+__device__ __forceinline__ uint32_t row_sum(uint32_t x) {  // over the first 16 lanes
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(row_inclusive_scan(x)), 15));
+}
 
 template <int E, bool kAlignedOut>
 __global__ __launch_bounds__(64 * kSmallWaves) void endor_decompress_small_kernel(MatParams M) {
-    __shared__ WaveScratch<E> s_scratch[kSmallWaves];
+    typedef WaveScratch<E, kPartElems> WS;
+    __shared__ WS s_scratch[kSmallWaves];
     __shared__ uint32_t s_before[2][kSmallWaves];  // 1 bits before the workgroup's chunk, and from there to its first tile
     __shared__ uint32_t s_cnt[kSmallWaves];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
-    const uint32_t tile0 = blockIdx.x * kSmallWaves;  // a chunk's tiles are a multiple of a workgroup's
-    const uint32_t tile = tile0 + wave;
+    const uint32_t tile0 = blockIdx.x * kSmallTiles;  // a chunk's tiles are a multiple of a workgroup's
+    const uint32_t tile = tile0 + wave / kParts;
     const uint32_t c = tile0 / kTilesPerChunk;
-    const int64_t full_words = M.n >> 6;
-    const uint32_t tail_bits = static_cast<uint32_t>(M.n & 63);
-    const uint32_t ntiles = static_cast<uint32_t>((M.n + kTileElems - 1) / kTileElems);
-    const uint64_t word = load_word_guarded(M.bitmap, int64_t(tile) * kTileWords + lane, full_words, tail_bits);
+    const uint32_t n = static_cast<uint32_t>(M.n);
+    const uint32_t ntiles = (n + kTileElems - 1) / kTileElems, last_word = (n - 1) >> 6;
+    // this wave's words, one in each of 16 lanes (and again in the others)
+    const uint32_t w_own = tile0 * kTileWords + wave * kPartWords + (lane & 15);
+    uint64_t word = M.bitmap[w_own < last_word ? w_own : last_word];
 
-    // the words before the workgroup's tiles (all of them complete), eight per thread and pass
+    // the words before the workgroup's tiles (all of them complete), two a load
+    struct alignas(8) Words2 {
+        uint64_t a, b;
+    };
+    constexpr uint32_t kBatch = 8;
     uint32_t before[2] = {0, 0};
-    const uint32_t nwords = tile0 * kTileWords, chunk_word = c * kTilesPerChunk * kTileWords;
-    for (uint32_t w0 = 0; w0 < nwords; w0 += 8 * 64 * kSmallWaves) {
-        uint64_t x[8];
+    const uint32_t npairs = tile0 * (kTileWords / 2), chunk_pair = c * kTilesPerChunk * (kTileWords / 2);
+    for (uint32_t w0 = 0; w0 < npairs; w0 += kBatch * 64 * kSmallWaves) {
+        Words2 x[kBatch];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (uint32_t k = 0; k < kBatch; ++k) {
             const uint32_t w = w0 + k * 64 * kSmallWaves + threadIdx.x;
-            x[k] = M.bitmap[w < nwords ? w : nwords - 1];
+            x[k] = reinterpret_cast<const Words2 *>(M.bitmap)[w < npairs ? w : npairs - 1];
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (uint32_t k = 0; k < kBatch; ++k) {
             const uint32_t w = w0 + k * 64 * kSmallWaves + threadIdx.x;
-            const uint32_t pc = w < nwords ? __popcll(x[k]) : 0;
-            before[0] += w < chunk_word ? pc : 0u;
-            before[1] += w < chunk_word ? 0u : pc;
+            const uint32_t pc = w < npairs ? __popcll(x[k].a) + __popcll(x[k].b) : 0;
+            before[0] += w < chunk_pair ? pc : 0u;
+            before[1] += w < chunk_pair ? 0u : pc;
         }
     }
-    const uint32_t b0 = wave_sum(before[0]), b1 = wave_sum(before[1]), cnt = wave_sum(__popcll(word));
+    if (w_own == last_word && (n & 63)) word &= (uint64_t(1) << (n & 63)) - 1;
+    if (w_own > last_word) word = 0;
+    const uint32_t pc = __popcll(word), incl = row_inclusive_scan(pc);
+    const uint32_t cnt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 15));
+    const uint32_t b0 = wave_sum(before[0]), b1 = wave_sum(before[1]);
     if (lane == 0) {
         s_before[0][wave] = b0;
         s_before[1][wave] = b1;
         s_cnt[wave] = cnt;
     }
     __syncthreads();
-    uint32_t base = 0, off = 0, total = 0;  // before the chunk; from there to this tile; and to the end of the workgroup's tiles
-#pragma unroll
-    for (uint32_t v = 0; v < kSmallWaves; ++v) {
-        base += s_before[0][v];
-        off += s_before[1][v] + (v < wave ? s_cnt[v] : 0u);
-        total += s_before[1][v] + s_cnt[v];
-    }
+    // before the chunk; from there to the workgroup's tiles; to this tile, to this part; and to the end of the workgroup's tiles
+    const uint32_t v = lane & 15, of_v = s_cnt[v];
+    const uint32_t base = row_sum(s_before[0][v]), first = row_sum(s_before[1][v]);
+    const uint32_t off_tile = first + row_sum(v < (wave & ~(kParts - 1u)) ? of_v : 0u), off = first + row_sum(v < wave ? of_v : 0u);
+    const uint32_t total = first + row_sum(of_v);
     uint32_t *to = M.tile_off + size_t(c) * kChunkStride;
-    const uint32_t tl = tile % kTilesPerChunk;
-    if (lane == 0) to[tl] = off;
+    if (wave % kParts == 0 && lane == 0) to[tile % kTilesPerChunk] = off_tile;
     // the chunk's last workgroup with a tile completes its table: tiles past the end count as empty
-    if (tile0 + kSmallWaves >= ntiles || tl + kSmallWaves - wave == kTilesPerChunk) {
-        for (uint32_t t = (tile0 % kTilesPerChunk) + kSmallWaves + threadIdx.x; t <= kTilesPerChunk; t += 64 * kSmallWaves) to[t] = total;
+    if (tile0 + kSmallTiles >= ntiles || tile0 % kTilesPerChunk + kSmallTiles == kTilesPerChunk) {
+        for (uint32_t t = (tile0 % kTilesPerChunk) + kSmallTiles + threadIdx.x; t <= kTilesPerChunk; t += 64 * kSmallWaves) to[t] = total;
         if (threadIdx.x == 0) M.chunk_total[c] = total;
     }
-    if (tile >= ntiles) return;
-    const uintptr_t vbeg = reinterpret_cast<uintptr_t>(M.values);
-    const uintptr_t vend = vbeg + E * static_cast<uintptr_t>(M.nnz);
-    const int64_t e0 = int64_t(tile) * kTileElems;
-    const int64_t left = M.n - e0;
-    StoreSink<E, kAlignedOut, false> sink;
-    sink.out = reinterpret_cast<uint8_t *>(M.dense) + e0 * E;
-    sink.nvalid = left < kTileElems ? static_cast<uint32_t>(left) : uint32_t(kTileElems);
-    expand_tile<E>(s_scratch[wave], lane, word, vbeg + E * (uint64_t(base) + off), cnt, vbeg, vend, sink);
+    const uint32_t e0 = (tile0 * kParts + wave) * kPartElems;
+    if (e0 >= n) return;
+    WS &S = s_scratch[wave];
+    const uintptr_t vbeg = reinterpret_cast<uintptr_t>(M.values), vend = vbeg + E * static_cast<uintptr_t>(M.nnz);
+    const uintptr_t vaddr = vbeg + E * (uintptr_t(base) + off), a16 = vaddr & ~uintptr_t(15);
+    const uint32_t shift = static_cast<uint32_t>(vaddr - a16) / E, nch = cnt ? ((shift + cnt) * E + 15) >> 4 : 0;
+    const bool direct = nch != 0 && a16 >= vbeg && a16 + 16 * uintptr_t(nch) <= vend;
+    if (direct) {
+#pragma unroll
+        for (int q = 0; q < WS::kStageRounds; ++q) {
+            const uint32_t ch = q * 64 + lane;
+            if (ch < nch) load_to_lds16(reinterpret_cast<const u32x4 *>(a16) + ch, &S.stage[q * 64]);
+        }
+    }
+    if (E == 1 && lane < 16) S.nibble_sel[lane] = nibble_selector(lane);
+    if (lane < kPartWords) {
+        S.words[lane] = word;
+        S.start[lane] = incl - pc + shift;
+    }
+    if (direct) {
+        wait_loads_to_lds();
+    } else {
+#pragma unroll 1
+        for (uint32_t ch = lane; ch < nch; ch += 64) S.stage[ch] = load_values16<E>(a16 + 16 * uintptr_t(ch), vbeg, vend);
+    }
+    wave_lds_sync();
+    StoreSink<E, kAlignedOut, false, kPartElems> sink;
+    sink.out = reinterpret_cast<uint8_t *>(M.dense) + size_t(e0) * E;
+    sink.nvalid = n - e0 < kPartElems ? n - e0 : uint32_t(kPartElems);
+#pragma unroll
+    for (int k = 0; k < Shape<E>::kSteps / kParts; ++k) expand_step<E, kPartElems>(S, k, lane, sink);
 }
 
 // This lane's 64 bits of a segment of `nbits` (<= 4096) bits that starts at an arbitrary
@@ -1188,15 +1226,17 @@ void launch_expand(const Group &g, hipStream_t s) {
         hipLaunchKernelGGL((endor_expand_kernel<E, true, kTileElems, false>), grid, dim3(64), 0, s, g.P);
 }
 
-// Largest matrix (in elements) that the one-kernel form takes: two chunks.  Measured back to back,
-// half kept, fp16: 1024 x 1024 7.7 us against 10.0 with two kernels, 1024 x 2048 8.7 against 11.2,
-// 2048 x 2048 12.7 against 11.0 (every workgroup counts all of the bitmap before its tiles).
-constexpr int64_t kSmallElems = int64_t(1) << 21;
+// Largest matrix (in elements) that the one-kernel form takes: four chunks.  Measured back to back, half
+// kept, fp16, two kernels / one: 1024 x 1024 10 / 5.9 us (as long as the host takes to enqueue it), 1448 x
+// 1448 10.0 / 6.5, 2048 x 1500 11.3 / 7.5, 2048 x 2048 11.0 / 8.9, 2048 x 3000 11.2 / 13.9: every workgroup counts all of
+// the bitmap before its tiles.  (With one wave per tile, 256 threads and 8-byte pieces: 1024 x 1024 6.7,
+// 1024 x 2048 8.9.)
+constexpr int64_t kSmallElems = int64_t(1) << 22;
 
 template <int E>
 void launch_small(const Group &g, hipStream_t s) {
     const MatParams &M = g.P.m[0];
-    const dim3 grid(static_cast<unsigned>((M.n + kTileElems * kSmallWaves - 1) / (kTileElems * kSmallWaves)));
+    const dim3 grid(static_cast<unsigned>((M.n + kTileElems * kSmallTiles - 1) / (kTileElems * kSmallTiles)));
     if (g.aligned_out)
         hipLaunchKernelGGL((endor_decompress_small_kernel<E, true>), grid, dim3(64 * kSmallWaves), 0, s, M);
     else
