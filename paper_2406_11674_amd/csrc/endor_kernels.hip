@@ -969,7 +969,8 @@ __global__ __launch_bounds__(64) void endor_mask_kernel(CompressParams C) {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const int64_t w = tile * kTileWords + lane;
     const uint64_t word = s_words[lane];
-    if (w < ((C.n + 63) >> 6)) C.bitmap[w] = word;  // pad bits are zero: elements past n read as zero
+    // streamed, like the values (endor_pack_kernel); pad bits are zero: elements past n read as zero
+    if (w < ((C.n + 63) >> 6)) __builtin_nontemporal_store(word, &C.bitmap[w]);
     const uint32_t count = wave_sum(__popcll(word));
     if (lane == 0) C.table.tile_off[size_t(tile / kTilesPerChunk) * kChunkStride + tile % kTilesPerChunk] = count;
 }
@@ -1088,7 +1089,10 @@ __global__ __launch_bounds__(64) void endor_pack_kernel(CompressParams C) {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
     // write the slice out: elements [shift, shift + cnt) of the staging area go to
-    // values[first, first + cnt), never past `capacity`
+    // values[first, first + cnt), never past `capacity`.  Streamed stores: what goes through the memory-side
+    // cache pushes earlier writes out of it between this call's reads.  28672 x 8192, a call whose outputs are
+    // new buffers, a tenth / three tenths / half / nine tenths kept: 201 / 232 / 239 / 276 us without, 199 / 209 /
+    // 219 / 257 with (into the buffer of the call before, which that cache still holds, half kept: 215 / 220).
     const uint32_t nch = cnt ? (((shift + cnt) * E + 15) >> 4) : 0;
     const int64_t room = C.capacity - static_cast<int64_t>(first);  // elements this tile may write
     for (uint32_t ch = lane; ch < nch; ch += 64) {
@@ -1096,7 +1100,7 @@ __global__ __launch_bounds__(64) void endor_pack_kernel(CompressParams C) {
         const bool inside = el0 >= shift && el0 + Sh::kLaneElems <= shift + cnt &&
                             static_cast<int64_t>(el0 + Sh::kLaneElems - shift) <= room;
         if (inside) {
-            *global_ptr_mut<u32x4>(a16 + 16 * uintptr_t(ch)) = S.stage[ch];
+            __builtin_nontemporal_store(S.stage[ch], global_ptr_mut<u32x4>(a16 + 16 * uintptr_t(ch)));
         } else {
 #pragma unroll
             for (int j = 0; j < Sh::kLaneElems; ++j) {
