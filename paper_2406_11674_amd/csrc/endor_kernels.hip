@@ -722,16 +722,19 @@ __device__ __forceinline__ uint64_t row_word(const uint64_t *bitmap, int64_t nwo
 // of a down projection that belong to active neurons).  out[i][q] = W[i][sel[q]].  One
 // workgroup per row.  It first lays the row's bitmap out in LDS as 32-bit pieces, each with
 // the number of the row's 1 bits before it; a query is then one coalesced load of its
-// column index, two LDS reads and a handful of 32-bit operations for
+// column index, one LDS read of such a pair and a handful of 32-bit operations for
 //     rank = row_offsets[i] + before[piece] + popcount(bits of the piece below the column),
-// and one 2-byte load of values[rank] (or a zero).  Queries are taken four at a time so that
+// and one 2-byte load of values[rank] (or a zero).  Queries are taken several at a time so that
 // their loads are in flight together.
 //
 // kStaged: the row's whole value slice goes straight to LDS (no registers) while the bitmap is
 // worked on, and the queries read it there; the host says when that pays.
-template <int E, bool kStaged>
+//
+// kStreamed: the output is stored past the memory-side cache.  kQ: queries per thread and round.
+template <int E, bool kStaged, bool kStreamed, int kQ>
 __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C) {
-    // [np] 32-bit pieces of the row's bitmap | [np] 1 bits of the row before each | staged values
+    typedef std::conditional_t<E == 2, uint16_t, uint8_t> Elem;
+    // [np] pairs (32 bits of the row's bitmap, 1 bits of the row before them) | staged values
     extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
     __shared__ uint32_t s_wave[2][kWaves];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -740,8 +743,6 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     const int64_t nwords = (C.rows * C.cols + 63) >> 6;
     const int64_t row_bit = i * C.cols;
     const uint32_t nvw = static_cast<uint32_t>((C.cols + 63) >> 6);
-    uint32_t *s_piece = s_dyn;
-    uint32_t *s_before = s_dyn + 2 * nvw;
 
     // The row's values, on their way to LDS while the bitmap is worked on: 16-byte units from the
     // boundary at or below the first one.  A row that does not fit, or whose units reach over an end of
@@ -772,7 +773,6 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     }
 
     // first round of column indices: in flight during the bitmap work
-    constexpr int kQ = 4;  // queries per thread and round
     int64_t c[kQ];
 #pragma unroll
     for (int u = 0; u < kQ; ++u) {
@@ -800,10 +800,12 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
         }
         if (k < nvw) {
             const uint32_t excl = before + incl - pc;
-            s_piece[2 * k] = lo;
-            s_piece[2 * k + 1] = hi;
-            s_before[2 * k] = excl;
-            s_before[2 * k + 1] = excl + __popc(lo);
+            u32x4 pairs;
+            pairs.x = lo;
+            pairs.y = excl;
+            pairs.z = hi;
+            pairs.w = excl + __popc(lo);
+            reinterpret_cast<u32x4 *>(s_dyn)[k] = pairs;
         }
     }
     if (kStaged) {
@@ -837,9 +839,10 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
                 // an index outside the matrix (or past nsel) leaves its output column untouched
                 live[u] = static_cast<uint64_t>(c[u]) < ucols;
                 const uint32_t cc = live[u] ? static_cast<uint32_t>(c[u]) : 0u;
-                const uint32_t piece = s_piece[cc >> 5];
+                const uint64_t pair = reinterpret_cast<const uint64_t *>(s_dyn)[cc >> 5];
+                const uint32_t piece = static_cast<uint32_t>(pair);
                 const uint32_t b = cc & 31;
-                const uint32_t r = s_before[cc >> 5] + __popc(piece & ((1u << b) - 1));  // rank inside the row
+                const uint32_t r = static_cast<uint32_t>(pair >> 32) + __popc(piece & ((1u << b) - 1));  // rank inside the row
                 hit[u] = live[u] && ((piece >> b) & 1) != 0 && r < room;
                 if (kFromLds) {
                     // r is at most the row's 1 bits: one value past the staged ones, in the area's spare unit
@@ -858,10 +861,11 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
             for (int u = 0; u < kQ; ++u) {
                 const int64_t q = q0 + u * kBlock + threadIdx.x;
                 if (live[u]) {
-                    if (E == 2)
-                        reinterpret_cast<uint16_t *>(row_out)[q] = static_cast<uint16_t>(v[u]);
+                    Elem *at = reinterpret_cast<Elem *>(row_out) + q;
+                    if (kStreamed)
+                        __builtin_nontemporal_store(static_cast<Elem>(v[u]), at);
                     else
-                        row_out[q] = static_cast<uint8_t>(v[u]);
+                        *at = static_cast<Elem>(v[u]);
                 }
                 c[u] = cn[u];
             }
@@ -1693,6 +1697,22 @@ namespace {
 constexpr size_t kMaxColsLds = 40 * 1024, kMinColsStage = 6 * 1024, kLdsPerUnit = 160 * 1024;
 constexpr int64_t kMaxGatherCols = int64_t(1) << 18;  // the row's bitmap and its prefixes live in LDS (16 bytes per 64 columns)
 
+// Queries per thread and round.  A staged row takes 4 (6 against 4: 2048 x 16384, 8-bit, half, 20.6 / 19.3 us, 36864 x
+// 9216, three tenths, 136 / 128; 12 cost it the occupancy, 28672 x 8192, three tenths, 111 / 94).  A gathered row takes 6
+// (28672 x 8192, one in five kept, three tenths 134 / 125 before its stores were streamed), but 4 where
+// the last of several rounds would be mostly empty with 6 (2048 x 16384, a tenth, 9.9 / 9.2).  3 for few queries
+// (36864 x 2000, a tenth, 6 / 4 / 3: 47 / 47 / 44).
+template <int E, bool kStaged, bool kStreamed>
+void launch_cols(const ColsParams &C, dim3 grid, size_t lds, hipStream_t s) {
+    const int64_t rounds6 = (C.nsel + 6 * kBlock - 1) / (6 * kBlock), rounds4 = (C.nsel + 4 * kBlock - 1) / (4 * kBlock);
+    if (C.nsel <= 3 * kBlock)
+        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStreamed, 3>), grid, dim3(kBlock), lds, s, C);
+    else if (kStaged || (rounds6 == rounds4 && rounds6 > 1))
+        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStreamed, 4>), grid, dim3(kBlock), lds, s, C);
+    else
+        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStreamed, kStaged ? 4 : 6>), grid, dim3(kBlock), lds, s, C);
+}
+
 endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t *d_bitmap, const void *d_values,
                       int64_t nnz, const int64_t *d_row_offsets, const int64_t *d_sel, int64_t nsel, void *d_out,
                       void *stream) {
@@ -1742,16 +1762,22 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
                          nnz * elem_bytes <= rows * 20480;
     const bool staged = rows > 1 && rows_fit && (much || at_once);
     C.stage_units = static_cast<uint32_t>(stage / 16);
+    const size_t l = lds + (staged ? stage : 0);
+    // Streamed stores where values are gathered: the output then leaves the lines of `values`, which several
+    // queries of a row share, in the memory-side cache.  28672 x 8192, one in five kept, a tenth of the columns
+    // 57 / 44 us, three tenths 125 / 85, 36864 x 2000 three tenths 68 / 57.  Where rows are staged every line is
+    // read once, and only an output that would fill that cache is streamed: 8192 x 28672, three tenths (141
+    // MB) 113 / 101, half (235 MB) 152 / 134, but 4096 x 28672, one in five kept, three tenths (70 MB) 42.6 / 45.5.
+    // Very small outputs and 8-bit ones are not: 1024 x 16384, a tenth (3 MB), 6.5 / 6.8; 8-bit +-2 % throughout.
+    const int64_t out_bytes = asked * elem_bytes;
+    const bool streamed = elem_bytes == 2 && out_bytes >= (staged ? int64_t(96) << 20 : int64_t(8) << 20);
     if (elem_bytes == 2) {
         if (staged)
-            hipLaunchKernelGGL((endor_gather_cols_kernel<2, true>), grid, dim3(kBlock), lds + stage, s, C);
+            streamed ? launch_cols<2, true, true>(C, grid, l, s) : launch_cols<2, true, false>(C, grid, l, s);
         else
-            hipLaunchKernelGGL((endor_gather_cols_kernel<2, false>), grid, dim3(kBlock), lds, s, C);
+            streamed ? launch_cols<2, false, true>(C, grid, l, s) : launch_cols<2, false, false>(C, grid, l, s);
     } else {
-        if (staged)
-            hipLaunchKernelGGL((endor_gather_cols_kernel<1, true>), grid, dim3(kBlock), lds + stage, s, C);
-        else
-            hipLaunchKernelGGL((endor_gather_cols_kernel<1, false>), grid, dim3(kBlock), lds, s, C);
+        staged ? launch_cols<1, true, false>(C, grid, l, s) : launch_cols<1, false, false>(C, grid, l, s);
     }
     if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
     return ENDOR_OK;
