@@ -1748,7 +1748,7 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     // gather against staged: a tenth of 8192 x 28672 65 / 63 us, three tenths 135 / 114, 8-bit 50 / 41, one
     // in five kept 52 / 39, three tenths of 36864 x 9216 198 / 138; but 8192 x 28672 with four in five kept
     // (52 KB a row) 89 / 105, a fifth of 5003 x 3171 (4 KB) 11 / 13, a tenth of 30000 x 700 39 / 49.
-    const bool rows_fit = nsel >= cols / 16 && stage >= kMinColsStage && lds + stage <= kMaxColsLds;
+    const bool rows_fit = nsel >= cols / 16 && lds + stage <= kMaxColsLds;
     // And there has to be a lot to read or to answer: otherwise a workgroup's wait for its row shows, while
     // the gather finds values that the memory-side cache holds.  A tenth of 2048 x 16384 9 / 12 us, three
     // tenths 17 / 19, half 25 / 25; 3000 x 36864, 8-bit (55 MB), a tenth 21 / 25, a fifth 43 / 35; 4096 x
@@ -1760,7 +1760,16 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     // 17 / 13; fp16, four in five kept (26 KB a row), a fifth 9.7 / 11.2.
     const bool at_once = rows <= 2048 && static_cast<size_t>(rows) * (lds + stage) <= 256 * kLdsPerUnit && nsel >= cols / 5 &&
                          nnz * elem_bytes <= rows * 20480;
-    const bool staged = rows > 1 && rows_fit && (much || at_once);
+    // A shorter row only where so many of its values are asked that the gather's access for each outweighs a
+    // workgroup's wait for its row, and fewer where `values` is larger than the memory-side cache keeps.  Hits
+    // of a row, gather / staged: 18432 x 4608, half kept, four tenths (920) 64 / 47 us, 36864 x 6000, 8-bit,
+    // four tenths (1200) 141 / 107, 28672 x 8192, 8-bit, three tenths (1230) 110 / 80, 36864 x 9216 with 136 MB of
+    // values, three tenths (550) 170 / 119; but 36864 x 6000, one in five kept, four tenths (480) 109 / 119, 9216 x 9216, one
+    // in five kept, half (920, 8.5 million in all) 48.7 / 49.6, 14000 x 9216, 8-bit, 0.15 (690, 9.7 million) 29 / 34.
+    const double hits = static_cast<double>(nsel) * static_cast<double>(nnz) / static_cast<double>(cols);
+    const bool most_asked = hits >= 12e6 && hits >= rows * (nnz * elem_bytes >= (int64_t(128) << 20) ? 300.0 : 600.0);
+    const bool long_rows = stage >= kMinColsStage && (much || at_once);
+    const bool staged = rows > 1 && rows_fit && (long_rows || (stage < kMinColsStage && most_asked));
     C.stage_units = static_cast<uint32_t>(stage / 16);
     const size_t l = lds + (staged ? stage : 0);
     // Streamed stores where values are gathered: the output then leaves the lines of `values`, which several
