@@ -306,7 +306,7 @@ endor_status endor_decompress_cols_u8(int64_t rows, int64_t cols,
  * Section 7, "Efficient Compute Unit").  W: fp16 values; x: cols fp16 values (device);
  * y: rows fp32 results (device), y[i] = sum_j W[i][j]*x[j] with fp16 products exact and
  * accumulation in fp32.  Elements whose bit is 0 enter as +0.0, as from the dense matrix.
- * d_row_offsets as for endor_decompress_rows.  16-byte aligned d_x selects the fast path.
+ * d_row_offsets as for endor_decompress_rows.  d_x needs its element's alignment only.
  */
 endor_status endor_gemv_f16(int64_t rows, int64_t cols,
                             const uint8_t *d_bitmap, const uint16_t *d_values, int64_t nnz,
@@ -315,12 +315,13 @@ endor_status endor_gemv_f16(int64_t rows, int64_t cols,
 
 /*
  * DEVICE.  Fused consumer for a small batch: Y = X W^T for nb <= ENDOR_GEMM_MAX_BATCH
- * right-hand sides, straight from the compressed form, on the matrix cores (Section 7,
+ * right-hand sides, straight from the compressed form, on the matrix cores (few right-hand
+ * sides, by size: one at a time over the same windows, as endor_gemv_f16 does; Section 7,
  * "Efficient Compute Unit": compute on the sparse weight; Section 3.1: the linear operation
  * itself).  The expansion of W is done once and shared by all right-hand sides.
  *   d_x      nb vectors of cols fp16 values; vector b starts at d_x + b*ldx (ldx >= cols)
  *   d_y      out, nb x rows fp32: d_y[b*rows + i] = sum_j W[i][j] * x_b[j]; fp16 products are
- *            exact, sums are fp32 (32 products per matrix instruction); elements whose bit is
+ *            exact, sums are fp32 (up to 32 products per matrix instruction); elements whose bit is
  *            0 enter as +0.0, fp16 subnormals count in full
  *   d_workspace   the tile offset table of this bitmap (endor_build_offsets or any
  *            endor_decompress* call wrote it): it gives every wave its starting point

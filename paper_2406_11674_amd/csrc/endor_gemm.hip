@@ -26,8 +26,8 @@
 //
 // Measured on 28672 x 8192, half kept, 16 right-hand sides: 78 us (the form before, which read
 // every byte's 20-byte window from memory through the vector cache and handed the expanded bytes
-// on with ds_bpermute: 112 us; with 3 right-hand sides on 4099 x 5005, three in ten kept: 18
-// against 25 us).  What bounds it: LDS serves 65 clocks of every step's 95 (64 lanes at random
+// on with ds_bpermute: 112 us).  Few right-hand sides go to the vector form where that is faster
+// (endor_gemv.h).  What bounds it: LDS serves 65 clocks of every step's 95 (64 lanes at random
 // addresses cost 7 clocks per dword, six dwords per byte), the vector ALUs are busy 42 % of the
 // time, memory alone would take 45 us.  Measured alternatives: the windows as three aligned
 // 8-byte reads and selects (48 clocks of LDS, 25 % more vector instructions) 84 us; two rounds of

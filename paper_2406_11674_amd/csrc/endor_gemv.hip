@@ -11,8 +11,8 @@
 // pattern and multiplies them with the matching 8 entries of each x.  Elements whose bit is 0 enter as
 // +0.0, as they would from the dense matrix.
 //
-// What bounds it, at half density: reading.  8192 x 28672 takes 51 us (5.2 TB/s; the form before, a wave
-// per row and a barrier per segment, 62); a kernel that only reads as many bytes the same way 42, this
+// What bounds it, at half density: reading.  8192 x 28672 takes 48 us (5.5 TB/s; the form before, a wave
+// per row and a barrier per segment, 59); a kernel that only reads as many bytes the same way 42, this
 // one without its loads of values 37.  Below a tenth kept the work per bitmap byte bounds it: 44 us, as
 // before.  What made the difference, in turn (8192 x 28672): no barrier and no start per row 58 us;
 // streamed loads of the windows 53 (plain reads of this size reach 5.9 TB/s, streamed ones 6.6);
