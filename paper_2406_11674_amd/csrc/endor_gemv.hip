@@ -25,6 +25,7 @@
 #include "endor.h"
 #include "endor_device.h"
 #include "endor_gemv.h"
+#include "endor_gemv_windows.h"
 #include "endor_layout.h"
 
 namespace {
@@ -35,13 +36,20 @@ using endor_device::place_window;
 using endor_device::row_inclusive_scan;
 using endor_device::u32x4;
 using endor_device::wave_inclusive_scan;
-using endor_device::wave_sum;
 using endor_device::window_fifth;
 using endor_device::window_finish;
 using endor_device::window_guarded;
 using endor_device::window_tables_init;
-using endor_device::windows_inside;
 using endor_device::WindowTables;
+using endor_gemv_windows::edge_entry;
+using endor_gemv_windows::end_windows;
+using endor_gemv_windows::entry_of;
+using endor_gemv_windows::is_whole;
+using endor_gemv_windows::kEdge;
+using endor_gemv_windows::kElements;
+using endor_gemv_windows::kWhole;
+using endor_gemv_windows::whole_windows;
+using endor_gemv_windows::Windows;
 using endor_layout::dims_ok;
 using endor_layout::kChunkStride;
 using endor_layout::kTilesPerChunk;
@@ -49,7 +57,6 @@ using endor_layout::kTileWords;
 
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 
 __device__ const u32x4 g_dummy = {0u, 0u, 0u, 0u};  // read where there is nothing to read
@@ -119,6 +126,24 @@ struct Sums {
     }
 };
 
+// 8 halves without the first s (0 to 8) of them, zeros behind
+__device__ __forceinline__ u32x4 drop_halves(u32x4 d, uint32_t s) {
+    uint64_t lo = d.x | (uint64_t(d.y) << 32), hi = d.z | (uint64_t(d.w) << 32);
+    const uint32_t b = 16 * (s & 3u);
+    if (s >= 4) {
+        lo = hi;
+        hi = 0;
+    }
+    lo = (lo >> b) | ((hi << 1) << (63 - b));
+    hi >>= b;
+    if (s >= 8) lo = hi = 0;
+    d.x = static_cast<uint32_t>(lo);
+    d.y = static_cast<uint32_t>(lo >> 32);
+    d.z = static_cast<uint32_t>(hi);
+    d.w = static_cast<uint32_t>(hi >> 32);
+    return d;
+}
+
 // Entries [c, c + 8) of a vector of `cols`, zeros past its end.  In two halves: the load alone
 // (unconditional, from a place that exists), and what it means, once it is needed.
 // kShort: vectors of fewer than 8 entries.
@@ -137,25 +162,15 @@ __device__ __forceinline__ u32x4 x_load(const uint16_t *x, int64_t c, int64_t co
 }
 template <bool kShort>
 __device__ __forceinline__ u32x4 x_take(u32x4 d, int64_t c, int64_t cols) {
-    uint64_t lo = d.x | (uint64_t(d.y) << 32), hi = d.z | (uint64_t(d.w) << 32);
     if (!kShort) {  // the piece that was read began `late` entries before c
         const int64_t late = c - (cols - 8);
-        if (late > 0) {
-            const uint32_t s = 16 * (static_cast<uint32_t>(late) & 3u);
-            if (late >= 4) {
-                lo = hi;
-                hi = 0;
-            }
-            lo = (lo >> s) | ((hi << 1) << (63 - s));
-            hi >>= s;
-            if (late >= 8) lo = hi = 0;
-        }
-    } else {
-        const int64_t have = cols - c;  // entries that exist
-        if (have < 8) {
-            hi = have <= 4 ? 0 : hi & ((uint64_t(1) << (16 * (have - 4))) - 1);
-            if (have < 4) lo = have <= 0 ? 0 : lo & ((uint64_t(1) << (16 * have)) - 1);
-        }
+        return late <= 0 ? d : drop_halves(d, late < 8 ? static_cast<uint32_t>(late) : 8u);
+    }
+    uint64_t lo = d.x | (uint64_t(d.y) << 32), hi = d.z | (uint64_t(d.w) << 32);
+    const int64_t have = cols - c;  // entries that exist
+    if (have < 8) {
+        hi = have <= 4 ? 0 : hi & ((uint64_t(1) << (16 * (have - 4))) - 1);
+        if (have < 4) lo = have <= 0 ? 0 : lo & ((uint64_t(1) << (16 * have)) - 1);
     }
     d.x = static_cast<uint32_t>(lo);
     d.y = static_cast<uint32_t>(lo >> 32);
@@ -195,14 +210,13 @@ struct Segment {
     u32x4 win[kSteps];
     uint32_t end;  // the first dword after the segment's last window, for lane 63's last byte
     // wave-uniform
-    uintptr_t vbase;  // the dword boundary below the segment's first value
-    bool inside;      // no window reaches over an end of `values`
+    uint32_t how;    // its windows are read: kWhole, kEdge, kElements
+    uintptr_t base;  // that positions count from
 };
 
 // Entries to LDS, loads of the windows: streamed, although neighbouring windows overlap (the overlaps meet in
 // the vector cache; 58 us without, 53 with, on 8192 x 28672, half kept).  There is no branch around the loads (the compiler would wait
-// for them where it ends): a segment at an end of the array reads a dummy, and its windows are put
-// together element by element when they are used.
+// for them where it ends): a segment that is put together element by element when it is used reads a dummy.
 template <int kSteps>
 __device__ __forceinline__ void segment_issue(Segment<kSteps> &S, uint32_t *entry, uint64_t word, uint64_t &next_value,
                                               uintptr_t vbeg, uintptr_t vend, uint32_t lane) {
@@ -211,16 +225,30 @@ __device__ __forceinline__ void segment_issue(Segment<kSteps> &S, uint32_t *entr
     const uint32_t cnt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
     const uintptr_t vseg = vbeg + 2 * next_value;  // the segment's first value
     next_value += cnt;
-    S.vbase = vseg & ~uintptr_t(3);
+    const Windows whole = whole_windows(vseg);
+    uintptr_t base = static_cast<uintptr_t>(whole.base), end = (vseg + 2 * uintptr_t(cnt)) & ~uintptr_t(3);
+    uint32_t mask = whole.offset_mask;
+    S.how = kWhole;
+    S.base = base;
     {
-        // values of the segment before this lane's word, from the dword boundary below its first value
-        uint32_t at = incl - pc + (static_cast<uint32_t>(vseg) >> 1 & 1u);
+        uint32_t at = whole.first + incl - pc;  // position of the first value of this lane's word
         uint32_t e8[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             const uint32_t byte = static_cast<uint32_t>(word >> (8 * b)) & 0xffu;
-            e8[b] = (at << 9) | byte;
+            e8[b] = entry_of(at, byte);
             at += __popc(byte);
+        }
+        if (__builtin_expect(!is_whole(vbeg, vend, vseg, cnt), 0)) {  // wave-uniform
+            const Windows ends = end_windows(vbeg, vend, vseg);
+            const uintptr_t dummy = reinterpret_cast<uintptr_t>(&g_dummy);
+            S.how = ends.how;
+            S.base = static_cast<uintptr_t>(ends.base);
+            base = ends.how == kElements ? dummy : S.base;
+            mask = ends.offset_mask;
+            end = dummy;
+#pragma unroll
+            for (int b = 0; b < 8; ++b) e8[b] = edge_entry(e8[b] + ((ends.first - whole.first) << 9), ends.limit);
         }
         u32x4 lo, hi;
         lo.x = e8[0];
@@ -237,20 +265,16 @@ __device__ __forceinline__ void segment_issue(Segment<kSteps> &S, uint32_t *entr
         }
     }
     wave_lds_sync();
-    S.inside = vseg <= vend && windows_inside(vseg, vseg + 2 * uintptr_t(cnt), vbeg, vend);
-    const uintptr_t dummy = reinterpret_cast<uintptr_t>(&g_dummy);
-    const uintptr_t base = S.inside ? S.vbase : dummy;
-    const uint32_t mask = S.inside ? ~3u : 0u;
 #pragma unroll
-    for (int k = 0; k < kSteps; ++k) S.win[k] = __builtin_nontemporal_load(global_ptr<u32x4_a4>(base + ((entry[k * 64 + lane] >> 8) & mask)));
-    S.end = *global_ptr<uint32_t>(S.inside ? (vseg + 2 * uintptr_t(cnt)) & ~uintptr_t(3) : dummy);
+    for (int k = 0; k < kSteps; ++k) S.win[k] = __builtin_nontemporal_load(global_ptr<u32x4_a2>(base + ((entry[k * 64 + lane] >> 8) & mask)));
+    S.end = *global_ptr<uint32_t>(end);
 }
 
 // The segment's products.  x(k, b): the 8 entries of right-hand side b that step k of this lane takes.
 template <int kSteps, int kRhs, class X>
 __device__ __forceinline__ void segment_multiply(const Segment<kSteps> &S, const uint32_t *entry, const WindowTables &T,
                                                  uintptr_t vbeg, uintptr_t vend, uint32_t lane, X x, Sums (&acc)[kRhs]) {
-    if (S.inside) {  // wave-uniform
+    if (__builtin_expect(S.how == kWhole, 1)) {  // wave-uniform
 #pragma unroll
         for (int k = 0; k < kSteps; ++k) {
             const uint32_t e = entry[k * 64 + lane];
@@ -262,12 +286,20 @@ __device__ __forceinline__ void segment_multiply(const Segment<kSteps> &S, const
 #pragma unroll
             for (int b = 0; b < kRhs; ++b) acc[b](d, x(k, b));
         }
+    } else if (S.how == kEdge) {
+#pragma unroll
+        for (int k = 0; k < kSteps; ++k) {
+            const uint32_t e = entry[k * 64 + lane];
+            const u32x4 d = place_window(T, e & 0xffu, drop_halves(S.win[k], e >> 28));
+#pragma unroll
+            for (int b = 0; b < kRhs; ++b) acc[b](d, x(k, b));
+        }
     } else {
         wait_loads();  // the dummies: or the compiler counts them as still on their way in what follows
 #pragma unroll 1
         for (int k = 0; k < kSteps; ++k) {
             const uint32_t e = entry[k * 64 + lane];
-            const u32x4 d = place_window(T, e & 0xffu, window_guarded(S.vbase + (e >> 8), vbeg, vend));
+            const u32x4 d = place_window(T, e & 0xffu, window_guarded(S.base + (e >> 8), vbeg, vend));
 #pragma unroll
             for (int b = 0; b < kRhs; ++b) acc[b](d, x(k, b));
         }

@@ -1,0 +1,20 @@
+"""The vector products' value loads, replayed on the host: none outside `values`, every byte its values, and no
+segment element by element where a window fits the array (the last one of every product was, a trip per step)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_every_window_lies_inside_the_values(tmp_path):
+    exe = tmp_path / "gemv_windows_driver"
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-Wextra", "-Werror",
+                           "-I", os.path.join(ROOT, "paper_2406_11674_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "gemv_windows_driver.cpp"), "-o", str(exe)])
+    proc = subprocess.run([str(exe)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
+    assert proc.stdout.startswith("ok"), proc.stdout
