@@ -27,7 +27,7 @@
 // Measured on 28672 x 8192, half kept, 16 right-hand sides: 78 us (the form before, which read
 // every byte's 20-byte window from memory through the vector cache and handed the expanded bytes
 // on with ds_bpermute: 112 us).  Few right-hand sides go to the vector form where that is faster
-// (endor_gemv.h).  What bounds it: LDS serves 65 clocks of every step's 95 (64 lanes at random
+// (endor_gemv_plan.h).  What bounds it: LDS serves 65 clocks of every step's 95 (64 lanes at random
 // addresses cost 7 clocks per dword, six dwords per byte), the vector ALUs are busy 42 % of the
 // time, memory alone would take 45 us.  Measured alternatives: the windows as three aligned
 // 8-byte reads and selects (48 clocks of LDS, 25 % more vector instructions) 84 us; two rounds of
@@ -41,6 +41,7 @@
 #include "endor_gemm_plan.h"
 #include "endor_gemm_units.h"
 #include "endor_gemv.h"
+#include "endor_gemv_plan.h"
 #include "endor_layout.h"
 
 namespace {
@@ -648,7 +649,7 @@ extern "C" endor_status endor_gemm_f16(int64_t rows, int64_t cols, const uint8_t
         if (!d_scratch || (reinterpret_cast<uintptr_t>(d_scratch) & 255)) return ENDOR_ERR_INVALID_ARG;
         if (scratch_bytes < need) return ENDOR_ERR_BUFFER_TOO_SMALL;
     }
-    if (endor_gemv::takes(rows, cols, nb)) {  // a few right-hand sides: no scratch is used
+    if (endor_gemv_plan::takes(rows, cols, nb)) {  // a few right-hand sides: no scratch is used
         endor_gemv::SmallProduct q;
         q.bitmap = reinterpret_cast<const uint64_t *>(d_bitmap);
         q.values = d_values;

@@ -1,4 +1,4 @@
-// Fused products on the compressed form for one to endor_gemv::kMaxRhs right-hand sides:
+// Fused products on the compressed form for one to endor_gemv_plan::kMaxRhs right-hand sides:
 //     y_b[i] = sum_j W[i][j] * x_b[j],
 // with W in the Endor bitmap format (Section 4.1) and never written out densely: the linear operation
 // the decompressed weight is used for (Section 3.1), computed on the sparse form as Section 7
@@ -25,6 +25,7 @@
 #include "endor.h"
 #include "endor_device.h"
 #include "endor_gemv.h"
+#include "endor_gemv_plan.h"
 #include "endor_gemv_windows.h"
 #include "endor_layout.h"
 
@@ -41,6 +42,7 @@ using endor_device::window_finish;
 using endor_device::window_guarded;
 using endor_device::window_tables_init;
 using endor_device::WindowTables;
+using endor_gemv_plan::kMaxItems;
 using endor_gemv_windows::edge_entry;
 using endor_gemv_windows::end_windows;
 using endor_gemv_windows::entry_of;
@@ -359,10 +361,8 @@ __device__ __forceinline__ uint64_t rank_from_table(const GemvParams &G, int64_t
 // windows are asked for before the segment before it is multiplied, its bitmap words one segment earlier,
 // across the ends of items.
 //
-// kWaves: 12 for segments of 8 steps (see the top), else 16; two workgroups of 8 waves per compute unit,
+// kWaves: 12 for segments of 8 steps (see the top), else 16; the plan is endor_gemv_plan.h's; two workgroups of 8 waves per compute unit,
 // or of 10 with 96 registers, were slower (53 -> 66 and 80 us for segments of 4 steps).
-constexpr int kMaxItems = 512;  // of a workgroup; their starts and sums take up to 16 KB of LDS
-
 template <int kRhs, int kSteps, int kWaves, bool kShort>
 __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void endor_gemv_kernel(GemvParams G) {
     constexpr int kThreads = 64 * kWaves;
@@ -522,75 +522,28 @@ __global__ __launch_bounds__(256) void endor_zero_kernel(float *__restrict__ y, 
     if (i < count) y[i] = 0.0f;
 }
 
-constexpr int64_t kUnits = 256;  // compute units
-
 template <int kRhs, int kSteps, bool kShort = false>
-void launch_steps(GemvParams G, int64_t parts, hipStream_t s) {
-    constexpr int kWaves = kSteps == 8 ? 12 : 16;
-    constexpr int64_t kSeg = 512 * kSteps;
-    constexpr size_t kStatic = sizeof(WindowTables) + kWaves * 2 * 64 * kSteps * 4 + kMaxItems * (16 + 4 * kRhs);
-    const int64_t segs = (G.cols + kSeg - 1) / kSeg, room = (160 * 1024 - kStatic - 64) / (kSeg * 2 * kRhs);
-    if (parts > kWaves) parts = kWaves;
-    int64_t part_segs = (segs + parts - 1) / parts;
-    parts = (segs + part_segs - 1) / part_segs;
-    if (parts * part_segs > room) {  // x does not fit: panel by panel
-        if (parts > room) parts = room;
-        part_segs = room / parts;
-    }
-    G.part_segs = static_cast<uint32_t>(part_segs);
-    G.parts = static_cast<uint32_t>(parts);
-    G.panel = static_cast<uint32_t>(parts * part_segs * kSeg);
-    // no more workgroups than there are eight items for (1000 x 3000: 8.6 us with one for every 8 rows, 9.1 for
-    // every 16; 512 x 512: 8.4 for every 2, 7.6 for 8 or 16), and no more items per workgroup than LDS has room for
-    int64_t grid = (G.rows * parts + 7) / 8;
-    if (grid > kUnits) grid = kUnits;
-    if (grid > G.rows) grid = G.rows;
-    const int64_t least = (G.rows * parts + kMaxItems - kWaves - 1) / (kMaxItems - kWaves);  // a workgroup has up to one row more than the average
-    if (grid < least) grid = least;
-    hipLaunchKernelGGL((endor_gemv_kernel<kRhs, kSteps, kWaves, kShort>), dim3(static_cast<unsigned>(grid)), dim3(64 * kWaves),
+void launch_steps(GemvParams G, const endor_gemv_plan::Plan &p, hipStream_t s) {
+    constexpr int kWaves = endor_gemv_plan::waves_of(kSteps);
+    static_assert(sizeof(WindowTables) == endor_gemv_plan::kTableBytes, "LDS beside x");
+    G.part_segs = static_cast<uint32_t>(p.part_segs);
+    G.parts = static_cast<uint32_t>(p.parts);
+    G.panel = static_cast<uint32_t>(p.parts * p.part_segs * endor_gemv_plan::seg_cols(kSteps));
+    hipLaunchKernelGGL((endor_gemv_kernel<kRhs, kSteps, kWaves, kShort>), dim3(static_cast<unsigned>(p.grid)), dim3(64 * kWaves),
                        size_t(G.panel) * 2 * kRhs, s, G);
 }
 
-// The length of a segment: the one with the least work per row, where a step (512 columns) counts 30 and a
-// segment 40 beside its steps (the waves' vector instructions: 20 per step and 75 to 95 per segment, of which
-// part hides).  Long segments have the least of it but fewer, longer ones per wave and more code, which
-// shows at the start: 6 steps only where a compute unit has 50 of them (3000 x 3000: 8.7 us with 4 steps, 9.5
-// with 6; 9216 x 9216 26 and 22), 8 where it has 100 (3000 x 20000: 18 us with 4 steps, 20 with 8; 8192 x
-// 28672 53 and 50), or 70 of a sparse matrix, where the work counts and not the reading (20000 x 4000, a
-// tenth kept, 22.4 with 4, 21.1 with 8; half kept 23.8 and 24.3), and for up to two right-hand sides (more do
-// not fit the registers; nor do three and 6 steps).
-//
-// Parts: a row each for a wave from 12 rows per compute unit on; fewer are cut so that every wave has an
-// item or two (600 x 36864: 22 us with rows whole, 14 to 15 with 11 parts; 2000 x 5000 9.3 whole, 8.9 with 3;
-// from 24 rows on parts cost up to 2 us, as their starts have to be counted).
-//
-// Against the best of all lengths and parts that fit, measured over 16 shapes and 1, 2 and 4 right-hand
-// sides, these rules are 3.5 % slower on average.
 template <int kRhs>
 void launch(const GemvParams &G, hipStream_t s) {
-    if (G.cols < 8) {
-        launch_steps<1, 2, true>(G, 1, s);
-        return;
-    }
-    const int64_t per = (G.rows + kUnits - 1) / kUnits;  // rows per compute unit
-    constexpr int kMost = kRhs > 2 ? 4 : 8;
-    const bool sparse = G.nnz < G.rows * G.cols / 4;
-    int64_t best = -1;
-    int steps = 2;
-    for (int st = 2; st <= kMost; st += 2) {
-        const int64_t segs = (G.cols + 512 * st - 1) / (512 * st), cost = segs * (40 + 30 * st);
-        if (segs * per < (st == 8 ? (sparse ? 70 : 100) : st == 6 ? 50 : 0)) continue;
-        if (best < 0 || cost < best) best = cost, steps = st;
-    }
-    const int64_t parts = per >= 12 ? 1 : (32 + per - 1) / per;
-    if (steps == 2)
-        launch_steps<kRhs, 2>(G, parts, s);
-    else if (steps == 4)
-        launch_steps<kRhs, 4>(G, parts, s);
-    else if (steps == 6)
-        launch_steps<kRhs, kMost < 6 ? 4 : 6>(G, parts, s);
-    else
-        launch_steps<kRhs, kMost < 8 ? 4 : 8>(G, parts, s);
+    const endor_gemv_plan::Plan p = endor_gemv_plan::make_plan(G.rows, G.cols, G.nnz, kRhs);
+    if (G.cols < 8)  // one right-hand side
+        launch_steps<1, 2, true>(G, p, s);
+    else if (p.steps == 2)
+        launch_steps<kRhs, 2>(G, p, s);
+    else if (p.steps == 4)
+        launch_steps<kRhs, 4>(G, p, s);
+    else if constexpr (endor_gemv_plan::most_steps(kRhs) == 8)
+        p.steps == 6 ? launch_steps<kRhs, 6>(G, p, s) : launch_steps<kRhs, 8>(G, p, s);
 }
 
 }  // namespace

@@ -1,0 +1,57 @@
+// How the vector products share out their work (endor_gemv_plan.h), checked on the host over shapes of every
+// kind.  Built and run by tests/test_gemv_plan.py; not part of the library.
+#include <cstdint>
+#include <cstdio>
+
+#include "endor_gemv_plan.h"
+
+using namespace endor_gemv_plan;
+
+static uint64_t state = 0x243F6A8885A308D3ull;
+static uint64_t rnd() {
+    state ^= state << 13;
+    state ^= state >> 7;
+    state ^= state << 17;
+    return state;
+}
+static int64_t size(int bits) {  // spread over its logarithm
+    const int b = static_cast<int>(rnd() % (bits + 1));
+    return 1 + static_cast<int64_t>(rnd() % (uint64_t(1) << b));
+}
+
+// What must hold of any plan; a complaint, or null.
+static const char *check(int64_t rows, int64_t cols, int rhs, const Plan &p) {
+    const int64_t seg = seg_cols(p.steps), segs = ceil_div(cols, seg), slots = p.panels * p.parts * p.part_segs;
+    if (p.steps < 2 || p.steps > most_steps(rhs) || (p.steps & 1)) return "no such segment";
+    if (p.parts < 1 || p.part_segs < 1 || p.parts > waves_of(p.steps)) return "parts";
+    if (lds_beside_x(p.steps, rhs) + size_t(p.parts * p.part_segs * seg) * 2 * rhs > kLds) return "more LDS than there is";
+    if (slots < segs) return "columns left out";
+    if (p.grid < 1 || p.grid > rows || (rows < 2000000000 && p.grid * 64 * waves_of(p.steps) >= int64_t(1) << 32)) return "grid";
+    if (ceil_div(rows, p.grid) * p.parts > kMaxItems) return "more items than a workgroup has room for";
+    // waves walk every slot
+    if (slots - segs >= p.panels * p.parts + p.panels) return "a panel of segments without columns";
+    return nullptr;
+}
+
+int main() {
+    for (int rep = 0; rep < 400000; ++rep) {
+        const int rhs = 1 + static_cast<int>(rnd() % 4);
+        int64_t rows = size(rep % 50 ? 18 : 31), cols = size(rep % 50 ? 18 : 33);
+        if (rows > 0x7fffffff || cols > ((int64_t(1) << 34) - 1) / rows) continue;  // refused
+        if (rhs > 1 && cols < 8) continue;
+        const int64_t nnz = rnd() % 2 ? 0 : rows * cols;
+        Plan p = make_plan(rows, cols, nnz, rhs);
+        const char *bad = check(rows, cols, rhs, p);
+        // a product that is taken from the matrix cores has all of x in LDS
+        if (!bad && rhs > 1 && takes(rows, cols, rhs) && p.panels != 1) bad = "x in panels";
+        if (!bad && cols >= 8)
+            for (int st = 2; st <= most_steps(rhs) && !bad; st += 2) bad = check(rows, cols, rhs, p = plan_with(rows, cols, rhs, st, 1 + rnd() % 16));
+        if (bad) {
+            std::printf("%s: %lld x %lld, %d right-hand sides: steps %d parts %lld x %lld, %lld panels, %lld workgroups\n", bad, (long long)rows,
+                        (long long)cols, rhs, p.steps, (long long)p.parts, (long long)p.part_segs, (long long)p.panels, (long long)p.grid);
+            return 1;
+        }
+    }
+    std::printf("ok\n");
+    return 0;
+}
