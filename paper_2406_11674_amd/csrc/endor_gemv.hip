@@ -42,7 +42,6 @@ using endor_device::window_finish;
 using endor_device::window_guarded;
 using endor_device::window_tables_init;
 using endor_device::WindowTables;
-using endor_gemv_plan::kMaxItems;
 using endor_gemv_windows::edge_entry;
 using endor_gemv_windows::end_windows;
 using endor_gemv_windows::entry_of;
@@ -366,6 +365,7 @@ __device__ __forceinline__ uint64_t rank_from_table(const GemvParams &G, int64_t
 template <int kRhs, int kSteps, int kWaves, bool kShort>
 __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void endor_gemv_kernel(GemvParams G) {
     constexpr int kThreads = 64 * kWaves;
+    constexpr int kMaxItems = endor_gemv_plan::max_items(kSteps, kRhs);
     constexpr int kSeg = 512 * kSteps;
     extern __shared__ u32x4 s_x[];  // kRhs panels
     __shared__ WindowTables s_tables;

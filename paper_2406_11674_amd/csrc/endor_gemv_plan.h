@@ -9,16 +9,17 @@
 namespace endor_gemv_plan {
 
 constexpr int64_t kUnits = 256;    // compute units; one workgroup each (registers of all its waves)
-constexpr int kMaxItems = 496;     // of a workgroup; their starts and sums take up to 16 KB of LDS (of 512, two
-                                   // vectors of 24576 would miss one panel by 200 bytes)
 constexpr size_t kLds = 160 * 1024;
 constexpr size_t kTableBytes = 4224;  // the windows' selector tables
 
 constexpr int waves_of(int steps) { return steps == 8 ? 12 : 16; }
+// items of a workgroup, whose starts and sums take up to 16 KB of LDS (of 512, two vectors of 24576 would miss one
+// panel of 8-step segments by 200 bytes)
+constexpr int max_items(int steps, int rhs) { return steps == 8 && rhs == 2 ? 496 : 512; }
 constexpr int64_t seg_cols(int steps) { return 512 * steps; }
 // LDS of a workgroup beside x: tables, two segments' entries per wave, starts, ends and sums of its items
 constexpr size_t lds_beside_x(int steps, int rhs) {
-    return kTableBytes + size_t(waves_of(steps)) * 2 * 64 * steps * 4 + size_t(kMaxItems) * (16 + 4 * rhs);
+    return kTableBytes + size_t(waves_of(steps)) * 2 * 64 * steps * 4 + size_t(max_items(steps, rhs)) * (16 + 4 * rhs);
 }
 // segments of x that fit beside that
 constexpr int64_t room_of(int steps, int rhs) {
@@ -75,8 +76,10 @@ constexpr Plan plan_with(int64_t rows, int64_t cols, int rhs, int steps, int64_t
     int64_t grid = ceil_div(rows * p.parts, 8);
     if (grid > kUnits) grid = kUnits;
     if (grid > rows) grid = rows;
-    const int64_t least = ceil_div(rows * p.parts, kMaxItems - waves_of(steps));  // a workgroup has up to one row more than the average
-    if (grid < least) grid = least;
+    const int64_t least = ceil_div(rows * p.parts, max_items(steps, rhs) - waves_of(steps));  // a workgroup has up to one row more than the average
+    // a compute unit holds one workgroup: more than there are units in whole generations of about equal length
+    // (131072 x 64 in 265 workgroups, 9 of them by themselves at the end, 90 us, in 512 51; 300000 x 100 in 605 135, in 768 109)
+    if (grid < least) grid = least > kUnits ? ceil_div(least, kUnits) * kUnits : least;
     p.grid = grid;
     return p;
 }

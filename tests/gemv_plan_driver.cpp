@@ -27,7 +27,8 @@ static const char *check(int64_t rows, int64_t cols, int rhs, const Plan &p) {
     if (lds_beside_x(p.steps, rhs) + size_t(p.parts * p.part_segs * seg) * 2 * rhs > kLds) return "more LDS than there is";
     if (slots < segs) return "columns left out";
     if (p.grid < 1 || p.grid > rows || (rows < 2000000000 && p.grid * 64 * waves_of(p.steps) >= int64_t(1) << 32)) return "grid";
-    if (ceil_div(rows, p.grid) * p.parts > kMaxItems) return "more items than a workgroup has room for";
+    if (ceil_div(rows, p.grid) * p.parts > max_items(p.steps, rhs)) return "more items than a workgroup has room for";
+    if (p.grid > kUnits && p.grid % kUnits) return "a last generation of a few workgroups";
     // waves walk every slot
     if (slots - segs >= p.panels * p.parts + p.panels) return "a panel of segments without columns";
     return nullptr;
