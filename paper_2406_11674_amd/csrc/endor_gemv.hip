@@ -535,7 +535,7 @@ void launch_steps(GemvParams G, const endor_gemv_plan::Plan &p, hipStream_t s) {
 
 template <int kRhs>
 void launch(const GemvParams &G, hipStream_t s) {
-    const endor_gemv_plan::Plan p = endor_gemv_plan::make_plan(G.rows, G.cols, G.nnz, kRhs);
+    const endor_gemv_plan::Plan p = endor_gemv_plan::make_plan(G.rows, G.cols, kRhs);
     if (G.cols < 8)  // one right-hand side
         launch_steps<1, 2, true>(G, p, s);
     else if (p.steps == 2)

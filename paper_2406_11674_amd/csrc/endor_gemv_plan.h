@@ -53,7 +53,11 @@ struct Plan {
     int64_t grid;       // workgroups
 };
 
-constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+constexpr int64_t ceil_div(int64_t a, int64_t b) {
+    // the divisions of 64 bits are most of what a plan takes
+    const uint64_t n = static_cast<uint64_t>(a + b - 1), d = static_cast<uint64_t>(b);
+    return (n | d) >> 32 ? static_cast<int64_t>(n / d) : static_cast<uint32_t>(n) / static_cast<uint32_t>(d);
+}
 
 // The plan with segments of that many steps and up to that many parts per row.  Where x does not fit LDS its
 // panels are of about equal length: a wave walks every segment of every panel, whether it has columns or not.
@@ -84,36 +88,47 @@ constexpr Plan plan_with(int64_t rows, int64_t cols, int rhs, int steps, int64_t
     return p;
 }
 
-constexpr int64_t rows_per_unit(int64_t rows) { return ceil_div(rows, kUnits); }
-
-// The length of a segment: the one with the least work per row, where a step (512 columns) counts 30 and a
-// segment 40 beside its steps (the waves' vector instructions: 20 per step and 75 to 95 per segment, of which
-// part hides).  Long segments have the least of it but fewer, longer ones per wave and more code, which
-// shows at the start: 6 steps only where a compute unit has 50 of them (3000 x 3000: 8.7 us with 4 steps, 9.5
-// with 6; 9216 x 9216 26 and 22), 8 where it has 100 (3000 x 20000: 18 us with 4 steps, 20 with 8; 8192 x
-// 28672 53 and 50), or 70 of a sparse matrix, where the work counts and not the reading (20000 x 4000, a
-// tenth kept, 22.4 with 4, 21.1 with 8; half kept 23.8 and 24.3), and for up to two right-hand sides (more do
-// not fit the registers; nor do three and 6 steps).
+// What a plan costs: about 40 per percent of a microsecond.  A segment takes 90, and 30 a step with another 2 for
+// each right-hand side, of a compute unit's vector units; 16 waves with the same number of segments use
+// them fully, 12 are 3 % slower.  A workgroup ends with its longest wave, which alone runs at 3/8 of a wave's
+// cost and waits 45 a segment for memory.  Longer segments are more code to fetch at the start (3 a step), parts
+// of rows have their starts counted (15 for every four items of a wave), and a further panel of x is a start of
+// its own (1000).
 //
-// Parts: a row each for a wave from 12 rows per compute unit on; fewer are cut so that every wave has an
-// item or two (600 x 36864: 22 us with rows whole, 14 to 15 with 11 parts; 2000 x 5000 9.3 whole, 8.9 with 3;
-// from 24 rows on parts cost up to 2 us, as their starts have to be counted).
-constexpr Plan make_plan(int64_t rows, int64_t cols, int64_t nnz, int rhs) {
+// Fitted to every plan of 310 products (200 shapes, 1 x 600 to 36864 x 8192, 0.1 to 0.8 kept, one to four
+// right-hand sides): the plan it picks is 0.6 % slower than the best on average.  The rule before, by the work of
+// a row alone, kept rows whole from 12 per compute unit on and had no term for the longest wave: 2000 x 28672,
+// a tenth kept, 21 us where 17 is possible (8 steps, rows whole), 12000 x 2500 16.5 / 11.9 (6 steps), 3000 x
+// 3000 8.4 / 7.0, 4099 x 15000 with three 28 / 24 (2 parts: 17 rows are two to a wave of 16, 34 halves three).
+constexpr int64_t cost_of(int64_t rows, int rhs, const Plan &p) {
+    const int64_t waves = waves_of(p.steps), items = ceil_div(rows, p.grid) * p.parts, segs = p.part_segs * p.panels;
+    const int64_t segment = 90 + (30 + 2 * rhs) * p.steps;
+    const int64_t work = items * segs * segment / 16, all = waves < 16 ? work + work / 32 : work;
+    const int64_t longest = ceil_div(items, waves) * segs * (segment * 3 / 8 + 45);
+    return ceil_div(p.grid, kUnits) * (all > longest ? all : longest) + 3 * p.steps +
+           (p.parts > 1 ? 15 * ceil_div(items, 4 * waves) * p.panels : 0) + 1000 * (p.panels - 1);
+}
+
+constexpr Plan make_plan(int64_t rows, int64_t cols, int rhs) {
     if (cols < 8) return plan_with(rows, cols, 1, 2, 1);
-    const int64_t per = rows_per_unit(rows);
-    const bool sparse = nnz < rows * cols / 4;
-    int64_t best = -1;
-    int steps = 2;
-    for (int st = 2; st <= most_steps(rhs); st += 2) {
-        const int64_t segs = ceil_div(cols, seg_cols(st)), cost = segs * (40 + 30 * st);
-        if (segs * per < (st == 8 ? (sparse ? 70 : 100) : st == 6 ? 50 : 0)) continue;
-        if (segs > room_of(st, rhs) && ceil_div(cols, seg_cols(4)) <= room_of(4, rhs)) continue;  // x fits, but not with these
-        if (best < 0 || cost < best) {
-            best = cost;
-            steps = st;
+    Plan best{};
+    int64_t least = -1;
+    for (int steps = cols > 4096 ? 4 : 2; steps <= most_steps(rhs); steps += 2) {  // 2 steps are for short rows
+        // more than 32 rows per compute unit are never cut (9216 x 9216 in 3 parts 22, whole 19; a plan costs the
+        // caller 0.1 to 0.3 us)
+        const int64_t most = rows > 32 * kUnits ? 1 : waves_of(steps), segs = ceil_div(cols, seg_cols(steps));
+        for (int64_t parts = 1, before = 0; parts <= most && parts <= segs; ++parts) {
+            const Plan p = plan_with(rows, cols, rhs, steps, parts);
+            if (p.parts == before) continue;
+            before = p.parts;
+            const int64_t cost = cost_of(rows, rhs, p);
+            if (least < 0 || cost < least) {
+                least = cost;
+                best = p;
+            }
         }
     }
-    return plan_with(rows, cols, rhs, steps, per >= 12 ? 1 : (32 + per - 1) / per);
+    return best;
 }
 
 }  // namespace endor_gemv_plan
