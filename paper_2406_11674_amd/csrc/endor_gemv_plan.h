@@ -27,22 +27,36 @@ constexpr int64_t room_of(int steps, int rhs) {
 }
 constexpr int most_steps(int rhs) { return rhs > 2 ? 4 : 8; }
 
+constexpr int64_t ceil_div(int64_t a, int64_t b) {
+    // the divisions of 64 bits are most of what a plan takes
+    const uint64_t n = static_cast<uint64_t>(a + b - 1), d = static_cast<uint64_t>(b);
+    return (n | d) >> 32 ? static_cast<int64_t>(n / d) : static_cast<uint32_t>(n) / static_cast<uint32_t>(d);
+}
+
 constexpr int kMaxRhs = 4;
 
-// Whether the vector form is the faster one for nb right-hand sides of the small-batch product.  Measured,
-// us, the form on the matrix cores / this one:
-//  - short rows, many of them: 36864 x 768 and one right-hand side 18.6 / 19 to 21, 131072 x 256 22 / 104;
-//    12000 x 600 13 / 9.5, 20000 x 1200 24 / 16, 36864 x 1500 with two 29.6 / 27.4, with three 29.6 / 30.2;
-//  - all of x has to fit LDS: two right-hand sides 4096 x 20000 39 / 28, 8192 x 28672 74 / 82; three
-//    2000 x 16000 21.7 / 19.2, 4096 x 20000 39 / 46;
-//  - four only pay on small matrices: 4096 x 4096 15 / 12, 12000 x 2500 27 / 22, 16384 x 4096 27 / 29,
-//    36864 x 9216 107 / 117;
-//  - else 28672 x 8192 with one to three 75 / 52, 59, 70; 4099 x 5005, three in ten kept, 18 / 12, 14, 15.
+// Whether the vector form is the faster one for nb right-hand sides of the small-batch product.  The form on the
+// matrix cores takes 16 rows of 256 columns in a round and starts slowly, this one takes a segment for every row however short
+// the row is: so for narrow matrices it depends on the rows, up to `most` of them per compute unit for the widths below.
+// Lines that do not begin at a bitmap word cost the matrix form more: a quarter more rows then.
+// Measured, a tenth and 0.6 kept, us, the form on the matrix cores / this one:
+//   64 columns  2000 rows, one vector, 7.3 / 6.9, two 7.3 / 7.3, 4099, three, 7.3 / 8.5, 16384, one, 7.3 / 11.7, four 7.4 / 14.7
+//   512         9216, one 9 / 8.9, 12672, one, 8.9 / 11.0, four 9.2 / 13.7; 4099, three, 9.1 / 8.9
+//   1024        16384, one, 11.8 to 13.7 / 12.1, 28672 14.9 / 17.3, 131072 48 / 61; 9216, four, 11.8 to 13 / 10.9
+//   1300, 1536  20000, two, 22 to 25 / 19; 12672, three, 18 / 16, 28672, three, 22 to 26 / 29
+//   2500        20000, three, 37 / 31, 28672 41 / 44 (a segment of 4 steps and one nearly empty)
+//   wider       28672 x 8192 with one to three 75 / 50, 58, 70; 4099 x 5005, 0.3 kept, 18 / 12, 14, 15
+// All of x has to fit LDS (two vectors of 8192 x 28672 74 / 82); four are left to the matrix cores from 2^25 elements on.
 //  cols >= 8: shorter vectors are read element by element, which is there for one right-hand side only.
 constexpr bool takes(int64_t rows, int64_t cols, int nb) {
     if (cols < 8 || nb > kMaxRhs || cols * nb > 48 * 1024) return false;
     if (nb == 4 && rows * cols > int64_t(1) << 25) return false;
-    return rows <= 16384 || cols >= 1024 * (nb == 1 ? 1 : nb == 2 ? 1.4 : 2);
+    constexpr int kAny = 1 << 24;
+    constexpr int most[6][kMaxRhs] = {{17, 8, 4, 0}, {36, 24, 18, 16}, {79, 36, 36, 36}, {144, 79, 60, 40}, {kAny, kAny, 79, 79}, {kAny, kAny, 79, 50}};
+    if (cols > 3072) return true;
+    const int width = cols <= 256 ? 0 : cols <= 512 ? 1 : cols <= 1024 ? 2 : cols <= 1536 ? 3 : cols <= 2048 ? 4 : 5;
+    const int64_t limit = most[width][nb - 1];
+    return ceil_div(rows, kUnits) <= (cols % 64 ? limit + limit / 4 : limit);
 }
 
 struct Plan {
@@ -52,12 +66,6 @@ struct Plan {
     int64_t panels;     // of parts * part_segs segments
     int64_t grid;       // workgroups
 };
-
-constexpr int64_t ceil_div(int64_t a, int64_t b) {
-    // the divisions of 64 bits are most of what a plan takes
-    const uint64_t n = static_cast<uint64_t>(a + b - 1), d = static_cast<uint64_t>(b);
-    return (n | d) >> 32 ? static_cast<int64_t>(n / d) : static_cast<uint32_t>(n) / static_cast<uint32_t>(d);
-}
 
 // The plan with segments of that many steps and up to that many parts per row.  Where x does not fit LDS its
 // panels are of about equal length: a wave walks every segment of every panel, whether it has columns or not.

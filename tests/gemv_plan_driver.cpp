@@ -52,6 +52,19 @@ int main() {
             return 1;
         }
     }
+    // narrow products with few right-hand sides: those that the matrix cores do in half the time to four fifths, and others
+    const int64_t kNot[][3] = {{16384, 256, 1}, {16384, 64, 2}, {16384, 256, 4}, {9216, 64, 2}, {9216, 8, 4}, {4099, 64, 4}, {131072, 1024, 1}, {16384, 1024, 4}, {131072, 256, 1}};
+    for (const auto &s : kNot)
+        if (takes(s[0], s[1], static_cast<int>(s[2]))) {
+            std::printf("%lld x %lld with %lld taken from the matrix cores\n", (long long)s[0], (long long)s[1], (long long)s[2]);
+            return 1;
+        }
+    const int64_t kYes[][3] = {{1, 600, 4}, {2000, 64, 2}, {4099, 5005, 3}, {12000, 600, 1}, {4096, 4096, 4}, {28672, 8192, 3}, {4400, 24570, 2}};
+    for (const auto &s : kYes)
+        if (!takes(s[0], s[1], static_cast<int>(s[2]))) {
+            std::printf("%lld x %lld with %lld left to the matrix cores\n", (long long)s[0], (long long)s[1], (long long)s[2]);
+            return 1;
+        }
     std::printf("ok\n");
     return 0;
 }
