@@ -52,7 +52,7 @@ constexpr bool takes(int64_t rows, int64_t cols, int nb) {
     if (cols < 8 || nb > kMaxRhs || cols * nb > 48 * 1024) return false;
     if (nb == 4 && rows * cols > int64_t(1) << 25) return false;
     constexpr int kAny = 1 << 24;
-    constexpr int most[6][kMaxRhs] = {{17, 8, 4, 0}, {36, 24, 18, 16}, {79, 36, 36, 36}, {144, 79, 60, 40}, {kAny, kAny, 79, 79}, {kAny, kAny, 79, 50}};
+    constexpr int most[6][kMaxRhs] = {{17, 8, 4, 0}, {36, 24, 18, 16}, {79, 44, 36, 36}, {144, 79, 60, 40}, {kAny, kAny, 79, 79}, {kAny, kAny, 79, 50}};
     if (cols > 3072) return true;
     const int width = cols <= 256 ? 0 : cols <= 512 ? 1 : cols <= 1024 ? 2 : cols <= 1536 ? 3 : cols <= 2048 ? 4 : 5;
     const int64_t limit = most[width][nb - 1];
