@@ -704,6 +704,13 @@ struct ColsParams {
     uint32_t stage_units;        // 16-byte units the staging area holds, one of them spare (kStaged)
 };
 
+constexpr uint32_t kLineBytes = 128;  // of the second-level cache
+
+// Plain; past the memory-side cache; so, and each wave's part of a row in whole lines, where rows of the output do
+// not begin at one.  A streamed store of parts of lines costs about a third more than one of whole ones: 8192 x
+// 28672, four in five kept, 0.35 of the columns (rows of 20070 bytes) plain 157 us, streamed 179, in whole lines 153.
+enum class Store { kPlain, kStreamed, kLines };
+
 // 64 bits of row-aligned "virtual word" k of a row that starts at bit row_bit: bits
 // row_bit + 64k .. +63, clipped to the row's `cols` bits and to the bitmap.
 __device__ __forceinline__ uint64_t row_word(const uint64_t *bitmap, int64_t nwords, int64_t row_bit,
@@ -730,8 +737,8 @@ __device__ __forceinline__ uint64_t row_word(const uint64_t *bitmap, int64_t nwo
 // kStaged: the row's whole value slice goes straight to LDS (no registers) while the bitmap is
 // worked on, and the queries read it there; the host says when that pays.
 //
-// kStreamed: the output is stored past the memory-side cache.  kQ: queries per thread and round.
-template <int E, bool kStaged, bool kStreamed, int kQ>
+// kStore: how the output is stored (Store).  kQ: queries per thread and round.
+template <int E, bool kStaged, Store kStore, int kQ>
 __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C) {
     typedef std::conditional_t<E == 2, uint16_t, uint8_t> Elem;
     // [np] pairs (32 bits of the row's bitmap, 1 bits of the row before them) | staged values
@@ -772,12 +779,20 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
         stage += vaddr - a16;
     }
 
+    // kLines: a row's queries are counted from the start of the line that its output begins in; the `early` numbers
+    // before its first are no queries.
+    uint8_t *row_out = static_cast<uint8_t *>(C.out) + E * i * C.nsel;
+    const uint32_t early = kStore == Store::kLines ? static_cast<uint32_t>(reinterpret_cast<uintptr_t>(row_out) % kLineBytes / E) : 0;
+    const int64_t nsel = C.nsel + early;
+    const int64_t *sel = C.sel - early;
+    row_out -= E * early;
+
     // first round of column indices: in flight during the bitmap work
     int64_t c[kQ];
 #pragma unroll
     for (int u = 0; u < kQ; ++u) {
         const int64_t q = u * kBlock + threadIdx.x;
-        c[u] = q < C.nsel ? C.sel[q] : -1;
+        c[u] = q < nsel && (kStore != Store::kLines || u || threadIdx.x >= early) ? sel[q] : -1;
     }
 
     // scan of the word popcounts, kBlock words per round: wave scan, then the waves' totals
@@ -819,18 +834,17 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
     // values from the row's first to the end of the array; none if the offset is not inside it
     const uint64_t room = (row_first >= 0 && row_first <= C.nnz) ? static_cast<uint64_t>(C.nnz - row_first) : 0;
     const uint8_t *row_values = static_cast<const uint8_t *>(C.values) + E * row_first;
-    uint8_t *row_out = static_cast<uint8_t *>(C.out) + E * i * C.nsel;
     const uint64_t ucols = static_cast<uint64_t>(C.cols);
     // The queries.  kFromLds: the row's values are staged.  (Two loops, not one with a test: the test cost the
     // staged form 15 % and the gather up to 5 %.)
     auto answer = [&](auto from_lds) {
         constexpr bool kFromLds = decltype(from_lds)::value;
-        for (int64_t q0 = 0; q0 < C.nsel; q0 += kQ * kBlock) {
+        for (int64_t q0 = 0; q0 < nsel; q0 += kQ * kBlock) {
             int64_t cn[kQ];
 #pragma unroll
             for (int u = 0; u < kQ; ++u) {  // the next round's indices
                 const int64_t q = q0 + (kQ + u) * kBlock + threadIdx.x;
-                cn[u] = q < C.nsel ? C.sel[q] : -1;
+                cn[u] = q < nsel ? sel[q] : -1;
             }
             uint32_t v[kQ];
             bool live[kQ], hit[kQ];
@@ -862,7 +876,7 @@ __global__ __launch_bounds__(kBlock) void endor_gather_cols_kernel(ColsParams C)
                 const int64_t q = q0 + u * kBlock + threadIdx.x;
                 if (live[u]) {
                     Elem *at = reinterpret_cast<Elem *>(row_out) + q;
-                    if (kStreamed)
+                    if (kStore != Store::kPlain)
                         __builtin_nontemporal_store(static_cast<Elem>(v[u]), at);
                     else
                         *at = static_cast<Elem>(v[u]);
@@ -1702,15 +1716,28 @@ constexpr int64_t kMaxGatherCols = int64_t(1) << 18;  // the row's bitmap and it
 // (28672 x 8192, one in five kept, three tenths 134 / 125 before its stores were streamed), but 4 where
 // the last of several rounds would be mostly empty with 6 (2048 x 16384, a tenth, 9.9 / 9.2).  3 for few queries
 // (36864 x 2000, a tenth, 6 / 4 / 3: 47 / 47 / 44).
-template <int E, bool kStaged, bool kStreamed>
-void launch_cols(const ColsParams &C, dim3 grid, size_t lds, hipStream_t s) {
-    const int64_t rounds6 = (C.nsel + 6 * kBlock - 1) / (6 * kBlock), rounds4 = (C.nsel + 4 * kBlock - 1) / (4 * kBlock);
-    if (C.nsel <= 3 * kBlock)
-        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStreamed, 3>), grid, dim3(kBlock), lds, s, C);
-    else if (kStaged || (rounds6 == rounds4 && rounds6 > 1))
-        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStreamed, 4>), grid, dim3(kBlock), lds, s, C);
-    else
-        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStreamed, kStaged ? 4 : 6>), grid, dim3(kBlock), lds, s, C);
+int cols_round(bool staged, int64_t nsel) {
+    const int64_t rounds6 = (nsel + 6 * kBlock - 1) / (6 * kBlock), rounds4 = (nsel + 4 * kBlock - 1) / (4 * kBlock);
+    return nsel <= 3 * kBlock ? 3 : staged || (rounds6 == rounds4 && rounds6 > 1) ? 4 : 6;
+}
+
+template <int E, bool kStaged, Store kStore>
+void launch_cols(const ColsParams &C, int round, dim3 grid, size_t lds, hipStream_t s) {
+    if (round == 3)
+        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStore, 3>), grid, dim3(kBlock), lds, s, C);
+    else if (round == 4)
+        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStore, 4>), grid, dim3(kBlock), lds, s, C);
+    else if constexpr (!kStaged)
+        hipLaunchKernelGGL((endor_gather_cols_kernel<E, kStaged, kStore, 6>), grid, dim3(kBlock), lds, s, C);
+}
+
+template <int E, bool kStaged>
+void launch_cols(const ColsParams &C, Store store, int round, dim3 grid, size_t lds, hipStream_t s) {
+    if constexpr (E == 2) {
+        if (store == Store::kLines) return launch_cols<E, kStaged, Store::kLines>(C, round, grid, lds, s);
+        if (store == Store::kStreamed) return launch_cols<E, kStaged, Store::kStreamed>(C, round, grid, lds, s);
+    }
+    launch_cols<E, kStaged, Store::kPlain>(C, round, grid, lds, s);
 }
 
 endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t *d_bitmap, const void *d_values,
@@ -1779,15 +1806,26 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     // MB) 113 / 101, half (235 MB) 152 / 134, but 4096 x 28672, one in five kept, three tenths (70 MB) 42.6 / 45.5.
     // Very small outputs and 8-bit ones are not: 1024 x 16384, a tenth (3 MB), 6.5 / 6.8; 8-bit +-2 % throughout.
     const int64_t out_bytes = asked * elem_bytes;
-    const bool streamed = elem_bytes == 2 && out_bytes >= (staged ? int64_t(96) << 20 : int64_t(8) << 20);
-    if (elem_bytes == 2) {
-        if (staged)
-            streamed ? launch_cols<2, true, true>(C, grid, l, s) : launch_cols<2, true, false>(C, grid, l, s);
-        else
-            streamed ? launch_cols<2, false, true>(C, grid, l, s) : launch_cols<2, false, false>(C, grid, l, s);
-    } else {
-        staged ? launch_cols<1, true, false>(C, grid, l, s) : launch_cols<1, false, false>(C, grid, l, s);
+    const int round = cols_round(staged, nsel);
+    Store store = Store::kPlain;
+    if (elem_bytes == 2 && out_bytes >= (staged ? int64_t(96) << 20 : int64_t(8) << 20)) {
+        store = Store::kStreamed;
+        if ((reinterpret_cast<uintptr_t>(d_out) | static_cast<uintptr_t>(2 * nsel)) % kLineBytes) {
+            // Rows that begin inside a line.  Whole lines, unless the queries then take a round more; a gathered row
+            // has to be long for it (28672 x 8192, one in five kept, 0.22 of the columns (1802) 79 / 80 us in lines; 9216 x 9216
+            // 2027 28.1 / 28.9, 3225 equal).  A staged row is stored plainly instead (17274 x 13952, 0.22 79 / 82 streamed).
+            const int64_t taken = (nsel + round * kBlock - 1) / (round * kBlock) * (round * kBlock);
+            const bool room = nsel + int64_t(kLineBytes) / 2 <= taken;
+            if (staged)
+                store = room ? Store::kLines : Store::kPlain;
+            else if (room && nsel >= 3072)
+                store = Store::kLines;
+        }
     }
+    if (elem_bytes == 2)
+        staged ? launch_cols<2, true>(C, store, round, grid, l, s) : launch_cols<2, false>(C, store, round, grid, l, s);
+    else
+        staged ? launch_cols<1, true>(C, store, round, grid, l, s) : launch_cols<1, false>(C, store, round, grid, l, s);
     if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
     return ENDOR_OK;
 }
