@@ -1792,9 +1792,10 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     // of a row, gather / staged: 18432 x 4608, half kept, four tenths (920) 64 / 47 us, 36864 x 6000, 8-bit,
     // four tenths (1200) 141 / 107, 28672 x 8192, 8-bit, three tenths (1230) 110 / 80, 36864 x 9216 with 136 MB of
     // values, three tenths (550) 170 / 119; but 36864 x 6000, one in five kept, four tenths (480) 109 / 119, 9216 x 9216, one
-    // in five kept, half (920, 8.5 million in all) 48.7 / 49.6, 14000 x 9216, 8-bit, 0.15 (690, 9.7 million) 29 / 34.
+    // in five kept, half (920, 8.5 million in all) 48.7 / 49.6, 14000 x 9216, 8-bit, 0.15 (690, 9.7 million) 29 / 34, 20000 x
+    // 1500, 0.8 kept, half (600, 12 million) 33 / 37, 28672 x 8192, 8-bit, 0.16 (655) 63 / 66.
     const double hits = static_cast<double>(nsel) * static_cast<double>(nnz) / static_cast<double>(cols);
-    const bool most_asked = hits >= 12e6 && hits >= rows * (nnz * elem_bytes >= (int64_t(128) << 20) ? 300.0 : 600.0);
+    const bool most_asked = hits >= 12e6 && hits >= rows * (nnz * elem_bytes >= (int64_t(128) << 20) ? 300.0 : 800.0);
     const bool long_rows = stage >= kMinColsStage && (much || at_once);
     const bool staged = rows > 1 && rows_fit && (long_rows || (stage < kMinColsStage && most_asked));
     C.stage_units = static_cast<uint32_t>(stage / 16);
