@@ -1812,15 +1812,13 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     if (elem_bytes == 2 && out_bytes >= (staged ? int64_t(96) << 20 : int64_t(8) << 20)) {
         store = Store::kStreamed;
         if ((reinterpret_cast<uintptr_t>(d_out) | static_cast<uintptr_t>(2 * nsel)) % kLineBytes) {
-            // Rows that begin inside a line.  Whole lines, unless the queries then take a round more; a gathered row
-            // has to be long for it (28672 x 8192, one in five kept, 0.22 of the columns (1802) 79 / 80 us in lines; 9216 x 9216
-            // 2027 28.1 / 28.9, 3225 equal).  A staged row is stored plainly instead (17274 x 13952, 0.22 79 / 82 streamed).
+            // Rows that begin inside a line.  Whole lines, where the queries then take no round more, or one more of
+            // at least four (28672 x 8192, four in five kept, 3055 columns 128 / 118, 17274 x 13952, half, 3069 82 / 77; but 36864 x
+            // 9216, one in five, 2027 91 / 102).  A gathered row has to be long for it (28672 x 8192, one in five kept,
+            // 1802 columns 79 / 80 us in lines; 9216 x 9216 2027 28.1 / 28.9, 3225 equal).
             const int64_t taken = (nsel + round * kBlock - 1) / (round * kBlock) * (round * kBlock);
             const bool room = nsel + int64_t(kLineBytes) / 2 <= taken;
-            if (staged)
-                store = room ? Store::kLines : Store::kPlain;
-            else if (room && nsel >= 3072)
-                store = Store::kLines;
+            if (staged ? room || nsel > 2048 : room && nsel >= 3072) store = Store::kLines;
         }
     }
     if (elem_bytes == 2)
