@@ -49,8 +49,9 @@ def test_gemv_forms_are_exact(shape):
 
 
 GEMM = [(1, 8, 1), (5, 9, 4), (70, 511, 3), (300, 1030, 2), (33, 4099, 4), (600, 5005, 3), (3200, 3001, 2),
-        (2, 24500, 2), (3, 16384, 3), (1, 49152, 1), (9000, 60, 4),   # x that just fits, and that takes two panels
-        (2, 24577, 2), (5, 7, 3), (32770, 3100, 5)]                   # left to the matrix cores
+        (2, 24500, 2), (3, 16384, 3), (1, 49152, 1),                  # x that just fits LDS
+        (9000, 60, 1), (4096, 40, 2), (9000, 500, 1),                 # narrow, up to the most rows that are taken
+        (9000, 60, 4), (2, 24577, 2), (5, 7, 3), (32770, 3100, 5)]    # left to the matrix cores
 
 
 @pytest.mark.parametrize("shape", GEMM, ids=str)

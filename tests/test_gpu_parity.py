@@ -774,6 +774,9 @@ def test_gemv_full_size(shape):
 # ---------------------------------------------------------------------------
 # fused small-batch product on the matrix cores: Y = X W^T, nb <= 16
 # ---------------------------------------------------------------------------
+VECTOR_RHS = 4  # up to so many right-hand sides may be taken by the vector form (endor_gemv_plan.h); more never are
+
+
 def _gemm_tolerance(w_bits, X16, cols):
     """fp16 products are exact in fp32.  A matrix instruction adds 32 of them to the fp32
     accumulator; its internal order is not documented, so each instruction is charged two
@@ -798,7 +801,7 @@ GEMM_SHAPES = [(1, 1), (3, 5), (7, 13), (16, 256), (17, 257), (33, 65), (5, 4095
 
 
 @pytest.mark.parametrize("shape", GEMM_SHAPES, ids=str)
-@pytest.mark.parametrize("nb", [1, 3, 16])
+@pytest.mark.parametrize("nb", [1, 3, VECTOR_RHS + 1, 16])
 def test_gemm_matches_oracle(shape, nb):
     rows, cols = shape
     _say(f"gemm case shape={shape} nb={nb}")
@@ -852,8 +855,9 @@ def test_gemm_rounds_parts_and_overfull_rows_are_exact(shape, keep, nb):
     assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.gemm_f16(rows, cols, c.bitmap, c.values, X16))
 
 
+@pytest.mark.parametrize("nb", [3, VECTOR_RHS + 1])
 @pytest.mark.parametrize("shape", [(32769, 100), (33000, 256), (33000, 257), (32800, 768), (32770, 3100)], ids=str)
-def test_gemm_more_row_blocks_than_workgroups_on_the_chip(shape):
+def test_gemm_more_row_blocks_than_workgroups_on_the_chip(shape, nb):
     """Tall matrices: a workgroup per row block of one, two, three rounds (odd numbers leave the loop in
     the middle), and blocks of 13 rounds, which workgroups share.  Small integers: the result is exact."""
     rows, cols = shape
@@ -862,17 +866,19 @@ def test_gemm_more_row_blocks_than_workgroups_on_the_chip(shape):
     wi = np.zeros((rows, cols), np.float16)
     at = g.random((rows, cols), dtype=np.float32) < 0.4
     wi[at] = g.integers(1, 9, int(at.sum()))
-    X16 = g.integers(-8, 9, (3, cols)).astype(np.float16)
+    X16 = g.integers(-8, 9, (nb, cols)).astype(np.float16)
     c = endor.compress(wi)
     got = _gpu_gemm(c, X16)
     assert np.array_equal(got, orc.gemm_f16(rows, cols, c.bitmap, c.values, X16))
 
 
-def test_gemm_subnormal_inputs_count_in_full():
+@pytest.mark.parametrize("nb", [4, VECTOR_RHS + 1, 16])
+def test_gemm_subnormal_inputs_count_in_full(nb):
+    """In the vector form, and in both widths of the form on the matrix cores (8 and 16 right-hand sides)."""
     rows, cols = 20, 700
     g = np.random.default_rng(5)
     wi = (g.integers(1, 1024, (rows, cols)) * (g.random((rows, cols)) < 0.5)).astype(np.uint16)   # fp16 subnormals
-    X16 = g.integers(-4, 5, (4, cols)).astype(np.float16)
+    X16 = g.integers(-4, 5, (nb, cols)).astype(np.float16)
     c = endor.compress(wi)
     got = _gpu_gemm(c, X16)
     ref = orc.gemm_f16(rows, cols, c.bitmap, c.values, X16)
@@ -904,12 +910,13 @@ def test_gemm_unaligned_x_and_padded_rows_of_x():
     assert np.all(np.abs(Y2.cpu().numpy().astype(np.float64) - ref) <= tol)
 
 
+@pytest.mark.parametrize("nb", [3, VECTOR_RHS + 1, 16])
 @pytest.mark.parametrize("voff", [1, 3, 6])
 @pytest.mark.parametrize("shape", [(50, 9001), (200, 4096), (33, 700)], ids=str)
-def test_products_with_values_at_2_byte_alignment(voff, shape):
-    """`values` starting 2, 6 or 12 bytes off a 16-byte boundary, with guard patterns around it:
-    the products read 20-byte windows from dword boundaries, and those at the two ends of the
-    array must take the guarded path."""
+def test_products_with_values_at_2_byte_alignment(voff, shape, nb):
+    """`values` starting 2, 6 or 12 bytes off a 16-byte boundary, with guard patterns around it: the vector
+    form reads windows from dword boundaries, the form on the matrix cores whole 16-byte units, and both
+    have a path of their own at the two ends of the array."""
     rows, cols = shape
     _say(f"products, values offset {voff} elements, shape {shape}")
     w = synth.pruned_fp16(rows, cols, 0.5, seed=21 + voff)
@@ -921,7 +928,7 @@ def test_products_with_values_at_2_byte_alignment(voff, shape):
     ws, ro = endor.build_offsets(m, row_offsets=True)
     x16 = np.random.default_rng(2).standard_normal(cols).astype(np.float16)
     y = endor.gemv_f16(m, ro, torch.from_numpy(x16.view(np.int16)).cuda().view(torch.float16))
-    X16 = np.random.default_rng(3).standard_normal((3, cols)).astype(np.float16)
+    X16 = np.random.default_rng(3).standard_normal((nb, cols)).astype(np.float16)
     Y = endor.gemm_f16(m, ws, torch.from_numpy(X16.view(np.int16)).cuda().view(torch.float16))
     torch.cuda.synchronize()
     ref = orc.gemv_f16(rows, cols, c.bitmap, c.values, x16)
@@ -930,13 +937,15 @@ def test_products_with_values_at_2_byte_alignment(voff, shape):
     assert np.all(np.abs(Y.cpu().numpy().astype(np.float64) - refm) <= _gemm_tolerance(w, X16, cols))
 
 
-def test_gemm_nonfinite_x_like_the_dense_product():
+@pytest.mark.parametrize("nb", [3, VECTOR_RHS + 1, 16])
+def test_gemm_nonfinite_x_like_the_dense_product(nb):
     rows, cols = 4, 100
     w = synth.pruned_fp16(rows, cols, 0.5, seed=9)
     w[0, 7] = 0            # a zero element meets x = inf: 0 * inf = nan, as with the dense matrix
     w[1, 7] = 0x3C00
-    X16 = np.random.default_rng(2).standard_normal((3, cols)).astype(np.float16)
+    X16 = np.random.default_rng(2).standard_normal((nb, cols)).astype(np.float16)
     X16[1, 7] = np.inf
+    X16[2, 50] = np.nan
     c = endor.compress(w)
     got = _gpu_gemm(c, X16)
     ref = orc.gemm_f16(rows, cols, c.bitmap, c.values, X16)
