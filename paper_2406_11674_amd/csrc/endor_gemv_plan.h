@@ -96,32 +96,38 @@ constexpr Plan plan_with(int64_t rows, int64_t cols, int rhs, int steps, int64_t
     return p;
 }
 
-// What a plan costs: about 40 per percent of a microsecond.  A segment takes 90, and 30 a step with another 2 for
-// each right-hand side, of a compute unit's vector units; 16 waves with the same number of segments use
-// them fully, 12 are 3 % slower.  A workgroup ends with its longest wave, which alone runs at 3/8 of a wave's
-// cost and waits 45 a segment for memory.  Longer segments are more code to fetch at the start (3 a step), parts
-// of rows have their starts counted (15 for every four items of a wave), and a further panel of x is a start of
-// its own (1000).
+// What a plan costs, in units of some 7 ns.  A segment takes 90, and 30 a step with another 2 for each right-hand
+// side, of a compute unit's vector units; 16 waves with the same number of segments use them fully, 12 are 3 %
+// slower.  A workgroup ends with its longest wave, which alone runs at 3/8 of a wave's cost and waits 52 a
+// segment for memory.  Longer segments are more code to fetch at the start (3 a step).  Parts of rows have their
+// starts found, four items of a wave at a time (10; one vector's from the bitmap, 120 for 16384 columns), and
+// a further panel of x is a start of its own (150).
 //
-// Fitted to every plan of 310 products (200 shapes, 1 x 600 to 36864 x 8192, 0.1 to 0.8 kept, one to four
-// right-hand sides): the plan it picks is 0.6 % slower than the best on average.  The rule before, by the work of
+// Fitted to every plan of 358 products (224 shapes, 1 x 600 to 36864 x 8192 and 1 x 2^22, 0.1 to 0.8 kept, one to
+// four right-hand sides): the plan it picks is 0.75 % slower than the best on average.  The rule before, by the work of
 // a row alone, kept rows whole from 12 per compute unit on and had no term for the longest wave: 2000 x 28672,
 // a tenth kept, 21 us where 17 is possible (8 steps, rows whole), 12000 x 2500 16.5 / 11.9 (6 steps), 3000 x
-// 3000 8.4 / 7.0, 4099 x 15000 with three 28 / 24 (2 parts: 17 rows are two to a wave of 16, 34 halves three).
+// 3000 8.4 / 7.0, 4099 x 15000 with three 28 / 24 (2 parts: 17 rows are two to a wave of 16, 34 halves three),
+// 3264 x 50000 97 / 43.
 constexpr int64_t cost_of(int64_t rows, int rhs, const Plan &p) {
     const int64_t waves = waves_of(p.steps), items = ceil_div(rows, p.grid) * p.parts, segs = p.part_segs * p.panels;
     const int64_t segment = 90 + (30 + 2 * rhs) * p.steps;
     const int64_t work = items * segs * segment / 16, all = waves < 16 ? work + work / 32 : work;
-    const int64_t longest = ceil_div(items, waves) * segs * (segment * 3 / 8 + 45);
+    const int64_t longest = ceil_div(items, waves) * segs * (segment * 3 / 8 + 52);
+    const int64_t start = 10 + (rhs == 1 ? 120 * p.parts * p.part_segs * seg_cols(p.steps) / 16384 : 0);
     return ceil_div(p.grid, kUnits) * (all > longest ? all : longest) + 3 * p.steps +
-           (p.parts > 1 ? 15 * ceil_div(items, 4 * waves) * p.panels : 0) + 1000 * (p.panels - 1);
+           (p.parts > 1 ? start * ceil_div(items, 4 * waves) * p.panels : 0) + 150 * (p.panels - 1);
 }
 
 constexpr Plan make_plan(int64_t rows, int64_t cols, int rhs) {
     if (cols < 8) return plan_with(rows, cols, 1, 2, 1);
     Plan best{};
     int64_t least = -1;
-    for (int steps = cols > 4096 ? 4 : 2; steps <= most_steps(rhs); steps += 2) {  // 2 steps are for short rows
+    // 2 steps are for short rows; three panels and more for the longest segments alone, which have the fewest of both (5 x
+    // 1000000 145 us, with 4 steps 155, 40 x 500000 76, with 6 steps 85)
+    const int longest = most_steps(rhs);
+    const bool panels = ceil_div(cols, seg_cols(longest)) > 2 * room_of(longest, rhs);
+    for (int steps = panels ? longest : cols > 4096 ? 4 : 2; steps <= longest; steps += 2) {
         // more than 32 rows per compute unit are never cut (9216 x 9216 in 3 parts 22, whole 19; a plan costs the
         // caller 0.1 to 0.3 us)
         const int64_t most = rows > 32 * kUnits ? 1 : waves_of(steps), segs = ceil_div(cols, seg_cols(steps));
