@@ -327,7 +327,8 @@ endor_status endor_gemv_f16(int64_t rows, int64_t cols,
  *            endor_decompress* call wrote it): it gives every wave its starting point
  *   d_scratch     endor_gemm_scratch_bytes(rows, cols, nb) bytes (256-byte aligned; may be NULL
  *            when that is 0): partial sums of the column ranges the work is split into; they
- *            are added in a fixed order, so results are reproducible from run to run
+ *            are added in a fixed order, so results are reproducible from run to run.  Its size is
+ *            asked for and checked whichever form a product takes; the form of endor_gemv_f16 leaves it alone
  * A 16-byte aligned d_x with ldx a multiple of 8 selects the fast load path.  rows < 2^31.
  */
 #define ENDOR_GEMM_MAX_BATCH 16

@@ -155,19 +155,13 @@ __device__ __forceinline__ u32x4 place_window(const WindowTables &T, uint32_t bi
 
 // The 16 bytes (8 values of 16 bits) at byte address p, which is 2-byte aligned only.  Read as
 // the 20 bytes from the dword boundary below p and shifted into place: a load whose address
-// is not a multiple of 4 costs the cache nearly twice the accesses (measured).  The first 16 of the 20 bytes are loaded, the last 4 come from
-// another lane's window (window_fifth).
+// is not a multiple of 4 costs the cache nearly twice the accesses (measured).  The first 16 of the 20 bytes
+// are loaded, the last 4 come from another lane's window (window_fifth).
 //
-// The caller issues the loads of all its windows before it uses the first, and guarantees that the
-// 20 bytes lie inside the array.  (With the load under a per-lane bounds test the compiler puts a full
-// wait behind every one of them, and a wave's eight windows became eight trips to memory, one after the
-// other; so the caller tests a whole segment at once, wave-uniformly, and sends the few segments at the
-// very ends of the array through window_guarded in a loop of their own.)
-
-// true when every window that starts in [first, last] can be read whole
-__device__ __forceinline__ bool windows_inside(uintptr_t first, uintptr_t last, uintptr_t vbeg, uintptr_t vend) {
-    return (first & ~uintptr_t(3)) >= vbeg && last + 20 <= vend;
-}
+// The caller issues the loads of all its windows before it uses the first, and sees to it that they lie inside the
+// array (endor_gemv_windows.h): a whole segment at a time, wave-uniformly.  (With the load under a per-lane bounds
+// test the compiler puts a full wait behind every one of them, and a wave's eight windows became eight trips to
+// memory, one after the other.)
 
 // The fifth dword, which holds the last value of a shifted window, matters to a byte with all 8 bits
 // set only, and then it is the first dword of the next byte's window.  So where lane l + 1 holds

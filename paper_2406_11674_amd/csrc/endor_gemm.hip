@@ -27,9 +27,11 @@
 // Measured on 28672 x 8192, half kept, 16 right-hand sides: 78 us (the form before, which read
 // every byte's 20-byte window from memory through the vector cache and handed the expanded bytes
 // on with ds_bpermute: 112 us).  Few right-hand sides go to the vector form where that is faster
-// (endor_gemv_plan.h).  What bounds it: LDS serves 65 clocks of every step's 95 (64 lanes at random
+// (endor_gemv_plan.h).  No unit bounds it by itself: LDS serves 65 clocks of every step's 95 (64 lanes at random
 // addresses cost 7 clocks per dword, six dwords per byte), the vector ALUs are busy 42 % of the
-// time, memory alone would take 45 us.  Measured alternatives: the windows as three aligned
+// time, memory alone would take 45 us; but without the LDS windows 69, with nothing multiplied 64,
+// without the values 70 to 76: a round's phases follow one another in step, as all waves of a workgroup
+// meet at every round's tile of X.  Measured alternatives: the windows as three aligned
 // 8-byte reads and selects (48 clocks of LDS, 25 % more vector instructions) 84 us; two rounds of
 // values in flight 84; three workgroups per compute unit 85; units of 64 aligned bytes 84.
 #include <hip/hip_runtime.h>

@@ -13,10 +13,10 @@
 //
 // What bounds it, at half density: reading.  8192 x 28672 takes 48 us (5.5 TB/s; the form before, a wave
 // per row and a barrier per segment, 59); a kernel that only reads as many bytes the same way 42, this
-// one without its loads of values 37.  Below a tenth kept the work per bitmap byte bounds it: 44 us, as
-// before.  What made the difference, in turn (8192 x 28672): no barrier and no start per row 58 us;
+// one without its loads of values 37.  At a tenth kept the work per bitmap byte bounds it: 40 us (the form
+// before 44).  What made the difference, in turn (8192 x 28672): no barrier and no start per row 58 us;
 // streamed loads of the windows 53 (plain reads of this size reach 5.9 TB/s, streamed ones 6.6);
-// 12 waves of up to 168 registers instead of 16 of 128 for the longest segments 51 (with 128 the
+// 12 waves of up to 168 registers instead of 16 of 128 for the longest segments 50 (with 128 the
 // compiler reads a segment's entries one after the other, 51 to 58 us from one build to the next).
 #include <hip/hip_runtime.h>
 
@@ -216,8 +216,8 @@ struct Segment {
 };
 
 // Entries to LDS, loads of the windows: streamed, although neighbouring windows overlap (the overlaps meet in
-// the vector cache; 58 us without, 53 with, on 8192 x 28672, half kept).  There is no branch around the loads (the compiler would wait
-// for them where it ends): a segment that is put together element by element when it is used reads a dummy.
+// the vector cache; 58 us without, 53 with, on 8192 x 28672, half kept).  There is no branch around the loads
+// (the compiler would wait for them where it ends): a segment that is put together element by element when it is used reads a dummy.
 template <int kSteps>
 __device__ __forceinline__ void segment_issue(Segment<kSteps> &S, uint32_t *entry, uint64_t word, uint64_t &next_value,
                                               uintptr_t vbeg, uintptr_t vend, uint32_t lane) {
@@ -267,7 +267,8 @@ __device__ __forceinline__ void segment_issue(Segment<kSteps> &S, uint32_t *entr
     }
     wave_lds_sync();
 #pragma unroll
-    for (int k = 0; k < kSteps; ++k) S.win[k] = __builtin_nontemporal_load(global_ptr<u32x4_a2>(base + ((entry[k * 64 + lane] >> 8) & mask)));
+    for (int k = 0; k < kSteps; ++k)
+        S.win[k] = __builtin_nontemporal_load(global_ptr<u32x4_a2>(base + ((entry[k * 64 + lane] >> 8) & mask)));
     S.end = *global_ptr<uint32_t>(end);
 }
 

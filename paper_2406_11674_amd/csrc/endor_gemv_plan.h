@@ -36,11 +36,13 @@ constexpr int64_t ceil_div(int64_t a, int64_t b) {
 constexpr int kMaxRhs = 4;
 
 // Whether the vector form is the faster one for nb right-hand sides of the small-batch product.  The form on the
-// matrix cores takes 16 rows of 256 columns in a round and starts slowly, this one takes a segment for every row however short
-// the row is: so for narrow matrices it depends on the rows, up to `most` of them per compute unit for the widths below.
+// matrix cores takes 16 rows of 256 columns in a round and starts slowly, this one takes a segment for every row
+// however short the row is: so for narrow matrices it depends on the rows, up to `most` of them per compute unit for
+// the widths below.
 // Lines that do not begin at a bitmap word cost the matrix form more: a quarter more rows then.
 // Measured, a tenth and 0.6 kept, us, the form on the matrix cores / this one:
-//   64 columns  2000 rows, one vector, 7.3 / 6.9, two 7.3 / 7.3, 4099, three, 7.3 / 8.5, 16384, one, 7.3 / 11.7, four 7.4 / 14.7
+//   64 columns  2000 rows, one vector, 7.3 / 6.9, two 7.3 / 7.3, 4099, three, 7.3 / 8.5, 16384, one, 7.3 / 11.7, four
+//               7.4 / 14.7
 //   512         9216, one 9 / 8.9, 12672, one, 8.9 / 11.0, four 9.2 / 13.7; 4099, three, 9.1 / 8.9
 //   1024        16384, one, 11.8 to 13.7 / 12.1, 28672 14.9 / 17.3, 131072 48 / 61; 9216, four, 11.8 to 13 / 10.9
 //   1300, 1536  20000, two, 22 to 25 / 19; 12672, three, 18 / 16, 28672, three, 22 to 26 / 29
@@ -52,7 +54,8 @@ constexpr bool takes(int64_t rows, int64_t cols, int nb) {
     if (cols < 8 || nb > kMaxRhs || cols * nb > 48 * 1024) return false;
     if (nb == 4 && rows * cols > int64_t(1) << 25) return false;
     constexpr int kAny = 1 << 24;
-    constexpr int most[6][kMaxRhs] = {{17, 8, 4, 0}, {36, 24, 18, 16}, {79, 44, 36, 36}, {144, 79, 60, 40}, {kAny, kAny, 79, 79}, {kAny, kAny, 79, 50}};
+    constexpr int most[6][kMaxRhs] = {{17, 8, 4, 0},     {36, 24, 18, 16},     {79, 44, 36, 36},
+                                      {144, 79, 60, 40}, {kAny, kAny, 79, 79}, {kAny, kAny, 79, 50}};
     if (cols > 3072) return true;
     const int width = cols <= 256 ? 0 : cols <= 512 ? 1 : cols <= 1024 ? 2 : cols <= 1536 ? 3 : cols <= 2048 ? 4 : 5;
     const int64_t limit = most[width][nb - 1];
@@ -90,7 +93,8 @@ constexpr Plan plan_with(int64_t rows, int64_t cols, int rhs, int steps, int64_t
     if (grid > rows) grid = rows;
     const int64_t least = ceil_div(rows * p.parts, max_items(steps, rhs) - waves_of(steps));  // a workgroup has up to one row more than the average
     // a compute unit holds one workgroup: more than there are units in whole generations of about equal length
-    // (131072 x 64 in 265 workgroups, 9 of them by themselves at the end, 90 us, in 512 51; 300000 x 100 in 605 135, in 768 109)
+    // (131072 x 64 in 265 workgroups, 9 of them by themselves at the end, 90 us, in 512 51; 300000 x 100 in 605 135, in
+    // 768 109)
     if (grid < least) grid = least > kUnits ? ceil_div(least, kUnits) * kUnits : least;
     p.grid = grid;
     return p;

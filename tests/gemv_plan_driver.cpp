@@ -45,21 +45,27 @@ int main() {
         // a product that is taken from the matrix cores has all of x in LDS
         if (!bad && rhs > 1 && takes(rows, cols, rhs) && p.panels != 1) bad = "x in panels";
         if (!bad && cols >= 8)
-            for (int st = 2; st <= most_steps(rhs) && !bad; st += 2) bad = check(rows, cols, rhs, p = plan_with(rows, cols, rhs, st, 1 + rnd() % 16));
+            for (int st = 2; st <= most_steps(rhs) && !bad; st += 2) {
+                p = plan_with(rows, cols, rhs, st, 1 + rnd() % 16);
+                bad = check(rows, cols, rhs, p);
+            }
         if (bad) {
-            std::printf("%s: %lld x %lld, %d right-hand sides: steps %d parts %lld x %lld, %lld panels, %lld workgroups\n", bad, (long long)rows,
-                        (long long)cols, rhs, p.steps, (long long)p.parts, (long long)p.part_segs, (long long)p.panels, (long long)p.grid);
+            std::printf("%s: %lld x %lld, %d right-hand sides: steps %d parts %lld x %lld, %lld panels, %lld workgroups\n", bad,
+                        (long long)rows, (long long)cols, rhs, p.steps, (long long)p.parts, (long long)p.part_segs,
+                        (long long)p.panels, (long long)p.grid);
             return 1;
         }
     }
-    // narrow products with few right-hand sides: those that the matrix cores do in half the time to four fifths, and others
-    const int64_t kNot[][3] = {{16384, 256, 1}, {16384, 64, 2}, {16384, 256, 4}, {9216, 64, 2}, {9216, 8, 4}, {4099, 64, 4}, {131072, 1024, 1}, {16384, 1024, 4}, {131072, 256, 1}};
+    // products with few right-hand sides: narrow ones that the matrix cores do in half to four fifths of the time, and others
+    const int64_t kNot[][3] = {{16384, 256, 1}, {16384, 64, 2},    {16384, 256, 4}, {9216, 64, 2},   {9216, 8, 4},
+                               {4099, 64, 4},   {131072, 1024, 1}, {16384, 1024, 4}, {131072, 256, 1}};
     for (const auto &s : kNot)
         if (takes(s[0], s[1], static_cast<int>(s[2]))) {
             std::printf("%lld x %lld with %lld taken from the matrix cores\n", (long long)s[0], (long long)s[1], (long long)s[2]);
             return 1;
         }
-    const int64_t kYes[][3] = {{1, 600, 4}, {2000, 64, 2}, {4099, 5005, 3}, {12000, 600, 1}, {4096, 4096, 4}, {28672, 8192, 3}, {4400, 24570, 2}};
+    const int64_t kYes[][3] = {{1, 600, 4},     {2000, 64, 2},    {4099, 5005, 3},  {12000, 600, 1},
+                               {4096, 4096, 4}, {28672, 8192, 3}, {4400, 24570, 2}};
     for (const auto &s : kYes)
         if (!takes(s[0], s[1], static_cast<int>(s[2]))) {
             std::printf("%lld x %lld with %lld left to the matrix cores\n", (long long)s[0], (long long)s[1], (long long)s[2]);

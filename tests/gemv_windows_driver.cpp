@@ -98,7 +98,9 @@ int main() {
             default: break;
         }
         bad = segment(vbeg, nnz, first, bytes);
-        if (bad) std::printf("%s: vbeg %llx nnz %llu first %llu cnt %u\n", bad, (unsigned long long)vbeg, (unsigned long long)nnz, (unsigned long long)first, cnt);
+        if (bad)
+            std::printf("%s: vbeg %llx nnz %llu first %llu cnt %u\n", bad, (unsigned long long)vbeg, (unsigned long long)nnz,
+                        (unsigned long long)first, cnt);
     }
     if (bad) return 1;
     std::printf("ok %ld windows, %ld segments at an end, %ld element by element\n", windows, edges, elements);
