@@ -1815,10 +1815,11 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
             // Rows that begin inside a line.  Whole lines, where the queries then take no round more, or one more of
             // at least four (28672 x 8192, four in five kept, 3055 columns 128 / 118, 17274 x 13952, half, 3069 82 / 77; but 36864 x
             // 9216, one in five, 2027 91 / 102).  A gathered row has to be long for it (28672 x 8192, one in five kept,
-            // 1802 columns 79 / 80 us in lines; 9216 x 9216 2027 28.1 / 28.9, 3225 equal).
+            // 1802 columns 79 / 80 us in lines; 9216 x 9216 2027 28.1 / 28.9, 3225 equal) and its output large (3200 x 8704,
+            // 0.47 (26 MB) 19.1 / 19.8, 1000 x 20000 to 30000 15 to 19, 2 to 3 % slower; 3000 x 36864, 0.22 (49 MB) 57 / 54).
             const int64_t taken = (nsel + round * kBlock - 1) / (round * kBlock) * (round * kBlock);
             const bool room = nsel + int64_t(kLineBytes) / 2 <= taken;
-            if (staged ? room || nsel > 2048 : room && nsel >= 3072) store = Store::kLines;
+            if (staged ? room || nsel > 2048 : room && nsel >= 3072 && out_bytes >= int64_t(32) << 20) store = Store::kLines;
         }
     }
     if (elem_bytes == 2)
