@@ -1787,15 +1787,15 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     // 17 / 13; fp16, four in five kept (26 KB a row), a fifth 9.7 / 11.2.
     const bool at_once = rows <= 2048 && static_cast<size_t>(rows) * (lds + stage) <= 256 * kLdsPerUnit && nsel >= cols / 5 &&
                          nnz * elem_bytes <= rows * 20480;
-    // A shorter row only where so many of its values are asked that the gather's access for each outweighs a
-    // workgroup's wait for its row, and fewer where `values` is larger than the memory-side cache keeps.  Hits
-    // of a row, gather / staged: 18432 x 4608, half kept, four tenths (920) 64 / 47 us, 36864 x 6000, 8-bit,
-    // four tenths (1200) 141 / 107, 28672 x 8192, 8-bit, three tenths (1230) 110 / 80, 36864 x 9216 with 136 MB of
-    // values, three tenths (550) 170 / 119; but 36864 x 6000, one in five kept, four tenths (480) 109 / 119, 9216 x 9216, one
-    // in five kept, half (920, 8.5 million in all) 48.7 / 49.6, 14000 x 9216, 8-bit, 0.15 (690, 9.7 million) 29 / 34, 20000 x
-    // 1500, 0.8 kept, half (600, 12 million) 33 / 37, 28672 x 8192, 8-bit, 0.16 (655) 63 / 66.
+    // A shorter row only where every thread of its workgroup has six queries or more, and there are 8 million hits in
+    // all: otherwise the wait for the row outweighs the gather's accesses.  Fewer where `values` is larger than the
+    // memory-side cache keeps.  By columns asked of a row, gather / staged: 17233 x 2473, 0.66 kept, 1162 35.4 / 44.3 us,
+    // 20000 x 1500, 0.8 kept, 750 33 / 37, 9216 x 9216, 8-bit, 1474 (6.8 million) 22 / 25; 18432 x 4608, half kept, 1843 64 /
+    // 47, 18923 x 15575, 8-bit, 0.14 kept, 4828 133 / 87, 28672 x 8192, 8-bit, 2457 110 / 80; 95868 x 3763, 8-bit (238 MB), 940
+    // 194 / 168.  Over 285 calls (rows of 250 bytes to 6 KB) the choice is 0.6 % slower than the better form on average; by
+    // hits of a row alone, 600 or 300, it was 1.9 %.
     const double hits = static_cast<double>(nsel) * static_cast<double>(nnz) / static_cast<double>(cols);
-    const bool most_asked = hits >= 12e6 && hits >= rows * (nnz * elem_bytes >= (int64_t(128) << 20) ? 300.0 : 800.0);
+    const bool most_asked = hits >= 8e6 && (nsel >= 6 * kBlock || (nnz * elem_bytes >= (int64_t(128) << 20) && hits >= rows * 300.0));
     const bool long_rows = stage >= kMinColsStage && (much || at_once);
     const bool staged = rows > 1 && rows_fit && (long_rows || (stage < kMinColsStage && most_asked));
     C.stage_units = static_cast<uint32_t>(stage / 16);
