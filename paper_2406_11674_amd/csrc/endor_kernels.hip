@@ -938,6 +938,15 @@ template <int E>
 __device__ __forceinline__ uint32_t nonzero_bits(u32x4 d) {
     const uint32_t dd[4] = {d.x, d.y, d.z, d.w};
     uint32_t bits = 0;
+    if constexpr (E == 2) {  // both halves of a dword at once; a compare and a select each where the compiler sees the minimum
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t ones;
+            asm("v_pk_min_u16 %0, %1, %2" : "=v"(ones) : "v"(dd[i]), "s"(0x00010001u));
+            bits |= ones << (2 * i);
+        }
+        return (bits | bits >> 15) & 0xffu;
+    }
 #pragma unroll
     for (int j = 0; j < Shape<E>::kLaneElems; ++j) {
         const uint32_t v = (dd[(E * j) >> 2] >> (8 * ((E * j) & 3))) & ((E == 2) ? 0xffffu : 0xffu);
@@ -1133,6 +1142,12 @@ __global__ __launch_bounds__(64) void endor_pack_kernel(CompressParams C) {
         }
     }
 }
+
+}  // namespace
+
+#include "endor_compress_pass.h"
+
+namespace {
 
 // total number of 1 bits of a matrix whose table has been built: one wave
 __global__ __launch_bounds__(64) void endor_total_kernel(MatParams M, int64_t *__restrict__ nnz_out) {
@@ -1624,6 +1639,16 @@ extern "C" endor_status endor_decompress_rows_u8(int64_t rows, int64_t cols, con
 
 namespace {
 
+// From how many elements on one pass over the dense matrix is faster than two, whose second finds a small matrix
+// in the memory-side cache and which have nothing to wait for at the start.  Us a call, two passes / one, a tenth,
+// half and nine tenths kept: fp16 8192 x 4096 55 / 56, 58.4 / 57.8, 62.5 / 57.7, 8192 x 8192 78 / 71, 85 / 77, 93 / 86;
+// 8-bit 16384 x 8192 92 / 93, 99 / 94, 102 / 96, 36864 x 9216 with a tenth 186 / 173.
+template <int E>
+constexpr int64_t kPassMinElems = int64_t(E == 2 ? 40 : 160) << 20;
+static_assert(kPassMinElems<2> / kTileElems >= kPackGroups * Blocks<2>::kTiles && kPassMinElems<1> / kTileElems >= kPackGroups * Blocks<1>::kTiles,
+              "a block for every workgroup");
+static_assert(kPassMinElems<2> >> 20 >= kPassMinChunks, "a party for every slice");
+
 template <int E>
 endor_status run_compress_device(int64_t rows, int64_t cols, const void *d_dense, uint8_t *d_bitmap,
                                  void *d_values, int64_t values_capacity, void *d_workspace,
@@ -1645,6 +1670,7 @@ endor_status run_compress_device(int64_t rows, int64_t cols, const void *d_dense
         if (workspace_bytes < workspace_bytes_n(n)) return ENDOR_ERR_BUFFER_TOO_SMALL;
     }
     if (d_row_offsets && !row_offsets_ok(rows)) return ENDOR_ERR_UNSUPPORTED;
+    // one kernel between two small ones, or:
     // mask kernel: the bitmap, and each tile's count in its slot of the table; scan kernel: the table;
     // pack kernel: the values, the row offsets and the total
     CompressParams C{};
@@ -1670,6 +1696,16 @@ endor_status run_compress_device(int64_t rows, int64_t cols, const void *d_dense
     C.row_offsets = d_row_offsets;
     C.rows = rows;
     C.cols = cols;
+    if (aligned_in && n >= kPassMinElems<E>) {  // 16-byte loads; others go piece by piece in two passes
+        const uint32_t nblocks = (ntiles + Blocks<E>::kTiles - 1) / Blocks<E>::kTiles;
+        hipLaunchKernelGGL(endor_clear_blocks_kernel, dim3(C.table.nchunks), dim3(64), 0, s, C.table);
+        if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
+        hipLaunchKernelGGL(endor_compress_kernel<E>, dim3(kPackGroups), dim3(Blocks<E>::kThreads), 0, s, C, nblocks);
+        if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
+        hipLaunchKernelGGL(endor_finish_table_kernel, dim3(C.table.nchunks), dim3(kTilesPerChunk), 0, s, C.table);
+        if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
+        return ENDOR_OK;
+    }
     const dim3 grid(ntiles);
     if (aligned_in)
         hipLaunchKernelGGL((endor_mask_kernel<E, true>), grid, dim3(64), 0, s, C);
