@@ -47,6 +47,7 @@
 #include "endor.h"
 #include "endor_device.h"
 #include "endor_layout.h"
+#include "endor_value_units.h"
 
 namespace {
 
@@ -242,20 +243,24 @@ __device__ __forceinline__ uint32_t nibble_selector(uint32_t n) {
     return sel;
 }
 
-// 16 bytes of `values` at byte address p, with bytes outside [vbeg, vend) read as 0
+// 16 bytes of `values`, which are not empty, at byte address p, with elements outside [vbeg, vend) read as 0.  For
+// the units over an end of the array, element by element: all loads unconditional, from a place that exists, so
+// that they are one trip to memory (under a test each is waited for, 8 or 16 trips one after the other, 4 to 9 us
+// at the end of every call whose last value does not end a unit).
 template <int E>
 __device__ __forceinline__ u32x4 load_values16(uintptr_t p, uintptr_t vbeg, uintptr_t vend) {
-    // values are read once: streamed past the caches (the bitmap, read by both kernels, stays cacheable)
-    if (p >= vbeg && p + 16 <= vend) return __builtin_nontemporal_load(global_ptr<u32x4>(p));
-    uint32_t d[4] = {0u, 0u, 0u, 0u};
+    uint32_t v[16 / E];
 #pragma unroll
     for (int j = 0; j < 16 / E; ++j) {
         const uintptr_t q = p + E * j;
-        uint32_t v = 0;
-        if (q >= vbeg && q + E <= vend)
-            v = (E == 2) ? uint32_t(*global_ptr<uint16_t>(q)) : uint32_t(*global_ptr<uint8_t>(q));
-        d[(E * j) >> 2] |= v << (8 * ((E * j) & 3));
+        const bool in = q >= vbeg && q + E <= vend;
+        const uintptr_t at = in ? q : vbeg;
+        v[j] = (E == 2) ? uint32_t(*global_ptr<uint16_t>(at)) : uint32_t(*global_ptr<uint8_t>(at));
+        v[j] = in ? v[j] : 0u;
     }
+    uint32_t d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 16 / E; ++j) d[(E * j) >> 2] |= v[j] << (8 * ((E * j) & 3));
     u32x4 r;
     r.x = d[0];
     r.y = d[1];
@@ -263,6 +268,52 @@ __device__ __forceinline__ u32x4 load_values16(uintptr_t p, uintptr_t vbeg, uint
     r.w = d[3];
     return r;
 }
+
+// A tile's slice of `values`, as 16-byte units from the boundary a16 at or below its first value, goes to the staging
+// area: units that lie inside the array as a whole straight from memory (global_load_lds_dwordx4: lane l of an
+// instruction deposits its 16 bytes at the LDS address in M0 plus 16*l), no registers in between, streamed past the
+// caches as values are read once (the bitmap, read by both kernels, stays cacheable); the units over an end of the
+// array, usually one, element by element.  ask() puts the loads out, finish() is what remains to be done when the
+// bitmap has been worked on, with a wait.
+// Only the unit itself goes that way: with all units of the array's first and last tiles put together from their
+// elements, trip after trip, 2048 x 2048, four in five kept, took 8.9 us (now 5.5), 4096 x 4096 15.0 (13.5).
+template <int E, int kRounds>
+struct ValueSlice {
+    uintptr_t a16, vbeg, vend;
+    uint32_t units;
+    bool inside;  // wave-uniform: all of them lie inside `values`
+
+    __device__ __forceinline__ ValueSlice(uintptr_t a16_, uint32_t units_, uintptr_t vbeg_, uintptr_t vend_)
+        : a16(a16_), vbeg(vbeg_), vend(vend_), units(units_), inside(endor_value_units::all_inside(a16_, units_, vbeg_, vend_)) {}
+    // those that do: [first, last)
+    __device__ __forceinline__ uint32_t first() const { return endor_value_units::first_whole(a16, units, vbeg); }
+    __device__ __forceinline__ uint32_t last() const { return endor_value_units::end_of_whole(a16, units, vbeg, vend); }
+    __device__ __forceinline__ void ask(u32x4 *stage, uint32_t lane) const {
+        if (inside) {
+#pragma unroll
+            for (int q = 0; q < kRounds; ++q) {
+                const uint32_t ch = q * 64 + lane;
+                if (ch < units) load_to_lds16(reinterpret_cast<const u32x4 *>(a16) + ch, &stage[q * 64]);
+            }
+        } else {
+            const uint32_t f = first(), l = last();
+            for (int q = 0; q < kRounds; ++q) {
+                const uint32_t ch = q * 64 + lane;
+                if (ch >= f && ch < l) load_to_lds16(reinterpret_cast<const u32x4 *>(a16) + ch, &stage[q * 64]);
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(u32x4 *stage, uint32_t lane) const {
+        if (!inside) {
+            const uint32_t f = first(), whole = last() - f;
+            for (uint32_t i = lane; i < units - whole; i += 64) {  // (more than two behind a table that is not the bitmap's)
+                const uint32_t ch = i < f ? i : i + whole;
+                stage[ch] = vbeg < vend ? load_values16<E>(a16 + 16 * uintptr_t(ch), vbeg, vend) : u32x4{0u, 0u, 0u, 0u};
+            }
+        }
+        wait_loads_to_lds();
+    }
+};
 
 // 0xffff in the halves whose bit is set: bits 0,1 of `b` -> low, high half
 __device__ __forceinline__ uint32_t half_mask(uint32_t b) {
@@ -389,19 +440,8 @@ __device__ __forceinline__ void expand_tile(WaveScratch<E, kCap> &S, uint32_t la
     if (E == 1 && lane < 16) S.nibble_sel[lane] = nibble_selector(lane);
     cnt = cnt > kCap ? kCap : cnt;  // a stale or foreign table must not overrun the staging area
     const uint32_t nch = cnt ? (((shift + cnt) * E + 15) >> 4) : 0;  // < kStageChunks
-    // the whole slice lies inside `values`: all tiles but the first and last of an array that
-    // does not begin and end on 16-byte boundaries
-    const bool direct = nch != 0 && a16 >= vbeg && a16 + 16 * uintptr_t(nch) <= vend;
-    if (direct) {
-        // Straight from memory into the staging area (global_load_lds_dwordx4: lane l of an
-        // instruction deposits its 16 bytes at the LDS address in M0 plus 16*l), no registers
-        // in between.  Values are read once: streamed past the caches.
-#pragma unroll
-        for (int q = 0; q < WS::kStageRounds; ++q) {
-            const uint32_t ch = q * 64 + lane;
-            if (ch < nch) load_to_lds16(reinterpret_cast<const u32x4 *>(a16) + ch, &S.stage[q * 64]);
-        }
-    }
+    const ValueSlice<E, WS::kStageRounds> slice(a16, nch, vbeg, vend);
+    slice.ask(S.stage, lane);
     const uint32_t pc = __popcll(word);
     const uint32_t incl = wave_inclusive_scan(pc);
     const uint32_t excl = incl - pc;
@@ -410,7 +450,7 @@ __device__ __forceinline__ void expand_tile(WaveScratch<E, kCap> &S, uint32_t la
         // table): stage and expand the tile one step at a time; a step has at most 1024 values
         const uint32_t ones = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
         if (ones > kCap) {  // wave-uniform
-            if (direct) wait_loads_to_lds();  // what is on its way into the staging area lands before it is reused
+            wait_loads_to_lds();  // what is on its way into the staging area lands before it is reused
             S.words[lane] = word;
 #pragma unroll Sink::kStepUnroll
             for (int k = 0; k < Sh::kSteps; ++k) {
@@ -425,8 +465,9 @@ __device__ __forceinline__ void expand_tile(WaveScratch<E, kCap> &S, uint32_t la
                 const uint32_t n = last - first;  // <= 1024 <= kCap
                 const uint32_t nc = n ? (((sh + n) * E + 15) >> 4) : 0;
                 S.start[lane] = excl - first + sh;  // meaningful for the step's words only
-                for (uint32_t ch = lane; ch < nc; ch += 64)
-                    S.stage[ch] = load_values16<E>(b16 + 16 * uintptr_t(ch), vbeg, vend);
+                const ValueSlice<E, WS::kStageRounds> of_step(b16, nc, vbeg, vend);
+                of_step.ask(S.stage, lane);
+                of_step.finish(S.stage, lane);
                 wave_lds_sync();
                 expand_step<E, kCap>(S, k, lane, sink);
                 wave_lds_sync();
@@ -436,13 +477,7 @@ __device__ __forceinline__ void expand_tile(WaveScratch<E, kCap> &S, uint32_t la
     }
     S.words[lane] = word;
     S.start[lane] = excl + shift;
-    if (direct) {
-        wait_loads_to_lds();
-    } else {
-#pragma unroll 1
-        for (uint32_t ch = lane; ch < nch; ch += 64)
-            S.stage[ch] = load_values16<E>(a16 + 16 * uintptr_t(ch), vbeg, vend);
-    }
+    slice.finish(S.stage, lane);
     wave_lds_sync();
 #pragma unroll
     for (int k = 0; k < Sh::kSteps; ++k) expand_step<E, kCap>(S, k, lane, sink);
@@ -569,25 +604,14 @@ __global__ __launch_bounds__(64 * kSmallWaves) void endor_decompress_small_kerne
     const uintptr_t vbeg = reinterpret_cast<uintptr_t>(M.values), vend = vbeg + E * static_cast<uintptr_t>(M.nnz);
     const uintptr_t vaddr = vbeg + E * (uintptr_t(base) + off), a16 = vaddr & ~uintptr_t(15);
     const uint32_t shift = static_cast<uint32_t>(vaddr - a16) / E, nch = cnt ? ((shift + cnt) * E + 15) >> 4 : 0;
-    const bool direct = nch != 0 && a16 >= vbeg && a16 + 16 * uintptr_t(nch) <= vend;
-    if (direct) {
-#pragma unroll
-        for (int q = 0; q < WS::kStageRounds; ++q) {
-            const uint32_t ch = q * 64 + lane;
-            if (ch < nch) load_to_lds16(reinterpret_cast<const u32x4 *>(a16) + ch, &S.stage[q * 64]);
-        }
-    }
+    const ValueSlice<E, WS::kStageRounds> slice(a16, nch, vbeg, vend);
+    slice.ask(S.stage, lane);
     if (E == 1 && lane < 16) S.nibble_sel[lane] = nibble_selector(lane);
     if (lane < kPartWords) {
         S.words[lane] = word;
         S.start[lane] = incl - pc + shift;
     }
-    if (direct) {
-        wait_loads_to_lds();
-    } else {
-#pragma unroll 1
-        for (uint32_t ch = lane; ch < nch; ch += 64) S.stage[ch] = load_values16<E>(a16 + 16 * uintptr_t(ch), vbeg, vend);
-    }
+    slice.finish(S.stage, lane);
     wave_lds_sync();
     StoreSink<E, kAlignedOut, false, kPartElems> sink;
     sink.out = reinterpret_cast<uint8_t *>(M.dense) + size_t(e0) * E;
@@ -899,14 +923,17 @@ template <int E, bool kAlignedIn>
 __device__ __forceinline__ u32x4 load_dense16(const uint8_t *tile_in, uint32_t le, uint32_t nvalid) {
     if (kAlignedIn && le + Shape<E>::kLaneElems <= nvalid)
         return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(tile_in + size_t(le) * E));
-    uint32_t d[4] = {0u, 0u, 0u, 0u};
+    // unconditional loads, from an element that exists, sorted out afterwards: one trip, not one for every element
+    uint32_t v[Shape<E>::kLaneElems];
 #pragma unroll
     for (int j = 0; j < Shape<E>::kLaneElems; ++j) {
-        uint32_t v = 0;
-        if (le + j < nvalid)
-            v = (E == 2) ? uint32_t(reinterpret_cast<const uint16_t *>(tile_in)[le + j]) : uint32_t(tile_in[le + j]);
-        d[(E * j) >> 2] |= v << (8 * ((E * j) & 3));
+        const uint32_t at = le + j < nvalid ? le + j : 0u;
+        v[j] = (E == 2) ? uint32_t(reinterpret_cast<const uint16_t *>(tile_in)[at]) : uint32_t(tile_in[at]);
+        v[j] = le + j < nvalid ? v[j] : 0u;
     }
+    uint32_t d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < Shape<E>::kLaneElems; ++j) d[(E * j) >> 2] |= v[j] << (8 * ((E * j) & 3));
     u32x4 r;
     r.x = d[0];
     r.y = d[1];
