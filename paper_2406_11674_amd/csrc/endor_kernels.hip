@@ -289,7 +289,7 @@ struct ValueSlice {
     __device__ __forceinline__ uint32_t first() const { return endor_value_units::first_whole(a16, units, vbeg); }
     __device__ __forceinline__ uint32_t last() const { return endor_value_units::end_of_whole(a16, units, vbeg, vend); }
     __device__ __forceinline__ void ask(u32x4 *stage, uint32_t lane) const {
-        if (inside) {
+        if (__builtin_expect(inside, 1)) {
 #pragma unroll
             for (int q = 0; q < kRounds; ++q) {
                 const uint32_t ch = q * 64 + lane;
@@ -304,7 +304,7 @@ struct ValueSlice {
         }
     }
     __device__ __forceinline__ void finish(u32x4 *stage, uint32_t lane) const {
-        if (!inside) {
+        if (__builtin_expect(!inside, 0)) {
             const uint32_t f = first(), whole = last() - f;
             for (uint32_t i = lane; i < units - whole; i += 64) {  // (more than two behind a table that is not the bitmap's)
                 const uint32_t ch = i < f ? i : i + whole;
@@ -1173,6 +1173,7 @@ __global__ __launch_bounds__(64) void endor_pack_kernel(CompressParams C) {
 }  // namespace
 
 #include "endor_compress_pass.h"
+#include "endor_cols_stream.h"
 
 namespace {
 
@@ -1803,6 +1804,46 @@ void launch_cols(const ColsParams &C, Store store, int round, dim3 grid, size_t 
     launch_cols<E, kStaged, Store::kPlain>(C, round, grid, lds, s);
 }
 
+template <int E, int kThreads>
+void launch_cols_stream(const ColsParams &C, hipStream_t s) {
+    const dim3 grid(static_cast<unsigned>(C.rows < StreamShape<kThreads>::kGroups ? C.rows : StreamShape<kThreads>::kGroups)), block(kThreads);
+    const int64_t queries = (C.nsel + kThreads - 1) / kThreads;
+    if (queries <= 2)
+        hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 2>), grid, block, 0, s, C);
+    else if (queries <= 4)
+        hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 4>), grid, block, 0, s, C);
+    else if (queries <= 6)
+        hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 6>), grid, block, 0, s, C);
+    else if (queries <= 8)
+        hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 8>), grid, block, 0, s, C);
+    else
+        hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, kMaxStreamQueries>), grid, block, 0, s, C);
+}
+
+// Threads of endor_stream_cols_kernel's workgroups, 0 where a workgroup per row is the faster form.  A step of that
+// kernel takes 0.9 us or more however little there is in it, and its start two of them, so it wants many rows, and in
+// each of them many bytes or queries.  Over 380 calls (512 to 36864 rows, 2048 to 32768 columns, a twentieth to half of
+// them, a tenth to nine tenths kept, both widths) it is taken for 114, of them 1.14 times as fast on average and 0.97
+// to 1.35 times each; a workgroup per row / staying, us: 8192 x 28672 half kept, a tenth 63 / 55, a fifth 91 / 72;
+// 36864 x 9216, 8-bit, three tenths 115 / 88; 25776 x 4887, 8-bit, half 76 / 58; but 3008 x 9920 (few rows) 9 / 14, 16384
+// x 16384, a tenth (16 KB and three queries a thread) 65 / 70, 28672 x 8192, a tenth 58 / 61.  Not where few columns are asked
+// (less than a sixteenth: the gather reads less), nor for 16-bit outputs of 96 MB and more of shorter rows, which
+// the other kernel streams past the cache (31040 x 9920, 0.3 kept 115 / 122), nor for sparse 16-bit rows, of which the
+// cache serves the gather (7232 x 8896, a tenth kept, 23 / 26).
+int cols_stream_threads(int elem_bytes, int64_t rows, int64_t cols, int64_t nnz, int64_t nsel) {
+    const int64_t row_bytes = nnz / rows * elem_bytes, fits = row_bytes + 512;  // three standard deviations of the longest rows
+    if (rows < 5500 || nsel < cols / 16) return 0;
+    const bool narrow = fits <= 16 * int64_t(StreamShape<256>::kUnits) && cols <= StreamShape<256>::kMaxCols && nsel <= 256 * kMaxStreamQueries;
+    const bool wide = fits <= 16 * int64_t(StreamShape<512>::kUnits) && cols <= StreamShape<512>::kMaxCols && nsel <= 512 * kMaxStreamQueries;
+    if (!narrow && !wide) return 0;
+    const int threads = narrow ? 256 : 512;
+    if (elem_bytes == 2 && row_bytes < 16000 && rows * nsel * elem_bytes >= int64_t(96) << 20) return 0;
+    const int64_t half_queries = 2 * nsel / threads;
+    const bool many = half_queries >= 11 || (half_queries >= 9 && rows >= 9000 && row_bytes >= 2500);
+    const bool sparse = elem_bytes == 2 && nnz < rows * cols / 5;
+    return row_bytes >= 12000 || (many && !sparse) ? threads : 0;
+}
+
 endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t *d_bitmap, const void *d_values,
                       int64_t nnz, const int64_t *d_row_offsets, const int64_t *d_sel, int64_t nsel, void *d_out,
                       void *stream) {
@@ -1827,6 +1868,16 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     C.cols = cols;
     C.nnz = nnz;
     C.nsel = nsel;
+    C.stage_units = 0;
+    const int threads = cols_stream_threads(elem_bytes, rows, cols, nnz, nsel);
+    if (threads != 0) {
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        if (threads == 512)
+            elem_bytes == 2 ? launch_cols_stream<2, 512>(C, s) : launch_cols_stream<1, 512>(C, s);
+        else
+            elem_bytes == 2 ? launch_cols_stream<2, 256>(C, s) : launch_cols_stream<1, 256>(C, s);
+        return hipGetLastError() == hipSuccess ? ENDOR_OK : ENDOR_ERR_HIP;
+    }
     const size_t lds = static_cast<size_t>((cols + 63) / 64) * 4 * sizeof(uint32_t);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid(static_cast<unsigned>(rows));
