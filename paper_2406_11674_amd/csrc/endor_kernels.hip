@@ -116,11 +116,35 @@ __device__ __forceinline__ uint64_t load_word_guarded(const uint64_t *bitmap, in
     return 0;
 }
 
-__device__ __forceinline__ int find_matrix(const BatchParams &P, uint32_t chunk) {
-    int mi = 0;
+// The chunk's number inside its matrix, in a way that has all of the descriptor in registers by then: otherwise the
+// compiler loads each field before its first use, and a wave waits for the scalar cache four times before it knows where
+// its values are.
+__device__ __forceinline__ uint32_t chunk_in(const MatParams &M, uint32_t chunk) {
+    uint32_t c;
+    asm("s_sub_u32 %0, %1, %2"
+        : "=s"(c)
+        : "s"(chunk), "s"(M.chunk_begin), "s"(M.bitmap), "s"(M.values), "s"(M.dense), "s"(M.chunk_total), "s"(M.tile_off), "s"(M.n), "s"(M.nnz)
+        : "scc");
+    return c;
+}
+
+// The matrix that a chunk belongs to, and the chunk's number in it.  The first one's descriptor comes with the number that
+// says whether it is the one; the others are counted off the vector unit, two scalar instructions a matrix.  (The
+// compiler's own form was a vector addition, or a trip through a vector register, for each of the sixteen, 100 instructions in a row
+// at the start of every wave.  Expanding 5003 x 3171, 0.7 kept, 12.2 us, now 11.3; the matrices of a Llama2-70B layer in one
+// batch 450.4, now 448.9; 9216 x 36864, 8-bit, 93.4, now 92.6.)
+__device__ __forceinline__ MatParams matrix_of(const BatchParams &P, uint32_t chunk, uint32_t &c) {
+    MatParams M = P.m[0];
+    c = chunk_in(M, chunk);
+    if (chunk >= P.first_chunk[1]) {
+        uint32_t mi = 1;
 #pragma unroll
-    for (int i = 1; i < ENDOR_MAX_BATCH; ++i) mi += (chunk >= P.first_chunk[i]) ? 1 : 0;  // ascending, so a count
-    return mi;
+        for (int i = 2; i < ENDOR_MAX_BATCH; ++i)  // ascending, so a count
+            asm("s_cmp_ge_u32 %1, %2\n\ts_addc_u32 %0, %0, 0" : "+s"(mi) : "s"(chunk), "s"(P.first_chunk[i]) : "scc");
+        M = P.m[mi];
+        c = chunk_in(M, chunk);
+    }
+    return M;
 }
 
 // ---------------------------------------------------------------- kernel 1: tile offsets
@@ -138,8 +162,8 @@ __global__ __launch_bounds__(kCountBlock) void endor_tile_offsets_kernel(BatchPa
     __shared__ uint32_t s_wave[kTilesPerChunk / 64];
 
     const uint32_t gc = blockIdx.x;
-    const MatParams &M = P.m[find_matrix(P, gc)];
-    const uint32_t c = gc - M.chunk_begin;
+    uint32_t c;
+    const MatParams M = matrix_of(P, gc, c);
     const uint64_t *bitmap = M.bitmap;
     const int64_t full_words = M.n >> 6;
     const uint32_t tail_bits = static_cast<uint32_t>(M.n & 63);
@@ -297,6 +321,7 @@ struct ValueSlice {
             }
         } else {
             const uint32_t f = first(), l = last();
+#pragma unroll 1
             for (int q = 0; q < kRounds; ++q) {
                 const uint32_t ch = q * 64 + lane;
                 if (ch >= f && ch < l) load_to_lds16(reinterpret_cast<const u32x4 *>(a16) + ch, &stage[q * 64]);
@@ -306,6 +331,7 @@ struct ValueSlice {
     __device__ __forceinline__ void finish(u32x4 *stage, uint32_t lane) const {
         if (__builtin_expect(!inside, 0)) {
             const uint32_t f = first(), whole = last() - f;
+#pragma unroll 1
             for (uint32_t i = lane; i < units - whole; i += 64) {  // (more than two behind a table that is not the bitmap's)
                 const uint32_t ch = i < f ? i : i + whole;
                 stage[ch] = vbeg < vend ? load_values16<E>(a16 + 16 * uintptr_t(ch), vbeg, vend) : u32x4{0u, 0u, 0u, 0u};
@@ -492,8 +518,8 @@ __global__ __launch_bounds__(64) void endor_expand_kernel(BatchParams P) {
     __shared__ WaveScratch<E, kCap> s_scratch;
     const uint32_t gc = blockIdx.x / kTilesPerChunk;
     const uint32_t tl = blockIdx.x % kTilesPerChunk;  // tile, relative to the chunk
-    const MatParams &M = P.m[find_matrix(P, gc)];
-    const uint32_t c = gc - M.chunk_begin;
+    uint32_t c;
+    const MatParams M = matrix_of(P, gc, c);
     const uint32_t lane = threadIdx.x;
 
     const int64_t n = M.n;
@@ -501,19 +527,21 @@ __global__ __launch_bounds__(64) void endor_expand_kernel(BatchParams P) {
     const int64_t tile = int64_t(c) * kTilesPerChunk + tl;
     if (tile >= ntiles) return;
 
-    const int64_t full_words = n >> 6;
-    const uint32_t tail_bits = static_cast<uint32_t>(n & 63);
     const uintptr_t vbeg = reinterpret_cast<uintptr_t>(M.values);
     const uintptr_t vend = vbeg + E * static_cast<uintptr_t>(M.nnz);
+    const int64_t e0 = tile * kTileElems;
+    const int64_t left = n - e0;
     // the bitmap word first: its load is in flight while the table is looked up
-    const uint64_t word = load_word_guarded(M.bitmap, tile * kTileWords + lane, full_words, tail_bits);
+    uint64_t word = M.bitmap[tile * kTileWords + (64 * int64_t(lane) < left ? lane : 0u)];
+    if (left < kTileElems) {  // wave-uniform
+        const int64_t bits = left - 64 * int64_t(lane);
+        if (bits < 64) word = bits > 0 ? word & ((uint64_t(1) << bits) - 1) : 0;
+    }
     const uint32_t *tile_off = M.tile_off + size_t(c) * kChunkStride + tl;
     const uint32_t o0 = tile_off[0];
     const uint32_t o1 = tile_off[1];
     const uint64_t base = chunk_base(M.chunk_total, c, lane);
     const uint32_t cnt = o1 - o0;  // 1 bits in this tile
-    const int64_t e0 = tile * kTileElems;
-    const int64_t left = n - e0;
     StoreSink<E, kAlignedOut, kBurst> sink;
     sink.out = reinterpret_cast<uint8_t *>(M.dense) + e0 * E;
     sink.nvalid = left < kTileElems ? static_cast<uint32_t>(left) : uint32_t(kTileElems);
@@ -661,8 +689,13 @@ template <int E, bool kAlignedOut, int kCap = kTileElems>
 __global__ __launch_bounds__(64) void endor_expand_rows_kernel(RowsParams R) {
     __shared__ WaveScratch<E, kCap> s_scratch;
     const uint32_t lane = threadIdx.x;
-    const int64_t r = blockIdx.x / R.segs;
-    const uint32_t g = blockIdx.x % R.segs;
+    // (the block's number, once all parameters are in registers: a wait for them less when the row is known)
+    uint32_t block;
+    asm("s_mov_b32 %0, %1"
+        : "=s"(block)
+        : "s"(blockIdx.x), "s"(R.bitmap), "s"(R.values), "s"(R.out), "s"(R.row_offsets), "s"(R.sel), "s"(R.rows), "s"(R.cols), "s"(R.nnz), "s"(R.segs));
+    const int64_t r = block / R.segs;
+    const uint32_t g = block % R.segs;
     const int64_t i = R.sel[r];
     if (i < 0 || i >= R.rows) return;  // an index outside the matrix leaves its output row untouched
 
