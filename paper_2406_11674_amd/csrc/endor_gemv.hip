@@ -74,6 +74,10 @@ struct GemvParams {
     uint32_t panel;      // columns of x in LDS at a time: whole segments
     uint32_t parts;      // items per row and panel
     uint32_t part_segs;  // segments per item
+    // What a workgroup would begin with dividing, 64 bits by 32 twice and 32 by 32 five times, two hundred scalar
+    // instructions before its first load: rows / workgroups and the remainder (the first workgroups have one more),
+    // waves / parts and the remainder, and 65536 / parts rounded up or one more.
+    uint32_t rows_each, rows_more, row_step, part_step, part_inverse;
 };
 
 __device__ __forceinline__ float wave_sum_f32(float x) {
@@ -376,14 +380,16 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void endor_gemv_kernel(Gem
     __shared__ float s_sum[kMaxItems * kRhs];  // an item's sums
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
-    const int64_t row_begin = static_cast<int64_t>(uint64_t(blockIdx.x) * G.rows / gridDim.x);
-    const int64_t row_end = static_cast<int64_t>(uint64_t(blockIdx.x + 1) * G.rows / gridDim.x);
-    const uint32_t parts = G.parts, nrows = static_cast<uint32_t>(row_end - row_begin), items = nrows * parts;
+    const uint32_t group = blockIdx.x, rows_more = G.rows_more;
+    const int64_t row_begin = static_cast<int64_t>(uint64_t(group) * G.rows_each) + (group < rows_more ? group : rows_more);
+    const uint32_t parts = G.parts, nrows = G.rows_each + (group < rows_more ? 1u : 0u), items = nrows * parts;
+    // x / parts, for numbers of items: x * part_inverse is off by at most x * parts, less than 65536
+    auto by_parts = [&](uint32_t x) { return x * G.part_inverse >> 16; };
     const int64_t nwords = (G.rows * G.cols + 63) >> 6;
     const uintptr_t vbeg = reinterpret_cast<uintptr_t>(G.values);
     const uintptr_t vend = vbeg + 2 * static_cast<uintptr_t>(G.nnz);
     const uint32_t pieces = G.panel / 8;  // of x, per right-hand side
-    const uint32_t row_step = kWaves / parts, part_step = kWaves % parts;  // from one of a wave's items to the next
+    const uint32_t row_step = G.row_step, part_step = G.part_step;  // from one of a wave's items to the next
 
     for (int64_t p_begin = 0; p_begin < G.cols; p_begin += G.panel) {
         const int64_t p_end = G.cols - p_begin < G.panel ? G.cols : p_begin + G.panel;
@@ -412,8 +418,8 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void endor_gemv_kernel(Gem
             return P;
         };
         Place next;  // the segment whose bitmap words have been asked for
-        next.row = wave / parts;
-        next.part = wave % parts;
+        next.row = by_parts(wave);
+        next.part = wave - next.row * parts;
         next.seg = 0;
         locate(next);
         WordLoad words = word_load(G.bitmap, nwords, next.bit, lane);
@@ -438,7 +444,7 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void endor_gemv_kernel(Gem
             const uint32_t c_first = static_cast<uint32_t>((row_begin * G.cols) >> 20);
             const uint64_t first = chunk_base(G.chunk_total, c_first, lane);
             for (uint32_t it0 = 4 * wave; it0 < items; it0 += 4 * kWaves) {
-                const uint32_t it = it0 + lane / 16, r = it / parts;
+                const uint32_t it = it0 + lane / 16, r = by_parts(it);
                 const int64_t c = p_begin + int64_t(it - r * parts) * G.part_segs * kSeg;
                 if (it < items && c < p_end) {
                     const uint64_t rank = rank_from_table(G, (row_begin + r) * G.cols + c, c_first, first, lane);
@@ -450,7 +456,7 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void endor_gemv_kernel(Gem
                 s_start[r] = p_begin == 0 ? static_cast<uint64_t>(G.row_offsets[row_begin + r]) : s_end[r];
         } else {  // the row's first value and the 1 bits of its earlier parts, 16 lanes each
             for (uint32_t it0 = 4 * wave; it0 < items; it0 += 4 * kWaves) {
-                const uint32_t it = it0 + lane / 16, r = it / parts;
+                const uint32_t it = it0 + lane / 16, r = by_parts(it);
                 const int64_t c = p_begin + int64_t(it - r * parts) * G.part_segs * kSeg, bit = (row_begin + r) * G.cols;
                 if (it < items && c < p_end) {
                     uint64_t at = p_begin == 0 ? static_cast<uint64_t>(G.row_offsets[row_begin + r]) : s_end[r];
@@ -510,7 +516,7 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void endor_gemv_kernel(Gem
         __syncthreads();
     }
     for (uint32_t k = threadIdx.x; k < nrows * kRhs; k += kThreads) {
-        const uint32_t r = k % nrows, b = k / nrows;
+        const uint32_t b = kRhs == 1 ? 0 : k / nrows, r = k - b * nrows;
         float s = s_sum[r * parts * kRhs + b];
         for (uint32_t p = 1; p < parts; ++p) s += s_sum[(r * parts + p) * kRhs + b];
         G.y[int64_t(b) * G.rows + row_begin + r] = s;
@@ -523,6 +529,9 @@ __global__ __launch_bounds__(256) void endor_zero_kernel(float *__restrict__ y, 
     if (i < count) y[i] = 0.0f;
 }
 
+// by_parts: items and the numbers a wave looks at past them, by parts
+static_assert((512 + 4 * 16) * 16 < 65536, "exact");
+
 template <int kRhs, int kSteps, bool kShort = false>
 void launch_steps(GemvParams G, const endor_gemv_plan::Plan &p, hipStream_t s) {
     constexpr int kWaves = endor_gemv_plan::waves_of(kSteps);
@@ -530,6 +539,11 @@ void launch_steps(GemvParams G, const endor_gemv_plan::Plan &p, hipStream_t s) {
     G.part_segs = static_cast<uint32_t>(p.part_segs);
     G.parts = static_cast<uint32_t>(p.parts);
     G.panel = static_cast<uint32_t>(p.parts * p.part_segs * endor_gemv_plan::seg_cols(kSteps));
+    G.rows_each = static_cast<uint32_t>(G.rows / p.grid);
+    G.rows_more = static_cast<uint32_t>(G.rows % p.grid);
+    G.row_step = static_cast<uint32_t>(kWaves / p.parts);
+    G.part_step = static_cast<uint32_t>(kWaves % p.parts);
+    G.part_inverse = static_cast<uint32_t>(65536 / p.parts + 1);
     hipLaunchKernelGGL((endor_gemv_kernel<kRhs, kSteps, kWaves, kShort>), dim3(static_cast<unsigned>(p.grid)), dim3(64 * kWaves),
                        size_t(G.panel) * 2 * kRhs, s, G);
 }
