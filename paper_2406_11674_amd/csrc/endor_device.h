@@ -52,27 +52,40 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
     return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_inclusive_scan(x)), 63));
 }
 
+struct ChunkTotals {
+    uint32_t t[4];
+};
+// 256 totals from the j0-th on, the four loads of a lane issued together (an index past the end reads the last total, or
+// the first, again and is dropped: a load under a test is waited for on the spot)
+__device__ __forceinline__ ChunkTotals chunk_totals(const uint32_t *chunk_total, uint32_t c, uint32_t j0, uint32_t lane) {
+    ChunkTotals x;
+    const uint32_t last = c == 0 ? 0 : c - 1;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t j = j0 + 64 * k + lane;
+        x.t[k] = chunk_total[j < c ? j : last];
+    }
+    return x;
+}
 // Number of 1 bits before chunk c of the matrix: sum of the earlier chunks' totals.
 // c < 2^14 and a total is at most 2^20, so a lane's partial sum fits 32 bits; the
 // two 16-bit halves are summed across lanes separately to keep 64 bits.
-__device__ __forceinline__ uint64_t chunk_base(const uint32_t *chunk_total, uint32_t c, uint32_t lane) {
-    if (c == 0) return 0;
+// x: the first pass's totals, which a caller with other loads to put out behind them asks for by itself.
+__device__ __forceinline__ uint64_t chunk_base_of(const uint32_t *chunk_total, uint32_t c, uint32_t lane, ChunkTotals x) {
     uint32_t part = 0;
-    // 256 totals per pass, the four loads of a lane issued together (an index past the end reads
-    // the last total again and drops it: a load under a test is waited for on the spot)
-    for (uint32_t j0 = 0; j0 < c; j0 += 256) {
-        uint32_t t[4];
+    for (uint32_t j0 = 0;;) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t j = j0 + 64 * k + lane;
-            t[k] = chunk_total[j < c ? j : c - 1];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) part += (j0 + 64 * k + lane < c) ? t[k] : 0u;
+        for (int k = 0; k < 4; ++k) part += (j0 + 64 * k + lane < c) ? x.t[k] : 0u;
+        j0 += 256;
+        if (j0 >= c) break;
+        x = chunk_totals(chunk_total, c, j0, lane);
     }
     const uint32_t lo = wave_sum(part & 0xffffu);
     const uint32_t hi = wave_sum(part >> 16);
     return uint64_t(lo) + (uint64_t(hi) << 16);
+}
+__device__ __forceinline__ uint64_t chunk_base(const uint32_t *chunk_total, uint32_t c, uint32_t lane) {
+    return c == 0 ? 0 : chunk_base_of(chunk_total, c, lane, chunk_totals(chunk_total, c, 0, lane));
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane l writes lds_base + 16*l

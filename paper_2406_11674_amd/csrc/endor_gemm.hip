@@ -48,7 +48,6 @@
 
 namespace {
 
-using endor_device::chunk_base;
 using endor_device::global_ptr;
 using endor_device::u32x4;
 using endor_device::wave_sum;
@@ -468,8 +467,9 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
         // Cursor of every row at the first column of the range: the number of 1 bits before flat
         // position e_r = row*cols + c_begin is (start of its chunk) + (tile offset) + (1 bits of
         // the tile's words below e_r).  Lane r < 16 looks up the first two terms of row r, the
-        // whole wave counts the third for each row in turn; all loads go out before the first
-        // result is needed, so the 16 lookups cost one trip to memory, not sixteen.
+        // whole wave counts the third for each row in turn.  All loads go out, without a test, before the
+        // first result is needed, so the lookups cost one trip to memory: under their tests they were three in a
+        // row at the start of every block (16 right-hand sides of 28672 x 8192 78.7 us, now 77.2; 131072 x 256 24.9, now 23.4).
         uintptr_t cursor = vbeg;
         if (c_begin < G.cols && row0 < G.rows) {  // wave-uniform
             const int64_t e_first = row0 * G.cols + c_begin;
@@ -477,47 +477,41 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
             int64_t last_row = row0 + kRows - 1;
             if (last_row >= G.rows) last_row = G.rows - 1;
             const uint32_t span = static_cast<uint32_t>((last_row * G.cols + c_begin) >> 20) - c_first;  // chunks after the first
-            // totals of the chunks the 16 rows start in, scanned: lane k holds sum of chunks c_first .. c_first+k
-            uint32_t incl = 0;
-            uint64_t wide = 0;  // the same for rows so wide that the 16 starts span more than 64 chunks
-            if (span <= 64) {
-                const uint32_t ct = lane < span ? G.chunk_total[c_first + lane] : 0u;
-                incl = endor_device::wave_inclusive_scan(ct);  // < 2^26
-            }
-            const uint64_t cb0 = chunk_base(G.chunk_total, c_first, lane);
-            // per-row part, lane r for row r
-            uint64_t head = 0;  // chunk start + tile offset of row `lane`
-            {
-                const int64_t row = row0 + (lane & 15);
-                const int64_t e = (row < G.rows ? row : last_row) * G.cols + c_begin;
-                const uint32_t c = static_cast<uint32_t>(e >> 20);
-                const uint32_t k = c - c_first;  // <= span
-                uint32_t before_chunk = static_cast<uint32_t>(
-                    __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * (k ? k - 1 : 0)), static_cast<int>(incl)));
-                if (k == 0) before_chunk = 0;
-                if (span > 64) {
-                    for (uint32_t j = c_first; j < c; ++j) wide += G.chunk_total[j];
-                    before_chunk = 0;
-                }
-                const uint32_t tl = static_cast<uint32_t>((e >> 12) % kTilesPerChunk);
-                head = cb0 + wide + before_chunk + G.tile_off[size_t(c) * kChunkStride + tl];
-            }
-            // the tile's words below e_r, for each row
+            // lane r: where row r starts
+            const int64_t e = (row0 + (lane & 15) < G.rows ? row0 + (lane & 15) : last_row) * G.cols + c_begin;
+            const uint32_t c = static_cast<uint32_t>(e >> 20);
+            const uint32_t k = c - c_first;  // <= span
+            const endor_device::ChunkTotals before_first = endor_device::chunk_totals(G.chunk_total, c_first, 0, lane);
+            const uint32_t ct = G.chunk_total[c_first + (lane < span ? lane : 0u)];
+            const uint32_t tile = G.tile_off[size_t(c) * kChunkStride + static_cast<uint32_t>((e >> 12) % kTilesPerChunk)];
+            // the words of the tile that row r starts in, up to that position
             uint64_t words[kRows];
     #pragma unroll
             for (int r = 0; r < kRows; ++r) {
-                const int64_t row = row0 + r < G.rows ? row0 + r : last_row;
-                const int64_t e = row * G.cols + c_begin;
-                const int64_t w = (e >> 12) * kTileWords + lane, we = e >> 6;
-                uint64_t word = 0;
-                if (w <= we) word = G.bitmap[w];  // w <= we < number of words
-                if (w == we) word &= (uint64_t(1) << (e & 63)) - 1;
-                words[r] = word;
+                const int64_t e_r = (row0 + r < G.rows ? row0 + r : last_row) * G.cols + c_begin;
+                const uint32_t we = static_cast<uint32_t>(e_r >> 6) % kTileWords;  // of the tile
+                words[r] = G.bitmap[(e_r >> 12) * kTileWords + (lane < we ? lane : we)];  // (a word of the bitmap: e_r is a position)
             }
+            __builtin_amdgcn_sched_barrier(0);
+            // totals of the chunks the 16 rows start in, scanned: lane k holds sum of chunks c_first .. c_first+k
+            const uint32_t incl = endor_device::wave_inclusive_scan(lane < span ? ct : 0u);  // < 2^26
+            uint32_t before_chunk = static_cast<uint32_t>(
+                __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * (k ? k - 1 : 0)), static_cast<int>(incl)));
+            if (k == 0) before_chunk = 0;
+            uint64_t wide = 0;  // the same for rows so wide that the 16 starts span more than 64 chunks
+            if (span > 64) {
+                for (uint32_t j = c_first; j < c; ++j) wide += G.chunk_total[j];
+                before_chunk = 0;
+            }
+            // chunk start + tile offset of row `lane`
+            const uint64_t head = endor_device::chunk_base_of(G.chunk_total, c_first, lane, before_first) + wide + before_chunk + tile;
             uint32_t below = 0;  // lane r: 1 bits of row r's tile below e_r
     #pragma unroll
             for (int r = 0; r < kRows; ++r) {
-                const uint32_t sum = wave_sum(__popcll(words[r]));
+                const int64_t e_r = (row0 + r < G.rows ? row0 + r : last_row) * G.cols + c_begin;
+                const uint32_t we = static_cast<uint32_t>(e_r >> 6) % kTileWords;
+                const uint64_t keep = lane < we ? ~uint64_t(0) : lane == we ? (uint64_t(1) << (e_r & 63)) - 1 : 0;
+                const uint32_t sum = wave_sum(__popcll(words[r] & keep));
                 if (lane == static_cast<uint32_t>(r)) below = sum;
             }
             const uint64_t rank = head + below;  // lane r < 16: row r
