@@ -37,6 +37,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "endor.h"
 #include "endor_device.h"
@@ -575,7 +576,8 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
 // y[b][i] = the parts of row i's block, added in ascending order.  An output a thread, so that it is one trip to memory, and
 // 32-bit divisions (rounds are fewer than 2^32): with a workgroup for all of a block's outputs, four a thread in turn, and two
 // divisions of 64 bits, 16 right-hand sides of 28672 x 8192 took 77.2 us,
-// now 76.6, 4096 x 4096 18.1, now 14.7.
+// now 76.6, 4096 x 4096 18.1, now 14.2; 1024 x 8192 (8 right-hand sides, many parts) 14.4, with four parts a trip 12.6, with
+// three or eight and no test around a load 12.0.
 __global__ __launch_bounds__(256) void endor_gemm_reduce_kernel(const float *__restrict__ partial, float *__restrict__ y,
                                                                 int64_t rows, int32_t nb, uint32_t segs, uint32_t per_wg) {
     const uint32_t block = blockIdx.x;
@@ -586,13 +588,21 @@ __global__ __launch_bounds__(256) void endor_gemm_reduce_kernel(const float *__r
     if (i >= uint32_t(nb) * kBlockRows || row >= rows) return;
     const float *src = partial + size_t(first + block) * nb * kBlockRows + i;
     const size_t step = size_t(nb) * kBlockRows;
+    // (parts that there are not read the last one again)
     float s = src[0];
-    uint32_t k = first + 1;
-    for (; k + 3 <= last; k += 4, src += 4 * step) {
-        const float a = src[step], b = src[2 * step], c = src[3 * step], d = src[4 * step];
-        s = (((s + a) + b) + c) + d;
-    }
-    for (; k <= last; ++k, src += step) s += src[step];
+    auto add = [&](auto many, uint32_t k) {
+        constexpr uint32_t kMany = decltype(many)::value;
+        float part[kMany];
+#pragma unroll
+        for (uint32_t j = 0; j < kMany; ++j) part[j] = src[(k + j < last ? k + j - first : last - first) * step];
+#pragma unroll
+        for (uint32_t j = 0; j < kMany; ++j)
+            if (k + j <= last) s += part[j];
+    };
+    if (last - first <= 3)
+        add(std::integral_constant<uint32_t, 3>(), first + 1);
+    else
+        for (uint32_t k = first + 1; k <= last; k += 8) add(std::integral_constant<uint32_t, 8>(), k);
     y[(i / kBlockRows) * rows + row] = s;
 }
 
