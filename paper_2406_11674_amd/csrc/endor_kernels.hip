@@ -27,7 +27,8 @@
 // selective load) and - run backwards, as a scatter - the pack step of the device-side
 // compressor (Algorithm 1).  The element width (2 bytes, or 1 for the 8-bit variant of
 // Section 4.2) is a template parameter throughout.  The products on the compressed form
-// have files of their own.
+// have files of their own; the compressor that reads a large matrix once and the column
+// subset by workgroups that stay are in endor_compress_pass.h and endor_cols_stream.h.
 //
 // One rule shaped all of these kernels: a load under a per-lane test whose result is used
 // after the test is waited for on the spot, so several of them in a row are as many trips
