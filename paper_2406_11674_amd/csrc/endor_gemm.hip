@@ -473,17 +473,22 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
         // row at the start of every block (16 right-hand sides of 28672 x 8192 78.7 us, now 77.2; 131072 x 256 24.9, now 23.4).
         uintptr_t cursor = vbeg;
         if (c_begin < G.cols && row0 < G.rows) {  // wave-uniform
+            // (opaque: what follows from the lane alone would be kept in registers over all blocks, and three workgroups
+            // of the dense form with unaligned columns would no longer fit a compute unit: 169 registers;
+            // 2999 x 9001, 0.7 kept, 7 right-hand sides 29.1 us, so 23.3)
+            uint32_t l = lane;
+            asm volatile("" : "+v"(l));
             const int64_t e_first = row0 * G.cols + c_begin;
             const uint32_t c_first = static_cast<uint32_t>(e_first >> 20);  // chunk = 2^20 positions
             int64_t last_row = row0 + kRows - 1;
             if (last_row >= G.rows) last_row = G.rows - 1;
             const uint32_t span = static_cast<uint32_t>((last_row * G.cols + c_begin) >> 20) - c_first;  // chunks after the first
             // lane r: where row r starts
-            const int64_t e = (row0 + (lane & 15) < G.rows ? row0 + (lane & 15) : last_row) * G.cols + c_begin;
+            const int64_t e = (row0 + (l & 15) < G.rows ? row0 + (l & 15) : last_row) * G.cols + c_begin;
             const uint32_t c = static_cast<uint32_t>(e >> 20);
             const uint32_t k = c - c_first;  // <= span
-            const endor_device::ChunkTotals before_first = endor_device::chunk_totals(G.chunk_total, c_first, 0, lane);
-            const uint32_t ct = G.chunk_total[c_first + (lane < span ? lane : 0u)];
+            const endor_device::ChunkTotals before_first = endor_device::chunk_totals(G.chunk_total, c_first, 0, l);
+            const uint32_t ct = G.chunk_total[c_first + (l < span ? l : 0u)];
             const uint32_t tile = G.tile_off[size_t(c) * kChunkStride + static_cast<uint32_t>((e >> 12) % kTilesPerChunk)];
             // the words of the tile that row r starts in, up to that position
             uint64_t words[kRows];
@@ -491,11 +496,11 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
             for (int r = 0; r < kRows; ++r) {
                 const int64_t e_r = (row0 + r < G.rows ? row0 + r : last_row) * G.cols + c_begin;
                 const uint32_t we = static_cast<uint32_t>(e_r >> 6) % kTileWords;  // of the tile
-                words[r] = G.bitmap[(e_r >> 12) * kTileWords + (lane < we ? lane : we)];  // (a word of the bitmap: e_r is a position)
+                words[r] = G.bitmap[(e_r >> 12) * kTileWords + (l < we ? l : we)];  // (a word of the bitmap: e_r is a position)
             }
             __builtin_amdgcn_sched_barrier(0);
             // totals of the chunks the 16 rows start in, scanned: lane k holds sum of chunks c_first .. c_first+k
-            const uint32_t incl = endor_device::wave_inclusive_scan(lane < span ? ct : 0u);  // < 2^26
+            const uint32_t incl = endor_device::wave_inclusive_scan(l < span ? ct : 0u);  // < 2^26
             uint32_t before_chunk = static_cast<uint32_t>(
                 __builtin_amdgcn_ds_bpermute(static_cast<int>(4 * (k ? k - 1 : 0)), static_cast<int>(incl)));
             if (k == 0) before_chunk = 0;
@@ -505,15 +510,15 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
                 before_chunk = 0;
             }
             // chunk start + tile offset of row `lane`
-            const uint64_t head = endor_device::chunk_base_of(G.chunk_total, c_first, lane, before_first) + wide + before_chunk + tile;
+            const uint64_t head = endor_device::chunk_base_of(G.chunk_total, c_first, l, before_first) + wide + before_chunk + tile;
             uint32_t below = 0;  // lane r: 1 bits of row r's tile below e_r
     #pragma unroll
             for (int r = 0; r < kRows; ++r) {
                 const int64_t e_r = (row0 + r < G.rows ? row0 + r : last_row) * G.cols + c_begin;
                 const uint32_t we = static_cast<uint32_t>(e_r >> 6) % kTileWords;
-                const uint64_t keep = lane < we ? ~uint64_t(0) : lane == we ? (uint64_t(1) << (e_r & 63)) - 1 : 0;
+                const uint64_t keep = l < we ? ~uint64_t(0) : l == we ? (uint64_t(1) << (e_r & 63)) - 1 : 0;
                 const uint32_t sum = wave_sum(__popcll(words[r] & keep));
-                if (lane == static_cast<uint32_t>(r)) below = sum;
+                if (l == static_cast<uint32_t>(r)) below = sum;
             }
             const uint64_t rank = head + below;  // lane r < 16: row r
             const uint32_t lo = static_cast<uint32_t>(
