@@ -75,9 +75,9 @@ struct GemvParams {
     uint32_t parts;      // items per row and panel
     uint32_t part_segs;  // segments per item
     // What a workgroup would begin with dividing, 64 bits by 32 twice and 32 by 32 five times, two hundred scalar
-    // instructions before its first load: rows / workgroups and the remainder (the first workgroups have one more),
-    // waves / parts and the remainder, and 65536 / parts rounded up or one more.
-    uint32_t rows_each, rows_more, row_step, part_step, part_inverse;
+    // instructions before its first load: rows / workgroups, the share of them that has one more, waves / parts and
+    // the remainder, and 65536 / parts rounded up or one more.
+    uint32_t rows_each, more_share, row_step, part_step, part_inverse;
 };
 
 __device__ __forceinline__ float wave_sum_f32(float x) {
@@ -380,9 +380,9 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void endor_gemv_kernel(Gem
     __shared__ float s_sum[kMaxItems * kRhs];  // an item's sums
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
-    const uint32_t group = blockIdx.x, rows_more = G.rows_more;
-    const int64_t row_begin = static_cast<int64_t>(uint64_t(group) * G.rows_each) + (group < rows_more ? group : rows_more);
-    const uint32_t parts = G.parts, nrows = G.rows_each + (group < rows_more ? 1u : 0u), items = nrows * parts;
+    const uint32_t group = blockIdx.x, more = endor_gemv_plan::more_before(group, G.more_share);
+    const int64_t row_begin = static_cast<int64_t>(uint64_t(group) * G.rows_each) + more;
+    const uint32_t parts = G.parts, nrows = G.rows_each + (endor_gemv_plan::more_before(group + 1, G.more_share) - more), items = nrows * parts;
     // x / parts, for numbers of items: x * part_inverse is off by at most x * parts, less than 65536
     auto by_parts = [&](uint32_t x) { return x * G.part_inverse >> 16; };
     const int64_t nwords = (G.rows * G.cols + 63) >> 6;
@@ -540,7 +540,7 @@ void launch_steps(GemvParams G, const endor_gemv_plan::Plan &p, hipStream_t s) {
     G.parts = static_cast<uint32_t>(p.parts);
     G.panel = static_cast<uint32_t>(p.parts * p.part_segs * endor_gemv_plan::seg_cols(kSteps));
     G.rows_each = static_cast<uint32_t>(G.rows / p.grid);
-    G.rows_more = static_cast<uint32_t>(G.rows % p.grid);
+    G.more_share = endor_gemv_plan::more_share(static_cast<uint32_t>(G.rows % p.grid), static_cast<uint32_t>(p.grid));
     G.row_step = static_cast<uint32_t>(kWaves / p.parts);
     G.part_step = static_cast<uint32_t>(kWaves % p.parts);
     G.part_inverse = static_cast<uint32_t>(65536 / p.parts + 1);

@@ -34,7 +34,29 @@ static const char *check(int64_t rows, int64_t cols, int rhs, const Plan &p) {
     return nullptr;
 }
 
+// Every row has one workgroup, none more than its share rounded up, and the larger ones lie at regular distances: a run of
+// workgroups of one size is no longer than it has to be.
+static const char *check_rows(int64_t rows, uint32_t groups) {
+    const uint32_t each = static_cast<uint32_t>(rows / groups), more = static_cast<uint32_t>(rows % groups), share = more_share(more, groups);
+    if (more_before(0, share) != 0 || more_before(groups, share) != more) return "rows left over";
+    for (int k = 0; k < 64; ++k) {
+        const uint32_t g = static_cast<uint32_t>(rnd() % groups), a = more_before(g, share), b = more_before(g + 1, share);
+        if (b < a || b - a > 1 || each + (b - a) > ceil_div(rows, groups)) return "a workgroup's rows";
+        const int64_t even = static_cast<int64_t>(static_cast<unsigned __int128>(rows) * g / groups) - int64_t(each) * g;
+        if (a < even || a > even + 1) return "rows bunched";
+    }
+    return nullptr;
+}
+
 int main() {
+    for (int rep = 0; rep < 100000; ++rep) {
+        const int64_t rows = size(rep % 20 ? 18 : 31);
+        const uint32_t groups = static_cast<uint32_t>(1 + rnd() % uint64_t(rep % 2 && rows > 256 ? 256 : rows));
+        if (const char *bad = check_rows(rows, groups)) {
+            std::printf("%s: %lld rows, %u workgroups\n", bad, (long long)rows, groups);
+            return 1;
+        }
+    }
     for (int rep = 0; rep < 400000; ++rep) {
         const int rhs = 1 + static_cast<int>(rnd() % 4);
         int64_t rows = size(rep % 50 ? 18 : 31), cols = size(rep % 50 ? 18 : 33);
