@@ -14,9 +14,17 @@
 // (Numbers taken from one counter, instead of every groups-th block, were 25 us slower: additions to one
 // address cost 25 to 50 ns each.)
 //
+// Where not all workgroups run, because other work holds compute units, blocks are given out a few a workgroup at a
+// time, so that workgroups that start late, as the other work ends, share in what is left.  When those left instead, a
+// call that had begun on a few units stayed on them: a pair of calls on two streams, 28672 x 8192 fp16, took 320 to 670
+// us, at worst 1090, and 36864 x 9216 8-bit 320 to 820, at worst 1290, where it now takes 285 and 309, at worst 297 and
+// 327 (of two passes 416 and 350).  (Numbers from a counter do not do here: workgroups that start one after the other take
+// several in a row each, and every one waits for the last of the one before, 4 us a workgroup.)
+//
 // Every wait ends: only workgroups that have registered, and so are running, own blocks; the lowest block
 // that is not counted belongs to one that waits for the places of lower blocks alone, and those are counted.
-// A workgroup that starts too late to be given blocks leaves.
+// The wave that looks places up gives the blocks out as it goes and waits for nothing but counts; with the last
+// place it says that there are no more.
 //
 // Bound by memory: 28672 x 8192 fp16, half kept, 734 MB in 137 us, 5.4 TB/s; two passes take 199, loads
 // and stores without the scatter 13 us less than this.  Of it, 10 us pass before the first values are written
@@ -38,8 +46,18 @@ struct Blocks {
     static constexpr int kPerChunk = (kTilesPerChunk + kTiles - 1) / kTiles;  // block words kept in a chunk's slice of the table
 };
 constexpr uint32_t kPackGroups = 256;  // workgroups: one a compute unit
-constexpr uint32_t kHeld = 3;          // blocks a workgroup holds
-constexpr uint32_t kRing = kHeld + 1;  // a wave that has counted block n + 3 may find another at block n still
+using endor_compress_plan::counted_word;
+using endor_compress_plan::kCounted;
+using endor_compress_plan::kHeld;
+using endor_compress_plan::kPlaced;
+using endor_compress_plan::kRing;
+using endor_compress_plan::kSpanSlots;
+using endor_compress_plan::Part;
+using endor_compress_plan::placed_word;
+using endor_compress_plan::Span;
+using endor_compress_plan::span_of;
+using endor_compress_plan::word_own;
+using endor_compress_plan::word_upto;
 
 // The table's memory while the kernel runs, slice by slice: the words of some blocks, two parties, the counts of the
 // chunk's tiles in 16 bits.
@@ -47,13 +65,6 @@ constexpr int kMaxPerChunk = Blocks<2>::kPerChunk > Blocks<1>::kPerChunk ? Block
 constexpr int kPartyAt = 2 * kMaxPerChunk + 2 + 32;
 constexpr int kCountsAt = kChunkStride - kTilesPerChunk / 2;
 constexpr uint32_t kPassMinChunks = 16;  // whose slices hold all parties
-
-// A block's word: how many non-zeros it has, and once it is placed, how many there are up to its end.
-constexpr uint64_t kCounted = uint64_t(1) << 62, kPlaced = uint64_t(1) << 63;
-__device__ __forceinline__ uint64_t counted_word(uint32_t own) { return kCounted | uint64_t(own) << 40; }
-__device__ __forceinline__ uint64_t placed_word(uint64_t upto, uint32_t own) { return kPlaced | uint64_t(own) << 40 | upto; }
-__device__ __forceinline__ uint32_t word_own(uint64_t w) { return static_cast<uint32_t>(w >> 40) & 0x3fffffu; }
-__device__ __forceinline__ uint64_t word_upto(uint64_t w) { return w & ((uint64_t(1) << 40) - 1); }
 
 template <int E>
 __device__ __forceinline__ uint64_t *block_word(const MatParams &M, uint32_t block) {
@@ -64,11 +75,11 @@ __device__ __forceinline__ uint64_t *block_word(const MatParams &M, uint32_t blo
 // Workgroups register in parties of 16: 256 additions to one counter take 25 us, to 16 counters two.
 constexpr uint32_t kParty = 16;
 constexpr uint32_t kParties = kPackGroups / kParty;
-constexpr uint32_t kClosed = 1u << 31;
+static_assert(kParty < 32 && kPackGroups < 1024 && kMaxElems / kTileElems / Blocks<2>::kTiles < int64_t(1) << 20, "a span's word");
 struct alignas(8) Party {
-    uint64_t reply;    // 1 << 63 | running << 32 | running in the parties before << 16 | in this one
-    uint32_t apart[30];  // (a line of its own: the others' polls would hold the counter up)
-    uint32_t started;  // workgroups of the party that run; kClosed: later ones get no blocks
+    uint64_t span[kSpanSlots];
+    uint32_t apart[32 - 2 * kSpanSlots];  // (a line of its own: the others' polls would hold the counter up)
+    uint32_t started;  // workgroups of the party that run
     uint32_t first;    // (of the first party) parties that have asked who looks the places up
 };
 static_assert(kPartyAt % 2 == 0 && kPartyAt + int(sizeof(Party) / 4) < kCountsAt && kParties <= kPassMinChunks, "a party fits into a slice");
@@ -130,8 +141,10 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
     __shared__ uint32_t s_count[kRing][kTiles];
     __shared__ uint32_t s_arrived[kRing];  // waves that have counted their tile << 24 | its non-zeros
     __shared__ uint64_t s_first[kRing];    // non-zeros before the block
-    __shared__ uint32_t s_rank, s_groups;  // which blocks are this workgroup's: every s_groups-th from s_rank on; 0: none
-    __shared__ uint32_t s_placed;          // 1 when that is known, then one more for every block of it that is placed
+    // The workgroup's blocks: the first kHeld of them, then the n + kHeld-th by the time the n-th is placed.  (A slot is
+    // written again when all waves have counted the block after the one it held, so they have read it.)
+    __shared__ uint32_t s_block[kRing];
+    __shared__ uint32_t s_placed;  // 1 when the first are known, then one more for every block that is placed
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
     if (threadIdx.x < kRing) s_arrived[threadIdx.x] = 0;
@@ -143,48 +156,76 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
             if (lane == 0) __hip_atomic_store(&s_placed, placed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         };
-        // who takes part: the first to register looks the places up, and says who is running when all are, or when
-        // waiting for more has cost what they would save (a poll, about 0.7 us, against 4 us a block)
+        // Who takes part: the first to register gives the first span out when all are running or have been waited for.  Where
+        // all are, the first of the grid looks the places up; else the one that gave it out does, beside its own blocks.
+        const uint32_t groups = gridDim.x;
         Party *own_party = party(C.table, blockIdx.x / kParty);
-        uint32_t number = 0, scans = 0;
+        uint32_t registered = 0, scans = 0;
         if (lane == 0) {
-            number = __hip_atomic_fetch_add(&own_party->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (number == 0) scans = __hip_atomic_fetch_add(&party(C.table, 0)->first, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+            registered = __hip_atomic_fetch_add(&own_party->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (registered == 0) scans = __hip_atomic_fetch_add(&party(C.table, 0)->first, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
         }
-        number = first_lane(number);
+        registered = first_lane(registered);
         scans = first_lane(scans);
-        uint64_t reply;
+        auto started = [&]() { return lane < kParties ? peek(&party(C.table, lane)->started) : 0u; };
+        auto give_out = [&](uint32_t number, uint32_t start, uint32_t here) {
+            const uint32_t upto = wave_inclusive_scan(here);
+            const Span span{number, start, lane_of(upto, 63), upto - here, here};
+            if (lane < kParties) publish(&party(C.table, lane)->span[number % kSpanSlots], endor_compress_plan::span_word(span));
+            return span;  // before and here: of the lane's party
+        };
+        uint32_t given = 0, given_start = 0, given_end = 0;  // the last span given out
         if (scans) {
-            Party *P = party(C.table, lane < kParties ? lane : 0u);
-            for (uint32_t i = 0;; ++i) {
-                const uint32_t running = wave_sum(lane < kParties ? peek(&P->started) : 0u);
-                if (running >= gridDim.x || i * running >= nblocks) break;
+            uint32_t here;
+            for (uint32_t polls = 0;; ++polls) {
+                here = started();
+                if (endor_compress_plan::has_waited(polls, wave_sum(here), groups)) break;
             }
-            uint32_t here = 0;
-            if (lane < kParties) here = __hip_atomic_fetch_or(&P->started, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t upto = wave_inclusive_scan(here), running = lane_of(upto, 63), at = blockIdx.x / kParty;
-            reply = uint64_t(1) << 63 | uint64_t(running) << 32 | uint64_t(upto - here) << 16 | here;
-            if (lane < kParties) publish(&P->reply, reply);
-            reply = uint64_t(lane_of(static_cast<uint32_t>(reply >> 32), at)) << 32 | lane_of(static_cast<uint32_t>(reply), at);
-        } else {
-            while ((reply = peek(&own_party->reply)) == 0) {}
+            given_end = span_end(give_out(0, 0, here), groups, nblocks);
         }
-        const uint32_t running = static_cast<uint32_t>(reply >> 32) & 0xffffu;
-        const bool late = number >= (static_cast<uint32_t>(reply) & 0xffffu);
-        // where all run, the first looks the places up and packs nothing; else the one that said so does, beside its blocks
-        const bool all = running == gridDim.x;
-        if (all) scans = blockIdx.x == 0;
-        const uint32_t groups = late || (all && scans) ? 0u : all ? running - 1 : running;
-        const uint32_t rank = all ? blockIdx.x - 1 : (static_cast<uint32_t>(reply) >> 16) + number;
+        Span span;
+        auto uniform_span = [&](uint64_t w, uint32_t from) {
+            return span_of(uint64_t(lane_of(static_cast<uint32_t>(w >> 32), from)) << 32 | lane_of(static_cast<uint32_t>(w), from));
+        };
+        for (bool found = false; !found;) {  // the first span this workgroup has blocks in
+            const uint64_t w = lane < kSpanSlots ? peek(&own_party->span[lane]) : 0;
+#pragma unroll
+            for (uint32_t i = 0; i < kSpanSlots; ++i) {
+                span = uniform_span(w, i);
+                const uint64_t before = uint64_t(lane_of(static_cast<uint32_t>(w >> 32), (i + kSpanSlots - 1) % kSpanSlots)) << 32 |
+                                        lane_of(static_cast<uint32_t>(w), (i + kSpanSlots - 1) % kSpanSlots);
+                found = (lane_of(static_cast<uint32_t>(w >> 32), i) >> 31) != 0 &&
+                        endor_compress_plan::begins_with(span, before, registered, nblocks);
+                if (found) break;
+            }
+        }
+        Part part = part_of(span, blockIdx.x, registered, groups, nblocks);
+        const bool whole = is_whole(span, groups);
+        if (whole) scans = blockIdx.x == 0;
+        auto next = [&](uint32_t b) -> uint32_t {
+            if (b + part.stride < part.end || part.end >= nblocks) return b + part.stride;
+            const uint32_t number = span.number + 1;
+            uint64_t w;
+            do {
+                w = peek(&own_party->span[number % kSpanSlots]);
+                span = uniform_span(w, 0);
+            } while ((first_lane(static_cast<uint32_t>(w >> 32)) >> 31) == 0 || span.number != number);
+            part = part_of(span, blockIdx.x, registered, groups, nblocks);
+            return part.first;
+        };
+        uint32_t b0 = part.first, b1 = next(b0), b2 = next(b1);
         if (lane == 0) {
-            s_rank = rank;
-            s_groups = groups;
+            s_block[0] = b0;
+            s_block[1] = b1;
+            s_block[2] = b2;
         }
         tell(1);
-        if (late) return;
 
-        auto place = [&](uint32_t n, uint32_t b, uint64_t w) {
+        uint32_t n = 0;
+        auto place = [&](uint64_t w) {  // of the workgroup's n-th block, b0, whose word is w
+            const uint32_t b = b0, b3 = next(b2);
             if (lane == 0) {
+                s_block[(n + kHeld) % kRing] = b3;
                 s_first[n % kRing] = word_upto(w) - word_own(w);
                 if (b + 1 == nblocks) {
                     *C.nnz_out = static_cast<int64_t>(word_upto(w));
@@ -192,22 +233,35 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
                 }
             }
             tell(n + 2);
+            ++n;
+            b0 = b1;
+            b1 = b2;
+            b2 = b3;
         };
-        uint32_t n = 0;
         if (!scans) {
-            for (uint32_t b = rank; b < nblocks; b += groups, ++n) {
+            while (b0 < nblocks) {
                 uint64_t w;
-                while (!((w = peek(block_word<E>(C.table, b))) & kPlaced)) __builtin_amdgcn_s_sleep(1);
-                place(n, b, w);
+                while (!((w = peek(block_word<E>(C.table, b0))) & kPlaced)) __builtin_amdgcn_s_sleep(1);
+                place(w);
             }
             return;
         }
         __builtin_amdgcn_s_setprio(3);
         uint64_t before = 0;
-        for (uint32_t pos = 0, own = groups ? rank : nblocks; own < nblocks || pos < nblocks;) {
+        uint32_t pos = 0;
+        // The spans that are due, and when all blocks have places the one that says that there are no more, which a workgroup
+        // that starts late waits for.  (Where all are running there is nothing more to give out.)
+        auto give_out_due = [&]() {
+            while (!whole && pos >= given_start && given_start < nblocks) {
+                given_start = given_end;
+                given_end = span_end(give_out(++given, given_start, started()), groups, nblocks);
+            }
+        };
+        give_out_due();
+        while (b0 < nblocks || pos < nblocks) {
             const uint32_t j = pos + lane;  // (two or four words a lane: no faster where counts arrive steadily, 167 -> 170, 175)
             const uint64_t w = peek(block_word<E>(C.table, j < nblocks ? j : nblocks - 1));
-            const uint64_t mine = peek(block_word<E>(C.table, own < nblocks ? own : nblocks - 1));
+            const uint64_t mine = peek(block_word<E>(C.table, b0 < nblocks ? b0 : nblocks - 1));
             const uint64_t missing = ~__builtin_amdgcn_ballot_w64(j < nblocks && (w & kCounted) != 0);
             const uint32_t run = missing ? __builtin_ctzll(missing) : 64u;  // blocks from `pos` on that have been counted
             const uint32_t cnt = lane < run ? word_own(w) : 0u;
@@ -215,11 +269,8 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
             if (lane < run) publish(block_word<E>(C.table, j), placed_word(before + incl, cnt));
             before += lane_of(incl, 63);
             pos += run;
-            if (own < nblocks && (mine & kPlaced)) {
-                place(n, own, mine);
-                own += groups;
-                ++n;
-            }
+            give_out_due();
+            if (b0 < nblocks && (mine & kPlaced)) place(mine);
         }
         return;
     }
@@ -366,14 +417,14 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
     load(b0, T0);
     load(b0 + gridDim.x - 1, T1);
     until(1);
-    const uint32_t rank = first_lane(s_rank), stride = first_lane(s_groups);
-    if (stride == 0) return;
-    if (stride != gridDim.x - 1 || rank != b0) {
-        b0 = rank;
+    const uint32_t first = first_lane(s_block[0]);
+    uint32_t b1 = first_lane(s_block[1]), b2 = first_lane(s_block[2]);
+    if (first >= nblocks) return;
+    if (first != b0 || b1 != b0 + gridDim.x - 1) {
+        b0 = first;
         load(b0, T0);
-        load(b0 + stride, T1);
+        load(b1, T1);
     }
-    uint32_t b1 = b0 + stride, b2 = b1 + stride;
     load(b2, T2);
     count(0, b0, T0);
     wait_loads_to_lds();
@@ -381,8 +432,9 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
     auto step = [&](uint32_t &ba, uint32_t bb, TileData<E> &A, TileData<E> &B) __attribute__((always_inline)) {
         count(n + 1, bb, B);
         until(n + 2);
+        const uint32_t further = s_block[(n + kHeld) % kRing];
         pack(n, ba, A);
-        ba += kHeld * stride;
+        ba = first_lane(further);
         load(ba, A);
         ++n;
     };

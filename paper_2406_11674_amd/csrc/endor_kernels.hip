@@ -46,6 +46,7 @@
 #include <type_traits>
 
 #include "endor.h"
+#include "endor_compress_plan.h"
 #include "endor_device.h"
 #include "endor_layout.h"
 #include "endor_value_units.h"

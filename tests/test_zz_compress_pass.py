@@ -124,6 +124,39 @@ def test_one_pass_beside_other_work():
         del p
 
 
+@pytest.mark.parametrize("held_rows", [24, 250])
+@pytest.mark.parametrize("wide", [True, False], ids=["fp16", "u8"])
+def test_one_pass_begins_on_some_of_the_compute_units(wide, held_rows):
+    """Vector products on another stream hold a compute unit for every row (all of its LDS), 0.2 ms at a time: longer than the
+    compressor waits for its last workgroups.  It begins with the others, and these share what is left when they start:
+    noted by a build for that, 232 workgroups to the end, and 6 that become 256 over seven spans.  (Several streams: some
+    pairs of them share a hardware queue, and then nothing is held.)"""
+    rows, cols = (9001, 8447) if wide else (16385, 13653)
+    dense = _matrix(rows, cols, 0.5, wide, held_rows)
+    b, v, r = _expect(dense)
+    held = _matrix(held_rows, 2000000 if held_rows < 100 else 1000000, 0.5, True, 1)
+    m, _, held_ro = endor.compress_device(held, row_offsets=True)
+    x = torch.zeros(held.shape[1], device="cuda").half()
+    y = torch.empty(held_rows, dtype=torch.float32, device="cuda")
+    poison = POISON if wide else 0x7F
+    side = [torch.cuda.Stream() for _ in range(4)]
+    for k in (1, 2, 3):
+        print("held rows", held_rows, "stream", k, flush=True)
+        values = torch.full((v.size + 64,), poison, dtype=dense.dtype, device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side[0]):
+            for _ in range(4):
+                endor.gemv_f16(m, held_ro, x, y=y)
+        bitmap, ro, ws, nnz = _call(dense, values, v.size, stream=side[k])
+        torch.cuda.synchronize()
+        assert int(nnz) == v.size and torch.all(values[v.size:] == poison)
+        assert np.array_equal(values[:v.size].cpu().numpy().view(v.dtype), v)
+        assert np.array_equal(bitmap.cpu().numpy()[:b.size], b) and np.array_equal(ro.cpu().numpy(), r)
+        ws2, _ = endor.build_offsets(endor.DeviceMatrix(rows, cols, bitmap, values[:v.size], v.size))
+        torch.cuda.synchronize()
+        assert torch.equal(_table(ws, rows * cols), _table(ws2, rows * cols))
+
+
 def test_one_pass_in_a_hip_graph_replays_correctly():
     rows, cols = 5003, 8447
     inputs = [_matrix(rows, cols, k, True, 20 + i) for i, k in enumerate((0.5, 0.2, 0.8))]
