@@ -17,17 +17,8 @@
 namespace {
 
 constexpr uint32_t kOutside = 0x7fffffffu;  // an offset past every range
-constexpr int kMaxStreamQueries = 12;       // of a thread; 16 take more registers than there are
-
-// A workgroup of kThreads and the LDS it may take for 1024 / kThreads of them to share a compute unit.
-template <int kThreads>
-struct StreamShape {
-    static constexpr int kWaves = kThreads / 64;
-    static constexpr uint32_t kGroups = 256 * (1024 / kThreads);
-    static constexpr uint32_t kUnits = 15 * kThreads / 4;  // 16-byte units of a row's values: 30 KB for 512 threads, 15 for 256
-    static constexpr int kRounds = (kUnits + kThreads - 1) / kThreads;
-    static constexpr int64_t kMaxCols = 64 * kThreads;     // a bitmap word a thread
-};
+using endor_cols_plan::kMaxStreamQueries;
+using endor_cols_plan::StreamShape;
 
 // vmcnt(N) and lgkmcnt(0)
 template <int N>

@@ -46,6 +46,7 @@
 #include <type_traits>
 
 #include "endor.h"
+#include "endor_cols_plan.h"
 #include "endor_compress_plan.h"
 #include "endor_device.h"
 #include "endor_layout.h"
@@ -73,7 +74,10 @@ using endor_layout::align256;
 using endor_layout::chunks_of;
 using endor_layout::dims_ok;
 using endor_layout::workspace_bytes_n;
-constexpr int kBlock = 256;                   // threads per workgroup of the row-offset and column kernels
+
+using endor_cols_plan::kBlock;  // threads per workgroup of the row-offset and column kernels
+using endor_cols_plan::kLineBytes;
+using endor_cols_plan::Store;
 constexpr int kWaves = kBlock / 64;
 // Launch shapes.  Both were settled by measurement on MI355X (Llama2-70B layer, half the
 // elements kept): the tile-offset kernel with 16 waves per 256-tile chunk, the expand kernel
@@ -762,13 +766,6 @@ struct ColsParams {
     int64_t rows, cols, nnz, nsel;
     uint32_t stage_units;        // 16-byte units the staging area holds, one of them spare (kStaged)
 };
-
-constexpr uint32_t kLineBytes = 128;  // of the second-level cache
-
-// Plain; past the memory-side cache; so, and each wave's part of a row in whole lines, where rows of the output do
-// not begin at one.  A streamed store of parts of lines costs about a third more than one of whole ones: 8192 x
-// 28672, four in five kept, 0.35 of the columns (rows of 20070 bytes) plain 157 us, streamed 179, in whole lines 153.
-enum class Store { kPlain, kStreamed, kLines };
 
 // 64 bits of row-aligned "virtual word" k of a row that starts at bit row_bit: bits
 // row_bit + 64k .. +63, clipped to the row's `cols` bits and to the bitmap.
@@ -1807,18 +1804,7 @@ extern "C" endor_status endor_compress_device_u8(int64_t rows, int64_t cols, con
 
 namespace {
 
-constexpr size_t kMaxColsLds = 40 * 1024, kMinColsStage = 6 * 1024, kLdsPerUnit = 160 * 1024;
 constexpr int64_t kMaxGatherCols = int64_t(1) << 18;  // the row's bitmap and its prefixes live in LDS (16 bytes per 64 columns)
-
-// Queries per thread and round.  A staged row takes 4 (6 against 4: 2048 x 16384, 8-bit, half, 20.6 / 19.3 us, 36864 x
-// 9216, three tenths, 136 / 128; 12 cost it the occupancy, 28672 x 8192, three tenths, 111 / 94).  A gathered row takes 6
-// (28672 x 8192, one in five kept, three tenths 134 / 125 before its stores were streamed), but 4 where
-// the last of several rounds would be mostly empty with 6 (2048 x 16384, a tenth, 9.9 / 9.2).  3 for few queries
-// (36864 x 2000, a tenth, 6 / 4 / 3: 47 / 47 / 44).
-int cols_round(bool staged, int64_t nsel) {
-    const int64_t rounds6 = (nsel + 6 * kBlock - 1) / (6 * kBlock), rounds4 = (nsel + 4 * kBlock - 1) / (4 * kBlock);
-    return nsel <= 3 * kBlock ? 3 : staged || (rounds6 == rounds4 && rounds6 > 1) ? 4 : 6;
-}
 
 template <int E, bool kStaged, Store kStore>
 void launch_cols(const ColsParams &C, int round, dim3 grid, size_t lds, hipStream_t s) {
@@ -1840,43 +1826,18 @@ void launch_cols(const ColsParams &C, Store store, int round, dim3 grid, size_t 
 }
 
 template <int E, int kThreads>
-void launch_cols_stream(const ColsParams &C, hipStream_t s) {
+void launch_cols_stream(const ColsParams &C, int queries, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>(C.rows < StreamShape<kThreads>::kGroups ? C.rows : StreamShape<kThreads>::kGroups)), block(kThreads);
-    const int64_t queries = (C.nsel + kThreads - 1) / kThreads;
-    if (queries <= 2)
+    if (queries == 2)
         hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 2>), grid, block, 0, s, C);
-    else if (queries <= 4)
+    else if (queries == 4)
         hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 4>), grid, block, 0, s, C);
-    else if (queries <= 6)
+    else if (queries == 6)
         hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 6>), grid, block, 0, s, C);
-    else if (queries <= 8)
+    else if (queries == 8)
         hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 8>), grid, block, 0, s, C);
     else
         hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, kMaxStreamQueries>), grid, block, 0, s, C);
-}
-
-// Threads of endor_stream_cols_kernel's workgroups, 0 where a workgroup per row is the faster form.  A step of that
-// kernel takes 0.9 us or more however little there is in it, and its start two of them, so it wants many rows, and in
-// each of them many bytes or queries.  Over 380 calls (512 to 36864 rows, 2048 to 32768 columns, a twentieth to half of
-// them, a tenth to nine tenths kept, both widths) it is taken for 114, of them 1.14 times as fast on average and 0.97
-// to 1.35 times each; a workgroup per row / staying, us: 8192 x 28672 half kept, a tenth 63 / 55, a fifth 91 / 72;
-// 36864 x 9216, 8-bit, three tenths 115 / 88; 25776 x 4887, 8-bit, half 76 / 58; but 3008 x 9920 (few rows) 9 / 14, 16384
-// x 16384, a tenth (16 KB and three queries a thread) 65 / 70, 28672 x 8192, a tenth 58 / 61.  Not where few columns are asked
-// (less than a sixteenth: the gather reads less), nor for 16-bit outputs of 96 MB and more of shorter rows, which
-// the other kernel streams past the cache (31040 x 9920, 0.3 kept 115 / 122), nor for sparse 16-bit rows, of which the
-// cache serves the gather (7232 x 8896, a tenth kept, 23 / 26).
-int cols_stream_threads(int elem_bytes, int64_t rows, int64_t cols, int64_t nnz, int64_t nsel) {
-    const int64_t row_bytes = nnz / rows * elem_bytes, fits = row_bytes + 512;  // three standard deviations of the longest rows
-    if (rows < 5500 || nsel < cols / 16) return 0;
-    const bool narrow = fits <= 16 * int64_t(StreamShape<256>::kUnits) && cols <= StreamShape<256>::kMaxCols && nsel <= 256 * kMaxStreamQueries;
-    const bool wide = fits <= 16 * int64_t(StreamShape<512>::kUnits) && cols <= StreamShape<512>::kMaxCols && nsel <= 512 * kMaxStreamQueries;
-    if (!narrow && !wide) return 0;
-    const int threads = narrow ? 256 : 512;
-    if (elem_bytes == 2 && row_bytes < 16000 && rows * nsel * elem_bytes >= int64_t(96) << 20) return 0;
-    const int64_t half_queries = 2 * nsel / threads;
-    const bool many = half_queries >= 11 || (half_queries >= 9 && rows >= 9000 && row_bytes >= 2500);
-    const bool sparse = elem_bytes == 2 && nnz < rows * cols / 5;
-    return row_bytes >= 12000 || (many && !sparse) ? threads : 0;
 }
 
 endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t *d_bitmap, const void *d_values,
@@ -1903,78 +1864,21 @@ endor_status run_cols(int elem_bytes, int64_t rows, int64_t cols, const uint8_t 
     C.cols = cols;
     C.nnz = nnz;
     C.nsel = nsel;
-    C.stage_units = 0;
-    const int threads = cols_stream_threads(elem_bytes, rows, cols, nnz, nsel);
-    if (threads != 0) {
-        hipStream_t s = static_cast<hipStream_t>(stream);
-        if (threads == 512)
-            elem_bytes == 2 ? launch_cols_stream<2, 512>(C, s) : launch_cols_stream<1, 512>(C, s);
+    const endor_cols_plan::Plan p = endor_cols_plan::make_plan(elem_bytes, rows, cols, nnz, nsel, reinterpret_cast<uintptr_t>(d_out));
+    C.stage_units = p.stage_units;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (p.threads != 0) {
+        if (p.threads == 512)
+            elem_bytes == 2 ? launch_cols_stream<2, 512>(C, p.round, s) : launch_cols_stream<1, 512>(C, p.round, s);
         else
-            elem_bytes == 2 ? launch_cols_stream<2, 256>(C, s) : launch_cols_stream<1, 256>(C, s);
+            elem_bytes == 2 ? launch_cols_stream<2, 256>(C, p.round, s) : launch_cols_stream<1, 256>(C, p.round, s);
         return hipGetLastError() == hipSuccess ? ENDOR_OK : ENDOR_ERR_HIP;
     }
-    const size_t lds = static_cast<size_t>((cols + 63) / 64) * 4 * sizeof(uint32_t);
-    hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid(static_cast<unsigned>(rows));
-    // room for an eighth more values than a row has on average, and a spare unit
-    const size_t stage = (static_cast<size_t>(nnz / rows) * 9 / 8 * elem_bytes + 256 + 15) & ~size_t(15);
-    // Staging pays when most 64-byte lines of a row's values are wanted anyway (a sixteenth of the
-    // columns; the gather then costs a cache access per value, staging one per 64 bytes), the row is
-    // long enough for that to matter and short enough for four workgroups per compute unit.  Measured,
-    // gather against staged: a tenth of 8192 x 28672 65 / 63 us, three tenths 135 / 114, 8-bit 50 / 41, one
-    // in five kept 52 / 39, three tenths of 36864 x 9216 198 / 138; but 8192 x 28672 with four in five kept
-    // (52 KB a row) 89 / 105, a fifth of 5003 x 3171 (4 KB) 11 / 13, a tenth of 30000 x 700 39 / 49.
-    const bool rows_fit = nsel >= cols / 16 && lds + stage <= kMaxColsLds;
-    // And there has to be a lot to read or to answer: otherwise a workgroup's wait for its row shows, while
-    // the gather finds values that the memory-side cache holds.  A tenth of 2048 x 16384 9 / 12 us, three
-    // tenths 17 / 19, half 25 / 25; 3000 x 36864, 8-bit (55 MB), a tenth 21 / 25, a fifth 43 / 35; 4096 x
-    // 28672, one in five kept (47 MB), 0.07 of the columns 17 / 19, 0.15 37 / 29; 0.07 of 7200 x 12000,
-    // 8-bit, 16 / 18; of 9216 x 9216, two in five kept (68 MB) 20 / 21, half kept (85 MB) 24 / 22.
-    const int64_t asked = rows * nsel;
-    const bool much = nnz * elem_bytes >= (int64_t(9) << 23) || asked >= 14000000 || (rows >= 28 * 256 && asked >= 8000000);
-    // Or all rows on the chip at once, none of them long: a fifth of 1024 x 16384, 8-bit, 9.5 / 8.3 us, half
-    // 17 / 13; fp16, four in five kept (26 KB a row), a fifth 9.7 / 11.2.
-    const bool at_once = rows <= 2048 && static_cast<size_t>(rows) * (lds + stage) <= 256 * kLdsPerUnit && nsel >= cols / 5 &&
-                         nnz * elem_bytes <= rows * 20480;
-    // A shorter row only where every thread of its workgroup has six queries or more, and there are 8 million hits in
-    // all: otherwise the wait for the row outweighs the gather's accesses.  Fewer where `values` is larger than the
-    // memory-side cache keeps.  By columns asked of a row, gather / staged: 17233 x 2473, 0.66 kept, 1162 35.4 / 44.3 us,
-    // 20000 x 1500, 0.8 kept, 750 33 / 37, 9216 x 9216, 8-bit, 1474 (6.8 million) 22 / 25; 18432 x 4608, half kept, 1843 64 /
-    // 47, 18923 x 15575, 8-bit, 0.14 kept, 4828 133 / 87, 28672 x 8192, 8-bit, 2457 110 / 80; 95868 x 3763, 8-bit (238 MB), 940
-    // 194 / 168.  Over 285 calls (rows of 250 bytes to 6 KB) the choice is 0.6 % slower than the better form on average; by
-    // hits of a row alone, 600 or 300, it was 1.9 %.
-    const double hits = static_cast<double>(nsel) * static_cast<double>(nnz) / static_cast<double>(cols);
-    const bool most_asked = hits >= 8e6 && (nsel >= 6 * kBlock || (nnz * elem_bytes >= (int64_t(128) << 20) && hits >= rows * 300.0));
-    const bool long_rows = stage >= kMinColsStage && (much || at_once);
-    const bool staged = rows > 1 && rows_fit && (long_rows || (stage < kMinColsStage && most_asked));
-    C.stage_units = static_cast<uint32_t>(stage / 16);
-    const size_t l = lds + (staged ? stage : 0);
-    // Streamed stores where values are gathered: the output then leaves the lines of `values`, which several
-    // queries of a row share, in the memory-side cache.  28672 x 8192, one in five kept, a tenth of the columns
-    // 57 / 44 us, three tenths 125 / 85, 36864 x 2000 three tenths 68 / 57.  Where rows are staged every line is
-    // read once, and only an output that would fill that cache is streamed: 8192 x 28672, three tenths (141
-    // MB) 113 / 101, half (235 MB) 152 / 134, but 4096 x 28672, one in five kept, three tenths (70 MB) 42.6 / 45.5.
-    // Very small outputs and 8-bit ones are not: 1024 x 16384, a tenth (3 MB), 6.5 / 6.8; 8-bit +-2 % throughout.
-    const int64_t out_bytes = asked * elem_bytes;
-    const int round = cols_round(staged, nsel);
-    Store store = Store::kPlain;
-    if (elem_bytes == 2 && out_bytes >= (staged ? int64_t(96) << 20 : int64_t(8) << 20)) {
-        store = Store::kStreamed;
-        if ((reinterpret_cast<uintptr_t>(d_out) | static_cast<uintptr_t>(2 * nsel)) % kLineBytes) {
-            // Rows that begin inside a line.  Whole lines, where the queries then take no round more, or one more of
-            // at least four (28672 x 8192, four in five kept, 3055 columns 128 / 118, 17274 x 13952, half, 3069 82 / 77; but 36864 x
-            // 9216, one in five, 2027 91 / 102).  A gathered row has to be long for it (28672 x 8192, one in five kept,
-            // 1802 columns 79 / 80 us in lines; 9216 x 9216 2027 28.1 / 28.9, 3225 equal) and its output large (3200 x 8704,
-            // 0.47 (26 MB) 19.1 / 19.8, 1000 x 20000 to 30000 15 to 19, 2 to 3 % slower; 3000 x 36864, 0.22 (49 MB) 57 / 54).
-            const int64_t taken = (nsel + round * kBlock - 1) / (round * kBlock) * (round * kBlock);
-            const bool room = nsel + int64_t(kLineBytes) / 2 <= taken;
-            if (staged ? room || nsel > 2048 : room && nsel >= 3072 && out_bytes >= int64_t(32) << 20) store = Store::kLines;
-        }
-    }
     if (elem_bytes == 2)
-        staged ? launch_cols<2, true>(C, store, round, grid, l, s) : launch_cols<2, false>(C, store, round, grid, l, s);
+        p.staged ? launch_cols<2, true>(C, p.store, p.round, grid, p.lds, s) : launch_cols<2, false>(C, p.store, p.round, grid, p.lds, s);
     else
-        staged ? launch_cols<1, true>(C, store, round, grid, l, s) : launch_cols<1, false>(C, store, round, grid, l, s);
+        p.staged ? launch_cols<1, true>(C, p.store, p.round, grid, p.lds, s) : launch_cols<1, false>(C, p.store, p.round, grid, p.lds, s);
     if (hipGetLastError() != hipSuccess) return ENDOR_ERR_HIP;
     return ENDOR_OK;
 }
