@@ -91,6 +91,10 @@ template <class T>
 __device__ __forceinline__ T peek(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 template <class T>
 __device__ __forceinline__ void publish(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// What a wave has written to LDS is given out with the next word it writes, and what others gave out taken in with a word it has
+// read: a wait for the wave's own LDS accesses, none for memory.
+__device__ __forceinline__ void give_out_lds() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent", "local"); }
+__device__ __forceinline__ void take_in_lds() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent", "local"); }
 __device__ __forceinline__ uint32_t first_lane(uint32_t v) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v))); }
 __device__ __forceinline__ uint32_t lane_of(uint32_t v, uint32_t lane) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), lane)); }
 
@@ -223,6 +227,7 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
 
         uint32_t n = 0;
         auto place = [&](uint64_t w) {  // of the workgroup's n-th block, b0, whose word is w
+            take_in_lds();
             const uint32_t b = b0, b3 = next(b2);
             if (lane == 0) {
                 s_block[(n + kHeld) % kRing] = b3;
@@ -266,6 +271,8 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
             const uint32_t run = missing ? __builtin_ctzll(missing) : 64u;  // blocks from `pos` on that have been counted
             const uint32_t cnt = lane < run ? word_own(w) : 0u;
             const uint32_t incl = wave_inclusive_scan(cnt);
+            take_in_lds();
+            give_out_lds();
             if (lane < run) publish(block_word<E>(C.table, j), placed_word(before + incl, cnt));
             before += lane_of(incl, 63);
             pos += run;
@@ -317,12 +324,25 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
         T.before = incl - pc;
         T.cnt = lane_of(incl, 63);
         if (lane == 0) {
-            s_count[slot][wave] = T.cnt;
-            const uint32_t had = __hip_atomic_fetch_add(&s_arrived[slot], T.cnt | 1u << 24, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (had >> 24 == kTiles - 1) {  // the last of the block
-                if (block < nblocks) publish(block_word<E>(C.table, block), counted_word((had + T.cnt) & 0xffffffu));
-                s_arrived[slot] = 0;
-            }
+            struct Mem {
+                uint32_t *mine, *arrived;
+                const MatParams &table;
+                uint32_t block, nblocks;
+                __device__ __forceinline__ void count(uint32_t own) { *mine = own; }
+                __device__ __forceinline__ uint32_t arrive(uint32_t v) {
+                    give_out_lds();
+                    const uint32_t had = __hip_atomic_fetch_add(arrived, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    take_in_lds();
+                    return had;
+                }
+                __device__ __forceinline__ void clear_arrived() { __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+                __device__ __forceinline__ void publish(uint64_t w) {
+                    give_out_lds();
+                    if (block < nblocks) ::publish(block_word<E>(table, block), w);
+                }
+            };
+            const Mem mem{&s_count[slot][wave], &s_arrived[slot], C.table, block, nblocks};
+            endor_compress_plan::tile_counted(mem, kTiles, T.cnt);
         }
         {
             const uint32_t nw = (nvalid + 63) / 64;

@@ -17,6 +17,20 @@ constexpr uint64_t placed_word(uint64_t upto, uint32_t own) { return kPlaced | u
 constexpr uint32_t word_own(uint64_t w) { return static_cast<uint32_t>(w >> 40) & 0x3fffffu; }
 constexpr uint64_t word_upto(uint64_t w) { return w & ((uint64_t(1) << 40) - 1); }
 
+// A wave has counted its tile of a block: `own` non-zeros.  The waves that pack the block's later tiles read that when they have been
+// told the block's place, by a wave that has it from the block's word, which another one completes, when the last wave to
+// count has published it.  Every link of that chain hands on what the one before it has written: `arrive` gives out what its
+// wave has written and takes in what those that arrived before it gave out, `publish` gives out, and whoever reads a
+// word takes in.
+template <class Mem>
+constexpr void tile_counted(Mem mem, uint32_t tiles, uint32_t own) {
+    mem.count(own);
+    const uint32_t had = mem.arrive(own | 1u << 24);
+    if (had >> 24 != tiles - 1) return;
+    mem.clear_arrived();  // (before the word: the slot's next block is counted by waves that have been told this one's place)
+    mem.publish(counted_word((had + own) & 0xffffffu));
+}
+
 // The first workgroup to register says how blocks are shared out when all are running, or after that many polls, 0.7 us
 // each (by themselves all of them run within 10 us).
 constexpr uint32_t kMostPolls = 32;

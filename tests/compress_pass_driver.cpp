@@ -1,6 +1,7 @@
 // How the one-pass compressor's workgroups share out their blocks (endor_compress_plan.h), replayed on the host with a
 // thread for every wave: workgroups that start in any order, late, or only when others have ended.  Built and run by
-// tests/test_compress_plan.py; not part of the library.
+// tests/test_compress_plan.py, by itself and under ThreadSanitizer: every access has the order that it has in the kernel,
+// so what one wave reads of another's without having been given it is a race.  Not part of the library.
 #include <atomic>
 #include <cstdint>
 #include <cstdio>
@@ -66,12 +67,12 @@ void look_up(Shared &S, Local &L, uint32_t group, Rng r) {
     const uint32_t groups = S.groups, nblocks = S.nblocks, parties = static_cast<uint32_t>(S.parties.size());
     Shared::Party &own = S.parties[group / kParty];
     auto tell = [&](uint32_t placed) { L.placed.store(placed, std::memory_order_release); };
-    const uint32_t registered = own.started.fetch_add(1);
+    const uint32_t registered = own.started.fetch_add(1, std::memory_order_relaxed);
     breathe(r);
-    bool scans = registered == 0 && S.parties[0].first.fetch_add(1) == 0;
+    bool scans = registered == 0 && S.parties[0].first.fetch_add(1, std::memory_order_relaxed) == 0;
     auto started = [&]() {
         std::vector<uint32_t> here;
-        for (auto &p : S.parties) here.push_back(p.started.load());
+        for (auto &p : S.parties) here.push_back(p.started.load(std::memory_order_relaxed));
         return here;
     };
     auto give_out = [&](uint32_t number, uint32_t start, const std::vector<uint32_t> &here) {
@@ -80,7 +81,7 @@ void look_up(Shared &S, Local &L, uint32_t group, Rng r) {
         const Span all = s;
         for (uint32_t p = 0; p < parties; ++p) {
             s.here = here[p];
-            S.parties[p].span[number % kSpanSlots].store(span_word(s));
+            S.parties[p].span[number % kSpanSlots].store(span_word(s), std::memory_order_relaxed);
             breathe(r);
             s.before += here[p];
         }
@@ -101,7 +102,7 @@ void look_up(Shared &S, Local &L, uint32_t group, Rng r) {
     Span span{};
     for (bool found = false; !found;) {
         uint64_t w[kSpanSlots];
-        for (uint32_t i = 0; i < kSpanSlots; ++i) w[i] = own.span[i].load();
+        for (uint32_t i = 0; i < kSpanSlots; ++i) w[i] = own.span[i].load(std::memory_order_relaxed);
         for (uint32_t i = 0; i < kSpanSlots && !found; ++i) {
             span = span_of(w[i]);
             found = is_span(w[i]) && begins_with(span, w[(i + kSpanSlots - 1) % kSpanSlots], registered, nblocks);
@@ -111,12 +112,12 @@ void look_up(Shared &S, Local &L, uint32_t group, Rng r) {
     Part part = part_of(span, group, registered, groups, nblocks);
     const bool whole = is_whole(span, groups);
     if (whole) scans = group == 0;
-    if (scans && S.scanners.fetch_add(1) != 0) complain("two workgroups look the places up", group);
+    if (scans && S.scanners.fetch_add(1, std::memory_order_relaxed) != 0) complain("two workgroups look the places up", group);
     auto next = [&](uint32_t b) -> uint32_t {
         if (b + part.stride < part.end || part.end >= nblocks) return b + part.stride;
         const uint32_t number = span.number + 1;
         for (;;) {
-            const uint64_t w = own.span[number % kSpanSlots].load();
+            const uint64_t w = own.span[number % kSpanSlots].load(std::memory_order_relaxed);
             span = span_of(w);
             if (is_span(w) && span.number == number) break;
             if (is_span(w) && span.number > number) complain("a span overwritten before it was read", number, span.number);
@@ -145,7 +146,7 @@ void look_up(Shared &S, Local &L, uint32_t group, Rng r) {
     if (!scans) {
         while (b0 < nblocks) {
             uint64_t w;
-            while (!((w = S.words[b0].load()) & kPlaced)) std::this_thread::yield();
+            while (!((w = S.words[b0].load(std::memory_order_acquire)) & kPlaced)) std::this_thread::yield();
             place(w);
         }
         return;
@@ -161,12 +162,12 @@ void look_up(Shared &S, Local &L, uint32_t group, Rng r) {
     };
     give_out_due();
     while (b0 < nblocks || pos < nblocks) {
-        const uint64_t mine = S.words[b0 < nblocks ? b0 : nblocks - 1].load();
+        const uint64_t mine = S.words[b0 < nblocks ? b0 : nblocks - 1].load(std::memory_order_acquire);
         for (uint32_t i = 0; i < lanes && pos < nblocks; ++i, ++pos) {
-            const uint64_t w = S.words[pos].load();
+            const uint64_t w = S.words[pos].load(std::memory_order_acquire);
             if (!(w & kCounted)) break;
             before += word_own(w);
-            S.words[pos].store(placed_word(before, word_own(w)));
+            S.words[pos].store(placed_word(before, word_own(w)), std::memory_order_release);
         }
         give_out_due();
         if (b0 < nblocks && (mine & kPlaced)) place(mine);
@@ -182,13 +183,21 @@ void pack_tiles(Shared &S, Local &L, uint32_t wave, const std::vector<uint64_t> 
     auto count = [&](uint32_t n, uint32_t block) {
         const uint32_t slot = n % kRing, own = block < nblocks ? S.count[block * kPackers + wave] : 0;
         breathe(r);
-        L.count[slot][wave] = own;
-        L.counted_block[slot][wave] = block;
-        const uint32_t had = L.arrived[slot].fetch_add(own | 1u << 24);
-        if (had >> 24 == kPackers - 1) {
-            L.arrived[slot].store(0);
-            if (block < nblocks && S.words[block].exchange(counted_word((had + own) & 0xffffff)) != 0) complain("a block counted twice", block);
-        }
+        struct Mem {
+            Shared &S;
+            Local &L;
+            uint32_t slot, wave, block;
+            void count(uint32_t v) {
+                L.count[slot][wave] = v;
+                L.counted_block[slot][wave] = block;
+            }
+            uint32_t arrive(uint32_t v) { return L.arrived[slot].fetch_add(v, std::memory_order_acq_rel); }
+            void clear_arrived() { L.arrived[slot].store(0, std::memory_order_relaxed); }
+            void publish(uint64_t w) {
+                if (block < S.nblocks && S.words[block].exchange(w, std::memory_order_release) != 0) complain("a block counted twice", block);
+            }
+        };
+        tile_counted(Mem{S, L, slot, wave, block}, kPackers, own);
     };
     auto pack = [&](uint32_t n, uint32_t block) {
         const uint32_t slot = n % kRing;
@@ -198,7 +207,7 @@ void pack_tiles(Shared &S, Local &L, uint32_t wave, const std::vector<uint64_t> 
             first += L.count[slot][v];
         }
         if (first != sums[block * kPackers + wave]) complain("a wrong place", block, wave);
-        S.packed[block].fetch_add(1);
+        S.packed[block].fetch_add(1, std::memory_order_relaxed);
         breathe(r);
     };
     until(1);
