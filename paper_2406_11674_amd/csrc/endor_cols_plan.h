@@ -88,7 +88,7 @@ constexpr bool fits_stream(int64_t row_bytes, int64_t cols, int64_t nsel) {
 //       but 13120 x 5120, 1280 (13 of 15), 25 / 30, 9088 x 2624, 1278 (9 of 11), 18.4 / 22.1; otherwise a second round of the
 //       other kernel, 6375 x 3321, 1577, 19.3 / 17.6, 8-bit 6469 x 12229, 1810, 20.0 / 16.9, 5718 x 11811, 1465, 16.4 / 18.8, and
 //       not with nine queries, which take twelve, 5824 x 11712, 2249, 22.0 / 25.4, 6016 x 6656, 2110, 20.2 / 22.5
-//   512 threads, rows of 20 KB and more: two queries a thread, 8192 x 28672, a tenth 63 / 55, a fifth 93 / 71; of 12 KB: four,
+//   512 threads, rows of 20 KB and more: three queries a thread, 8192 x 28672, a tenth 63 / 55, a fifth 93 / 71; of 12 KB: four,
 //       16384 x 16384, 0.07 of the columns 59 / 65, a tenth 62 / 66, 0.3 of them 100 / 96, 6656 x 12224, 978, 22.0 / 27.2;
 //       shorter ones: five
 // Not where few columns are asked (less than a sixteenth: the gather reads less), nor for sparse 16-bit rows, of which the
@@ -98,7 +98,7 @@ constexpr bool fits_stream(int64_t row_bytes, int64_t cols, int64_t nsel) {
 //
 // Fitted to 1499 calls of both kernels (5500 to 36864 rows, 800 to 32768 columns, a sixteenth to half of them, a tenth to
 // nine tenths kept, both widths, rows alike and not): taken for 426 of them, 1.15 times as fast on average, at worst 0.95;
-// of 899 others for 261, 1.14 times, at worst 0.95.  (Without the steps in it the rule lost 5 % and more, up to a fifth, on 21
+// of 899 others for 260, 1.14 times, at worst 0.95.  (Without the steps in it the rule lost 5 % and more, up to a fifth, on 21
 // of the 470 that it took.)
 constexpr int stream_threads(int elem_bytes, int64_t rows, int64_t cols, int64_t nnz, int64_t nsel) {
     const int64_t row_bytes = nnz / rows * elem_bytes;
@@ -110,7 +110,7 @@ constexpr int stream_threads(int elem_bytes, int64_t rows, int64_t cols, int64_t
     const int64_t places = groups * ((rows + groups - 1) / groups + 2);
     const int64_t half_queries = 2 * nsel / threads;
     if (elem_bytes == 2 && rows * nsel * elem_bytes >= 96 * kMB && (row_bytes < 16000 || half_queries < 15)) return 0;
-    if (!narrow && row_bytes >= 12000) return half_queries >= (row_bytes >= 20000 ? 4 : 8) ? threads : 0;
+    if (!narrow && row_bytes >= 12000) return half_queries >= (row_bytes >= 20000 ? 5 : 8) ? threads : 0;
     if (elem_bytes == 2 && nnz < rows * cols / 5) return 0;
     int least = rows >= 9000 && row_bytes >= 2500 ? 9 : 11;
     if (narrow && !rows_staged(elem_bytes, rows, cols, nnz, nsel)) {
@@ -153,7 +153,7 @@ constexpr Plan make_plan(int elem_bytes, int64_t rows, int64_t cols, int64_t nnz
     p.threads = stream_threads(elem_bytes, rows, cols, nnz, nsel);
     if (p.threads != 0) {
         const int64_t queries = (nsel + p.threads - 1) / p.threads;
-        p.round = queries <= 2 ? 2 : queries <= 4 ? 4 : queries <= 6 ? 6 : queries <= 8 ? 8 : kMaxStreamQueries;
+        p.round = queries <= 4 && p.threads == 512 ? 4 : queries <= 6 ? 6 : queries <= 8 ? 8 : kMaxStreamQueries;
         return p;
     }
     const size_t lds = bitmap_lds(cols), stage = stage_bytes(elem_bytes, nnz / rows);

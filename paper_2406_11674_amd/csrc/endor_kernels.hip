@@ -1828,11 +1828,13 @@ void launch_cols(const ColsParams &C, Store store, int round, dim3 grid, size_t 
 template <int E, int kThreads>
 void launch_cols_stream(const ColsParams &C, int queries, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>(C.rows < StreamShape<kThreads>::kGroups ? C.rows : StreamShape<kThreads>::kGroups)), block(kThreads);
-    if (queries == 2)
-        hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 2>), grid, block, 0, s, C);
-    else if (queries == 4)
-        hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 4>), grid, block, 0, s, C);
-    else if (queries == 6)
+    if constexpr (kThreads == 512) {  // (256 threads have five queries and more)
+        if (queries == 4) {
+            hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 4>), grid, block, 0, s, C);
+            return;
+        }
+    }
+    if (queries == 6)
         hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 6>), grid, block, 0, s, C);
     else if (queries == 8)
         hipLaunchKernelGGL((endor_stream_cols_kernel<E, kThreads, 8>), grid, block, 0, s, C);

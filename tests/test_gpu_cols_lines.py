@@ -10,9 +10,11 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 # (rows, cols, columns asked, keep): outputs of 32 MB and more gathered, of 96 MB and more staged
-CASES = [(5500, 9000, n, 0.2) for n in (3071, 3072, 3073, 3136, 4545, 4609, 6143)]      # a row of 6-query rounds: full, one over
+# (test_cols_plan.py says which form each takes)
+CASES = [(5500, 9000, n, 0.15) for n in (3071, 3072, 3073, 3136, 4545, 4609, 6143)]     # a row of 6-query rounds: full, one over
 CASES += [(9300, 13001, n, 0.5) for n in (5569, 6081, 6144, 6145)]                      # staged, 4-query rounds
 CASES += [(70000, 800, 767, 0.9), (1, 262144, 262143, 0.4)]                             # short rows; one row of 512 KB
+CASES += [(30000, 3000, 1700, 0.8)]                                                     # short rows, staged
 
 
 @pytest.mark.parametrize("case,off", [(c, off) for c in CASES for off in (0, 1, 37, 64) if off == 37 or c[0] * c[2] < 40_000_000], ids=str)

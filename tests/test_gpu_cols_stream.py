@@ -46,11 +46,17 @@ def _check(w, sel, shift=0, out_shift=0, m=None, ro=None, want=None):
 
 
 # rows, cols, keep, wide, columns asked: groups of 4 and 8 waves; words of the bitmap per row around a wave's and a
-# workgroup's; rounds of 2, 4, 6, 8, 12 queries, full and not; rows of a workgroup odd and even; values to the last unit
-CASES = [(5500, 4096, 0.5, True, 1500), (5501, 4097, 0.7, True, 1409), (6143, 4159, 0.5, False, 1600), (6145, 16384, 0.44, True, 1024),
-         (5600, 16320, 0.46, True, 3072), (5500, 16385, 0.5, True, 1100), (5700, 20011, 0.7, True, 5000), (5500, 32768, 0.46, True, 2049),
-         (5777, 32705, 0.9, False, 6144), (9001, 3333, 0.95, False, 1300), (5503, 12345, 0.02, False, 3071),
-         (5500, 8000, 0.0, False, 3000), (6500, 16400, 0.49, True, 1025), (5500, 16385, 0.5, True, 1024)]
+# workgroup's; rounds of 4, 6, 8, 12 queries, full and not; rows of a workgroup odd and even; values to the last unit.
+# Each takes this form, and together all of its instantiations: test_cols_plan.py.
+CASES = [(5500, 4096, 0.5, True, 1600), (5501, 4097, 0.7, True, 1537), (6143, 4159, 0.5, False, 1600), (6145, 16384, 0.44, True, 1409),
+         (5600, 16320, 0.46, True, 3072), (5500, 16385, 0.5, True, 2048), (5700, 20011, 0.7, True, 5000), (5500, 32768, 0.46, True, 2049),
+         (5777, 32705, 0.9, False, 6144), (9001, 3333, 0.95, False, 1536), (5503, 12345, 0.02, False, 3071),
+         (5500, 8000, 0.0, False, 3000), (6500, 16400, 0.49, True, 2049), (5500, 20500, 0.6, True, 1281),
+         (5501, 8000, 0.45, True, 3071), (5500, 20011, 0.7, True, 4000), (5500, 32705, 0.9, False, 2048), (5501, 32705, 0.9, False, 3000),
+         (5500, 32705, 0.9, False, 4000)]
+# of the tests below: rows, cols, keep, columns asked
+ANY_ORDER, NOT_STAGED = (5600, 8000, 0.6, 2900), (5555, 16001, 2500)
+OWN_ENTRY, IN_A_GRAPH = (5504, 6000, 0.5, 1600), (5520, 9000, 0.7, 2000)
 
 
 @pytest.mark.parametrize("rows, cols, keep, wide, nsel", CASES, ids=str)
@@ -63,8 +69,8 @@ def test_rows_one_after_the_other(rows, cols, keep, wide, nsel):
 
 @pytest.mark.parametrize("wide", [True, False], ids=["fp16", "u8"])
 def test_any_order_repeats_and_indices_outside(wide):
-    rows, cols, nsel = 5600, 8000, 2900
-    w = _dense(rows, cols, 0.6, wide, 3)
+    rows, cols, keep, nsel = ANY_ORDER
+    w = _dense(rows, cols, keep, wide, 3)
     g = torch.Generator(device="cuda").manual_seed(2)
     sel = torch.randint(0, cols, (nsel,), device="cuda", generator=g)
     outside = torch.tensor([-1, cols, cols + 31, 1 << 40, -(1 << 50)], device="cuda")
@@ -78,7 +84,7 @@ def test_any_order_repeats_and_indices_outside(wide):
 @pytest.mark.parametrize("wide", [True, False], ids=["fp16", "u8"])
 def test_rows_that_are_not_staged(wide):
     """Full rows among sparse ones (more values than the staging area holds), empty rows, and the last row."""
-    rows, cols, nsel = 5555, 16001, 2222
+    rows, cols, nsel = NOT_STAGED
     keep = torch.full((rows, 1), 0.4 if wide else 0.8, device="cuda")
     keep[::97] = 1.0
     keep[5::101] = 0.0
@@ -88,8 +94,8 @@ def test_rows_that_are_not_staged(wide):
 
 def test_only_a_rows_own_entry_says_where_its_values_are():
     """Entries that are not in order: the next one is too small, too large, or another row's."""
-    rows, cols, nsel = 5504, 6000, 1600
-    w = _dense(rows, cols, 0.5, True, 5)
+    rows, cols, keep, nsel = OWN_ENTRY
+    w = _dense(rows, cols, keep, True, 5)
     m, ro = _compressed(w)
     sel = torch.arange(0, nsel * 3, 3, device="cuda")
     order = torch.randperm(rows, device="cuda", generator=torch.Generator(device="cuda").manual_seed(6))
@@ -106,8 +112,8 @@ def test_only_a_rows_own_entry_says_where_its_values_are():
 
 
 def test_columns_in_a_hip_graph():
-    rows, cols, nsel = 5520, 9000, 2000
-    ws = [_dense(rows, cols, k, True, 7 + i) for i, k in enumerate((0.5, 0.3, 0.7))]
+    rows, cols, most, nsel = IN_A_GRAPH
+    ws = [_dense(rows, cols, k, True, 7 + i) for i, k in enumerate((0.5, 0.3, most))]
     ms = [_compressed(w) for w in ws]
     cap = max(m.nnz for m, _ in ms)
     bitmap, values, ro = torch.zeros_like(ms[0][0].bitmap), torch.zeros(cap, dtype=torch.int16, device="cuda"), torch.zeros_like(ms[0][1])
