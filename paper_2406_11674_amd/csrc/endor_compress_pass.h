@@ -27,9 +27,9 @@
 // place it says that there are no more.
 //
 // Bound by memory: 28672 x 8192 fp16, half kept, 734 MB in 137 us, 5.4 TB/s; two passes take 199, loads
-// and stores without the scatter 13 us less than this.  Of it, 10 us pass before the first values are written
+// and stores without the scatter 13 us less than this; 473 MB read, the matrix once, and 272 written, counted.  Of it, 10 us pass before the first values are written
 // (the registration waits behind the first loads) and 6 after the last block has arrived.  Us a call, two
-// passes / one: 28672 x 8192 fp16 a tenth, half, nine tenths kept 199 / 145, 221 / 167, 257 / 200;
+// passes / one: 28672 x 8192 fp16 a tenth, half, nine tenths kept 199 / 145, 220 / 165, 257 / 200;
 // 8192 x 8192 85 / 77; 28672 x 8192 8-bit 148 / 132.
 #ifndef ENDOR_COMPRESS_PASS_H_
 #define ENDOR_COMPRESS_PASS_H_
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(Blocks<E>::kThreads, Blocks<E>::kThreads / 256) voi
         };
         give_out_due();
         while (b0 < nblocks || pos < nblocks) {
-            const uint32_t j = pos + lane;  // (two or four words a lane: no faster where counts arrive steadily, 167 -> 170, 175)
+            const uint32_t j = pos + lane;  // (two or four words a lane: no faster where counts arrive steadily, by 3 and 8 us slower)
             const uint64_t w = peek(block_word<E>(C.table, j < nblocks ? j : nblocks - 1));
             const uint64_t mine = peek(block_word<E>(C.table, b0 < nblocks ? b0 : nblocks - 1));
             const uint64_t missing = ~__builtin_amdgcn_ballot_w64(j < nblocks && (w & kCounted) != 0);

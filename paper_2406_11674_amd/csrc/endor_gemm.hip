@@ -24,11 +24,11 @@
 // X goes to LDS once per workgroup and round (four row groups share it), in the order in which
 // the steps read it, double buffered.
 //
-// Measured on 28672 x 8192, half kept, 16 right-hand sides: 78 us (the form before, which read
+// Measured on 28672 x 8192, half kept, 16 right-hand sides: 76 us, 8192 x 28672 72 (the form before, which read
 // every byte's 20-byte window from memory through the vector cache and handed the expanded bytes
-// on with ds_bpermute: 112 us).  Few right-hand sides go to the vector form where that is faster
-// (endor_gemv_plan.h).  No unit bounds it by itself: LDS serves 65 clocks of every step's 95 (64 lanes at random
-// addresses cost 7 clocks per dword, six dwords per byte), the vector ALUs are busy 42 % of the
+// on with ds_bpermute: 112 and 104).  Few right-hand sides go to the vector form where that is faster
+// (endor_gemv_plan.h).  No unit bounds it by itself: LDS serves 70 % of the clocks (64 lanes at random
+// addresses cost 7 clocks per dword, six dwords per byte), the vector ALUs are busy 43 % of the
 // time, memory alone would take 45 us; but without the LDS windows 69, with nothing multiplied 64,
 // without the values 70 to 76: a round's phases follow one another in step, as all waves of a workgroup
 // meet at every round's tile of X.  Measured alternatives: the windows as three aligned
@@ -470,12 +470,13 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
         // the tile's words below e_r).  Lane r < 16 looks up the first two terms of row r, the
         // whole wave counts the third for each row in turn.  All loads go out, without a test, before the
         // first result is needed, so the lookups cost one trip to memory: under their tests they were three in a
-        // row at the start of every block (16 right-hand sides of 28672 x 8192 78.7 us, now 77.2; 131072 x 256 24.9, now 23.4).
+        // row at the start of every block (16 right-hand sides of 131072 x 256 24.3 us, now 22.5,
+        // of 28672 x 8192 1.5 us less).
         uintptr_t cursor = vbeg;
         if (c_begin < G.cols && row0 < G.rows) {  // wave-uniform
             // (opaque: what follows from the lane alone would be kept in registers over all blocks, and three workgroups
             // of the dense form with unaligned columns would no longer fit a compute unit: 169 registers;
-            // 2999 x 9001, 0.7 kept, 7 right-hand sides 29.1 us, so 23.3)
+            // 2999 x 9001, 0.7 kept, 7 right-hand sides 29.1 us, so 22.6)
             uint32_t l = lane;
             asm volatile("" : "+v"(l));
             const int64_t e_first = row0 * G.cols + c_begin;
@@ -580,9 +581,8 @@ __global__ __launch_bounds__(64 * kGemmWaves, 2) void endor_gemm_f16_kernel(Gemm
 
 // y[b][i] = the parts of row i's block, added in ascending order.  An output a thread, so that it is one trip to memory, and
 // 32-bit divisions (rounds are fewer than 2^32): with a workgroup for all of a block's outputs, four a thread in turn, and two
-// divisions of 64 bits, 16 right-hand sides of 28672 x 8192 took 77.2 us,
-// now 76.6, 4096 x 4096 18.1, now 14.2; 1024 x 8192 (8 right-hand sides, many parts) 14.4, with four parts a trip 12.6, with
-// three or eight and no test around a load 12.0.
+// divisions of 64 bits, 4096 x 4096 with 16 right-hand sides took 18.2 us, now 13.6; 1024 x 8192 (8 right-hand sides, many
+// parts) 14.7, with four parts a trip 12.6, with three or eight and no test around a load 11.7.
 __global__ __launch_bounds__(256) void endor_gemm_reduce_kernel(const float *__restrict__ partial, float *__restrict__ y,
                                                                 int64_t rows, int32_t nb, uint32_t segs, uint32_t per_wg) {
     const uint32_t block = blockIdx.x;

@@ -103,7 +103,7 @@ constexpr Plan plan_with(int64_t rows, int64_t cols, int rhs, int steps, int64_t
 // The rows past a whole number for each workgroup go to workgroups at regular distances.  With the first ones having them,
 // long runs of workgroups began at a common stride, and where that is an unlucky one all of them read the same channels of
 // memory at a time: 9280 x 11648, 0.62 kept, 34.7 us, so 31.6 (9216 rows, 36 for each, 39); 9413 x 35233, 0.71 kept,
-// 100.6, so 89.5.
+// 100.6, so 88.0.
 //   more_share: ceil(2^32 * more / groups), more < groups; more_before: how many of the workgroups before have one more
 constexpr uint32_t more_share(uint32_t more, uint32_t groups) {
     return static_cast<uint32_t>(((uint64_t(more) << 32) + groups - 1) / groups);

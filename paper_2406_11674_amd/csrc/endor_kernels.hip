@@ -137,8 +137,8 @@ __device__ __forceinline__ uint32_t chunk_in(const MatParams &M, uint32_t chunk)
 // The matrix that a chunk belongs to, and the chunk's number in it.  The first one's descriptor comes with the number that
 // says whether it is the one; the others are counted off the vector unit, two scalar instructions a matrix.  (The
 // compiler's own form was a vector addition, or a trip through a vector register, for each of the sixteen, 100 instructions in a row
-// at the start of every wave.  Expanding 5003 x 3171, 0.7 kept, 12.2 us, now 11.3; the matrices of a Llama2-70B layer in one
-// batch 450.4, now 448.9; 9216 x 36864, 8-bit, 93.4, now 92.6.)
+// at the start of every wave.  Expanding 5003 x 3171, 0.7 kept, 12.2 us, now 11.4; the matrices of a Llama2-70B layer in one
+// batch 450.8, now 448.5; 9216 x 36864, 8-bit, 92.8, now 92.3.)
 __device__ __forceinline__ MatParams matrix_of(const BatchParams &P, uint32_t chunk, uint32_t &c) {
     MatParams M = P.m[0];
     c = chunk_in(M, chunk);
@@ -306,7 +306,7 @@ __device__ __forceinline__ u32x4 load_values16(uintptr_t p, uintptr_t vbeg, uint
 // array, usually one, element by element.  ask() puts the loads out, finish() is what remains to be done when the
 // bitmap has been worked on, with a wait.
 // Only the unit itself goes that way: with all units of the array's first and last tiles put together from their
-// elements, trip after trip, 2048 x 2048, four in five kept, took 8.9 us (now 5.5), 4096 x 4096 15.0 (13.5).
+// elements, trip after trip, 2048 x 2048, four in five kept, took 8.6 us (now 5.0), 4096 x 4096 14.4 (11.7).
 template <int E, int kRounds>
 struct ValueSlice {
     uintptr_t a16, vbeg, vend;

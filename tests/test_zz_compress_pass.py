@@ -102,7 +102,8 @@ def test_one_pass_keeps_to_the_capacity(wide):
 
 
 def test_one_pass_beside_other_work():
-    """Calls on two streams at once, beside products on a third: workgroups start late, or not at all at first."""
+    """Calls on two streams at once, beside products on a third.  (How many workgroups run from the start is up to the dispatch;
+    the next test holds compute units for that, and test_compress_plan.py replays every order on the host.)"""
     dense = [_matrix(5003, 8447, 0.5, True, 8), _matrix(12289, 13653, 0.5, False, 9)]
     want = [_expect(d) for d in dense]
     a = torch.randn((4096, 4096), device="cuda").half()
