@@ -28,7 +28,7 @@ constexpr int kBlockRows = endor_gemm_units::kRows * kGemmWaves;
 // 144 / 88 us, 1000000 x 128 279 / 165, 262144 x 512 80 / 62, 131072 x 1024 59 / 51, 36864 x 1024
 // 29 / 21, 36864 x 2048 38 / 33, 33000 x 3072 47 / 46; but 36000 x 3584 51.5 / 52.3 and 36864 x 4096
 // 56.9 / 59.2.  (The kernel before this form, of which four workgroups fit a compute unit and three of
-// this one, was slower everywhere else but took 146 us on 10^6 x 256 with one in ten kept: now 158.)
+// this one, was slower everywhere else but took 146 us on 10^6 x 256 with one in ten kept: now 147.)
 constexpr int64_t kResident = 256 * 2;
 constexpr int64_t kMaxParts = 16;
 constexpr int64_t kWholeSlack = 2;

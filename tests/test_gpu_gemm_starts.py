@@ -10,9 +10,9 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 # rows, cols, keep: rows at every word; at every tile; at every chunk, in 15, 16 and 17 rows; several chunks to a row;
-# 64 chunks to a group of rows, and one more; 300 chunks
+# up to 64 chunks between the first and the last row of a group, which one wave scans, and 65; 300 chunks
 CASES = [(130, 64, 0.5), (70, 4096, 0.3), (35, 1 << 20, 0.1), (17, 1 << 20, 0.3), (33, (1 << 20) + 64, 0.02), (16, 4 << 20, 0.05),
-         (19, (4 << 20) + (1 << 18), 0.05), (18, (4 << 20) + 70001, 0.05), (79, 4 << 20, 0.01), (2000, 513, 0.0), (65, 65537, 1.0)]
+         (19, (4 << 20) + (1 << 18), 0.05), (19, (4 << 20) + (5 << 16), 0.05), (18, (4 << 20) + 70001, 0.05), (79, 4 << 20, 0.01), (2000, 513, 0.0), (65, 65537, 1.0)]
 
 
 @pytest.mark.parametrize("nb", [8, 16])
