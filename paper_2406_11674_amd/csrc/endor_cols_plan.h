@@ -81,12 +81,14 @@ constexpr bool fits_stream(int64_t row_bytes, int64_t cols, int64_t nsel) {
 // Threads of such workgroups, 0 where a workgroup per row is the faster form.
 //
 // A step takes 0.9 us or more however little there is in it, and a workgroup two steps more than it has rows, the last of which
-// may be of a few workgroups: of groups * steps places, how many have a row?  The other kernel is slow where it stages rows
-// and where a thread takes a second round of queries (1537 columns).  So, a workgroup per row / staying, us:
+// may be of a few workgroups: of groups * steps places, how many have a row?  The other kernel is slow where it stages rows,
+// where it gathers what the memory-side cache does not keep, and where a thread takes a second round of queries (1537 columns).
+// So, a workgroup per row / staying, us:
 //   256 threads, rows that would be staged: five queries a thread, 9782 x 8261, 1239 columns, 29 / 25, 12538 x 3715, 1523, 36 / 28
-//     gathered: the same where nearly all places have a row, 27893 x 4938, 1264 columns, 72 / 54, 8-bit 23844 x 3531, 1395, 60 / 41,
-//       but 13120 x 5120, 1280 (13 of 15), 25 / 30, 9088 x 2624, 1278 (9 of 11), 18.4 / 22.1; otherwise a second round of the
-//       other kernel, 6375 x 3321, 1577, 19.3 / 17.6, 8-bit 6469 x 12229, 1810, 20.0 / 16.9, 5718 x 11811, 1465, 16.4 / 18.8, and
+//     gathered: the same from 105 MB of values and output on (8-bit 70), 27893 x 4938, 1264 columns, 72 / 54, 17637 x 4565, 1233,
+//       45 / 37, 8-bit 23844 x 3531, 1395, 60 / 41, but 13120 x 5120, 1280 (86 MB), 25 / 30, 9088 x 2624, 1278 (49 MB), 18.4 / 22.1;
+//       six queries where four in five places have a row, 14663 x 3546, 1624, 38 / 32; else a second round of the other
+//       kernel, 6375 x 3321, 1577, 19.3 / 17.6, 8-bit 6469 x 12229, 1810, 20.0 / 16.9, 5718 x 11811, 1465, 16.4 / 18.8, and
 //       not with nine queries, which take twelve, 5824 x 11712, 2249, 22.0 / 25.4, 6016 x 6656, 2110, 20.2 / 22.5
 //   512 threads, rows of 20 KB and more: three queries a thread, 8192 x 28672, a tenth 63 / 55, a fifth 93 / 71; of 12 KB: four,
 //       16384 x 16384, 0.07 of the columns 59 / 65, a tenth 62 / 66, 0.3 of them 100 / 96, 6656 x 12224, 978, 22.0 / 27.2;
@@ -97,8 +99,9 @@ constexpr bool fits_stream(int64_t row_bytes, int64_t cols, int64_t nsel) {
 // columns, 106 / 116).
 //
 // Fitted to 1499 calls of both kernels (5500 to 36864 rows, 800 to 32768 columns, a sixteenth to half of them, a tenth to
-// nine tenths kept, both widths, rows alike and not): taken for 426 of them, 1.15 times as fast on average, at worst 0.95;
-// of 899 others for 260, 1.14 times, at worst 0.95.  (Without the steps in it the rule lost 5 % and more, up to a fifth, on 21
+// nine tenths kept, both widths, rows alike and not): taken for 429 of them, 1.15 times as fast on average, at worst 0.95;
+// of 899 others for 259, 1.15 times, at worst 0.95.  Rows that are not alike do not all fit LDS near its limits: 447 calls of such
+// rows (deviations of 3 to 10 of 100 columns) 1.15 times, but of 14.5 KB and more with 256 threads 1.01.  (Without the steps in it the rule lost 5 % and more, up to a fifth, on 21
 // of the 470 that it took.)
 constexpr int stream_threads(int elem_bytes, int64_t rows, int64_t cols, int64_t nnz, int64_t nsel) {
     const int64_t row_bytes = nnz / rows * elem_bytes;
@@ -114,8 +117,8 @@ constexpr int stream_threads(int elem_bytes, int64_t rows, int64_t cols, int64_t
     if (elem_bytes == 2 && nnz < rows * cols / 5) return 0;
     int least = rows >= 9000 && row_bytes >= 2500 ? 9 : 11;
     if (narrow && !rows_staged(elem_bytes, rows, cols, nnz, nsel)) {
-        const int64_t share = rows * 100 / places;
-        if (share < (elem_bytes == 2 ? 88 : 84)) least = share >= 80 ? 11 : 12;
+        const int64_t share = rows * 100 / places, moved = nnz * elem_bytes + rows * nsel * elem_bytes;
+        if (moved < (elem_bytes == 2 ? 105 : 70) * kMB) least = share >= 80 ? 11 : 12;
         if (share < 79 && elem_bytes == 2 && nsel > 8 * threads && half_queries < 19) return 0;
     }
     return half_queries >= least ? threads : 0;

@@ -43,7 +43,8 @@ FASTER_STAYING = [(2, 8192, 28672, 0.5, 2867), (2, 8192, 28672, 0.5, 5734),     
                   (1, 28672, 8192, 0.5, 2867), (1, 25776, 4887, 0.5, 2443),        # 90 / 67, 76 / 58
                   (2, 6505, 9210, 0.71, 2745), (1, 6469, 12229, 0.88, 1810),       # 25.5 / 22.7, 20.0 / 16.9
                   (2, 16464, 5143, 0.64, 1193), (2, 12538, 3715, 0.79, 1523),      # 45 / 36, 36 / 28
-                  (2, 9782, 8261, 0.32, 1239), (2, 6375, 3321, 0.5, 1577)]                                     # 28.7 / 24.6, 19.3 / 17.6
+                  (2, 9782, 8261, 0.32, 1239), (2, 6375, 3321, 0.5, 1577),        # 28.7 / 24.6, 19.3 / 17.6
+                  (2, 17637, 4565, 0.53, 1233)]                                    # 45.2 / 37.2
 
 
 def test_the_faster_form_is_taken(forms):
